@@ -221,8 +221,8 @@ int lance_conv3x3_winograd_q8_noalloc(const lance_conv_desc *desc, const float *
  * returns each kernel's duration, averaged over the passes, in milliseconds in
  * kernel_ms_host[LANCE_PROFILE_KERNELS] (HOST memory): [0] range pass over X, [1] range
  * reduction + quantizer/de-quantizer constants, [2] transform+quantize pass,
- * [3] GEMM+epilogue.  Layers with one 64-channel block and m = 2 run as two kernels (V's codes
- * never leave the chip): then [1] and [2] are exactly 0 and [3] covers range reduction,
+ * [3] GEMM+epilogue.  Layers of few tiles, and m = 2 layers of 17 to 128 channels, run as two
+ * kernels (V's codes never leave the chip): then [1] and [2] are exactly 0 and [3] covers range reduction,
  * transform+quantize, GEMM and epilogue.  Where the quantize pass reduces the range records
  * itself [1] is the time between two adjacent events.  A duration includes the launch gap in
  * front of its kernel.  repeats: 1 .. LANCE_PROFILE_MAX_REPEATS, else LANCE_ERR_INVALID_ARG.

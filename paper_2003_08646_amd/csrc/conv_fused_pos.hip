@@ -1,0 +1,96 @@
+// Host side of conv_fused_pos.h and its F(2x2,3x3) instances.
+#include "conv_fused_pos.h"
+
+namespace lance {
+namespace pos {
+hipError_t launch_m4(const CpArgs& a, bool clamp, int cpl, int load, int kg, hipStream_t s);
+
+// How a layer is cut into workgroups: 16 tiles x 16*kg filters, nw waves each.
+struct Shape {
+  int kg, nw, nky;
+  long long groups;
+};
+
+// The shape with the smallest (rounds of resident workgroups) x (relative time of a workgroup).  A
+// compute unit holds one workgroup of 16 (m = 4: 12) waves, or two of eight, which then share its
+// units but overlap their phases.  Relative times from sweeps over layers of 3 to 512 channels: a
+// workgroup of 16 waves takes 1.08x and 1.25x as long with twice and four times the filters, two of
+// eight waves side by side 1.3x .. 1.6x (64 channels, 64 filters, 784 blocks of tiles: 36 us with 16
+// waves, 27 us with eight; 61 filters, 135 blocks: 15.5 and 15.9 us); m = 4: 1.12x and 1.45x.
+static Shape shape_of(const Geo& g) {
+  const long long tb = (g.P + 15) / 16;
+  const bool multi = g.NB > (g.m == 2 ? chunk_blocks<2>() : chunk_blocks<4>());
+  Shape best{1, 16, 0, 0};
+  double best_cost = 0.0;
+  auto consider = [&](int nw, int kg, int slots, double cost) {
+    const int nky = (g.K + 16 * kg - 1) / (16 * kg);
+    const double c = (double)((tb * nky + slots - 1) / slots) * cost;
+    if (best.nky == 0 || c < best_cost) {
+      best = Shape{kg, nw, nky, tb * nky};
+      best_cost = c;
+    }
+  };
+  constexpr double kCost16[3] = {1.0, 1.08, 1.25}, kCost8[3] = {1.3, 1.4, 1.6}, kCost12[3] = {1.0, 1.12, 1.45};
+  for (int i = 0; i < (multi ? 1 : 3); i++) {
+    consider(g.m == 2 ? 16 : 12, 1 << i, 256, g.m == 2 ? kCost16[i] : kCost12[i]);
+    // (two workgroups of eight waves need half of the LDS each)
+    if (g.m == 2 && g.NB <= 4) consider(8, 1 << i, 512, kCost8[i]);
+  }
+  return best;
+}
+}  // namespace pos
+
+static bool conv_fused_pos_applicable(const Geo& g) {
+  return (long long)g.N * g.C * g.H * g.W * 4 < 0x7FF00000LL &&
+         (long long)g.N * g.K * g.Ho * g.Wo * 4 < 0xFFFFFFF0LL;
+}
+
+// Where the line lies (us per fused call, the plan that would run otherwise against this one; N, C,
+// K, image):
+//  * F(4x4), at most 16 channels: always (the fallback plan: N14 16->32 116x130 124 -> 41,
+//    N9 16->128 97^2 NHWC 194 -> 111, N5 16->512 12^2 123 -> 16).
+//  * F(2x2), at most 16 channels: while conv_fused_c16's workgroups of 256 tiles leave most of the
+//    chip idle (N3 4->43 112x95 32 -> 16, N11 5->58 58^2 46 -> 24, N1 3->64 224^2 20.5 -> 19.3,
+//    N4 3->64 224^2 33 against 66).
+//  * F(2x2), 17 to 128 channels: up to two workgroups of eight waves per compute unit (N4 32->128 63^2
+//    31.5 -> 21, N1 64->128 112^2 18.9 -> 14.4, N1 64->64 224^2 15.6 against 27).
+//  * the rest: one workgroup per compute unit (N1 512->512 28^2 23 -> 16.7, N1 128->256 56^2 F(4x4)
+//    44 -> 15, N4 256->512 28^2 24 against 28, N23 38->52 108^2 F(4x4) 51 against 95).
+bool conv_fused_pos_preferred(const Geo& g) {
+  if (!conv_fused_pos_applicable(g)) return false;
+  if (g.C <= 16) return g.m == 4 || g.P <= 12800;
+  return pos::shape_of(g).groups <= (g.m == 2 && g.NB <= 2 ? 512 : 256);
+}
+
+hipError_t launch_conv_fused_pos(const Geo& g, const float* x, const int8_t* uq,
+                                 const float* u_range, const int32_t* u_rowsum,
+                                 const float* partial, int count, float* v_range, float* y,
+                                 hipStream_t s) {
+  if (!conv_fused_pos_applicable(g)) return hipErrorInvalidValue;
+  const bool is_static = (g.flags & LANCE_INPUT_RANGE_STATIC) != 0;
+  const pos::Shape sh = pos::shape_of(g);
+  if (sh.groups > 0x7FFFFFFFLL) return hipErrorInvalidValue;
+  const pos::CpArgs a{x, uq, u_range, u_rowsum, partial, v_range, y, count,
+                      (g.flags & LANCE_RANGE_PER_TENSOR) ? 1 : 0, is_static ? 1 : 0,
+                      g.N, g.C, g.H, g.W, g.K, g.pad, g.P, g.th, g.tw, g.Ho, g.Wo, g.bits, g.bits_w,
+                      g.NB, g.Q, g.CB == 16 ? 1 : (is_packed(g) ? 2 : 0), sh.nky,
+                      (unsigned)((size_t)g.N * g.C * g.H * g.W * 4),
+                      (unsigned)((size_t)g.N * g.K * g.Ho * g.Wo * 4)};
+  // One channel per lane where four would leave waves without work (at most two blocks), and where
+  // NHWC pixels cannot be loaded four channels at a time.
+  int load, cpl = g.NB > 2 ? 4 : 1;
+  if (is_nhwc(g)) {
+    const bool wide = g.m == 2 && cpl == 4 && g.C % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0;
+    load = wide ? pos::kNhwc4 : pos::kNhwc1;
+    if (!wide) cpl = 1;
+  } else {
+    load = patch_edge_cols_only(g) ? pos::kRowsEdge : pos::kRowsAny;
+  }
+  const bool clamp = is_static && g.bits < 8;  // dynamic ranges never exceed the last code
+  if (g.m == 4) return pos::launch_m4(a, clamp, cpl, load, sh.kg, s);
+  if (sh.nw == 16)
+    return clamp ? pos::launch<2, 16, true>(a, cpl, load, sh.kg, s) : pos::launch<2, 16, false>(a, cpl, load, sh.kg, s);
+  return clamp ? pos::launch<2, 8, true>(a, cpl, load, sh.kg, s) : pos::launch<2, 8, false>(a, cpl, load, sh.kg, s);
+}
+
+}  // namespace lance

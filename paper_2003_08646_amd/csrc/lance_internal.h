@@ -193,6 +193,14 @@ hipError_t launch_conv_fused_c16(const Geo& g, const float* x, const int8_t* uq,
                                  const float* qparams, const float* dq, const double* dqd,
                                  const int32_t* u_rowsum, float* y, const float* static_v_range,
                                  const float* u_range, hipStream_t s);
+// Range reduction, quantize pass, products and epilogue in one kernel for layers with few tiles
+// (conv_fused_pos.h): both tile sizes and layouts, any number of channels, packed filter codes.
+// partial/count and v_range as for launch_conv_fused_c64.
+bool conv_fused_pos_preferred(const Geo& g);
+hipError_t launch_conv_fused_pos(const Geo& g, const float* x, const int8_t* uq,
+                                 const float* u_range, const int32_t* u_rowsum,
+                                 const float* partial, int count, float* v_range, float* y,
+                                 hipStream_t s);
 // LDS-tiled fused GEMM for F(2x2,3x3) layers with several channel blocks (gemm_fused_tiled.hip).
 bool gemm_fused_tiled_applicable(const Geo& g);
 hipError_t launch_gemm_fused_tiled(const Geo& g, const int8_t* uq, const int8_t* vq,

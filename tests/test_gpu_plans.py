@@ -1,0 +1,92 @@
+"""GPU parity at the edges of the fused call's dispatch: every way conv_fused_pos cuts a layer (one,
+two and four groups of 16 filters, 8 and 16 waves, several turns of channel blocks, one and four
+channels per lane, caller-supplied ranges of narrow codes), and the other plans on layers large
+enough to be theirs with ragged sizes.  Same bars as test_gpu_parity.py."""
+import numpy as np
+import pytest
+
+from paper_2003_08646_amd import workloads as Wk
+from test_gpu_parity import _check_layer, O
+
+pytestmark = pytest.mark.gpu
+
+
+def _range_of_another_batch(L):
+    """Ranges calibrated on other inputs: some values of this batch fall outside and are clamped."""
+    X, Wt = Wk.make_inputs(L.with_(seed=L.seed + 1000))
+    return 0.7 * O.lance_conv(X, Wt, L.pad, L.m, L.bits, bits_w=L.bits_w).v_range
+
+
+# N, C, K, H, W, pad, m, bits, nhwc
+_SPLITS = [
+    (40, 20, 70, 14, 14, 1, 2, 8, False),    # four groups of filters, 16 waves
+    (20, 33, 60, 14, 14, 1, 2, 8, False),    # two groups, 16 waves
+    (90, 40, 70, 14, 15, 1, 2, 6, False),    # 8 waves, odd width
+    (60, 130, 40, 12, 12, 0, 2, 8, False),   # four channels per lane
+    (3, 600, 20, 9, 8, 1, 2, 8, False),      # two turns of channel blocks
+    (4, 580, 20, 7, 7, 2, 2, 5, True),       # the same with 16-byte NHWC loads
+    (3, 601, 17, 6, 6, 1, 2, 8, True),       # and with 4-byte ones
+    (33, 18, 70, 15, 16, 1, 4, 8, False),    # F(4x4): two groups
+    (90, 30, 70, 16, 13, 1, 4, 5, False),    # four groups, odd width
+    (20, 150, 24, 9, 11, 0, 4, 8, False),    # four channels per lane
+    (2, 330, 20, 9, 10, 1, 4, 6, False),     # two turns
+    (2, 200, 20, 9, 10, 1, 4, 8, True),
+    (30, 7, 70, 33, 31, 1, 4, 8, False),     # at most 16 channels
+    (8, 16, 40, 33, 31, 3, 4, 4, True),
+    (2, 5, 300, 20, 18, 1, 2, 7, True),
+    (1, 6, 5, 3, 2, 5, 2, 8, False),         # more padding than image
+]
+
+
+@pytest.mark.parametrize("shape", _SPLITS, ids=lambda s: "n%d_c%d_k%d_%dx%d_p%d_m%d_b%d%s" % (s[:8] + ("_nhwc" if s[8] else "",)))
+@pytest.mark.parametrize("static", [False, True], ids=["dynamic", "static"])
+def test_position_parallel_splits(shape, static):
+    from paper_2003_08646_amd import binding as B
+    N, C, K, H, W, pad, m, bits, nhwc = shape
+    L = Wk.Layer("split", N, C, K, H, W, pad=pad, m=m, bits=bits, seed=500 + C)
+    flags = (B.LANCE_LAYOUT_NHWC if nhwc else 0) | (B.LANCE_INPUT_RANGE_STATIC if static else 0)
+    _check_layer(L, flags=flags, static_v_range=_range_of_another_batch(L) if static else None, staged=False)
+
+
+@pytest.mark.parametrize("m", [2, 4])
+@pytest.mark.parametrize("nhwc", [False, True], ids=["nchw", "nhwc"])
+def test_position_parallel_packed(m, nhwc):
+    from paper_2003_08646_amd import binding as B
+    L = Wk.Layer("packed", 20, 70, 50, 13, 12, m=m, bits=4, bits_w=3, seed=520)
+    _check_layer(L, flags=B.LANCE_CODES_PACKED4 | (B.LANCE_LAYOUT_NHWC if nhwc else 0), staged=False)
+
+
+# layers of more tiles than conv_fused_pos takes: the other plans with partial blocks and odd sizes
+_LARGE = [
+    (330, 60, 40, 9, 11, 0, 2, 8, False),
+    (200, 50, 70, 13, 14, 1, 2, 5, False),
+    (60, 64, 130, 24, 24, 1, 2, 8, False),
+    (330, 60, 40, 10, 9, 1, 2, 8, True),
+    (120, 100, 130, 13, 15, 1, 2, 8, False),
+    (100, 96, 70, 16, 16, 1, 2, 6, False),
+    (110, 72, 130, 14, 13, 0, 2, 8, True),
+    (80, 150, 130, 13, 15, 1, 2, 8, False),
+    (60, 192, 300, 14, 14, 1, 2, 8, False),
+    (70, 140, 130, 14, 15, 0, 2, 7, True),
+    (100, 40, 130, 20, 21, 1, 4, 8, False),
+    (60, 100, 130, 24, 24, 1, 4, 6, False),
+    (60, 150, 300, 15, 17, 1, 4, 8, False),
+    (60, 70, 130, 17, 16, 0, 4, 8, True),
+    (60, 12, 40, 33, 31, 1, 2, 8, False),
+    (60, 3, 70, 32, 32, 1, 2, 8, True),
+]
+
+
+@pytest.mark.parametrize("shape", _LARGE, ids=lambda s: "n%d_c%d_k%d_%dx%d_p%d_m%d_b%d%s" % (s[:8] + ("_nhwc" if s[8] else "",)))
+def test_other_plans_on_many_tiles(shape):
+    from paper_2003_08646_amd import binding as B
+    N, C, K, H, W, pad, m, bits, nhwc = shape
+    L = Wk.Layer("many_tiles", N, C, K, H, W, pad=pad, m=m, bits=bits, seed=540 + C)
+    _check_layer(L, flags=B.LANCE_LAYOUT_NHWC if nhwc else 0, staged=False)
+
+
+@pytest.mark.parametrize("m", [2, 4])
+def test_packed_on_many_tiles(m):
+    from paper_2003_08646_amd import binding as B
+    L = Wk.Layer("packed_many", 80, 130, 200, 14, 16, m=m, bits=4, seed=560)
+    _check_layer(L, flags=B.LANCE_CODES_PACKED4, staged=False)
