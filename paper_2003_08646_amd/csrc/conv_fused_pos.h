@@ -31,13 +31,12 @@
 #pragma once
 #include "lance_device.h"
 #include "lance_internal.h"
+#include "tile_loader.h"
 
 namespace lance {
 namespace pos {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef float v2f __attribute__((ext_vector_type(2)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
 
@@ -57,15 +56,7 @@ struct CpArgs {
   unsigned x_bytes, y_bytes;
 };
 
-// How the patches are loaded.
-constexpr int kRowsEdge = 0;  // NCHW, one row load per patch row; only the edge columns can be outside
-constexpr int kRowsAny = 1;   // NCHW, one row load per patch row; any column can be outside
-constexpr int kNhwc1 = 2;     // NHWC, 4-byte loads (CPL = 1)
-constexpr int kNhwc4 = 3;     // NHWC, 16-byte loads of four channels (CPL = 4, C a multiple of 4)
-
-constexpr unsigned kOutside = 0x80000000u;  // x_bytes is below 2^31
 constexpr unsigned kOobY = 0xFFFFFFF0u;
-constexpr unsigned kGuard = 16;
 
 // channel blocks whose codes are in LDS at a time
 template <int M> constexpr int chunk_blocks() { return M == 2 ? 8 : 3; }
@@ -73,18 +64,6 @@ constexpr int kConstBytes = 2048;  // parameter tables at the start of LDS
 
 __device__ __forceinline__ int swz(int row) { return (row >> 2) & 3; }
 
-__device__ __forceinline__ v4f load_b128(const char* base, unsigned extent, unsigned off) {
-  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, extent, 0x00020000);
-  return __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
-}
-__device__ __forceinline__ v2f load_b64(const char* base, unsigned extent, unsigned off) {
-  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, extent, 0x00020000);
-  return __builtin_bit_cast(v2f, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
-}
-__device__ __forceinline__ float load_b32(const char* base, unsigned extent, unsigned off) {
-  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, extent, 0x00020000);
-  return __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
-}
 template <int M>
 __device__ __forceinline__ void store_row(float* y, unsigned y_bytes, unsigned off, const float (&v)[M]) {
   const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(y, 0, y_bytes, 0x00020000);
@@ -99,21 +78,6 @@ __device__ __forceinline__ void store_row(float* y, unsigned y_bytes, unsigned o
 __device__ __forceinline__ void store_b32(float* y, unsigned y_bytes, unsigned off, float v) {
   const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(y, 0, y_bytes, 0x00020000);
   __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, off, 0, 0);
-}
-
-// s = A^T v for one column or row of M+2 values (binary32, output transform of Eq. 9).
-template <int M>
-__device__ __forceinline__ void out1d(const float (&v)[M + 2], float (&s)[M]) {
-  if constexpr (M == 2) {
-    s[0] = (v[0] + v[1]) + v[2];
-    s[1] = (v[1] - v[2]) - v[3];
-  } else {
-    const float s1 = v[1] + v[2], d1 = v[1] - v[2], s2 = v[3] + v[4], d2 = v[3] - v[4];
-    s[0] = (v[0] + s1) + s2;
-    s[1] = __builtin_fmaf(2.0f, d2, d1);
-    s[2] = __builtin_fmaf(4.0f, s2, s1);
-    s[3] = __builtin_fmaf(8.0f, d2, d1) + v[5];
-  }
 }
 
 // MULTI: more channel blocks than LDS holds at a time (KG = 1 only: the sums live across phase T).
@@ -142,77 +106,16 @@ __global__ __launch_bounds__(NW * 64, (M == 2 ? 16 : 12) / 4) void conv_fused_po
   // holds few of them
   const int ky = blockIdx.x % a.nky, p0 = (blockIdx.x / a.nky) * 16, k0 = ky * 16 * KG;
   const int K = a.K, P = a.P, C = a.C;
-  const unsigned HW = (unsigned)a.H * (unsigned)a.W;
   const bool b8 = a.bits == 8;
 
   // ---- the lane's tile ----
   // NCHW: 16 tiles x 4 dwords per wave; NHWC: channels fastest, for the coalescing of the loads
   const int trow = LOAD == kNhwc4 ? lane >> 2 : (LOAD == kNhwc1 ? 4 * (wave & 3) + (lane >> 4) : lane & 15);
   const int dl = LOAD == kNhwc4 ? lane & 3 : (LOAD == kNhwc1 ? lane & 15 : lane >> 4);
-  const int pt = min(p0 + trow, P - 1);
-  const int tx = pt % a.tw, t2 = pt / a.tw;
-  const int ty = t2 % a.th, n = t2 / a.th;
-  const int iy0 = ty * M - a.pad, ix0 = tx * M - a.pad;
-  unsigned rowoff[A], cmask[A];
-  bool first = false, last = false;  // a row load in the tensor's first / last plane leaves the tensor
-#pragma unroll
-  for (int r = 0; r < A; r++) {
-    const int iy = iy0 + r;
-    const bool ok = iy >= 0 && iy < a.H;
-    if constexpr (kNhwc) {
-      rowoff[r] = ok ? (((unsigned)n * (unsigned)a.H + (unsigned)iy) * (unsigned)a.W + (unsigned)ix0) *
-                               (unsigned)C * 4u
-                     : kOutside;
-    } else {
-      rowoff[r] = ok ? (((unsigned)n * (unsigned)C + (unsigned)dl) * HW + (unsigned)iy * (unsigned)a.W +
-                        (unsigned)ix0) * 4u + kGuard
-                     : kOutside;
-      first |= ok && n == 0 && iy * a.W + ix0 < 0;
-      last |= ok && n == a.N - 1 && iy * a.W + ix0 + A > (int)HW;
-    }
-  }
-#pragma unroll
-  for (int s = 0; s < A; s++) cmask[s] = (ix0 + s >= 0 && ix0 + s < a.W) ? 0xFFFFFFFFu : 0u;
-  const bool any_first = __ballot(first) != 0, any_last = __ballot(last) != 0;
-
-  // One channel of the lane's patch.  NCHW: channel cu + dl (cu wave-uniform, below C); lanes whose
-  // channel does not exist read anything inside the tensor or zero.  A row load may start before
-  // or end after its image row (cmask deals with that), in the tensor's first and last plane also
-  // before or after the tensor: those load pixel by pixel.
-  auto load = [&](int cu, float (&b)[A * A]) {
-    if constexpr (LOAD == kNhwc1) {
-      const unsigned c4 = (unsigned)min(cu + dl, C - 1) * 4u, px = (unsigned)C * 4u;
-      const char* base = reinterpret_cast<const char*>(a.x);
-#pragma unroll
-      for (int r = 0; r < A; r++)
-#pragma unroll
-        for (int s = 0; s < A; s++) b[r * A + s] = load_b32(base, a.x_bytes, rowoff[r] + (c4 + (unsigned)s * px));
-    } else if constexpr (LOAD != kNhwc4) {
-      const unsigned plane = (unsigned)cu * HW * 4u;
-      const char* base = reinterpret_cast<const char*>(a.x) + plane - kGuard;
-      const unsigned extent = a.x_bytes + kGuard - plane;
-      if ((any_first && cu == 0) || (any_last && cu + 4 >= C)) {
-        // (offsets from a copy the compiler cannot see through: formed here, not kept in registers)
-        int ix = ix0;
-        asm volatile("" : "+v"(ix));
-#pragma unroll
-        for (int r = 0; r < A; r++)
-#pragma unroll
-          for (int s = 0; s < A; s++)
-            b[r * A + s] = load_b32(base, extent, (ix + s >= 0 && ix + s < a.W) ? rowoff[r] + 4u * s : kOutside);
-      } else {
-#pragma unroll
-        for (int r = 0; r < A; r++) {
-          const v4f v = load_b128(base, extent, rowoff[r]);
-          b[r * A] = v[0]; b[r * A + 1] = v[1]; b[r * A + 2] = v[2]; b[r * A + 3] = v[3];
-          if constexpr (A == 6) {
-            const v2f w = load_b64(base, extent, rowoff[r] + 16u);
-            b[r * A + 4] = w[0]; b[r * A + 5] = w[1];
-          }
-        }
-      }
-    }
-  };
+  const TileGeo tg{a.x, a.x_bytes, a.N, C, a.H, a.W, a.pad, P, a.th, a.tw};
+  TileLoader<M, LOAD> tl;
+  tl.setup(tg, min(p0 + trow, P - 1), dl);
+  auto load = [&](int cu, float (&b)[A * A]) { tl.load(tg, cu, b); };
   const float L = (float)((1 << a.bits) - 1);
   // code q (byte) of the dword codes[e] from the patch b
   auto quantize = [&](const float (&b)[A * A], auto qc, unsigned (&codes)[E]) {
@@ -220,13 +123,7 @@ __global__ __launch_bounds__(NW * 64, (M == 2 ? 16 : 12) / 4) void conv_fused_po
     // (F(4x4): the parameters are read again for every channel instead of living in 72 registers)
     if constexpr (M == 4) asm volatile("" ::: "memory");
     float d[A][A];
-#pragma unroll
-    for (int r = 0; r < A; r++)
-#pragma unroll
-      for (int s = 0; s < A; s++)
-        d[r][s] = (LOAD == kRowsEdge && s > 0 && s < A - 1)
-                      ? b[r * A + s]
-                      : __uint_as_float(__float_as_uint(b[r * A + s]) & cmask[s]);
+    tl.mask(b, d);
     dev::input_tile_transform<M>(d);
 #pragma unroll
     for (int e = 0; e < E; e++) {
@@ -367,14 +264,8 @@ __global__ __launch_bounds__(NW * 64, (M == 2 ? 16 : 12) / 4) void conv_fused_po
         if constexpr (LOAD == kNhwc4) {
           const int bb = it / per_block, dg = it % per_block;
           const int cb = c0 + bb * 64 + (4 * dg + dl) * 4;  // the lane's four channels
-          const unsigned c4 = (unsigned)min(cb, C - 4) * 4u, px = (unsigned)C * 4u;
           v4f w[A * A];
-#pragma unroll
-          for (int r = 0; r < A; r++)
-#pragma unroll
-            for (int s = 0; s < A; s++)
-              w[r * A + s] = load_b128(reinterpret_cast<const char*>(a.x), a.x_bytes,
-                                       rowoff[r] + (c4 + (unsigned)s * px));
+          tl.load4(tg, min(cb, C - 4), w);
           auto one = [&](auto qc) {
             float b[A * A];
 #pragma unroll
@@ -509,12 +400,12 @@ __global__ __launch_bounds__(NW * 64, (M == 2 ? 16 : 12) / 4) void conv_fused_po
       float v[A], s[M];
 #pragma unroll
       for (int r = 0; r < A; r++) v[r] = ex[((r * A + j) * KG + kg) * 256 + idx];
-      out1d<M>(v, s);
+      dev::out1d<M>(v, s);
 #pragma unroll
       for (int r = 0; r < M; r++) t[r][j] = s[r];
     }
 #pragma unroll
-    for (int r = 0; r < M; r++) out1d<M>(t[r], o[r]);
+    for (int r = 0; r < M; r++) dev::out1d<M>(t[r], o[r]);
     const int ox0 = (p % a.tw) * M, q2 = p / a.tw;
     const int oy0 = (q2 % a.th) * M, on = q2 / a.th;
     if constexpr (kNhwc) {
@@ -566,7 +457,7 @@ inline hipError_t launch_one(const CpArgs& a, unsigned grid, size_t lds, hipStre
 
 template <int M, int NW, int CPL, int LOAD, bool CLAMP>
 inline hipError_t launch_kg(const CpArgs& a, int kg, unsigned grid, size_t lds, hipStream_t s) {
-  if constexpr (CPL == 4 || LOAD == kNhwc1)
+  if constexpr (NW != 8 && (CPL == 4 || LOAD == kNhwc1))
     if (a.NB > chunk_blocks<M>()) return launch_one<M, NW, CPL, 1, LOAD, CLAMP, true>(a, grid, lds, s);
   switch (kg) {
     case 1: return launch_one<M, NW, CPL, 1, LOAD, CLAMP, false>(a, grid, lds, s);

@@ -103,6 +103,21 @@ __device__ __forceinline__ void input_tile_transform(float (&d)[Wino<M>::A][Wino
   }
 }
 
+// s = A^T v for one column or row of M+2 values (binary32, output transform of Eq. 9).
+template <int M>
+__device__ __forceinline__ void out1d(const float (&v)[M + 2], float (&s)[M]) {
+  if constexpr (M == 2) {
+    s[0] = (v[0] + v[1]) + v[2];
+    s[1] = (v[1] - v[2]) - v[3];
+  } else {
+    const float s1 = v[1] + v[2], d1 = v[1] - v[2], s2 = v[3] + v[4], d2 = v[3] - v[4];
+    s[0] = (v[0] + s1) + s2;
+    s[1] = __builtin_fmaf(2.0f, d2, d1);
+    s[2] = __builtin_fmaf(4.0f, s2, s1);
+    s[3] = __builtin_fmaf(8.0f, d2, d1) + v[5];
+  }
+}
+
 // U = G g G^T for one 3x3 filter.
 template <int M>
 __device__ __forceinline__ void filter_tile_transform(const float (&g)[3][3],

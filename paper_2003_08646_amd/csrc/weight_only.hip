@@ -1,20 +1,279 @@
 // Weight-only quantization (Sec. 4, the 4-32 row of Table 2): filters quantized in the Winograd
 // domain (Eq. 7, prepared by the filter transform), inputs transformed but not quantized:
 //   M[e,k,p] = sum_c Q'(u^[e,k,c]) * (B^T d_{p,c} B)[e],   S = A^T M A          (Eq. 8, Eq. 9)
-// The channel sum is a binary32 product in the Winograd domain, not this library's integer one,
-// so the matrix-core kernels do not apply; this is a plain vector-ALU kernel.
 //
-// Lane = tile, a workgroup takes 256 tiles and kF filters.  Per channel every lane transforms
-// its own patch; kF*E threads de-quantize the workgroup's filter codes of that channel into LDS
-// (u~ = code * scale_e + min_e with the unsigned code of Eq. 7); E multiply-adds per filter and
-// lane follow.  The patch transform is repeated per filter block (K / kF times).
+// The channel sum runs on the bf16 matrix cores without giving up binary32: a filter code is an
+// integer of at most 8 bits and exact in bf16, and a binary32 value is the exact sum of three bf16
+// values (its top 8 significant bits, the next 8, the rest), so three products per value pair, each
+// exact, are added up in binary32; Q' is applied to the sums:
+//   M = scale_e * sum_c code * V + ou_e * sum_c V,   ou = min + scale * 2^(b-1) (codes are signed),
+// the second sum from the same instructions with an operand of ones.
+//
+// weight_only_mfma_kernel: a workgroup of 16 waves (m = 4: 12) takes 16*TG tiles x 16*KG filters,
+// wave w the positions w*E/NW ..  Turn by turn over CH channels: every lane transforms one channel
+// of one tile and writes its three pieces to LDS (rows of 32 values, [E][3][CH/32][TG][16 rows]); the
+// waves multiply.  Then as in conv_fused_pos.h: M to LDS, A^T M A and the stores by (filter, tile)
+// pairs.  uq codes become bf16 in registers, two values per v_perm_b32.
+//
+// What bounds it: the vector ALUs (transform, three-way split, conversion of the codes) and, on small
+// layers, the chain of steps of a workgroup.  N32 64->64 32x32: 101 us on the vector-ALU kernel, 13.6
+// us now; N2 249->21 53x38: 407 -> 14.8 us; N2 16->64 106x106 F(4x4): 87 -> 10 us.  Relative error
+// against binary64 on the first: 2.7e-7 before, 1.5e-7 now.
+//
+// weight_only_kernel: the vector-ALU form (lane = tile, E multiply-adds per channel and filter), for
+// inputs of 2 GiB and more, beyond the 32-bit row offsets of the other.
 #include "lance_device.h"
 #include "lance_internal.h"
+#include "tile_loader.h"
 
 namespace lance {
 namespace {
 
 constexpr int kThreads = 256;
+
+typedef short bf8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned v4u __attribute__((ext_vector_type(4)));
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
+using pos::v4f;
+
+struct WmArgs {
+  const float* x;
+  const int8_t* uq;
+  const float* u_range;
+  float* y;
+  int N, C, H, W, K, pad, P, th, tw, Ho, Wo, bits_w, NB, cb16, nky;
+  unsigned x_bytes, y_bytes;
+};
+
+constexpr unsigned kOobY = 0xFFFFFFF0u;
+
+__device__ __forceinline__ void store1(float* y, unsigned y_bytes, unsigned off, float v) {
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(y, 0, y_bytes, 0x00020000);
+  __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, off, 0, 0);
+}
+template <int M>
+__device__ __forceinline__ void store_row(float* y, unsigned y_bytes, unsigned off, const float (&v)[M]) {
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(y, 0, y_bytes, 0x00020000);
+  if constexpr (M == 2) {
+    const v2u u = {__float_as_uint(v[0]), __float_as_uint(v[1])};
+    __builtin_amdgcn_raw_buffer_store_b64(u, r, off, 0, 0);
+  } else {
+    const v4u u = {__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
+    __builtin_amdgcn_raw_buffer_store_b128(u, r, off, 0, 0);
+  }
+}
+
+// Eight signed codes (two dwords of a code row) as bf16; exact.
+__device__ __forceinline__ bf16x8 codes_to_bf16(v2u c) {
+  v4u r;
+#pragma unroll
+  for (int i = 0; i < 2; i++) {
+    const unsigned u = c[i] ^ 0x80808080u;  // code + 128
+    float f[4];
+    f[0] = (float)(u & 0xFFu) - 128.0f;
+    f[1] = (float)((u >> 8) & 0xFFu) - 128.0f;
+    f[2] = (float)((u >> 16) & 0xFFu) - 128.0f;
+    f[3] = (float)(u >> 24) - 128.0f;
+    // the upper halves of two binary32 values side by side
+    r[2 * i] = __builtin_amdgcn_perm(__float_as_uint(f[1]), __float_as_uint(f[0]), 0x07060302u);
+    r[2 * i + 1] = __builtin_amdgcn_perm(__float_as_uint(f[3]), __float_as_uint(f[2]), 0x07060302u);
+  }
+  return __builtin_bit_cast(bf16x8, r);
+}
+
+template <int M, int TG, int KG, int LOAD>
+__global__ __launch_bounds__(M == 2 ? 1024 : 768) void weight_only_mfma_kernel(const WmArgs a) {
+  constexpr int A = M + 2, E = A * A, NW = M == 2 ? 16 : 12, NT = NW * 64, PW = E / NW;
+  constexpr bool kNhwc = LOAD == pos::kNhwc1;
+  constexpr int NH = M == 2 ? 2 / TG : 1;  // rows of 32 values per turn: CH = 32 * NH channels
+  static_assert(M == 2 || TG == 1, "LDS");
+  extern __shared__ char smem[];
+  float* sc_s = reinterpret_cast<float*>(smem);  // [E] scale
+  float* ou_s = sc_s + E;                        // [E] min + scale * 2^(b-1)
+  char* ring = smem + 512;                       // [E][3][NH][TG][16 rows][64 B]
+  float* ex = reinterpret_cast<float*>(ring);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ky = blockIdx.x % a.nky, p0 = (blockIdx.x / a.nky) * 16 * TG, k0 = ky * 16 * KG;
+  const int K = a.K, P = a.P, C = a.C;
+
+  // The wave's part of a turn, the same in every turn: NCHW: 16 tiles, the dwords 4g .. 4g+3 of row
+  // nh, byte q of each (the lane's channel is dl = lane / 16 dwords up); NHWC: 4 tiles, 16 channels.
+  const int item = kNhwc ? wave >> 2 : wave;
+  constexpr int kPerRow = kNhwc ? 2 : 8;
+  const bool has_item = item < kPerRow * NH * TG;
+  const int sub = item % kPerRow, nh = (item / kPerRow) % NH, tgi = (item / kPerRow / NH) % TG;
+  const int trow = kNhwc ? 4 * (wave & 3) + (lane >> 4) : lane & 15;
+  const int dl = kNhwc ? lane & 15 : lane >> 4;
+  const int g = sub >> 2, q = sub & 3;
+  const pos::TileGeo tg{a.x, a.x_bytes, a.N, C, a.H, a.W, a.pad, P, a.th, a.tw};
+  pos::TileLoader<M, LOAD> tl;
+  tl.setup(tg, min(p0 + 16 * tgi + trow, P - 1), dl);
+  // row of 32 values number r of the channel axis: half r & 1 of channel block r / 2
+  const int rows = a.cb16 ? 1 : 2 * a.NB;
+  // channel of the lane with dl = 0; >= C: no such channel (with 16-byte code rows the positions
+  // beyond the 16th stand for no channel)
+  auto chan = [&](int r) -> int {
+    if (a.cb16) return kNhwc ? (sub == 0 ? 0 : C) : (g == 0 ? 4 * q : C);
+    return kNhwc ? r * 32 + 16 * sub : (r >> 1) * 64 + 8 * (r & 1) + 4 * g + 16 * q;
+  };
+  const int j = kNhwc ? 16 * sub + dl : 4 * (4 * g + dl) + q;  // the lane's value in its row
+  const unsigned dst = (unsigned)((nh * TG + tgi) * 1024 + trow * 64 + (((j >> 3) ^ ((trow >> 2) & 3)) * 16) + (j & 7) * 2);
+  constexpr unsigned kPiece = NH * TG * 1024u;
+
+  float cur[A * A];
+  auto request = [&](int r0) {
+    if (has_item && r0 + nh < rows) tl.load(tg, min(chan(r0 + nh), C - 1), cur);
+  };
+  request(0);
+  if (tid < E) {
+    const float mn = a.u_range[2 * tid], mx = a.u_range[2 * tid + 1];
+    float inv, scale;
+    dev::quant_params(mn, mx, a.bits_w, &inv, &scale);
+    sc_s[tid] = scale;
+    ou_s[tid] = (float)((double)mn + (double)scale * (double)(1 << (a.bits_w - 1)));
+  }
+
+  const int col = lane & 15, kq = lane >> 4;
+  const unsigned f_off = (unsigned)(col * 64 + ((kq ^ ((col >> 2) & 3)) * 16));
+  v4f acc[PW][TG][KG], vsum[PW][TG];
+#pragma unroll
+  for (int w = 0; w < PW; w++)
+#pragma unroll
+    for (int t = 0; t < TG; t++) {
+      vsum[w][t] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int kg = 0; kg < KG; kg++) acc[w][t][kg] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+  const v4u ones_u = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+  const bf16x8 ones = __builtin_bit_cast(bf16x8, ones_u);
+
+  for (int r0 = 0; r0 < rows; r0 += NH) {
+    const int nrow = min(NH, rows - r0);
+    if (has_item && nh < nrow) {
+      float d[A][A];
+      tl.mask(cur, d);
+      if (chan(r0 + nh) + dl >= C) {
+#pragma unroll
+        for (int e = 0; e < E; e++) d[e / A][e % A] = 0.0f;
+      }
+      dev::input_tile_transform<M>(d);
+#pragma unroll
+      for (int e = 0; e < E; e++) {
+        const float v = d[e / A][e % A];
+        const unsigned hi = __float_as_uint(v) & 0xFFFF0000u;
+        const float r1 = v - __uint_as_float(hi);
+        const unsigned mid = __float_as_uint(r1) & 0xFFFF0000u;
+        const float r2 = r1 - __uint_as_float(mid);
+        char* at = ring + (unsigned)(e * 3) * kPiece + dst;
+        *reinterpret_cast<uint16_t*>(at) = (uint16_t)(hi >> 16);
+        *reinterpret_cast<uint16_t*>(at + kPiece) = (uint16_t)(mid >> 16);
+        *reinterpret_cast<uint16_t*>(at + 2 * kPiece) = (uint16_t)(__float_as_uint(r2) >> 16);
+      }
+    }
+    request(r0 + NH);  // in flight under the products
+    v2u code[PW][NH][KG];
+#pragma unroll
+    for (int w = 0; w < PW; w++)
+#pragma unroll
+      for (int r = 0; r < NH; r++)
+#pragma unroll
+        for (int kg = 0; kg < KG; kg++) {
+          const int e = wave * PW + w, krow = min(k0 + kg * 16 + col, K - 1);
+          const int rr = min(r0 + r, rows - 1);
+          const int8_t* src = a.cb16 ? a.uq + ((size_t)e * K + krow) * 16 + 8 * (kq & 1)
+                                     : a.uq + (((size_t)e * a.NB + (rr >> 1)) * K + krow) * 64 + 32 * (rr & 1) + 8 * kq;
+          code[w][r][kg] = *reinterpret_cast<const v2u*>(src);
+          if (a.cb16 && kq > 1) code[w][r][kg] = v2u{0u, 0u};
+        }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < PW; w++)
+#pragma unroll
+      for (int r = 0; r < NH; r++) {
+        if (r < nrow) {
+          bf16x8 af[KG];
+#pragma unroll
+          for (int kg = 0; kg < KG; kg++) af[kg] = codes_to_bf16(code[w][r][kg]);
+#pragma unroll
+          for (int t = 0; t < TG; t++)
+#pragma unroll
+            for (int pc = 2; pc >= 0; pc--) {  // the small pieces first
+              const char* bp = ring + (unsigned)((wave * PW + w) * 3 + pc) * kPiece + (unsigned)((r * TG + t) * 1024) + f_off;
+              const bf16x8 bf = *reinterpret_cast<const bf16x8*>(bp);
+              vsum[w][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, bf, vsum[w][t], 0, 0, 0);
+#pragma unroll
+              for (int kg = 0; kg < KG; kg++)
+                acc[w][t][kg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[kg], bf, acc[w][t][kg], 0, 0, 0);
+            }
+        }
+      }
+    __syncthreads();
+  }
+
+  // ---- M to LDS; lane: tile col, filters 4*kq .. of each group ----
+#pragma unroll
+  for (int w = 0; w < PW; w++) {
+    const int e = wave * PW + w;
+    const float sc = sc_s[e], ou = ou_s[e];
+#pragma unroll
+    for (int t = 0; t < TG; t++) {
+      const float off = ou * vsum[w][t][0];
+#pragma unroll
+      for (int kg = 0; kg < KG; kg++) {
+        float* dstm = ex + ((e * KG + kg) * TG + t) * 256;
+        v4f m;
+#pragma unroll
+        for (int r = 0; r < 4; r++) m[r] = __builtin_fmaf(sc, acc[w][t][kg][r], off);
+        if constexpr (kNhwc) {
+          *reinterpret_cast<v4f*>(dstm + col * 16 + 4 * kq) = m;
+        } else {
+#pragma unroll
+          for (int r = 0; r < 4; r++) dstm[r * 64 + kq * 16 + col] = m[r];
+        }
+      }
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < KG * TG * 256; i += NT) {
+    const int idx = i & 255, kt = i >> 8;
+    const int kg = kt / TG, t = kt % TG;
+    const int kin = kNhwc ? idx & 15 : 4 * ((idx >> 4) & 3) + (idx >> 6);
+    const int pin = kNhwc ? idx >> 4 : idx & 15;
+    const int k = k0 + kg * 16 + kin, p = p0 + 16 * t + pin;
+    if (k >= K || p >= P) continue;
+    float tt[M][A], o[M][M];
+#pragma unroll
+    for (int jj = 0; jj < A; jj++) {
+      float v[A], s[M];
+#pragma unroll
+      for (int r = 0; r < A; r++) v[r] = ex[(r * A + jj) * KG * TG * 256 + i];
+      dev::out1d<M>(v, s);
+#pragma unroll
+      for (int r = 0; r < M; r++) tt[r][jj] = s[r];
+    }
+#pragma unroll
+    for (int r = 0; r < M; r++) dev::out1d<M>(tt[r], o[r]);
+    const int ox0 = (p % a.tw) * M, q2 = p / a.tw;
+    const int oy0 = (q2 % a.th) * M, on = q2 / a.th;
+    const bool whole = !kNhwc && ox0 + M <= a.Wo;
+#pragma unroll
+    for (int r = 0; r < M; r++) {
+      const bool row = oy0 + r < a.Ho;
+      if (whole) {
+        const unsigned off = (unsigned)dev::act_index(false, on, k, oy0 + r, ox0, K, a.Ho, a.Wo) * 4u;
+        store_row<M>(a.y, a.y_bytes, row ? off : kOobY, o[r]);
+      } else {
+#pragma unroll
+        for (int s = 0; s < M; s++)
+          store1(a.y, a.y_bytes, row && ox0 + s < a.Wo
+                                     ? (unsigned)dev::act_index(kNhwc, on, k, oy0 + r, ox0 + s, K, a.Ho, a.Wo) * 4u
+                                     : kOobY, o[r][s]);
+      }
+    }
+  }
+}
 
 struct WoArgs {
   const float* x;
@@ -117,17 +376,68 @@ __global__ __launch_bounds__(kThreads) void weight_only_kernel(const WoArgs a) {
 
 }  // namespace
 
+template <int M, int TG, int KG>
+static hipError_t launch_mfma(const WmArgs& a, int load, hipStream_t s) {
+  constexpr int E = (M + 2) * (M + 2), NH = M == 2 ? 2 / TG : 1;
+  constexpr size_t codes = (size_t)E * 3 * NH * TG * 1024, exch = (size_t)E * KG * TG * 1024;
+  constexpr size_t lds = 512 + (codes > exch ? codes : exch);
+  const unsigned grid = (unsigned)((a.P + 16 * TG - 1) / (16 * TG)) * (unsigned)a.nky;
+  auto go = [&](auto kern) -> hipError_t {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    kern<<<grid, M == 2 ? 1024 : 768, lds, s>>>(a);
+    return hipGetLastError();
+  };
+  switch (load) {
+    case pos::kRowsEdge: return go(weight_only_mfma_kernel<M, TG, KG, pos::kRowsEdge>);
+    case pos::kRowsAny: return go(weight_only_mfma_kernel<M, TG, KG, pos::kRowsAny>);
+    default: return go(weight_only_mfma_kernel<M, TG, KG, pos::kNhwc1>);
+  }
+}
+
 hipError_t launch_weight_only(const Geo& g, const float* x, const int8_t* uq, const float* u_range,
                               float* y, hipStream_t s) {
-  const WoArgs a{x, uq, u_range, y, g.N, g.C, g.H, g.W, g.K, g.pad, g.th, g.tw, g.P, g.Ho, g.Wo,
-                 g.bits_w, is_nhwc(g) ? 1 : 0, g.CB, g.NB};
-  const int kf = g.m == 2 ? 8 : 4;
-  const long long bx = ((long long)g.P + kThreads - 1) / kThreads, by = (g.K + kf - 1) / kf;
-  if (bx > 0x7FFFFFFFLL || by > 65535) return hipErrorInvalidValue;
-  dim3 grid((unsigned)bx, (unsigned)by, 1);
-  if (g.m == 2) weight_only_kernel<2, 8><<<grid, kThreads, 0, s>>>(a);
-  else weight_only_kernel<4, 4><<<grid, kThreads, 0, s>>>(a);
-  return hipGetLastError();
+  if ((long long)g.N * g.C * g.H * g.W * 4 >= 0x7FF00000LL) {
+    const WoArgs a{x, uq, u_range, y, g.N, g.C, g.H, g.W, g.K, g.pad, g.th, g.tw, g.P, g.Ho, g.Wo,
+                   g.bits_w, is_nhwc(g) ? 1 : 0, g.CB, g.NB};
+    const int kf = g.m == 2 ? 8 : 4;
+    const long long bx = ((long long)g.P + kThreads - 1) / kThreads, by = (g.K + kf - 1) / kf;
+    if (bx > 0x7FFFFFFFLL || by > 65535) return hipErrorInvalidValue;
+    dim3 grid((unsigned)bx, (unsigned)by, 1);
+    if (g.m == 2) weight_only_kernel<2, 8><<<grid, kThreads, 0, s>>>(a);
+    else weight_only_kernel<4, 4><<<grid, kThreads, 0, s>>>(a);
+    return hipGetLastError();
+  }
+  // Smallest (rounds of one workgroup per compute unit: LDS) x (relative time of a workgroup).  The
+  // times are from sweeps of the six shapes over layers of 3 to 400 channels; 64 -> 64 channels, 8192
+  // tiles: 13.6 us with (2, 4) = 256 workgroups, 16.8 with (1, 4), 25 with (1, 2), 37 with (1, 1);
+  // 249 -> 21 channels, 1026 tiles: 14.8 with (1, 1), 33 with (2, 4).
+  static constexpr double kCost[2][3] = {{1.0, 1.2, 1.55}, {1.55, 1.85, 2.45}};
+  int best_tg = 1, best_kg = 1;
+  double best = 0.0;
+  for (int tgi = 1; tgi <= (g.m == 2 ? 2 : 1); tgi++)
+    for (int i = 0; i < (g.m == 2 ? 3 : 2); i++) {
+      const int kg = 1 << i;
+      const long long groups = ((g.P + 16LL * tgi - 1) / (16 * tgi)) * ((g.K + 16 * kg - 1) / (16 * kg));
+      const double c = (double)((groups + 255) / 256) * kCost[tgi - 1][i];
+      if (best == 0.0 || c < best) { best = c; best_tg = tgi; best_kg = kg; }
+    }
+  const int nky = (g.K + 16 * best_kg - 1) / (16 * best_kg);
+  if (((g.P + 15LL) / 16) * nky > 0x7FFFFFFFLL) return hipErrorInvalidValue;
+  const WmArgs a{x, uq, u_range, y, g.N, g.C, g.H, g.W, g.K, g.pad, g.P, g.th, g.tw, g.Ho, g.Wo,
+                 g.bits_w, g.NB, g.CB == 16 ? 1 : 0, nky,
+                 (unsigned)((size_t)g.N * g.C * g.H * g.W * 4),
+                 (unsigned)((size_t)g.N * g.K * g.Ho * g.Wo * 4)};
+  const int load = is_nhwc(g) ? pos::kNhwc1 : (patch_edge_cols_only(g) ? pos::kRowsEdge : pos::kRowsAny);
+  if (g.m == 4)
+    return best_kg == 1 ? launch_mfma<4, 1, 1>(a, load, s)
+                        : launch_mfma<4, 1, 2>(a, load, s);
+  if (best_tg == 1)
+    return best_kg == 1 ? launch_mfma<2, 1, 1>(a, load, s)
+                        : (best_kg == 2 ? launch_mfma<2, 1, 2>(a, load, s) : launch_mfma<2, 1, 4>(a, load, s));
+  return best_kg == 1 ? launch_mfma<2, 2, 1>(a, load, s)
+                      : (best_kg == 2 ? launch_mfma<2, 2, 2>(a, load, s) : launch_mfma<2, 2, 4>(a, load, s));
 }
 
 }  // namespace lance

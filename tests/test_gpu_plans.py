@@ -4,6 +4,7 @@ channels per lane, caller-supplied ranges of narrow codes), and the other plans 
 enough to be theirs with ragged sizes.  Same bars as test_gpu_parity.py."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2003_08646_amd import workloads as Wk
 from test_gpu_parity import _check_layer, O
@@ -90,3 +91,40 @@ def test_packed_on_many_tiles(m):
     from paper_2003_08646_amd import binding as B
     L = Wk.Layer("packed_many", 80, 130, 200, 14, 16, m=m, bits=4, seed=560)
     _check_layer(L, flags=B.LANCE_CODES_PACKED4, staged=False)
+
+
+# N, C, K, H, W, pad, m, bits_w: one and two tile groups, one, two and four filter groups, partial
+# rows of 32 channels
+_WEIGHT_ONLY = [
+    (1, 100, 20, 9, 11, 1, 2, 8),
+    (20, 40, 30, 14, 13, 0, 2, 6),
+    (40, 20, 70, 20, 19, 1, 2, 4),
+    (3, 33, 64, 40, 41, 2, 2, 8),
+    (90, 16, 33, 12, 12, 1, 2, 3),
+    (4, 140, 20, 15, 17, 1, 4, 8),
+    (60, 5, 40, 14, 16, 1, 4, 4),
+]
+
+
+@pytest.mark.parametrize("nhwc", [False, True], ids=["nchw", "nhwc"])
+@pytest.mark.parametrize("shape", _WEIGHT_ONLY, ids=lambda s: "n%d_c%d_k%d_%dx%d_p%d_m%d_w%d" % s)
+def test_weight_only_shapes(shape, nhwc):
+    """Relative error (2-norm) below that of binary32 sums: sqrt(C) * 2^-24 per sum of C terms, times
+    the growth of A^T M A (at most about 8 for F(4x4)): 4e-6 at 140 channels."""
+    from paper_2003_08646_amd import binding as B
+    from paper_2003_08646_amd.layer import LanceConv
+    N, C, K, H, W, pad, m, bits_w = shape
+    L = Wk.Layer("wo", N, C, K, H, W, pad=pad, m=m, bits_w=bits_w, seed=570 + C)
+    X, Wt = Wk.make_inputs(L)
+    ref = O.weight_only_conv_f64(X, Wt, pad, m, bits_w, filters=O.prepare_filters(Wt, m, bits_w))
+    conv = LanceConv(N, C, H, W, K, pad, m, 8, B.LANCE_LAYOUT_NHWC if nhwc else 0, bits_w=bits_w)
+    conv.prepare_filters(torch.from_numpy(Wt).cuda())
+    x = torch.from_numpy(np.ascontiguousarray(X.transpose(0, 2, 3, 1)) if nhwc else X).cuda()
+    conv.y.fill_(float("nan"))
+    B.lance_conv3x3_winograd_wq_f32(conv.desc, x, conv.uq, conv.u_range, conv.y)
+    torch.cuda.synchronize()
+    got = conv.y.cpu().numpy().astype(np.float64)
+    got = got.transpose(0, 3, 1, 2) if nhwc else got
+    rel = float(np.linalg.norm(got - ref) / np.linalg.norm(ref))
+    print(f"[case] {shape} nhwc={nhwc}: rel {rel:.2g}", flush=True)
+    assert rel <= 4e-6
