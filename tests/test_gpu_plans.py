@@ -7,7 +7,7 @@ import pytest
 import torch
 
 from paper_2003_08646_amd import workloads as Wk
-from test_gpu_parity import _check_layer, O
+from test_gpu_parity import _assert_codes, _check_layer, O
 
 pytestmark = pytest.mark.gpu
 
@@ -128,3 +128,34 @@ def test_weight_only_shapes(shape, nhwc):
     rel = float(np.linalg.norm(got - ref) / np.linalg.norm(ref))
     print(f"[case] {shape} nhwc={nhwc}: rel {rel:.2g}", flush=True)
     assert rel <= 4e-6
+
+
+# K, C, m, bits_w: one kernel / two kernels, 256- and 512-thread workgroups, workgroups with unequal
+# numbers of filters, few records per workgroup, rows of 16, 32 and 64 bytes
+_FILTERS = [
+    (1, 1, 2, 8), (65, 64, 2, 8), (64, 64, 4, 8), (400, 16, 2, 5), (67, 130, 2, 8), (9, 700, 4, 8),
+    (333, 250, 2, 8), (333, 250, 4, 3), (700, 7, 4, 8), (5000, 3, 2, 8),
+]
+
+
+@pytest.mark.parametrize("K,C,m,bits_w", _FILTERS)
+@pytest.mark.parametrize("flags", ["nchw", "nhwc", "packed", "per_tensor"])
+def test_filter_transform_shapes(K, C, m, bits_w, flags):
+    """Codes, ranges and row sums bit for bit, twice in a row on one set of buffers."""
+    from paper_2003_08646_amd import binding as B
+    from paper_2003_08646_amd.layer import LanceConv
+    if flags == "packed":
+        if C <= 16:
+            pytest.skip("packed codes need more than 16 channels")
+        bits_w = min(bits_w, 4)
+    f = {"nchw": 0, "nhwc": B.LANCE_LAYOUT_NHWC, "packed": B.LANCE_CODES_PACKED4, "per_tensor": B.LANCE_RANGE_PER_TENSOR}[flags]
+    conv = LanceConv(1, C, 8, 8, K, 1, m, min(bits_w, 4) if flags == "packed" else 8, f, bits_w=bits_w)
+    rng = np.random.default_rng(580 + K + C)
+    for _ in range(2):
+        Wt = rng.standard_normal((K, C, 3, 3), dtype=np.float32)
+        ref = O.prepare_filters(Wt, m, bits_w, per_tensor=flags == "per_tensor")
+        conv.prepare_filters(torch.from_numpy(Wt).cuda())
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(conv.u_range.cpu().numpy(), ref.u_range)
+        _assert_codes(conv.codes_to_logical(conv.uq, K), ref.Uq, "filter codes")
+        np.testing.assert_array_equal(conv.u_rowsum.cpu().numpy(), ref.u_rowsum)
