@@ -105,24 +105,42 @@ def lib() -> ctypes.CDLL:
     return _lib
 
 
-def _ptr(t) -> c_void_p:
-    """Device pointer of a torch tensor (or pass-through of an int / None)."""
-    if t is None:
-        return c_void_p(0)
-    if isinstance(t, int):
-        return c_void_p(t)
+def _ptr(t):
+    """Device address of a torch tensor (an int or None passes through); ctypes turns it into the
+    void* the prototype asks for."""
+    if t is None or t.__class__ is int:
+        return t
     if not t.is_contiguous():
         raise ValueError("liblance needs contiguous buffers")
-    return c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream(stream) -> c_void_p:
+_raw_stream = None
+
+
+def _stream(stream):
+    """hipStream_t of a stream object (an int passes through; None: torch's current stream of the
+    current device)."""
+    global _raw_stream
     if stream is None:
-        import torch
-        return c_void_p(torch.cuda.current_stream().cuda_stream)
-    if isinstance(stream, int):
-        return c_void_p(stream)
-    return c_void_p(stream.cuda_stream)
+        if _raw_stream is None:
+            import torch
+            # the handle without the Stream object that torch.cuda.current_stream() builds around it
+            # (2.7 us of a call that takes 8)
+            if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice"):
+                torch.cuda.current_stream()  # initialises the runtime
+                get, device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+                _raw_stream = lambda: get(device())
+            else:
+                _raw_stream = lambda: torch.cuda.current_stream().cuda_stream
+        return _raw_stream()
+    return stream if stream.__class__ is int else stream.cuda_stream
+
+
+def _nbytes(workspace, given):
+    if given is not None:
+        return given
+    return 0 if workspace is None else workspace.numel() * workspace.element_size()
 
 
 def _check(rc: int, where: str) -> None:
@@ -164,8 +182,7 @@ def lance_filter_transform_q8(desc, w, uq, u_range, u_rowsum, stream=None) -> No
 
 def lance_input_transform_q8(desc, x, vq, v_range, v_colsum, workspace, workspace_bytes=None,
                              stream=None) -> None:
-    nbytes = workspace_bytes if workspace_bytes is not None else (
-        0 if workspace is None else workspace.numel() * workspace.element_size())
+    nbytes = _nbytes(workspace, workspace_bytes)
     _check(lib().lance_input_transform_q8(byref(desc), _ptr(x), _ptr(vq), _ptr(v_range),
                                           _ptr(v_colsum), _ptr(workspace), nbytes,
                                           _stream(stream)), "lance_input_transform_q8")
@@ -185,8 +202,7 @@ def lance_output_transform_dq(desc, acc, u_range, u_rowsum, v_range, v_colsum, y
 
 def lance_conv3x3_winograd_q8(desc, x, uq, u_range, u_rowsum, v_range, y, workspace,
                               workspace_bytes=None, stream=None) -> None:
-    nbytes = workspace_bytes if workspace_bytes is not None else (
-        0 if workspace is None else workspace.numel() * workspace.element_size())
+    nbytes = _nbytes(workspace, workspace_bytes)
     _check(lib().lance_conv3x3_winograd_q8(byref(desc), _ptr(x), _ptr(uq), _ptr(u_range),
                                            _ptr(u_rowsum), _ptr(v_range), _ptr(y),
                                            _ptr(workspace), nbytes, _stream(stream)),
@@ -212,8 +228,7 @@ def lance_conv3x3_winograd_q8_profile(desc, x, uq, u_range, u_rowsum, v_range, y
                                       workspace_bytes=None, stream=None, repeats=1) -> list:
     """Returns the per-kernel durations [ms], averaged over `repeats` passes enqueued back to
     back, in the order of PROFILE_KERNELS."""
-    nbytes = workspace_bytes if workspace_bytes is not None else (
-        0 if workspace is None else workspace.numel() * workspace.element_size())
+    nbytes = _nbytes(workspace, workspace_bytes)
     ms = (ctypes.c_float * len(PROFILE_KERNELS))()
     _check(lib().lance_conv3x3_winograd_q8_profile(
         byref(desc), _ptr(x), _ptr(uq), _ptr(u_range), _ptr(u_rowsum), _ptr(v_range), _ptr(y),
@@ -228,10 +243,9 @@ def lance_conv3x3_winograd_q8_profile_rotating(desc, xs, ys, uq, u_range, u_rows
     """The timing twin over the buffer pairs (xs[i], ys[i]), pass r on pair r % len(xs)."""
     if len(xs) != len(ys) or not xs:
         raise ValueError("need as many outputs as inputs, at least one")
-    nbytes = workspace_bytes if workspace_bytes is not None else (
-        0 if workspace is None else workspace.numel() * workspace.element_size())
-    xp = (c_void_p * len(xs))(*[_ptr(t).value for t in xs])
-    yp = (c_void_p * len(ys))(*[_ptr(t).value for t in ys])
+    nbytes = _nbytes(workspace, workspace_bytes)
+    xp = (c_void_p * len(xs))(*[_ptr(t) for t in xs])
+    yp = (c_void_p * len(ys))(*[_ptr(t) for t in ys])
     ms = (ctypes.c_float * len(PROFILE_KERNELS))()
     _check(lib().lance_conv3x3_winograd_q8_profile_rotating(
         byref(desc), ctypes.cast(xp, c_void_p), ctypes.cast(yp, c_void_p), len(xs), _ptr(uq),

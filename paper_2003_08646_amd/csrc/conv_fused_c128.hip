@@ -355,8 +355,7 @@ bool conv_fused_c128_applicable(const Geo& g) {
 template <bool B8, bool FULL, int MODE>
 static hipError_t launch_variant(const CgArgs& a, unsigned grid, hipStream_t s) {
   auto kern = conv_fused_c128_kernel<B8, FULL, MODE>;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
+  hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)kLdsBytes);
   if (e != hipSuccess) return e;
   note_kernel("conv_fused_c128_kernel");
   kern<<<grid, kThreads, kLdsBytes, s>>>(a);

@@ -418,8 +418,7 @@ bool conv_fused_c64_applicable(const Geo& g) {
 template <bool B8, bool FULL, int MODE>
 static hipError_t launch_variant(const CfArgs& a, unsigned grid, hipStream_t s) {
   auto kern = conv_fused_c64_kernel<B8, FULL, MODE>;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
+  hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)kLdsBytes);
   if (e != hipSuccess) return e;
   note_kernel("conv_fused_c64_kernel");
   kern<<<grid, kThreads, kLdsBytes, s>>>(a);

@@ -334,8 +334,7 @@ long long block_reach_bytes(const Geo& g) {
 template <bool B8, bool FULL, int MODE, int NB>
 hipError_t launch_variant(const C4Args& a, unsigned grid, hipStream_t s) {
   auto kern = conv_fused_m4_kernel<B8, FULL, MODE, NB>;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes(NB));
+  hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds_bytes(NB));
   if (e != hipSuccess) return e;
   note_kernel("conv_fused_m4_kernel");
   kern<<<grid, kThreads, lds_bytes(NB), s>>>(a);

@@ -447,8 +447,8 @@ namespace pos {
 template <int M, int NW, int CPL, int KG, int LOAD, bool CLAMP, bool MULTI>
 inline hipError_t launch_one(const CpArgs& a, unsigned grid, size_t lds, hipStream_t s) {
   auto kern = conv_fused_pos_kernel<M, NW, CPL, KG, LOAD, CLAMP, MULTI>;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  constexpr int kMost = kConstBytes + (KG > chunk_blocks<M>() ? KG : chunk_blocks<M>()) * (M + 2) * (M + 2) * 1024;
+  const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), kMost);
   if (e != hipSuccess) return e;
   note_kernel("conv_fused_pos_kernel");
   kern<<<grid, NW * 64, lds, s>>>(a);

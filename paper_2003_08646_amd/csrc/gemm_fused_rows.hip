@@ -408,8 +408,7 @@ hipError_t launch_gemm_fused_rows(const Geo& g, const int8_t* uq, const int8_t* 
            (unsigned)((size_t)g.E * g.NB * g.K * 64), (unsigned)((size_t)g.E * g.NB * g.P * 64),
            (unsigned)((size_t)g.N * g.K * g.Ho * g.Wo * 4), is_nhwc(g) ? 1 : 0};
   const unsigned grid = (unsigned)(((g.P + kTileP - 1) / kTileP) * a.nky);
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_fused_rows_kernel),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsBytes);
+  hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(gemm_fused_rows_kernel), (int)kLdsBytes);
   if (e != hipSuccess) return e;
   note_kernel("gemm_fused_rows_kernel");
   gemm_fused_rows_kernel<<<grid, kThreads, kLdsBytes, s>>>(a);

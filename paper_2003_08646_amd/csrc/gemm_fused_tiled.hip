@@ -570,8 +570,7 @@ hipError_t launch_gemm_fused_tiled(const Geo& g, const int8_t* uq, const int8_t*
                     (unsigned)((long long)g.E * g.NB * g.P * 64)};
     const size_t lds = 3 * 2 * (size_t)kBlockBytes + kTailBytes;
     auto run = [&](auto kern) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds);
       if (e != hipSuccess) return e;
       note_kernel("gemm_fused_m2_stream_kernel");
       kern<<<grid, kThreads, lds, s>>>(as);
@@ -602,8 +601,7 @@ hipError_t launch_gemm_fused_packed(const Geo& g, const int8_t* uq, const int8_t
                   (unsigned)((long long)g.E * g.NB * g.P * kPkRow), 64 * g.Cp};
   const size_t lds = (g.NB % 4 == 0 ? 12 : 8) * (size_t)kPkBlockBytes + kTailBytes;
   auto run = [&](auto kern) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds);
     if (e != hipSuccess) return e;
     note_kernel("gemm_fused_m2_packed_kernel");
     kern<<<grid, kThreads, lds, s>>>(as);

@@ -611,8 +611,7 @@ hipError_t launch_gemm_fused_tiled_m4(const Geo& g, const int8_t* uq, const int8
     const G4sArgs as{a, (unsigned)uq_bytes, (unsigned)vq_bytes};
     const size_t lds = (size_t)kRing * kStepBytes + kTailBytes;
     auto run = [&](auto kern) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+      hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds);
       if (e != hipSuccess) return e;
       note_kernel("gemm_fused_m4_stream_kernel");
       kern<<<grid, kThreads, lds, s>>>(as);
@@ -659,8 +658,7 @@ hipError_t launch_gemm_fused_packed_m4(const Geo& g, const int8_t* uq, const int
   const int sb = g.NB % 4 == 0 ? 4 : (g.NB % 2 == 0 ? 2 : 1);
   const size_t lds = (size_t)(sb == 4 ? 16 : (sb == 2 ? 12 : 8)) * kPkBlockBytes4 + kTailBytes;
   auto run = [&](auto kern) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds);
     if (e != hipSuccess) return e;
     note_kernel("gemm_fused_m4_packed_kernel");
     kern<<<grid, kThreads, lds, s>>>(as);

@@ -265,8 +265,7 @@ static hipError_t launch_variant(GbArgs a, const Geo& g, hipStream_t s) {
   if (items >= (1LL << 31)) return hipErrorInvalidValue;
   const size_t lds = (size_t)kSlots * (TK + TP) * (PK ? pk::kRow : 64);
   auto kern = gemm_i8_tiled_kernel<WK, WP, NWK, NWP, PK>;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds);
   if (e != hipSuccess) return e;
   kern<<<(unsigned)items, 64 * NWK * NWP, lds, s>>>(a);
   return hipGetLastError();

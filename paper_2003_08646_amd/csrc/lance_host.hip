@@ -11,6 +11,33 @@ namespace lance {
 
 thread_local KernelNotes* g_kernel_notes = nullptr;
 
+// A table of the kernels whose attribute has been set, open addressing by the kernel's address; bit =
+// device.  An entry is claimed once and never released; threads that race set the same value twice.
+hipError_t allow_dynamic_lds(const void* kern, int bytes) {
+  struct Entry {
+    std::atomic<const void*> kern{nullptr};
+    std::atomic<unsigned long long> devices{0};
+  };
+  constexpr unsigned kSlots = 1024;  // several times the number of kernels in the library
+  static Entry table[kSlots];
+  int dev = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const unsigned long long bit = dev >= 0 && dev < 64 ? 1ULL << dev : 0ULL;
+  const unsigned h = (unsigned)((reinterpret_cast<uintptr_t>(kern) >> 4) * 2654435761u) >> 22;
+  Entry* entry = nullptr;
+  for (unsigned i = 0; i < kSlots && !entry; i++) {
+    Entry& t = table[(h + i) % kSlots];
+    const void* have = t.kern.load(std::memory_order_acquire);
+    if (!have && t.kern.compare_exchange_strong(have, kern, std::memory_order_acq_rel)) have = kern;
+    if (have == kern) entry = &t;
+  }
+  if (entry && (entry->devices.load(std::memory_order_acquire) & bit)) return hipSuccess;
+  e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  if (e == hipSuccess && entry) entry->devices.fetch_or(bit, std::memory_order_release);
+  return e;
+}
+
 int make_geo(const lance_conv_desc* d, Geo* g) {
   if (!d || !g) return LANCE_ERR_INVALID_ARG;
   if (d->N <= 0 || d->C <= 0 || d->H <= 0 || d->W <= 0 || d->K <= 0 || d->pad < 0)

@@ -66,6 +66,11 @@ inline void note_kernel(const char* name) {
     g_kernel_notes->name[g_kernel_notes->slot] = name;
 }
 
+// Lets kernel `kern` be launched with `bytes` of dynamic LDS (a constant of the kernel: the most it
+// ever asks for) on the current device.  Setting the attribute costs a runtime call; it is made once
+// per kernel and device and then remembered (lance_host.hip).
+hipError_t allow_dynamic_lds(const void* kern, int bytes);
+
 // Kernel launchers (each enqueues on `s` and returns the launch status).
 // Where the constants of the expanded Eq. 8 go (fused convolution only).
 struct DqOut {

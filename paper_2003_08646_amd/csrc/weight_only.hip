@@ -383,8 +383,7 @@ static hipError_t launch_mfma(const WmArgs& a, int load, hipStream_t s) {
   constexpr size_t lds = 512 + (codes > exch ? codes : exch);
   const unsigned grid = (unsigned)((a.P + 16 * TG - 1) / (16 * TG)) * (unsigned)a.nky;
   auto go = [&](auto kern) -> hipError_t {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds);
     if (e != hipSuccess) return e;
     kern<<<grid, M == 2 ? 1024 : 768, lds, s>>>(a);
     return hipGetLastError();
