@@ -19,7 +19,6 @@ struct Shape {
 // waves, 27 us with eight; 61 filters, 135 blocks: 15.5 and 15.9 us); m = 4: 1.12x and 1.45x.
 static Shape shape_of(const Geo& g) {
   const long long tb = (g.P + 15) / 16;
-  const bool multi = g.NB > (g.m == 2 ? chunk_blocks<2>() : chunk_blocks<4>());
   Shape best{1, 16, 0, 0};
   double best_cost = 0.0;
   auto consider = [&](int nw, int kg, int slots, double cost) {
@@ -31,7 +30,7 @@ static Shape shape_of(const Geo& g) {
     }
   };
   constexpr double kCost16[3] = {1.0, 1.08, 1.25}, kCost8[3] = {1.3, 1.4, 1.6}, kCost12[3] = {1.0, 1.12, 1.45};
-  for (int i = 0; i < (multi ? 1 : 3); i++) {
+  for (int i = 0; i < 3; i++) {
     consider(g.m == 2 ? 16 : 12, 1 << i, 256, g.m == 2 ? kCost16[i] : kCost12[i]);
     // (two workgroups of eight waves need half of the LDS each)
     if (g.m == 2 && g.NB <= 4) consider(8, 1 << i, 512, kCost8[i]);
@@ -42,7 +41,8 @@ static Shape shape_of(const Geo& g) {
 
 static bool conv_fused_pos_applicable(const Geo& g) {
   return (long long)g.N * g.C * g.H * g.W * 4 < 0x7FF00000LL &&
-         (long long)g.N * g.K * g.Ho * g.Wo * 4 < 0xFFFFFFF0LL;
+         (long long)g.N * g.K * g.Ho * g.Wo * 4 < 0xFFFFFFF0LL &&
+         g.NB <= (g.m == 2 ? pos::most_blocks<2>() : pos::most_blocks<4>());
 }
 
 // Where the line lies (us per fused call, the plan that would run otherwise against this one; N, C,
@@ -70,12 +70,12 @@ hipError_t launch_conv_fused_pos(const Geo& g, const float* x, const int8_t* uq,
   const bool is_static = (g.flags & LANCE_INPUT_RANGE_STATIC) != 0;
   const pos::Shape sh = pos::shape_of(g);
   if (sh.groups > 0x7FFFFFFFLL) return hipErrorInvalidValue;
-  const pos::CpArgs a{x, uq, u_range, u_rowsum, partial, v_range, y, count,
+  const pos::CpArgs a{x, uq, u_range, u_rowsum, partial, v_range, y, nullptr, count,
                       (g.flags & LANCE_RANGE_PER_TENSOR) ? 1 : 0, is_static ? 1 : 0,
                       g.N, g.C, g.H, g.W, g.K, g.pad, g.P, g.th, g.tw, g.Ho, g.Wo, g.bits, g.bits_w,
                       g.NB, g.Q, g.CB == 16 ? 1 : (is_packed(g) ? 2 : 0), sh.nky,
                       (unsigned)((size_t)g.N * g.C * g.H * g.W * 4),
-                      (unsigned)((size_t)g.N * g.K * g.Ho * g.Wo * 4)};
+                      (unsigned)((size_t)g.N * g.K * g.Ho * g.Wo * 4), 0};
   // One channel per lane where four would leave waves without work (at most two blocks), and where
   // NHWC pixels cannot be loaded four channels at a time.
   int load, cpl = g.NB > 2 ? 4 : 1;

@@ -247,7 +247,7 @@ enum ConvPlan { kPlanGeneral = 0, kPlanTwoKernels = 1, kPlanThreeKernels = 2 };
 // and F(4x4,3x3) layers of at most 128 channels: range pass, reduction kernel, one kernel for the
 // rest (the reduction kernel drops out where the last kernel can reduce for itself).
 struct PlanChoice {
-  bool fuse_p, fuse_q1, fuse_q2, fuse_s, fuse_m4;
+  bool split_p, fuse_p, fuse_q1, fuse_q2, fuse_s, fuse_m4;
   ConvPlan plan() const {
     return (fuse_p || fuse_q1 || fuse_q2) ? kPlanTwoKernels
                                 : ((fuse_s || fuse_m4) ? kPlanThreeKernels : kPlanGeneral);
@@ -256,6 +256,8 @@ struct PlanChoice {
 
 static PlanChoice choose_plan(const Geo& g, const float* x_dev) {
   PlanChoice c{};
+  c.split_p = gemm_fused_pos_preferred(g) && !(g.flags & LANCE_PLAN_WIDE_TILES);
+  if (c.split_p) return c;
   c.fuse_p = conv_fused_pos_preferred(g) && !(g.flags & LANCE_PLAN_WIDE_TILES);
   if (c.fuse_p) return c;
   if (is_packed(g)) return c;  // packed codes: the general plan (quantize pass, product kernel)
@@ -291,7 +293,22 @@ static int conv_launch(const Geo& g, const Workspace& wl, const float* x_dev, co
   const PlanChoice pc = choose_plan(g, x_dev);
   const bool fuse_q1 = pc.fuse_q1, fuse_q = pc.fuse_p || pc.fuse_q1 || pc.fuse_q2, fuse_s = pc.fuse_s;
   if (plan_out) *plan_out = pc.plan();
-  if (fuse_q) {
+  if (pc.split_p) {
+    const bool is_static = (g.flags & LANCE_INPUT_RANGE_STATIC) != 0;
+    float* partial = (float*)(ws + wl.off_partial);
+    int groups = 0;
+    if (e == hipSuccess && ev) e = hipEventRecord(ev[0], s);
+    note_slot(0);
+    if (e == hipSuccess && !is_static) e = launch_input_range(g, x_dev, partial, colsum, 0, &groups, s);
+    if (e == hipSuccess && ev) e = hipEventRecord(ev[1], s);
+    if (e == hipSuccess && ev) e = hipEventRecord(ev[2], s);
+    note_slot(2);
+    if (e == hipSuccess) e = launch_quant_pos(g, x_dev, u_range_dev, partial, groups, v_range, vq, s);
+    if (e == hipSuccess && ev) e = hipEventRecord(ev[3], s);
+    note_slot(3);
+    if (e == hipSuccess)
+      e = launch_gemm_pos(g, uq_dev, vq, u_range_dev, u_rowsum_dev, v_range, y_dev, s);
+  } else if (fuse_q) {
     const bool is_static = (g.flags & LANCE_INPUT_RANGE_STATIC) != 0;
     float* partial = (float*)(ws + wl.off_partial);
     int groups = 0;

@@ -206,6 +206,13 @@ hipError_t launch_conv_fused_pos(const Geo& g, const float* x, const int8_t* uq,
                                  const float* u_range, const int32_t* u_rowsum,
                                  const float* partial, int count, float* v_range, float* y,
                                  hipStream_t s);
+// The same in two kernels, with V's codes passing through vq (gemm_fused_pos.hip): the quantize pass
+// (partial/count and v_range as above) and the product kernel (which reads v_range).
+bool gemm_fused_pos_preferred(const Geo& g);
+hipError_t launch_quant_pos(const Geo& g, const float* x, const float* u_range, const float* partial,
+                            int count, float* v_range, int8_t* vq, hipStream_t s);
+hipError_t launch_gemm_pos(const Geo& g, const int8_t* uq, const int8_t* vq, const float* u_range,
+                           const int32_t* u_rowsum, float* v_range, float* y, hipStream_t s);
 // LDS-tiled fused GEMM for F(2x2,3x3) layers with several channel blocks (gemm_fused_tiled.hip).
 bool gemm_fused_tiled_applicable(const Geo& g);
 hipError_t launch_gemm_fused_tiled(const Geo& g, const int8_t* uq, const int8_t* vq,

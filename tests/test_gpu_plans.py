@@ -1,6 +1,6 @@
 """GPU parity at the edges of the fused call's dispatch: every way conv_fused_pos cuts a layer (one,
-two and four groups of 16 filters, 8 and 16 waves, several turns of channel blocks, one and four
-channels per lane, caller-supplied ranges of narrow codes), and the other plans on layers large
+two and four groups of 16 filters, 8 and 16 waves, the form in two kernels, one and four channels
+per lane, caller-supplied ranges of narrow codes), and the other plans on layers large
 enough to be theirs with ragged sizes.  Same bars as test_gpu_parity.py."""
 import numpy as np
 import pytest
@@ -24,14 +24,17 @@ _SPLITS = [
     (20, 33, 60, 14, 14, 1, 2, 8, False),    # two groups, 16 waves
     (90, 40, 70, 14, 15, 1, 2, 6, False),    # 8 waves, odd width
     (60, 130, 40, 12, 12, 0, 2, 8, False),   # four channels per lane
-    (3, 600, 20, 9, 8, 1, 2, 8, False),      # two turns of channel blocks
+    (3, 600, 20, 9, 8, 1, 2, 8, False),      # more channel blocks than LDS holds: two kernels
     (4, 580, 20, 7, 7, 2, 2, 5, True),       # the same with 16-byte NHWC loads
     (3, 601, 17, 6, 6, 1, 2, 8, True),       # and with 4-byte ones
+    (20, 530, 150, 13, 12, 1, 2, 8, False),  # two groups of filters and of tiles
     (33, 18, 70, 15, 16, 1, 4, 8, False),    # F(4x4): two groups
     (90, 30, 70, 16, 13, 1, 4, 5, False),    # four groups, odd width
     (20, 150, 24, 9, 11, 0, 4, 8, False),    # four channels per lane
-    (2, 330, 20, 9, 10, 1, 4, 6, False),     # two turns
+    (2, 330, 20, 9, 10, 1, 4, 6, False),     # F(4x4) in two kernels
     (2, 200, 20, 9, 10, 1, 4, 8, True),
+    (30, 210, 150, 14, 13, 1, 4, 7, False),  # two groups of filters
+    (40, 200, 150, 15, 16, 0, 4, 8, True),   # and of tiles
     (30, 7, 70, 33, 31, 1, 4, 8, False),     # at most 16 channels
     (8, 16, 40, 33, 31, 3, 4, 4, True),
     (2, 5, 300, 20, 18, 1, 2, 7, True),
