@@ -108,7 +108,7 @@ def lib() -> ctypes.CDLL:
 def _ptr(t):
     """Device address of a torch tensor (an int or None passes through); ctypes turns it into the
     void* the prototype asks for."""
-    if t is None or t.__class__ is int:
+    if t is None or isinstance(t, int):
         return t
     if not t.is_contiguous():
         raise ValueError("liblance needs contiguous buffers")
@@ -134,7 +134,7 @@ def _stream(stream):
             else:
                 _raw_stream = lambda: torch.cuda.current_stream().cuda_stream
         return _raw_stream()
-    return stream if stream.__class__ is int else stream.cuda_stream
+    return stream if isinstance(stream, int) else stream.cuda_stream
 
 
 def _nbytes(workspace, given):

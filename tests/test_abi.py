@@ -243,3 +243,10 @@ def test_packed_code_layout_is_a_bijection_onto_nibbles():
                 seen.add((off, sh))
     assert len(seen) == 3 * rows * sp.Cp
     assert B.lance_code_shift(d8, 3) == 0 and B.lance_code_shift(dp, sp.Cp) == -1
+
+
+def test_addresses_of_int_subclasses_pass_through():
+    class Address(int):
+        pass
+    assert B._ptr(Address(4096)) == 4096 and B._stream(Address(4096)) == 4096
+    assert B._ptr(None) is None and B._ptr(4096) == 4096 and B._stream(0) == 0
