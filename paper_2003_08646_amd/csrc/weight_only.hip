@@ -82,6 +82,61 @@ __device__ __forceinline__ bf16x8 codes_to_bf16(v2u c) {
   return __builtin_bit_cast(bf16x8, r);
 }
 
+// M[e] of one filter and tile in the plain form, channel by channel on the vector ALUs.  The split into
+// three pieces has none for an infinite value (inf - inf), and sums of codes overflow before the scaled
+// ones do: a result that is not finite is formed again from these.
+template <int M, bool NHWC>
+__device__ __forceinline__ void plain_sums(const WmArgs& a, const float* sc_s, int k, int p,
+                                           float (&acc)[M + 2][M + 2]) {
+  constexpr int A = M + 2, E = A * A;
+  const int y0 = (p / a.tw) % a.th * M - a.pad, x0 = p % a.tw * M - a.pad, n = p / a.tw / a.th;
+  const int CB = a.cb16 ? 16 : 64, Q = CB / 4, h = 1 << (a.bits_w - 1);
+#pragma unroll
+  for (int e = 0; e < E; e++) acc[e / A][e % A] = 0.0f;
+#pragma unroll 1
+  for (int c = 0; c < a.C; c++) {
+    asm volatile("" ::: "memory");  // (scales and minima read again, not kept in registers)
+    float d[A][A];
+#pragma unroll
+    for (int r = 0; r < A; r++)
+#pragma unroll
+      for (int s = 0; s < A; s++) {
+        const int gy = y0 + r, gx = x0 + s;
+        const bool ok = gy >= 0 && gy < a.H && gx >= 0 && gx < a.W;
+        const float v = a.x[dev::act_index(NHWC, n, c, min(max(gy, 0), a.H - 1),
+                                           min(max(gx, 0), a.W - 1), a.C, a.H, a.W)];
+        d[r][s] = ok ? v : 0.0f;
+      }
+    dev::input_tile_transform<M>(d);
+    const int b = c / CB, r = c % CB, at = NHWC ? r : 4 * (r % Q) + r / Q;
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+      if (e % A == 0) asm volatile("" ::: "memory");
+      const int code = (int)a.uq[(((size_t)e * a.NB + b) * a.K + k) * CB + at] + h;
+      const float u = (float)code * sc_s[e] + a.u_range[2 * e];
+      acc[e / A][e % A] = __builtin_fmaf(u, d[e / A][e % A], acc[e / A][e % A]);
+    }
+  }
+}
+
+// o = A^T v A
+template <int M>
+__device__ __forceinline__ void out2d(const float (&v)[M + 2][M + 2], float (&o)[M][M]) {
+  constexpr int A = M + 2;
+  float tt[M][A];
+#pragma unroll
+  for (int jj = 0; jj < A; jj++) {
+    float col[A], s[M];
+#pragma unroll
+    for (int r = 0; r < A; r++) col[r] = v[r][jj];
+    dev::out1d<M>(col, s);
+#pragma unroll
+    for (int r = 0; r < M; r++) tt[r][jj] = s[r];
+  }
+#pragma unroll
+  for (int r = 0; r < M; r++) dev::out1d<M>(tt[r], o[r]);
+}
+
 template <int M, int TG, int KG, int LOAD>
 __global__ __launch_bounds__(M == 2 ? 1024 : 768) void weight_only_mfma_kernel(const WmArgs a) {
   constexpr int A = M + 2, E = A * A, NW = M == 2 ? 16 : 12, NT = NW * 64, PW = E / NW;
@@ -243,18 +298,16 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void weight_only_mfma_kernel(c
     const int pin = kNhwc ? idx >> 4 : idx & 15;
     const int k = k0 + kg * 16 + kin, p = p0 + 16 * t + pin;
     if (k >= K || p >= P) continue;
-    float tt[M][A], o[M][M];
+    float mm[A][A], o[M][M], zero = 0.0f;
 #pragma unroll
-    for (int jj = 0; jj < A; jj++) {
-      float v[A], s[M];
+    for (int e = 0; e < E; e++) mm[e / A][e % A] = ex[e * KG * TG * 256 + i];
+    out2d<M>(mm, o);
 #pragma unroll
-      for (int r = 0; r < A; r++) v[r] = ex[(r * A + jj) * KG * TG * 256 + i];
-      dev::out1d<M>(v, s);
-#pragma unroll
-      for (int r = 0; r < M; r++) tt[r][jj] = s[r];
+    for (int r = 0; r < M * M; r++) zero += 0.0f * o[r / M][r % M];
+    if (zero != 0.0f) {  // not finite
+      plain_sums<M, kNhwc>(a, sc_s, k, p, mm);
+      out2d<M>(mm, o);
     }
-#pragma unroll
-    for (int r = 0; r < M; r++) dev::out1d<M>(tt[r], o[r]);
     const int ox0 = (p % a.tw) * M, q2 = p / a.tw;
     const int oy0 = (q2 % a.th) * M, on = q2 / a.th;
     const bool whole = !kNhwc && ox0 + M <= a.Wo;

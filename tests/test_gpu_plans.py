@@ -133,6 +133,63 @@ def test_weight_only_shapes(shape, nhwc):
     assert rel <= 4e-6
 
 
+_BT = {2: [[1, 0, -1, 0], [0, 1, 1, 0], [0, -1, 1, 0], [0, 1, 0, -1]],
+       4: [[4, 0, -5, 0, 1, 0], [0, -4, -4, 1, 1, 0], [0, 4, -4, -1, 1, 0], [0, -2, -1, 2, 1, 0],
+           [0, 2, -1, -2, 1, 0], [0, 4, 0, -5, 0, 1]]}
+_AT = {2: [[1, 1, 1, 0], [0, 1, -1, -1]],
+       4: [[1, 1, 1, 1, 1, 0], [0, 1, -1, 2, -2, 0], [0, 1, 1, 4, 4, 0], [0, 1, -1, 8, -8, 1]]}
+
+
+def _two_sided(rows, t):
+    """rows t rows^T over the last two axes, terms with coefficient 0 left out (0 * inf is no term)."""
+    for _ in range(2):
+        t = np.stack([sum(c * t[..., i, :] for i, c in enumerate(row) if c) for row in rows], -1)
+    return t
+
+
+@pytest.mark.parametrize("nhwc", [False, True], ids=["nchw", "nhwc"])
+@pytest.mark.parametrize("m", [2, 4])
+@pytest.mark.parametrize("C", [3, 40])
+def test_weight_only_infinities(C, m, nhwc):
+    """Infinities, a NaN and values whose sums of codes overflow: infinite and undefined results are
+    those of the plain sums, the others within 4e-6 of the largest term's scale."""
+    from paper_2003_08646_amd import binding as B
+    from paper_2003_08646_amd.layer import LanceConv
+    N, K, H, W = 2, 20, 12, 13
+    X, Wt = Wk.make_inputs(Wk.Layer("wo", N, C, K, H, W, pad=0, m=m, seed=590 + C))
+    X[0, 1, 0, 0] = np.inf
+    X[0, 2, 6, 7] = -np.inf
+    X[1, 0, 11, 12] = np.nan
+    X[1, 1, 0, 0] = 1e37
+    f = O.prepare_filters(Wt, m, 8)
+    lo, hi = (f.u_range[:, i, None, None].astype(np.float64) for i in range(2))
+    u = (f.Uq[:, :, :C].astype(np.float64) + 128) * ((hi - lo) / 255) + lo  # [E][K][C]
+    th, tw, a = -(-(H - 2) // m), -(-(W - 2) // m), m + 2
+    xp = np.zeros((N, C, th * m + 2, tw * m + 2))
+    xp[:, :, :H, :W] = X
+    ref = np.zeros((N, K, th * m, tw * m))
+    with np.errstate(invalid="ignore"):
+        for ty in range(th):
+            for tx in range(tw):
+                v = _two_sided(_BT[m], xp[:, :, ty * m:ty * m + a, tx * m:tx * m + a])
+                mm = (u.transpose(1, 2, 0)[None] * v.reshape(N, 1, C, a * a)).sum(2)
+                ref[:, :, ty * m:ty * m + m, tx * m:tx * m + m] = _two_sided(_AT[m], mm.reshape(N, K, a, a))
+    ref = ref[:, :, :H - 2, :W - 2]
+    conv = LanceConv(N, C, H, W, K, 0, m, 8, B.LANCE_LAYOUT_NHWC if nhwc else 0)
+    conv.prepare_filters(torch.from_numpy(Wt).cuda())
+    x = torch.from_numpy(np.ascontiguousarray(X.transpose(0, 2, 3, 1)) if nhwc else X).cuda()
+    B.lance_conv3x3_winograd_wq_f32(conv.desc, x, conv.uq, conv.u_range, conv.y)
+    got = conv.y.cpu().numpy().astype(np.float64)
+    got = got.transpose(0, 3, 1, 2) if nhwc else got
+    assert np.isinf(ref).any() and np.isnan(ref).any()
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(ref))
+    np.testing.assert_array_equal(np.where(np.isinf(got), got, 0), np.where(np.isinf(ref), ref, 0))
+    fin, big = np.isfinite(ref), np.abs(ref) > 1e30
+    assert (fin & big).any()
+    for part in (fin & big, fin & ~big & (np.arange(H - 2) >= m)[:, None]):  # (row 0's tiles hold the 1e37)
+        assert np.linalg.norm((got - ref)[part]) <= 4e-6 * np.linalg.norm(ref[part])
+
+
 # K, C, m, bits_w: one kernel / two kernels, 256- and 512-thread workgroups, workgroups with unequal
 # numbers of filters, few records per workgroup, rows of 16, 32 and 64 bytes
 _FILTERS = [
