@@ -86,7 +86,9 @@ hipError_t launch_conv_fused_pos(const Geo& g, const float* x, const int8_t* uq,
   } else {
     load = patch_edge_cols_only(g) ? pos::kRowsEdge : pos::kRowsAny;
   }
-  const bool clamp = is_static && g.bits < 8;  // dynamic ranges never exceed the last code
+  // 8-bit codes saturate in the conversion; ranges of the same tensor are exceeded by no number, but an
+  // undefined value (which ranges skip) takes the last code here as in every other plan
+  const bool clamp = g.bits < 8;
   if (g.m == 4) return pos::launch_m4(a, clamp, cpl, load, sh.kg, s);
   if (sh.nw == 16)
     return clamp ? pos::launch<2, 16, true>(a, cpl, load, sh.kg, s) : pos::launch<2, 16, false>(a, cpl, load, sh.kg, s);

@@ -210,7 +210,7 @@ hipError_t launch_quant_pos(const Geo& g, const float* x, const float* u_range, 
     load = g.m == 2 && g.C % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0 ? pos::kNhwc4 : pos::kNhwc1;
   else
     load = patch_edge_cols_only(g) ? pos::kRowsEdge : pos::kRowsAny;
-  const bool clamp = is_static && g.bits < 8;
+  const bool clamp = g.bits < 8;  // as in conv_fused_pos.hip
   if (g.m == 4) return clamp ? pos::launch_quant<4, true>(q, load, s) : pos::launch_quant<4, false>(q, load, s);
   return clamp ? pos::launch_quant<2, true>(q, load, s) : pos::launch_quant<2, false>(q, load, s);
 }

@@ -60,6 +60,27 @@ def test_position_parallel_packed(m, nhwc):
     _check_layer(L, flags=B.LANCE_CODES_PACKED4 | (B.LANCE_LAYOUT_NHWC if nhwc else 0), staged=False)
 
 
+@pytest.mark.parametrize("m", [2, 4])
+@pytest.mark.parametrize("C,bits", [(40, 6), (40, 8), (12, 5), (600, 4)])
+def test_undefined_value_takes_the_code_of_the_other_plans(C, bits, m):
+    """Ranges skip a NaN; its code decides finite outputs: those of the few-tile plans against those
+    of the plans that LANCE_PLAN_WIDE_TILES selects.  Codes and integer sums are equal, so what is
+    left is the binary32 rounding of the epilogue (at most 1e-5 of the largest output)."""
+    from paper_2003_08646_amd import binding as B
+    from paper_2003_08646_amd.layer import LanceConv
+    X, Wt = Wk.make_inputs(Wk.Layer("nan", 2, C, 20, 12, 13, m=m, bits=bits, seed=580 + C))
+    X[1, C // 2, 5, 6] = np.nan
+    x, w = torch.from_numpy(X).cuda(), torch.from_numpy(Wt).cuda()
+    ys = []
+    for flags in (0, B.LANCE_PLAN_WIDE_TILES):
+        conv = LanceConv(2, C, 12, 13, 20, 1, m, bits, flags)
+        conv.prepare_filters(w)
+        ys.append((conv.forward(x).cpu().numpy().astype(np.float64), conv.v_range.cpu().numpy()))
+    np.testing.assert_array_equal(ys[0][1], ys[1][1])
+    assert np.isfinite(ys[0][0]).all()
+    assert np.abs(ys[0][0] - ys[1][0]).max() <= 1e-5 * np.abs(ys[1][0]).max()
+
+
 # layers of more tiles than conv_fused_pos takes: the other plans with partial blocks and odd sizes
 _LARGE = [
     (330, 60, 40, 9, 11, 0, 2, 8, False),
