@@ -154,6 +154,34 @@ def test_weight_only_shapes(shape, nhwc):
     assert rel <= 4e-6
 
 
+@pytest.mark.parametrize("kind", ["one_sided_filter", "outlying_weight", "positive_range"])
+@pytest.mark.parametrize("C,m,bits_w", [(64, 2, 8), (512, 2, 8), (512, 2, 4), (100, 4, 8)])
+def test_weight_only_ranges_away_from_zero(kind, C, m, bits_w):
+    """Filter ranges that are not centred at zero: one filter far larger than the others and of one
+    sign (a folded batch norm), one outlying weight, and a range without zero.  The error of the other
+    filters stays that of binary32 sums of their own terms: sqrt(C) * 2^-24 = 1.4e-6 at 512 channels,
+    twice that for F(4x4) (measured: at most 9e-7 and 1.0e-6)."""
+    from paper_2003_08646_amd import binding as B
+    from paper_2003_08646_amd.layer import LanceConv
+    K, H = 40, 14
+    L = Wk.Layer("wo_asym", 1, C, K, H, H, m=m, bits_w=bits_w, seed=600 + C)
+    X, Wt = Wk.make_inputs(L)
+    if kind == "one_sided_filter":
+        Wt[0] = -10 * np.abs(Wt[0])
+    elif kind == "outlying_weight":
+        Wt[0, C // 2, 1, 1] = -3.0
+    else:
+        Wt = np.abs(Wt) + np.float32(0.5)
+    ref = O.weight_only_conv_f64(X, Wt, 1, m, bits_w, filters=O.prepare_filters(Wt, m, bits_w))
+    conv = LanceConv(1, C, H, H, K, 1, m, 8, 0, bits_w=bits_w)
+    conv.prepare_filters(torch.from_numpy(Wt).cuda())
+    B.lance_conv3x3_winograd_wq_f32(conv.desc, torch.from_numpy(X).cuda(), conv.uq, conv.u_range, conv.y)
+    got = conv.y.cpu().numpy().astype(np.float64)
+    rel = float(np.linalg.norm((got - ref)[:, 1:]) / np.linalg.norm(ref[:, 1:]))
+    print(f"[case] {kind} C{C} m{m} w{bits_w}: rel {rel:.2g}", flush=True)
+    assert rel <= (3e-6 if m == 4 else 1.5e-6)
+
+
 _BT = {2: [[1, 0, -1, 0], [0, 1, 1, 0], [0, -1, 1, 0], [0, 1, 0, -1]],
        4: [[4, 0, -5, 0, 1, 0], [0, -4, -4, 1, 1, 0], [0, 4, -4, -1, 1, 0], [0, -2, -1, 2, 1, 0],
            [0, 2, -1, -2, 1, 0], [0, 4, 0, -5, 0, 1]]}
