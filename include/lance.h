@@ -273,7 +273,8 @@ int lance_alg1_literal_f32(const lance_conv_desc *desc, const float *x_dev, cons
 /* Weight-only quantization -- the rows of Sec. 4 (Table 2) that quantize the weights and keep
  * full-precision inputs: Algorithm 1 with v^ replaced by the unquantized B^T d B,
  *   M[e,k,p] = sum_c Q'(u^[e,k,c]) * V[e,p,c] (Eq. 8 on the filter codes), Y tile = A^T M A,
- * summed in binary32 (every input value as three bf16 pieces on the matrix cores, exact products).
+ * summed in binary32 (every V times 2^24 as three bf16 pieces on the matrix cores, exact products;
+ * results that overflow there are summed again in the plain form).
  *   in : x as for lance_conv3x3_winograd_q8; uq_dev, u_range_dev from
  *        lance_filter_transform_q8 with the same descriptor (filter width = LANCE_FILTER_BITS,
  *        else bits; LANCE_RANGE_PER_TENSOR as there; LANCE_LAYOUT_NHWC honoured)

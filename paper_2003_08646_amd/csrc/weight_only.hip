@@ -10,7 +10,9 @@
 // the second sum from the same instructions with an operand of ones.  z is the code that stands for
 // the value next to zero (0 .. 2^b - 1; the difference is an integer of at most 255, still exact):
 // counted from there ou is at most half a step wherever the range holds zero, so the two terms do
-// not cancel however far the range is from symmetric.
+// not cancel however far the range is from symmetric.  V enters the split times 2^24 (the results
+// leave it again): the smallest binary32 value's pieces are then normal bf16 numbers, so the split is
+// exact for every V below 2^104; what overflows is formed again in the plain form (plain_sums).
 //
 // weight_only_mfma_kernel: a workgroup of 16 waves (m = 4: 12) takes 16*TG tiles x 16*KG filters,
 // wave w the positions w*E/NW ..  Turn by turn over CH channels: every lane transforms one channel
@@ -52,6 +54,7 @@ struct WmArgs {
 };
 
 constexpr unsigned kOobY = 0xFFFFFFF0u;
+constexpr float kUp = 16777216.0f;  // 2^24
 
 __device__ __forceinline__ void store1(float* y, unsigned y_bytes, unsigned off, float v) {
   const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(y, 0, y_bytes, 0x00020000);
@@ -88,8 +91,8 @@ __device__ __forceinline__ bf16x8 codes_to_bf16(v2u c, float zero) {
 }
 
 // M[e] of one filter and tile in the plain form, channel by channel on the vector ALUs.  The split into
-// three pieces has none for an infinite value (inf - inf), and sums of codes overflow before the scaled
-// ones do: a result that is not finite is formed again from these.
+// three pieces has none for an infinite value (inf - inf), and its sums overflow before these do (2^24
+// and the codes against scaled codes): a result that is not finite is formed again from these.
 template <int M, bool NHWC>
 __device__ __forceinline__ void plain_sums(const WmArgs& a, const float* sc_s, int k, int p,
                                            float (&acc)[M + 2][M + 2]) {
@@ -226,7 +229,7 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void weight_only_mfma_kernel(c
       dev::input_tile_transform<M>(d);
 #pragma unroll
       for (int e = 0; e < E; e++) {
-        const float v = d[e / A][e % A];
+        const float v = d[e / A][e % A] * kUp;
         const unsigned hi = __float_as_uint(v) & 0xFFFF0000u;
         const float r1 = v - __uint_as_float(hi);
         const unsigned mid = __float_as_uint(r1) & 0xFFFF0000u;
@@ -313,7 +316,10 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void weight_only_mfma_kernel(c
     for (int e = 0; e < E; e++) mm[e / A][e % A] = ex[e * KG * TG * 256 + i];
     out2d<M>(mm, o);
 #pragma unroll
-    for (int r = 0; r < M * M; r++) zero += 0.0f * o[r / M][r % M];
+    for (int r = 0; r < M * M; r++) {
+      zero += 0.0f * o[r / M][r % M];
+      o[r / M][r % M] *= 1.0f / kUp;
+    }
     if (zero != 0.0f) {  // not finite
       plain_sums<M, kNhwc>(a, sc_s, k, p, mm);
       out2d<M>(mm, o);

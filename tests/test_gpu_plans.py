@@ -182,6 +182,26 @@ def test_weight_only_ranges_away_from_zero(kind, C, m, bits_w):
     assert rel <= (3e-6 if m == 4 else 1.5e-6)
 
 
+@pytest.mark.parametrize("m", [2, 4])
+@pytest.mark.parametrize("exponent", [-110, -125, -140])
+def test_weight_only_tiny_inputs(exponent, m):
+    """Inputs near and below the smallest normal binary32 number: the split of the inputs stays exact,
+    so the bound is that of test_weight_only_shapes.  (Filters times 2^60: normal outputs.)"""
+    from paper_2003_08646_amd import binding as B
+    from paper_2003_08646_amd.layer import LanceConv
+    N, C, K, H = 1, 64, 40, 14
+    X, Wt = Wk.make_inputs(Wk.Layer("wo_tiny", N, C, K, H, H, m=m, seed=620))
+    X, Wt = np.ldexp(X, exponent).astype(np.float32), np.ldexp(Wt, 60).astype(np.float32)
+    ref = O.weight_only_conv_f64(X, Wt, 1, m, 8, filters=O.prepare_filters(Wt, m, 8))
+    conv = LanceConv(N, C, H, H, K, 1, m, 8)
+    conv.prepare_filters(torch.from_numpy(Wt).cuda())
+    B.lance_conv3x3_winograd_wq_f32(conv.desc, torch.from_numpy(X).cuda(), conv.uq, conv.u_range, conv.y)
+    got = conv.y.cpu().numpy().astype(np.float64)
+    rel = float(np.linalg.norm(got - ref) / np.linalg.norm(ref))
+    print(f"[case] 2^{exponent} m{m}: rel {rel:.2g}", flush=True)
+    assert rel <= 4e-6
+
+
 _BT = {2: [[1, 0, -1, 0], [0, 1, 1, 0], [0, -1, 1, 0], [0, 1, 0, -1]],
        4: [[4, 0, -5, 0, 1, 0], [0, -4, -4, 1, 1, 0], [0, 4, -4, -1, 1, 0], [0, -2, -1, 2, 1, 0],
            [0, 2, -1, -2, 1, 0], [0, 4, 0, -5, 0, 1]]}
