@@ -6,11 +6,12 @@
 // integer of at most 8 bits and exact in bf16, and a binary32 value is the exact sum of three bf16
 // values (its top 8 significant bits, the next 8, the rest), so three products per value pair, each
 // exact, are added up in binary32; Q' is applied to the sums:
-//   M = scale_e * sum_c (code - z_e) * V + ou_e * sum_c V,   ou = min + scale * z,
-// the second sum from the same instructions with an operand of ones.  z is the code that stands for
-// the value next to zero (0 .. 2^b - 1; the difference is an integer of at most 255, still exact):
-// counted from there ou is at most half a step wherever the range holds zero, so the two terms do
-// not cancel however far the range is from symmetric.  V enters the split times 2^24 (the results
+//   M = step_e * sum_c (code * 2^(8-b) - z_e) * V + ou_e * sum_c V,   step = scale / 2^(8-b),
+//   ou = min + step * z,
+// the second sum from the same instructions with an operand of ones.  z is the multiple of step next
+// to zero (0 .. (2^b - 1) * 2^(8-b); the difference is an integer of at most 255, still exact): counted
+// from there ou is at most half of 1/255 of the range wherever that holds zero, so the two terms do not
+// cancel, however far the range is from symmetric and however few the codes.  V enters the split times 2^24 (the results
 // leave it again): the smallest binary32 value's pieces are then normal bf16 numbers, so the split is
 // exact for every V below 2^104; what overflows is formed again in the plain form (plain_sums).
 //
@@ -23,9 +24,10 @@
 // What bounds it: the vector ALUs (transform, three-way split, conversion of the codes) and, on small
 // layers, the chain of steps of a workgroup.  N32 64->64 32x32: 101 us on the vector-ALU kernel, 13.6
 // us now; N2 249->21 53x38: 407 -> 14.8 us; N2 16->64 106x106 F(4x4): 87 -> 10 us.  Relative error
-// against binary64, vector-ALU kernel and this one: 64 channels 2.7e-7 and 1.3e-7; 512 channels 6.4e-7
+// against binary64, vector-ALU kernel and this one: 64 channels 2.6e-7 and 1.2e-7; 512 channels 6.2e-7
 // and 3.3e-7, with one filter ten times the others and of one sign (the others' error) 1.6e-6 and
-// 3.7e-7, with one outlying weight 9.1e-6 and 3.3e-7; F(4x4), 512 channels, 4.1e-6 and 2.1e-6.
+// 3.4e-7, with one outlying weight 9.1e-6 and 3.3e-7, 4-bit codes 6.4e-7 and 3.2e-7; F(4x4), 512
+// channels, 3.9e-6 and 2.0e-6.
 //
 // weight_only_kernel: the vector-ALU form (lane = tile, E multiply-adds per channel and filter), for
 // inputs of 2 GiB and more, beyond the 32-bit row offsets of the other.
@@ -72,17 +74,18 @@ __device__ __forceinline__ void store_row(float* y, unsigned y_bytes, unsigned o
   }
 }
 
-// Eight stored codes (two dwords of a code row) counted from z, as bf16; exact.  zero: z + 128 - 2^(b-1).
-__device__ __forceinline__ bf16x8 codes_to_bf16(v2u c, float zero) {
+// Eight stored codes (two dwords of a code row) as multiples of step counted from z, in bf16;
+// exact.  unit: 2^(8-b); zero: z + (128 - 2^(b-1)) * unit.
+__device__ __forceinline__ bf16x8 codes_to_bf16(v2u c, float unit, float zero) {
   v4u r;
 #pragma unroll
   for (int i = 0; i < 2; i++) {
     const unsigned u = c[i] ^ 0x80808080u;  // stored code + 128
     float f[4];
-    f[0] = (float)(u & 0xFFu) - zero;
-    f[1] = (float)((u >> 8) & 0xFFu) - zero;
-    f[2] = (float)((u >> 16) & 0xFFu) - zero;
-    f[3] = (float)(u >> 24) - zero;
+    f[0] = __builtin_fmaf((float)(u & 0xFFu), unit, -zero);
+    f[1] = __builtin_fmaf((float)((u >> 8) & 0xFFu), unit, -zero);
+    f[2] = __builtin_fmaf((float)((u >> 16) & 0xFFu), unit, -zero);
+    f[3] = __builtin_fmaf((float)(u >> 24), unit, -zero);
     // the upper halves of two binary32 values side by side
     r[2 * i] = __builtin_amdgcn_perm(__float_as_uint(f[1]), __float_as_uint(f[0]), 0x07060302u);
     r[2 * i + 1] = __builtin_amdgcn_perm(__float_as_uint(f[3]), __float_as_uint(f[2]), 0x07060302u);
@@ -153,8 +156,9 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void weight_only_mfma_kernel(c
   static_assert(M == 2 || TG == 1, "LDS");
   extern __shared__ char smem[];
   float* sc_s = reinterpret_cast<float*>(smem);  // [E] scale
-  float* ou_s = sc_s + E;                        // [E] min + scale * z
-  float* zero_s = ou_s + E;                      // [E] z + 128 - 2^(b-1)
+  float* ou_s = sc_s + E;                        // [E] min + step * z
+  float* zero_s = ou_s + E;                      // [E] z + (128 - 2^(b-1)) * unit
+  const float unit = (float)(1 << (8 - a.bits_w));
   static_assert(3 * E * sizeof(float) <= 512, "parameters");
   char* ring = smem + 512;                       // [E][3][NH][TG][16 rows][64 B]
   float* ex = reinterpret_cast<float*>(ring);
@@ -196,11 +200,11 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void weight_only_mfma_kernel(c
     const float mn = a.u_range[2 * tid], mx = a.u_range[2 * tid + 1];
     float inv, scale;
     dev::quant_params(mn, mx, a.bits_w, &inv, &scale);
-    const double most = (double)((1 << a.bits_w) - 1);
-    const double z = scale > 0.0f ? fmin(fmax(rint(-(double)mn / (double)scale), 0.0), most) : 0.0;
+    const double step = (double)scale / unit, most = (double)((1 << a.bits_w) - 1) * unit;
+    const double z = scale > 0.0f ? fmin(fmax(rint(-(double)mn / step), 0.0), most) : 0.0;
     sc_s[tid] = scale;
-    ou_s[tid] = (float)((double)mn + (double)scale * z);
-    zero_s[tid] = (float)z + (float)(128 - (1 << (a.bits_w - 1)));
+    ou_s[tid] = (float)((double)mn + step * z);
+    zero_s[tid] = (float)z + (float)(128 - (1 << (a.bits_w - 1))) * unit;
   }
 
   const int col = lane & 15, kq = lane >> 4;
@@ -263,7 +267,7 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void weight_only_mfma_kernel(c
         if (r < nrow) {
           bf16x8 af[KG];
 #pragma unroll
-          for (int kg = 0; kg < KG; kg++) af[kg] = codes_to_bf16(code[w][r][kg], zero_s[wave * PW + w]);
+          for (int kg = 0; kg < KG; kg++) af[kg] = codes_to_bf16(code[w][r][kg], unit, zero_s[wave * PW + w]);
 #pragma unroll
           for (int t = 0; t < TG; t++)
 #pragma unroll
@@ -284,7 +288,7 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void weight_only_mfma_kernel(c
 #pragma unroll
   for (int w = 0; w < PW; w++) {
     const int e = wave * PW + w;
-    const float sc = sc_s[e], ou = ou_s[e];
+    const float sc = sc_s[e] / unit, ou = ou_s[e];
 #pragma unroll
     for (int t = 0; t < TG; t++) {
       const float off = ou * vsum[w][t][0];
