@@ -221,6 +221,7 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void weight_only_mfma_kernel(c
   const v4u ones_u = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
   const bf16x8 ones = __builtin_bit_cast(bf16x8, ones_u);
 
+  float zero[PW];
   for (int r0 = 0; r0 < rows; r0 += NH) {
     const int nrow = min(NH, rows - r0);
     if (has_item && nh < nrow) {
@@ -260,6 +261,10 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void weight_only_mfma_kernel(c
           if (a.cb16 && kq > 1) code[w][r][kg] = v2u{0u, 0u};
         }
     __syncthreads();
+    if (r0 == 0) {
+#pragma unroll
+      for (int w = 0; w < PW; w++) zero[w] = zero_s[wave * PW + w];
+    }
 #pragma unroll
     for (int w = 0; w < PW; w++)
 #pragma unroll
@@ -267,7 +272,7 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void weight_only_mfma_kernel(c
         if (r < nrow) {
           bf16x8 af[KG];
 #pragma unroll
-          for (int kg = 0; kg < KG; kg++) af[kg] = codes_to_bf16(code[w][r][kg], unit, zero_s[wave * PW + w]);
+          for (int kg = 0; kg < KG; kg++) af[kg] = codes_to_bf16(code[w][r][kg], unit, zero[w]);
 #pragma unroll
           for (int t = 0; t < TG; t++)
 #pragma unroll
