@@ -30,7 +30,9 @@
 // channels, 3.9e-6 and 2.0e-6.
 //
 // weight_only_kernel: the vector-ALU form (lane = tile, E multiply-adds per channel and filter), for
-// inputs of 2 GiB and more, beyond the 32-bit row offsets of the other.
+// layers of few channels and filters (vector_form_faster), whose rows of 32 channels and groups of 16
+// filters would be mostly padding in the other, and for inputs of 2 GiB and more, beyond the 32-bit row
+// offsets of the other.
 #include "lance_device.h"
 #include "lance_internal.h"
 #include "tile_loader.h"
@@ -473,34 +475,86 @@ static hipError_t launch_mfma(const WmArgs& a, int load, hipStream_t s) {
   }
 }
 
-hipError_t launch_weight_only(const Geo& g, const float* x, const int8_t* uq, const float* u_range,
-                              float* y, hipStream_t s) {
-  if ((long long)g.N * g.C * g.H * g.W * 4 >= 0x7FF00000LL) {
-    const WoArgs a{x, uq, u_range, y, g.N, g.C, g.H, g.W, g.K, g.pad, g.th, g.tw, g.P, g.Ho, g.Wo,
-                   g.bits_w, is_nhwc(g) ? 1 : 0, g.CB, g.NB};
-    const int kf = g.m == 2 ? 8 : 4;
-    const long long bx = ((long long)g.P + kThreads - 1) / kThreads, by = (g.K + kf - 1) / kf;
-    if (bx > 0x7FFFFFFFLL || by > 65535) return hipErrorInvalidValue;
-    dim3 grid((unsigned)bx, (unsigned)by, 1);
-    if (g.m == 2) weight_only_kernel<2, 8><<<grid, kThreads, 0, s>>>(a);
-    else weight_only_kernel<4, 4><<<grid, kThreads, 0, s>>>(a);
-    return hipGetLastError();
-  }
-  // Smallest (rounds of one workgroup per compute unit: LDS) x (relative time of a workgroup).  The
-  // times are from sweeps of the six shapes over layers of 3 to 400 channels; 64 -> 64 channels, 8192
-  // tiles: 13.6 us with (2, 4) = 256 workgroups, 16.8 with (1, 4), 25 with (1, 2), 37 with (1, 1);
-  // 249 -> 21 channels, 1026 tiles: 14.8 with (1, 1), 33 with (2, 4).
+namespace {
+// How the matrix-core kernel's work is cut: 16*tg tiles x 16*kg filters per workgroup.
+struct WmShape {
+  int tg, kg;
+  long long groups;
+};
+
+// Smallest (rounds of one workgroup per compute unit: LDS) x (relative time of a workgroup).  The
+// times are from sweeps of the six shapes over layers of 3 to 400 channels; 64 -> 64 channels, 8192
+// tiles: 13.6 us with (2, 4) = 256 workgroups, 16.8 with (1, 4), 25 with (1, 2), 37 with (1, 1);
+// 249 -> 21 channels, 1026 tiles: 14.8 with (1, 1), 33 with (2, 4).
+WmShape wm_shape(const Geo& g) {
   static constexpr double kCost[2][3] = {{1.0, 1.2, 1.55}, {1.55, 1.85, 2.45}};
-  int best_tg = 1, best_kg = 1;
-  double best = 0.0;
+  WmShape best{1, 1, 0};
+  double best_cost = 0.0;
   for (int tgi = 1; tgi <= (g.m == 2 ? 2 : 1); tgi++)
     for (int i = 0; i < (g.m == 2 ? 3 : 2); i++) {
       const int kg = 1 << i;
       const long long groups = ((g.P + 16LL * tgi - 1) / (16 * tgi)) * ((g.K + 16 * kg - 1) / (16 * kg));
       const double c = (double)((groups + 255) / 256) * kCost[tgi - 1][i];
-      if (best == 0.0 || c < best) { best = c; best_tg = tgi; best_kg = kg; }
+      if (best_cost == 0.0 || c < best_cost) { best = WmShape{tgi, kg, groups}; best_cost = c; }
     }
-  const int nky = (g.K + 16 * best_kg - 1) / (16 * best_kg);
+  return best;
+}
+
+// Filters per workgroup of the vector-ALU kernel.
+int plain_filters(const Geo& g) { return g.m == 2 ? 8 : 4; }
+
+// Whether the vector-ALU kernel takes less time: both times in us from fits to sweeps over 1 to 64
+// channels, 1 to 512 filters, 49 to 506250 tiles, both layouts (3338 layers, each kernel on each: within
+// 5 % of the better one on all but 50 of them, within 40 % on all).  100352 tiles of F(2x2), vector and matrix
+// form: 1 -> 8 channels 9 and 58 us, 16 -> 8 40 and 58, 3 -> 40 42 and 88, 16 -> 64 220 and 93; NHWC
+// 3 -> 4 13 and 58, 3 -> 16 105 and 59.
+bool vector_form_faster(const Geo& g, const WmShape& sh) {
+  // Vector form: the latency of one workgroup or its rounds, each linear in C.  NHWC: its stores are
+  // K floats apart, worst at 16 filters (one 64-byte piece per pixel), and its loads C floats.
+  struct Fit { double lat, lat_c, base, round, round_c; int most_c, nhwc_most_c, nhwc_most_k; };
+  static constexpr Fit kFit[2] = {{6.0, 1.75, 2.2, 2.1, 1.1, 32, 12, 20}, {6.0, 4.4, 0.7, 7.1, 5.1, 20, 6, 12}};
+  const bool nhwc = is_nhwc(g), m4 = g.m == 4;
+  const Fit& f = kFit[m4];
+  if (g.C > (nhwc ? f.nhwc_most_c : f.most_c) || (nhwc && (g.K > f.nhwc_most_k || g.K == 16))) return false;
+  const long long blocks = ((g.P + kThreads - 1LL) / kThreads) * ((g.K + plain_filters(g) - 1) / plain_filters(g));
+  const double by_latency = f.lat + f.lat_c * g.C;
+  const double by_rounds = f.base + (double)((blocks + 255) / 256) * (f.round + f.round_c * g.C);
+  double vector_us = by_latency > by_rounds ? by_latency : by_rounds;
+  if (nhwc)
+    vector_us += (m4 ? 90e-6 : (g.C % 4 == 0 ? 25e-6 : 15e-6)) * (g.K > 16 ? 1.7 : 1.0) * (double)g.P * g.K;
+  // Matrix form: launch + rounds of one workgroup per compute unit, by shape: {launch, the first turn
+  // over 32 channels, the second}.
+  struct Turn { double launch, first, second; };
+  static constexpr Turn kTurn2[2][3] = {{{2.5, 2.5, 0.0}, {3.0, 3.0, 0.0}, {3.5, 3.5, 0.0}},
+                                        {{1.55, 4.33, 2.24}, {1.9, 5.3, 2.8}, {2.2, 7.3, 3.4}}};
+  static constexpr Turn kTurn4[2] = {{2.0, 6.2, 3.55}, {2.4, 7.6, 4.4}};
+  const int ki = sh.kg == 4 ? 2 : sh.kg - 1;
+  const Turn& t = m4 ? kTurn4[ki] : kTurn2[sh.tg - 1][ki];
+  const bool two_turns = g.C > 16 && (m4 || sh.tg == 2);
+  const double matrix_us = t.launch + (double)((sh.groups + 255) / 256) * (t.first + (two_turns ? t.second : 0.0));
+  return vector_us < matrix_us;
+}
+
+hipError_t launch_vector(const Geo& g, const float* x, const int8_t* uq, const float* u_range, float* y,
+                         hipStream_t s) {
+  const WoArgs a{x, uq, u_range, y, g.N, g.C, g.H, g.W, g.K, g.pad, g.th, g.tw, g.P, g.Ho, g.Wo,
+                 g.bits_w, is_nhwc(g) ? 1 : 0, g.CB, g.NB};
+  const int kf = plain_filters(g);
+  const long long bx = ((long long)g.P + kThreads - 1) / kThreads, by = (g.K + kf - 1) / kf;
+  if (bx > 0x7FFFFFFFLL || by > 65535) return hipErrorInvalidValue;
+  dim3 grid((unsigned)bx, (unsigned)by, 1);
+  if (g.m == 2) weight_only_kernel<2, 8><<<grid, kThreads, 0, s>>>(a);
+  else weight_only_kernel<4, 4><<<grid, kThreads, 0, s>>>(a);
+  return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_weight_only(const Geo& g, const float* x, const int8_t* uq, const float* u_range,
+                              float* y, hipStream_t s) {
+  const WmShape sh = wm_shape(g);
+  if ((long long)g.N * g.C * g.H * g.W * 4 >= 0x7FF00000LL || vector_form_faster(g, sh))
+    return launch_vector(g, x, uq, u_range, y, s);
+  const int nky = (g.K + 16 * sh.kg - 1) / (16 * sh.kg);
   if (((g.P + 15LL) / 16) * nky > 0x7FFFFFFFLL) return hipErrorInvalidValue;
   const WmArgs a{x, uq, u_range, y, g.N, g.C, g.H, g.W, g.K, g.pad, g.P, g.th, g.tw, g.Ho, g.Wo,
                  g.bits_w, g.NB, g.CB == 16 ? 1 : 0, nky,
@@ -508,13 +562,12 @@ hipError_t launch_weight_only(const Geo& g, const float* x, const int8_t* uq, co
                  (unsigned)((size_t)g.N * g.K * g.Ho * g.Wo * 4)};
   const int load = is_nhwc(g) ? pos::kNhwc1 : (patch_edge_cols_only(g) ? pos::kRowsEdge : pos::kRowsAny);
   if (g.m == 4)
-    return best_kg == 1 ? launch_mfma<4, 1, 1>(a, load, s)
-                        : launch_mfma<4, 1, 2>(a, load, s);
-  if (best_tg == 1)
-    return best_kg == 1 ? launch_mfma<2, 1, 1>(a, load, s)
-                        : (best_kg == 2 ? launch_mfma<2, 1, 2>(a, load, s) : launch_mfma<2, 1, 4>(a, load, s));
-  return best_kg == 1 ? launch_mfma<2, 2, 1>(a, load, s)
-                      : (best_kg == 2 ? launch_mfma<2, 2, 2>(a, load, s) : launch_mfma<2, 2, 4>(a, load, s));
+    return sh.kg == 1 ? launch_mfma<4, 1, 1>(a, load, s) : launch_mfma<4, 1, 2>(a, load, s);
+  if (sh.tg == 1)
+    return sh.kg == 1 ? launch_mfma<2, 1, 1>(a, load, s)
+                      : (sh.kg == 2 ? launch_mfma<2, 1, 2>(a, load, s) : launch_mfma<2, 1, 4>(a, load, s));
+  return sh.kg == 1 ? launch_mfma<2, 2, 1>(a, load, s)
+                      : (sh.kg == 2 ? launch_mfma<2, 2, 2>(a, load, s) : launch_mfma<2, 2, 4>(a, load, s));
 }
 
 }  // namespace lance

@@ -118,7 +118,7 @@ def test_packed_on_many_tiles(m):
 
 
 # N, C, K, H, W, pad, m, bits_w: one and two tile groups, one, two and four filter groups, partial
-# rows of 32 channels
+# rows of 32 channels; the last ones in the vector-ALU form (few channels and filters, many tiles)
 _WEIGHT_ONLY = [
     (1, 100, 20, 9, 11, 1, 2, 8),
     (20, 40, 30, 14, 13, 0, 2, 6),
@@ -127,6 +127,10 @@ _WEIGHT_ONLY = [
     (90, 16, 33, 12, 12, 1, 2, 3),
     (4, 140, 20, 15, 17, 1, 4, 8),
     (60, 5, 40, 14, 16, 1, 4, 4),
+    (70, 3, 5, 57, 55, 1, 2, 8),
+    (40, 1, 40, 56, 56, 0, 2, 4),
+    (70, 20, 9, 56, 54, 2, 2, 6),
+    (70, 2, 3, 60, 57, 1, 4, 8),
 ]
 
 
@@ -152,6 +156,29 @@ def test_weight_only_shapes(shape, nhwc):
     rel = float(np.linalg.norm(got - ref) / np.linalg.norm(ref))
     print(f"[case] {shape} nhwc={nhwc}: rel {rel:.2g}", flush=True)
     assert rel <= 4e-6
+
+
+@pytest.mark.parametrize("nhwc", [False, True], ids=["nchw", "nhwc"])
+@pytest.mark.parametrize("m", [2, 4])
+def test_weight_only_inputs_of_2gib(m, nhwc):
+    """Beyond the matrix-core kernel's 32-bit offsets: images from both ends and the middle of a
+    2047 MiB tensor, each as if it stood alone."""
+    from paper_2003_08646_amd import binding as B
+    from paper_2003_08646_amd.layer import LanceConv
+    N, C, K, H = 2047, 16, 4, 128
+    _, Wt = Wk.make_inputs(Wk.Layer("wo_2gib", 1, C, K, 8, 8, m=m, seed=630))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(630)
+    x = torch.randn((N, H, H, C) if nhwc else (N, C, H, H), generator=gen, device="cuda")
+    conv = LanceConv(N, C, H, H, K, 1, m, 8, B.LANCE_LAYOUT_NHWC if nhwc else 0)
+    conv.prepare_filters(torch.from_numpy(Wt).cuda())
+    B.lance_conv3x3_winograd_wq_f32(conv.desc, x, conv.uq, conv.u_range, conv.y)
+    filters = O.prepare_filters(Wt, m, 8)
+    for n in (0, 1, 1023, N - 2, N - 1):
+        X, got = x[n:n + 1].cpu().numpy(), conv.y[n:n + 1].cpu().numpy().astype(np.float64)
+        X, got = (X.transpose(0, 3, 1, 2), got.transpose(0, 3, 1, 2)) if nhwc else (X, got)
+        ref = O.weight_only_conv_f64(np.ascontiguousarray(X), Wt, 1, m, 8, filters=filters)
+        assert np.linalg.norm(got - ref) <= 4e-6 * np.linalg.norm(ref), n
 
 
 @pytest.mark.parametrize("kind", ["one_sided_filter", "outlying_weight", "positive_range"])
