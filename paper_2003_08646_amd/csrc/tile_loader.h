@@ -3,8 +3,11 @@
 //
 // NCHW patches are loaded by rows (one 16-byte load, for m = 4 also an 8-byte one, at any 4-byte
 // alignment) whatever the padding and the width: pixels of a neighbouring row are masked away
-// afterwards, rows outside the image have an offset beyond the buffer.  Only where such a load would
-// start before the tensor or end after it (its first and last plane) the wave takes pixel loads.
+// afterwards, rows without a pixel of the image have an offset beyond the buffer.  A row that has one
+// starts at most m+1 pixels before its plane and ends at most m+1 after it: with the guard in front of
+// the buffer's base no offset is negative, and in images of kTinyImage pixels or more the row stays
+// within the neighbouring planes.  Only where such a load would start before the tensor or end after it
+// (its first and last plane; any plane of a smaller image) the wave takes pixel loads.
 #pragma once
 #include "lance_device.h"
 
@@ -21,7 +24,8 @@ constexpr int kNhwc1 = 2;     // NHWC, 4-byte loads
 constexpr int kNhwc4 = 3;     // NHWC, 16-byte loads of four channels (C a multiple of 4)
 
 constexpr unsigned kOutside = 0x80000000u;
-constexpr unsigned kGuard = 16;
+constexpr unsigned kGuard = 20;   // bytes: five pixels, the most a row of F(4x4) starts before its plane
+constexpr int kTinyImage = 8;     // pixels: more than those five
 
 __device__ __forceinline__ v4f load_b128(const char* base, unsigned extent, unsigned off) {
   const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, extent, 0x00020000);
@@ -48,7 +52,9 @@ struct TileLoader {
   unsigned rowoff[A];  // byte offset of the patch row's first pixel (channel 0, NCHW: channel dl)
   unsigned cmask[A];   // all ones where the patch column lies inside the image
   int ix0, dl, C, W;
-  bool any_first, any_last;  // a row load of a lane in the tensor's first / last plane leaves the tensor
+  // Channels below first_end, and from last_begin on: a row load of some lane may leave the tensor (in
+  // its first or last plane; in images of fewer than kTinyImage pixels in any).
+  int first_end, last_begin;
 
   // p: the lane's tile (clamped); dl: its channel relative to the wave's (NCHW: below 4)
   __device__ __forceinline__ void setup(const TileGeo& g, int p, int dl_) {
@@ -59,10 +65,11 @@ struct TileLoader {
     ix0 = tx * M - g.pad;
     dl = dl_; C = g.C; W = g.W;
     bool first = false, last = false;
+    const bool cols = LOAD == kRowsEdge || (ix0 > -A && ix0 < W);  // some column lies inside the image
 #pragma unroll
     for (int r = 0; r < A; r++) {
       const int iy = iy0 + r;
-      const bool ok = iy >= 0 && iy < g.H;
+      const bool ok = cols && iy >= 0 && iy < g.H;
       if constexpr (kNhwc) {
         rowoff[r] = ok ? (((unsigned)n * (unsigned)g.H + (unsigned)iy) * (unsigned)W + (unsigned)ix0) *
                              (unsigned)C * 4u
@@ -77,8 +84,8 @@ struct TileLoader {
     }
 #pragma unroll
     for (int s = 0; s < A; s++) cmask[s] = (ix0 + s >= 0 && ix0 + s < W) ? 0xFFFFFFFFu : 0u;
-    any_first = __ballot(first) != 0;
-    any_last = __ballot(last) != 0;
+    first_end = HW < (unsigned)kTinyImage ? C : (__ballot(first) != 0 ? 1 : 0);
+    last_begin = __ballot(last) != 0 ? C - 4 : C;
   }
 
   // Channel cu + dl of the lane's patch (cu wave-uniform, below C).  NCHW lanes whose channel does not
@@ -96,7 +103,7 @@ struct TileLoader {
       base += (size_t)plane;
       base -= kGuard;
       const unsigned extent = g.x_bytes + kGuard - plane;
-      if ((any_first && cu == 0) || (any_last && cu + 4 >= C)) {
+      if (cu < first_end || cu >= last_begin) {
         // (offsets from a copy the compiler cannot see through: formed here, not kept in registers)
         int ix = ix0;
         asm volatile("" : "+v"(ix));

@@ -39,6 +39,12 @@ _SPLITS = [
     (8, 16, 40, 33, 31, 3, 4, 4, True),
     (2, 5, 300, 20, 18, 1, 2, 7, True),
     (1, 6, 5, 3, 2, 5, 2, 8, False),         # more padding than image
+    (3, 21, 10, 9, 8, 5, 4, 8, False),       # rows of F(4x4) that start five pixels before the image
+    (2, 6, 20, 4, 5, 13, 4, 8, False),       # tiles far outside the image
+    (3, 9, 20, 1, 1, 2, 2, 8, False),        # images smaller than a load
+    (2, 70, 5, 1, 3, 2, 4, 8, False),
+    (2, 4, 20, 3, 1, 5, 4, 6, False),
+    (2, 9, 6, 1, 2, 3, 2, 8, True),
 ]
 
 
@@ -131,6 +137,9 @@ _WEIGHT_ONLY = [
     (40, 1, 40, 56, 56, 0, 2, 4),
     (70, 20, 9, 56, 54, 2, 2, 6),
     (70, 2, 3, 60, 57, 1, 4, 8),
+    (3, 40, 20, 9, 8, 5, 4, 8),
+    (3, 41, 20, 1, 3, 2, 2, 8),
+    (2, 37, 5, 1, 1, 5, 4, 8),
 ]
 
 
