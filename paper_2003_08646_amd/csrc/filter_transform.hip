@@ -190,6 +190,7 @@ __global__ __launch_bounds__(NT) void filter_quant_kernel(const FtArgs a) {
   }
   __syncthreads();
 
+  const float L = (float)((1 << a.bits) - 1);
   const unsigned h = 1u << (a.bits - 1), hh = h * 0x01010101u, H8 = 0x80808080u;
   // codes: Eq. 7's unsigned codes of the four channels, 0 where the channel does not exist
   auto dword_of = [&](const float (&gw)[4][9], unsigned mask, unsigned (&codes)[E]) {
@@ -202,9 +203,11 @@ __global__ __launch_bounds__(NT) void filter_quant_kernel(const FtArgs a) {
 #pragma unroll
       for (int e = 0; e < E; e++) {
         const float2 p = qp_s[e];
-        // clamp(rne((x - min) * inv), 0, L): the conversion rounds to nearest even and saturates to
-        // [0, 255]; the ranges are those of these filters, so L is never exceeded
-        codes[e] = __builtin_amdgcn_cvt_pk_u8_f32((u[e / A][e % A] - p.x) * p.y, q, q == 0 ? 0u : codes[e]);
+        // clamp(rne((x - min) * inv), 0, L): the conversion rounds to nearest even.  The ranges are those
+        // of these filters, but where x - min overflows the product is infinite, and 0 * infinity is
+        // undefined: those are L and (the median with one undefined value is the least of the others) 0
+        const float t = __builtin_amdgcn_fmed3f((u[e / A][e % A] - p.x) * p.y, 0.0f, L);
+        codes[e] = __builtin_amdgcn_cvt_pk_u8_f32(t, q, q == 0 ? 0u : codes[e]);
       }
       // (one channel after the other, and the parameters read again for each)
 #pragma unroll

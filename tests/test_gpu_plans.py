@@ -324,3 +324,32 @@ def test_filter_transform_shapes(K, C, m, bits_w, flags):
         np.testing.assert_array_equal(conv.u_range.cpu().numpy(), ref.u_range)
         _assert_codes(conv.codes_to_logical(conv.uq, K), ref.Uq, "filter codes")
         np.testing.assert_array_equal(conv.u_rowsum.cpu().numpy(), ref.u_rowsum)
+
+
+@pytest.mark.parametrize("kind", ["overflow", "nan", "inf"])
+@pytest.mark.parametrize("bits_w,packed", [(8, False), (4, False), (4, True), (2, False)])
+@pytest.mark.parametrize("m", [2, 4])
+def test_filter_codes_at_the_end_of_binary32(m, bits_w, packed, kind):
+    """Ranges whose width overflows, undefined and infinite weights: codes stay within their width, and
+    an undefined product takes code 0."""
+    from paper_2003_08646_amd import binding as B
+    from paper_2003_08646_amd.layer import LanceConv
+    K, C = 20, 70
+    Wt = np.random.default_rng(640).standard_normal((K, C, 3, 3)).astype(np.float32)
+    if kind == "overflow":
+        Wt[3, 5], Wt[7, 60] = 0, 0
+        Wt[3, 5, 0, 0], Wt[7, 60, 0, 0] = 2e38, -2e38
+    else:
+        Wt[3, 5, 1, 1] = float(kind)
+    with np.errstate(invalid="ignore", over="ignore"):
+        U = O.filter_transform_f32(Wt, m)  # [E][K][C]
+        lo, hi = np.fmin.reduce(U, (1, 2)), np.fmax.reduce(U, (1, 2))
+        inv = ((2 ** bits_w - 1) / (hi.astype(np.float64) - lo)).astype(np.float32)
+        t = (U - lo[:, None, None]) * inv[:, None, None]
+        ref = np.where(np.isnan(t), 0, np.clip(np.rint(t), 0, 2 ** bits_w - 1)).astype(np.int32) - 2 ** (bits_w - 1)
+    conv = LanceConv(1, C, 8, 8, K, 1, m, 4, B.LANCE_CODES_PACKED4 if packed else 0, bits_w=bits_w)
+    conv.prepare_filters(torch.from_numpy(Wt).cuda())
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(conv.u_range.cpu().numpy(), np.stack([lo, hi], 1))
+    _assert_codes(conv.codes_to_logical(conv.uq, K), ref, "filter codes")
+    np.testing.assert_array_equal(conv.u_rowsum.cpu().numpy(), ref.sum(2))
