@@ -221,10 +221,12 @@ int lance_conv3x3_winograd_q8_noalloc(const lance_conv_desc *desc, const float *
  * returns each kernel's duration, averaged over the passes, in milliseconds in
  * kernel_ms_host[LANCE_PROFILE_KERNELS] (HOST memory): [0] range pass over X, [1] range
  * reduction + quantizer/de-quantizer constants, [2] transform+quantize pass,
- * [3] GEMM+epilogue.  Layers of few tiles, and m = 2 layers of 17 to 128 channels, run as two
- * kernels (V's codes never leave the chip): then [1] and [2] are exactly 0 and [3] covers range reduction,
- * transform+quantize, GEMM and epilogue.  Where the quantize pass reduces the range records
- * itself [1] is the time between two adjacent events.  A duration includes the launch gap in
+ * [3] GEMM+epilogue.  Layers of few tiles, m = 2 layers of at most 128 channels and m = 4 layers of
+ * at most 128 channels keep V's codes on chip: then [2] is exactly 0 and [3] covers
+ * transform+quantize, GEMM and epilogue.  [1] is exactly 0 where the last kernel always reduces the
+ * ranges itself (m = 2 layers of 17 to 128 channels, layers of few tiles but for those whose
+ * workgroups take many rounds); where a plan has both forms and this layer needs no reduction
+ * kernel, [1] is the time between two adjacent events.  A duration includes the launch gap in
  * front of its kernel.  repeats: 1 .. LANCE_PROFILE_MAX_REPEATS, else LANCE_ERR_INVALID_ARG.
  * (Times the kernels of Algorithm 1's steps; defines no operation of its own.) */
 #define LANCE_PROFILE_KERNELS 4

@@ -17,7 +17,8 @@
 //     (Eq. 9) and stores the patch.
 //
 // The transform is repeated by each of the ceil(K / (16*KG)) workgroups of a tile block: the plan
-// is for layers that leave the chip idle otherwise (conv_fused_pos_preferred).
+// is for layers that leave the chip idle otherwise (conv_fused_pos_preferred).  Every workgroup reduces
+// the records of the range pass for itself, unless that is repeated too often (conv_fused_pos_can_merge).
 //
 // What bounds it: the chain launch - pixels and ranges from memory (about 2 us) - constants -
 // transform - uq fragments - exchange - stores of one workgroup; 6 us for the smallest layers with

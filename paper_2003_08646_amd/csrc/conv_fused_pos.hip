@@ -48,7 +48,7 @@ static bool conv_fused_pos_applicable(const Geo& g) {
 // Where the line lies (us per fused call, the plan that would run otherwise against this one; N, C,
 // K, image):
 //  * F(4x4), at most 16 channels: always (the fallback plan: N14 16->32 116x130 124 -> 41,
-//    N9 16->128 97^2 NHWC 194 -> 111, N5 16->512 12^2 123 -> 16).
+//    N9 16->128 97^2 NHWC 194 -> 111, N5 16->512 12^2 123 -> 16; N62 4->68 213x224 1474 -> 1082).
 //  * F(2x2), at most 16 channels: while conv_fused_c16's workgroups of 256 tiles leave most of the
 //    chip idle (N3 4->43 112x95 32 -> 16, N11 5->58 58^2 46 -> 24, N1 3->64 224^2 20.5 -> 19.3,
 //    N4 3->64 224^2 33 against 66).
@@ -62,12 +62,24 @@ bool conv_fused_pos_preferred(const Geo& g) {
   return pos::shape_of(g).groups <= (g.m == 2 && g.NB <= 2 ? 512 : 256);
 }
 
+// Whether every workgroup reduces the records of the range pass for itself, or a reduction kernel does
+// it once (3 to 4 us).  A compute unit's workgroups of one round after the other each read the records
+// in batches of eight per thread, about 0.5 us a batch.  Over 1200 layers of both tile sizes the two
+// meet at 8 batches: at 10 to 14 the workgroups' own reduction costs 0.5 to 5 us more (N88 3->12 72x57
+// F(4x4) 60.0 -> 55.3 us per call with the kernel), on large first layers up to half of the call (N203
+// 1->128 123x123 F(4x4) 2024 -> 1272 us); below 4 the kernel costs 2 to 4.6 us more.
+bool conv_fused_pos_can_merge(const Geo& g, int count) {
+  const pos::Shape sh = pos::shape_of(g);
+  const long long slots = sh.nw == 8 ? 512 : 256, groups = sh.nw * 64 / (2 * g.E);
+  return (sh.groups + slots - 1) / slots * ((count + 8 * groups - 1) / (8 * groups)) <= 8;
+}
+
 hipError_t launch_conv_fused_pos(const Geo& g, const float* x, const int8_t* uq,
                                  const float* u_range, const int32_t* u_rowsum,
-                                 const float* partial, int count, float* v_range, float* y,
+                                 const float* partial, int count, int merge, float* v_range, float* y,
                                  hipStream_t s) {
   if (!conv_fused_pos_applicable(g)) return hipErrorInvalidValue;
-  const bool is_static = (g.flags & LANCE_INPUT_RANGE_STATIC) != 0;
+  const bool is_static = (g.flags & LANCE_INPUT_RANGE_STATIC) != 0 || !merge;
   const pos::Shape sh = pos::shape_of(g);
   if (sh.groups > 0x7FFFFFFFLL) return hipErrorInvalidValue;
   const pos::CpArgs a{x, uq, u_range, u_rowsum, partial, v_range, y, nullptr, count,

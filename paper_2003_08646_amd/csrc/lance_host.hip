@@ -291,7 +291,7 @@ static int conv_launch(const Geo& g, const Workspace& wl, const float* x_dev, co
   const DqOut dqo{u_range_dev, u_rowsum_dev, dq, rk, dqd, g.K, g.C, gemm_fused_wants_rk(g) ? 1 : 0,
                   g.bits_w, code_bias(g)};
   const PlanChoice pc = choose_plan(g, x_dev);
-  const bool fuse_q1 = pc.fuse_q1, fuse_q = pc.fuse_p || pc.fuse_q1 || pc.fuse_q2, fuse_s = pc.fuse_s;
+  const bool fuse_q1 = pc.fuse_q1, fuse_q = pc.fuse_q1 || pc.fuse_q2, fuse_s = pc.fuse_s;
   if (plan_out) *plan_out = pc.plan();
   if (pc.split_p) {
     const bool is_static = (g.flags & LANCE_INPUT_RANGE_STATIC) != 0;
@@ -308,6 +308,29 @@ static int conv_launch(const Geo& g, const Workspace& wl, const float* x_dev, co
     note_slot(3);
     if (e == hipSuccess)
       e = launch_gemm_pos(g, uq_dev, vq, u_range_dev, u_rowsum_dev, v_range, y_dev, s);
+  } else if (pc.fuse_p) {
+    // Layers of few tiles: range pass, the reduction kernel where it saves more than it costs (then the
+    // call counts as three kernels), one kernel that quantizes, multiplies and transforms back.
+    const bool is_static = (g.flags & LANCE_INPUT_RANGE_STATIC) != 0;
+    float* partial = (float*)(ws + wl.off_partial);
+    int groups = 0;
+    if (e == hipSuccess && ev) e = hipEventRecord(ev[0], s);
+    note_slot(0);
+    if (e == hipSuccess && !is_static) e = launch_input_range(g, x_dev, partial, colsum, 0, &groups, s);
+    if (e == hipSuccess && ev) e = hipEventRecord(ev[1], s);
+    const bool merge = is_static || conv_fused_pos_can_merge(g, groups);
+    if (!merge) {
+      note_slot(1);
+      if (plan_out) *plan_out = kPlanThreeKernels;
+      if (e == hipSuccess)
+        e = launch_range_finalize(partial, groups, g.E, (g.flags & LANCE_RANGE_PER_TENSOR) ? 1 : 0,
+                                  0, g.bits, v_range, nullptr, nullptr, s);
+      if (e == hipSuccess && ev) e = hipEventRecord(ev[2], s);
+    }
+    note_slot(3);
+    if (e == hipSuccess)
+      e = launch_conv_fused_pos(g, x_dev, uq_dev, u_range_dev, u_rowsum_dev, partial, groups,
+                                merge ? 1 : 0, v_range, y_dev, s);
   } else if (fuse_q) {
     const bool is_static = (g.flags & LANCE_INPUT_RANGE_STATIC) != 0;
     float* partial = (float*)(ws + wl.off_partial);
@@ -318,9 +341,7 @@ static int conv_launch(const Geo& g, const Workspace& wl, const float* x_dev, co
     if (e == hipSuccess && ev) e = hipEventRecord(ev[1], s);
     note_slot(3);
     if (e == hipSuccess)
-      e = pc.fuse_p ? launch_conv_fused_pos(g, x_dev, uq_dev, u_range_dev, u_rowsum_dev, partial,
-                                            groups, v_range, y_dev, s)
-          : fuse_q1 ? launch_conv_fused_c64(g, x_dev, uq_dev, u_range_dev, u_rowsum_dev, partial,
+      e = fuse_q1 ? launch_conv_fused_c64(g, x_dev, uq_dev, u_range_dev, u_rowsum_dev, partial,
                                           groups, v_range, y_dev, s)
                   : launch_conv_fused_c128(g, x_dev, uq_dev, u_range_dev, u_rowsum_dev, partial,
                                            groups, v_range, y_dev, s);

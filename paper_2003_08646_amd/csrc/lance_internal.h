@@ -200,11 +200,13 @@ hipError_t launch_conv_fused_c16(const Geo& g, const float* x, const int8_t* uq,
                                  const float* u_range, hipStream_t s);
 // Range reduction, quantize pass, products and epilogue in one kernel for layers with few tiles
 // (conv_fused_pos.h): both tile sizes and layouts, any number of channels, packed filter codes.
-// partial/count and v_range as for launch_conv_fused_c64.
+// merge != 0: every workgroup reduces the `count` records in `partial` and the first writes v_range
+// (with static ranges: all read v_range); merge == 0: v_range is finished (launch_range_finalize).
 bool conv_fused_pos_preferred(const Geo& g);
+bool conv_fused_pos_can_merge(const Geo& g, int count);
 hipError_t launch_conv_fused_pos(const Geo& g, const float* x, const int8_t* uq,
                                  const float* u_range, const int32_t* u_rowsum,
-                                 const float* partial, int count, float* v_range, float* y,
+                                 const float* partial, int count, int merge, float* v_range, float* y,
                                  hipStream_t s);
 // The same in two kernels, with V's codes passing through vq (gemm_fused_pos.hip): the quantize pass
 // (partial/count and v_range as above) and the product kernel (which reads v_range).

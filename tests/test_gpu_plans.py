@@ -58,6 +58,31 @@ def test_position_parallel_splits(shape, static):
     _check_layer(L, flags=flags, static_v_range=_range_of_another_batch(L) if static else None, staged=False)
 
 
+def _kernels(conv, x):
+    """Names of the kernels of one fused call, by slot of the timing twin."""
+    from paper_2003_08646_amd import binding as B
+    B.lance_conv3x3_winograd_q8_profile(conv.desc, x, conv.uq, conv.u_range, conv.u_rowsum, conv.v_range,
+                                        torch.empty_like(conv.y), conv.workspace)
+    return [B.lance_profile_kernel_name(i) for i in range(len(B.PROFILE_KERNELS))]
+
+
+# layers whose workgroups run in many rounds: the ranges are reduced in front of them
+_ROUNDS = [(40, 3, 70, 65, 63, 1, 4, 8, False), (64, 12, 150, 65, 63, 0, 4, 6, True), (11, 3, 500, 65, 63, 1, 2, 8, False)]
+
+
+@pytest.mark.parametrize("shape", _ROUNDS, ids=lambda s: "n%d_c%d_k%d_%dx%d_p%d_m%d_b%d%s" % (s[:8] + ("_nhwc" if s[8] else "",)))
+@pytest.mark.parametrize("per_tensor", [False, True], ids=["per_position", "per_tensor"])
+def test_position_parallel_reduction_kernel(shape, per_tensor):
+    from paper_2003_08646_amd import binding as B
+    N, C, K, H, W, pad, m, bits, nhwc = shape
+    L = Wk.Layer("rounds", N, C, K, H, W, pad=pad, m=m, bits=bits, seed=650 + C)
+    flags = (B.LANCE_LAYOUT_NHWC if nhwc else 0) | (B.LANCE_RANGE_PER_TENSOR if per_tensor else 0)
+    conv, ref = _check_layer(L, flags=flags, staged=False)
+    x = torch.zeros((N, H, W, C) if nhwc else (N, C, H, W), device="cuda")
+    names = _kernels(conv, x)
+    assert names[1:] == ["range_finalize_kernel", "", "conv_fused_pos_kernel"], names
+
+
 @pytest.mark.parametrize("m", [2, 4])
 @pytest.mark.parametrize("nhwc", [False, True], ids=["nchw", "nhwc"])
 def test_position_parallel_packed(m, nhwc):
