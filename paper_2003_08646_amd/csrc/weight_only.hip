@@ -504,22 +504,24 @@ WmShape wm_shape(const Geo& g) {
 int plain_filters(const Geo& g) { return g.m == 2 ? 8 : 4; }
 
 // Whether the vector-ALU kernel takes less time: both times in us from fits to sweeps over 1 to 64
-// channels, 1 to 512 filters, 49 to 506250 tiles, both layouts (3338 layers, each kernel on each: within
-// 5 % of the better one on all but 50 of them, within 40 % on all).  100352 tiles of F(2x2), vector and matrix
-// form: 1 -> 8 channels 9 and 58 us, 16 -> 8 40 and 58, 3 -> 40 42 and 88, 16 -> 64 220 and 93; NHWC
-// 3 -> 4 13 and 58, 3 -> 16 105 and 59.
+// channels, 1 to 600 filters, 9 to 506250 tiles, both layouts (each kernel on each of 3500 layers: of the
+// 20 on which the choice costs more than 5 %, twelve take up to 1.4 times the vector form's time, eight up to
+// 1.25 times the matrix form's).  100352 tiles of F(2x2), vector and matrix form: 1 -> 8 channels 9 and 58 us,
+// 16 -> 8 40 and 58, 3 -> 40 42 and 88, 16 -> 64 220 and 93; NHWC 3 -> 4 13 and 58, 3 -> 16 105 and 59.
 bool vector_form_faster(const Geo& g, const WmShape& sh) {
-  // Vector form: the latency of one workgroup or its rounds, each linear in C.  NHWC: its stores are
-  // K floats apart, worst at 16 filters (one 64-byte piece per pixel), and its loads C floats.
-  struct Fit { double lat, lat_c, base, round, round_c; int most_c, nhwc_most_c, nhwc_most_k; };
-  static constexpr Fit kFit[2] = {{6.0, 1.75, 2.2, 2.1, 1.1, 32, 12, 20}, {6.0, 4.4, 0.7, 7.1, 5.1, 20, 6, 12}};
+  // Vector form: the latency of one workgroup, or its rounds where the workgroups share compute units, each
+  // linear in C; the latency grows with the filters of a workgroup (their stores), too.  NHWC: stores are
+  // K floats apart, worst at 16 filters (one 64-byte piece per pixel), and loads C floats.
+  struct Fit { double lat, lat_c, lat_k, base, round, round_c; int most_c, nhwc_most_c, nhwc_most_k; };
+  static constexpr Fit kFit[2] = {{2.1, 1.5, 0.3, 1.4, 2.1, 0.95, 64, 12, 20}, {1.5, 4.5, 1.6, 0.7, 7.1, 5.1, 20, 6, 12}};
   const bool nhwc = is_nhwc(g), m4 = g.m == 4;
   const Fit& f = kFit[m4];
   if (g.C > (nhwc ? f.nhwc_most_c : f.most_c) || (nhwc && (g.K > f.nhwc_most_k || g.K == 16))) return false;
-  const long long blocks = ((g.P + kThreads - 1LL) / kThreads) * ((g.K + plain_filters(g) - 1) / plain_filters(g));
-  const double by_latency = f.lat + f.lat_c * g.C;
+  const int kf = plain_filters(g);
+  const long long blocks = ((g.P + kThreads - 1LL) / kThreads) * ((g.K + kf - 1) / kf);
+  double vector_us = f.lat + f.lat_c * g.C + f.lat_k * (g.K < kf ? g.K : kf);
   const double by_rounds = f.base + (double)((blocks + 255) / 256) * (f.round + f.round_c * g.C);
-  double vector_us = by_latency > by_rounds ? by_latency : by_rounds;
+  if (blocks > 128 && by_rounds > vector_us) vector_us = by_rounds;
   if (nhwc)
     vector_us += (m4 ? 90e-6 : (g.C % 4 == 0 ? 25e-6 : 15e-6)) * (g.K > 16 ? 1.7 : 1.0) * (double)g.P * g.K;
   // Matrix form: launch + rounds of one workgroup per compute unit, by shape: {launch, the first turn
