@@ -13,7 +13,7 @@
 // from there ou is at most half of 1/255 of the range wherever that holds zero, so the two terms do not
 // cancel, however far the range is from symmetric and however few the codes.  V enters the split times 2^24 (the results
 // leave it again): the smallest binary32 value's pieces are then normal bf16 numbers, so the split is
-// exact for every V below 2^104; what overflows is formed again in the plain form (plain_sums).
+// exact for every V below 2^104; what overflows is formed again in the plain form (plain_results).
 //
 // weight_only_mfma_kernel: a workgroup of 16 waves (m = 4: 12) takes 16*TG tiles x 16*KG filters,
 // wave w the positions w*E/NW ..  Turn by turn over CH channels: every lane transforms one channel
@@ -95,43 +95,6 @@ __device__ __forceinline__ bf16x8 codes_to_bf16(v2u c, float unit, float zero) {
   return __builtin_bit_cast(bf16x8, r);
 }
 
-// M[e] of one filter and tile in the plain form, channel by channel on the vector ALUs.  The split into
-// three pieces has none for an infinite value (inf - inf), and its sums overflow before these do (2^24
-// and the codes against scaled codes): a result that is not finite is formed again from these.
-template <int M, bool NHWC>
-__device__ __forceinline__ void plain_sums(const WmArgs& a, const float* sc_s, int k, int p,
-                                           float (&acc)[M + 2][M + 2]) {
-  constexpr int A = M + 2, E = A * A;
-  const int y0 = (p / a.tw) % a.th * M - a.pad, x0 = p % a.tw * M - a.pad, n = p / a.tw / a.th;
-  const int CB = a.cb16 ? 16 : 64, Q = CB / 4, h = 1 << (a.bits_w - 1);
-#pragma unroll
-  for (int e = 0; e < E; e++) acc[e / A][e % A] = 0.0f;
-#pragma unroll 1
-  for (int c = 0; c < a.C; c++) {
-    asm volatile("" ::: "memory");  // (scales and minima read again, not kept in registers)
-    float d[A][A];
-#pragma unroll
-    for (int r = 0; r < A; r++)
-#pragma unroll
-      for (int s = 0; s < A; s++) {
-        const int gy = y0 + r, gx = x0 + s;
-        const bool ok = gy >= 0 && gy < a.H && gx >= 0 && gx < a.W;
-        const float v = a.x[dev::act_index(NHWC, n, c, min(max(gy, 0), a.H - 1),
-                                           min(max(gx, 0), a.W - 1), a.C, a.H, a.W)];
-        d[r][s] = ok ? v : 0.0f;
-      }
-    dev::input_tile_transform<M>(d);
-    const int b = c / CB, r = c % CB, at = NHWC ? r : 4 * (r % Q) + r / Q;
-#pragma unroll
-    for (int e = 0; e < E; e++) {
-      if (e % A == 0) asm volatile("" ::: "memory");
-      const int code = (int)a.uq[(((size_t)e * a.NB + b) * a.K + k) * CB + at] + h;
-      const float u = (float)code * sc_s[e] + a.u_range[2 * e];
-      acc[e / A][e % A] = __builtin_fmaf(u, d[e / A][e % A], acc[e / A][e % A]);
-    }
-  }
-}
-
 // o = A^T v A
 template <int M>
 __device__ __forceinline__ void out2d(const float (&v)[M + 2][M + 2], float (&o)[M][M]) {
@@ -150,6 +113,96 @@ __device__ __forceinline__ void out2d(const float (&v)[M + 2][M + 2], float (&o)
   for (int r = 0; r < M; r++) dev::out1d<M>(tt[r], o[r]);
 }
 
+// The (filter, tile) pair that thread tid takes in turn t: filter kin and tile pin of the workgroup's.
+template <int M, int TG, int KG, bool NHWC>
+struct Pairs {
+  static constexpr int NT = M == 2 ? 1024 : 768, kPairs = KG * TG * 256, kTurns = (kPairs + NT - 1) / NT;
+  int i, kin, pin;
+  __device__ __forceinline__ Pairs(int tid, int t) : i(tid + t * NT) {
+    const int idx = i & 255, kt = i >> 8;
+    kin = kt / TG * 16 + (NHWC ? idx & 15 : 4 * ((idx >> 4) & 3) + (idx >> 6));
+    pin = kt % TG * 16 + (NHWC ? idx >> 4 : idx & 15);
+  }
+  __device__ __forceinline__ bool exists() const { return kPairs % NT == 0 || i < kPairs; }
+};
+
+// The workgroup's products in the plain form (binary32 on the vector ALUs, channel by channel), o of the
+// bad pairs from them.  The split into three pieces has none for an infinite value (inf - inf), and its
+// sums overflow before these do (2^24 and the codes against scaled codes): results that are not finite
+// are formed again here.  kC channels of all tiles and filters at a time go through buf; what bounds it is
+// the reads of these rows from LDS (twelve 16-byte ones per channel for two pairs).  All threads; buf is
+// free before and after.  N32 64->64 32x32 with one infinite value 112 us (312 with one thread per pair
+// reading its own codes and pixels, 100 on the vector-ALU kernel; 13.5 without it), with nothing else
+// 115 (394, 99); N4 512->512 14x14 420 (1035, 753).
+template <int M, int TG, int KG, bool NHWC>
+__device__ __forceinline__ void plain_results(const WmArgs& a, const float* sc_s, int k0, int p0, int tid, float* buf,
+                                           const bool (&bad)[Pairs<M, TG, KG, NHWC>::kTurns],
+                                           float (&o)[Pairs<M, TG, KG, NHWC>::kTurns][M][M]) {
+  using P = Pairs<M, TG, KG, NHWC>;
+  constexpr int A = M + 2, E = A * A, NT = P::NT, kC = 12, kTiles = 16 * TG, kFilters = 16 * KG;
+  constexpr int kRow = M == 2 ? 20 : 36;  // floats: the 16-byte pieces of 16 rows lie in different banks
+  float* vs = buf;                       // [kC][kTiles][kRow]
+  float* us = vs + kC * kTiles * kRow;   // [kC][kFilters][kRow]
+  static_assert(kC * (kTiles + kFilters) * kRow * sizeof(float) <= (size_t)E * 3 * (M == 2 ? 2 : 1) * 1024, "LDS");
+  const int lc = a.cb16 ? 4 : 6, h = 1 << (a.bits_w - 1);  // channels of a block: 2^lc
+  float acc[P::kTurns][E];
+#pragma unroll
+  for (int t = 0; t < P::kTurns; t++)
+#pragma unroll
+    for (int e = 0; e < E; e++) acc[t][e] = 0.0f;
+  for (int c0 = 0; c0 < a.C; c0 += kC) {
+    const int nc = min(kC, a.C - c0);
+    __syncthreads();
+    for (int i = tid; i < nc * kTiles; i += NT) {
+      const int c = c0 + i / kTiles, p = min(p0 + i % kTiles, a.P - 1);
+      const int y0 = (p / a.tw) % a.th * M - a.pad, x0 = p % a.tw * M - a.pad, n = p / a.tw / a.th;
+      float d[A][A];
+#pragma unroll
+      for (int r = 0; r < A; r++)
+#pragma unroll
+        for (int s = 0; s < A; s++) {
+          const int gy = y0 + r, gx = x0 + s;
+          const bool ok = gy >= 0 && gy < a.H && gx >= 0 && gx < a.W;
+          const float v = a.x[dev::act_index(NHWC, n, c, min(max(gy, 0), a.H - 1),
+                                             min(max(gx, 0), a.W - 1), a.C, a.H, a.W)];
+          d[r][s] = ok ? v : 0.0f;
+        }
+      dev::input_tile_transform<M>(d);
+#pragma unroll
+      for (int e = 0; e < E; e++) vs[i * kRow + e] = d[e / A][e % A];
+    }
+#pragma unroll 4
+    for (int i = tid; i < nc * kFilters * E; i += NT) {
+      const int e = i % E, kc = i / E;
+      const int c = c0 + kc / kFilters, k = min(k0 + kc % kFilters, a.K - 1);
+      const int b = c >> lc, r = c & ((1 << lc) - 1), lq = lc - 2;
+      const int at = NHWC ? r : 4 * (r & ((1 << lq) - 1)) + (r >> lq);
+      const int code = (int)a.uq[((((size_t)e * a.NB + b) * a.K + k) << lc) + at] + h;
+      us[kc * kRow + e] = (float)code * sc_s[e] + a.u_range[2 * e];
+    }
+    __syncthreads();
+    static_assert(P::kTurns == 1 || (P::kPairs % NT == 0 && NT % (256 * TG) == 0), "one tile per thread, whatever the turn");
+    for (int c = 0; c < nc && P(tid, 0).exists(); c++) {
+      const float* v = vs + (c * kTiles + P(tid, 0).pin) * kRow;
+#pragma unroll
+      for (int t = 0; t < P::kTurns; t++) {
+        const float* u = us + (c * kFilters + P(tid, t).kin) * kRow;
+#pragma unroll
+        for (int e = 0; e < E; e++) acc[t][e] = __builtin_fmaf(u[e], v[e], acc[t][e]);
+      }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < P::kTurns; t++)
+    if (bad[t]) {
+      float mm[A][A];
+#pragma unroll
+      for (int e = 0; e < E; e++) mm[e / A][e % A] = acc[t][e];
+      out2d<M>(mm, o[t]);
+    }
+}
+
 template <int M, int TG, int KG, int LOAD>
 __global__ __launch_bounds__(M == 2 ? 1024 : 768) void weight_only_mfma_kernel(const WmArgs a) {
   constexpr int A = M + 2, E = A * A, NW = M == 2 ? 16 : 12, NT = NW * 64, PW = E / NW;
@@ -160,8 +213,9 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void weight_only_mfma_kernel(c
   float* sc_s = reinterpret_cast<float*>(smem);  // [E] scale
   float* ou_s = sc_s + E;                        // [E] min + step * z
   float* zero_s = ou_s + E;                      // [E] z + (128 - 2^(b-1)) * unit
+  int* huge_s = reinterpret_cast<int*>(zero_s + E);  // some M might overflow on its way to an output
   const float unit = (float)(1 << (8 - a.bits_w));
-  static_assert(3 * E * sizeof(float) <= 512, "parameters");
+  static_assert((3 * E + 1) * sizeof(float) <= 512, "parameters");
   char* ring = smem + 512;                       // [E][3][NH][TG][16 rows][64 B]
   float* ex = reinterpret_cast<float*>(ring);
   const int tid = threadIdx.x, lane = tid & 63;
@@ -208,6 +262,7 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void weight_only_mfma_kernel(c
     ou_s[tid] = (float)((double)mn + step * z);
     zero_s[tid] = (float)z + (float)(128 - (1 << (a.bits_w - 1))) * unit;
   }
+  if (tid == 0) *huge_s = 0;
 
   const int col = lane & 15, kq = lane >> 4;
   const unsigned f_off = (unsigned)(col * 64 + ((kq ^ ((col >> 2) & 3)) * 16));
@@ -292,6 +347,7 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void weight_only_mfma_kernel(c
   }
 
   // ---- M to LDS; lane: tile col, filters 4*kq .. of each group ----
+  bool huge = false;
 #pragma unroll
   for (int w = 0; w < PW; w++) {
     const int e = wave * PW + w;
@@ -304,7 +360,10 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void weight_only_mfma_kernel(c
         float* dstm = ex + ((e * KG + kg) * TG + t) * 256;
         v4f m;
 #pragma unroll
-        for (int r = 0; r < 4; r++) m[r] = __builtin_fmaf(sc, acc[w][t][kg][r], off);
+        for (int r = 0; r < 4; r++) {
+          m[r] = __builtin_fmaf(sc, acc[w][t][kg][r], off);
+          huge |= !(fabsf(m[r]) < 0x1p118f);  // (A^T M A is at most 361 times the largest M)
+        }
         if constexpr (kNhwc) {
           *reinterpret_cast<v4f*>(dstm + col * 16 + 4 * kq) = m;
         } else {
@@ -314,27 +373,39 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void weight_only_mfma_kernel(c
       }
     }
   }
+  if (huge) *huge_s = 1;
   __syncthreads();
-  for (int i = tid; i < KG * TG * 256; i += NT) {
-    const int idx = i & 255, kt = i >> 8;
-    const int kg = kt / TG, t = kt % TG;
-    const int kin = kNhwc ? idx & 15 : 4 * ((idx >> 4) & 3) + (idx >> 6);
-    const int pin = kNhwc ? idx >> 4 : idx & 15;
-    const int k = k0 + kg * 16 + kin, p = p0 + 16 * t + pin;
-    if (k >= K || p >= P) continue;
-    float mm[A][A], o[M][M], zero = 0.0f;
+  using PairsT = Pairs<M, TG, KG, kNhwc>;
+  float o[PairsT::kTurns][M][M];
+  bool bad[PairsT::kTurns];
+  const bool check = __builtin_amdgcn_readfirstlane(*huge_s) != 0;
 #pragma unroll
-    for (int e = 0; e < E; e++) mm[e / A][e % A] = ex[e * KG * TG * 256 + i];
-    out2d<M>(mm, o);
+  for (int t = 0; t < PairsT::kTurns; t++) {
+    const PairsT pr(tid, t);
+    bad[t] = false;
+    if (!pr.exists()) continue;
+    float mm[A][A];
+#pragma unroll
+    for (int e = 0; e < E; e++) mm[e / A][e % A] = ex[e * KG * TG * 256 + pr.i];
+    out2d<M>(mm, o[t]);
+    float zero = 0.0f;
 #pragma unroll
     for (int r = 0; r < M * M; r++) {
-      zero += 0.0f * o[r / M][r % M];
-      o[r / M][r % M] *= 1.0f / kUp;
+      zero += 0.0f * o[t][r / M][r % M];
+      o[t][r / M][r % M] *= 1.0f / kUp;
     }
-    if (zero != 0.0f) {  // not finite
-      plain_sums<M, kNhwc>(a, sc_s, k, p, mm);
-      out2d<M>(mm, o);
-    }
+    bad[t] = zero != 0.0f;  // not finite
+  }
+  if (check) {
+    int own = tid;
+    asm volatile("" : "+v"(own));  // (nothing of that is computed ahead of here)
+    plain_results<M, TG, KG, kNhwc>(a, sc_s, k0, p0, own, ex, bad, o);
+  }
+#pragma unroll
+  for (int t = 0; t < PairsT::kTurns; t++) {
+    const PairsT pr(tid, t);
+    const int k = k0 + pr.kin, p = p0 + pr.pin;
+    if (!pr.exists() || k >= K || p >= P) continue;
     const int ox0 = (p % a.tw) * M, q2 = p / a.tw;
     const int oy0 = (q2 % a.th) * M, on = q2 / a.th;
     const bool whole = !kNhwc && ox0 + M <= a.Wo;
@@ -343,13 +414,13 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void weight_only_mfma_kernel(c
       const bool row = oy0 + r < a.Ho;
       if (whole) {
         const unsigned off = (unsigned)dev::act_index(false, on, k, oy0 + r, ox0, K, a.Ho, a.Wo) * 4u;
-        store_row<M>(a.y, a.y_bytes, row ? off : kOobY, o[r]);
+        store_row<M>(a.y, a.y_bytes, row ? off : kOobY, o[t][r]);
       } else {
 #pragma unroll
         for (int s = 0; s < M; s++)
           store1(a.y, a.y_bytes, row && ox0 + s < a.Wo
                                      ? (unsigned)dev::act_index(kNhwc, on, k, oy0 + r, ox0 + s, K, a.Ho, a.Wo) * 4u
-                                     : kOobY, o[r][s]);
+                                     : kOobY, o[t][r][s]);
       }
     }
   }

@@ -279,16 +279,17 @@ def _two_sided(rows, t):
 
 @pytest.mark.parametrize("nhwc", [False, True], ids=["nchw", "nhwc"])
 @pytest.mark.parametrize("m", [2, 4])
-@pytest.mark.parametrize("C", [3, 40])
-def test_weight_only_infinities(C, m, nhwc):
+@pytest.mark.parametrize("N,K,C", [(2, 20, 3), (2, 20, 40), (72, 125, 43)])
+def test_weight_only_infinities(N, K, C, m, nhwc):
     """Infinities, a NaN and values whose sums of codes overflow: infinite and undefined results are
     those of the plain sums, the others within 4e-6 of the largest term's scale."""
     from paper_2003_08646_amd import binding as B
     from paper_2003_08646_amd.layer import LanceConv
-    N, K, H, W = 2, 20, 12, 13
+    H, W = 12, 13
     X, Wt = Wk.make_inputs(Wk.Layer("wo", N, C, K, H, W, pad=0, m=m, seed=590 + C))
     X[0, 1, 0, 0] = np.inf
     X[0, 2, 6, 7] = -np.inf
+    X[N // 2, C - 1, 5, 5] = np.inf
     X[1, 0, 11, 12] = np.nan
     X[1, 1, 0, 0] = 1e37
     f = O.prepare_filters(Wt, m, 8)
@@ -302,8 +303,8 @@ def test_weight_only_infinities(C, m, nhwc):
         for ty in range(th):
             for tx in range(tw):
                 v = _two_sided(_BT[m], xp[:, :, ty * m:ty * m + a, tx * m:tx * m + a])
-                mm = (u.transpose(1, 2, 0)[None] * v.reshape(N, 1, C, a * a)).sum(2)
-                ref[:, :, ty * m:ty * m + m, tx * m:tx * m + m] = _two_sided(_AT[m], mm.reshape(N, K, a, a))
+                mm = np.matmul(u, v.reshape(N, C, a * a).transpose(2, 1, 0))  # [E][K][N]
+                ref[:, :, ty * m:ty * m + m, tx * m:tx * m + m] = _two_sided(_AT[m], mm.transpose(2, 1, 0).reshape(N, K, a, a))
     ref = ref[:, :, :H - 2, :W - 2]
     conv = LanceConv(N, C, H, W, K, 0, m, 8, B.LANCE_LAYOUT_NHWC if nhwc else 0)
     conv.prepare_filters(torch.from_numpy(Wt).cuda())
