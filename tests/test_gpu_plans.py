@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 import torch
 
+import test_gpu_parity as parity
 from paper_2003_08646_amd import workloads as Wk
 from test_gpu_parity import _assert_codes, _check_layer, O
 
@@ -66,6 +67,11 @@ def _kernels(conv, x):
     return [B.lance_profile_kernel_name(i) for i in range(len(B.PROFILE_KERNELS))]
 
 
+def _zeros(conv, nhwc):
+    d = conv.desc
+    return torch.zeros((d.N, d.H, d.W, d.C) if nhwc else (d.N, d.C, d.H, d.W), device="cuda")
+
+
 # layers whose workgroups run in many rounds: the ranges are reduced in front of them
 _ROUNDS = [(40, 3, 70, 65, 63, 1, 4, 8, False), (64, 12, 150, 65, 63, 0, 4, 6, True), (11, 3, 500, 65, 63, 1, 2, 8, False)]
 
@@ -78,8 +84,7 @@ def test_position_parallel_reduction_kernel(shape, per_tensor):
     L = Wk.Layer("rounds", N, C, K, H, W, pad=pad, m=m, bits=bits, seed=650 + C)
     flags = (B.LANCE_LAYOUT_NHWC if nhwc else 0) | (B.LANCE_RANGE_PER_TENSOR if per_tensor else 0)
     conv, ref = _check_layer(L, flags=flags, staged=False)
-    x = torch.zeros((N, H, W, C) if nhwc else (N, C, H, W), device="cuda")
-    names = _kernels(conv, x)
+    names = _kernels(conv, _zeros(conv, nhwc))
     assert names[1:] == ["range_finalize_kernel", "", "conv_fused_pos_kernel"], names
 
 
@@ -114,7 +119,7 @@ def test_undefined_value_takes_the_code_of_the_other_plans(C, bits, m):
 
 # layers of more tiles than conv_fused_pos takes: the other plans with partial blocks and odd sizes
 _LARGE = [
-    (330, 60, 40, 9, 11, 0, 2, 8, False),
+    (460, 60, 40, 9, 11, 0, 2, 8, False),
     (200, 50, 70, 13, 14, 1, 2, 5, False),
     (60, 64, 130, 24, 24, 1, 2, 8, False),
     (330, 60, 40, 10, 9, 1, 2, 8, True),
@@ -127,7 +132,7 @@ _LARGE = [
     (100, 40, 130, 20, 21, 1, 4, 8, False),
     (60, 100, 130, 24, 24, 1, 4, 6, False),
     (60, 150, 300, 15, 17, 1, 4, 8, False),
-    (60, 70, 130, 17, 16, 0, 4, 8, True),
+    (120, 70, 130, 17, 16, 0, 4, 8, True),
     (60, 12, 40, 33, 31, 1, 2, 8, False),
     (60, 3, 70, 32, 32, 1, 2, 8, True),
 ]
@@ -138,7 +143,8 @@ def test_other_plans_on_many_tiles(shape):
     from paper_2003_08646_amd import binding as B
     N, C, K, H, W, pad, m, bits, nhwc = shape
     L = Wk.Layer("many_tiles", N, C, K, H, W, pad=pad, m=m, bits=bits, seed=540 + C)
-    _check_layer(L, flags=B.LANCE_LAYOUT_NHWC if nhwc else 0, staged=False)
+    conv, _ = _check_layer(L, flags=B.LANCE_LAYOUT_NHWC if nhwc else 0, staged=False)
+    assert not _kernels(conv, _zeros(conv, nhwc))[3].endswith("_pos_kernel")
 
 
 @pytest.mark.parametrize("m", [2, 4])
@@ -146,6 +152,80 @@ def test_packed_on_many_tiles(m):
     from paper_2003_08646_amd import binding as B
     L = Wk.Layer("packed_many", 80, 130, 200, 14, 16, m=m, bits=4, seed=560)
     _check_layer(L, flags=B.LANCE_CODES_PACKED4, staged=False)
+
+
+# Every kernel that multiplies outside the few-tile plans, with a layer that reaches it: where a small one
+# does only with LANCE_PLAN_WIDE_TILES (last item), a layer large enough to be its own.
+_PLANS = [
+    ("conv_fused_c64_kernel", 200, 50, 70, 13, 14, 1, 2, 5, ""),
+    ("conv_fused_c64_kernel", 330, 60, 40, 10, 9, 1, 2, 8, "nhwc"),
+    ("conv_fused_c128_kernel", 100, 96, 70, 16, 16, 1, 2, 6, ""),
+    ("conv_fused_c128_kernel", 110, 72, 130, 14, 13, 0, 2, 8, "nhwc"),
+    ("conv_fused_c16_kernel", 60, 12, 40, 33, 31, 1, 2, 8, ""),
+    ("conv_fused_c16_kernel", 60, 3, 70, 32, 32, 1, 2, 4, "nhwc"),
+    ("conv_fused_m4_kernel", 100, 40, 130, 20, 21, 1, 4, 8, ""),
+    ("gemm_fused_rows_kernel", 90, 150, 40, 14, 14, 1, 2, 8, ""),
+    ("gemm_fused_rows_kernel", 70, 140, 130, 14, 15, 0, 2, 7, "nhwc"),
+    ("gemm_fused_m2_stream_kernel", 80, 150, 130, 13, 15, 1, 2, 8, ""),
+    ("gemm_fused_m4_stream_kernel", 60, 150, 200, 15, 17, 1, 4, 8, ""),
+    ("gemm_fused_m4_stream_kernel", 120, 70, 130, 17, 16, 0, 4, 8, "nhwc"),
+    ("gemm_fused_tiled_m4_kernel", 120, 40, 130, 17, 16, 0, 4, 8, "nhwc"),
+    ("gemm_fused_tiled_m4_kernel", 2, 600, 70, 12, 13, 1, 4, 8, "wide"),
+    ("gemm_fused_kernel", 3, 12, 70, 13, 11, 1, 4, 8, "wide"),
+    ("gemm_fused_kernel", 2, 3, 1030, 13, 11, 1, 2, 6, "wide"),
+    ("gemm_fused_m2_packed_kernel", 80, 130, 200, 14, 16, 1, 2, 4, "packed"),
+    ("gemm_fused_m4_packed_kernel", 80, 130, 200, 14, 16, 1, 4, 4, "packed"),
+]
+
+
+def _plan_id(p):
+    return "%s_c%d_m%d_%s" % (p[0][:-7], p[2], p[7], p[9] or "nchw")
+
+
+@pytest.mark.parametrize("option", ["static", "per_tensor", "widths", "ties"])
+@pytest.mark.parametrize("plan", _PLANS, ids=_plan_id)
+def test_options_of_every_plan(plan, option):
+    """Ranges narrower than the data, one range for the whole tensor, filter codes of another width, and
+    rounding ties with both clamps (as in test_rounding_ties_and_both_clamps)."""
+    from paper_2003_08646_amd import binding as B
+    kernel, N, C, K, H, W, pad, m, bits, form = plan
+    bits_w = {8: 5, 7: 8, 6: 8, 5: 8, 4: 3}[bits] if option == "widths" else None
+    L = Wk.Layer("plan", N, C, K, H, W, pad=pad, m=m, bits=bits, bits_w=bits_w, seed=660 + C)
+    flags = {"": 0, "nhwc": B.LANCE_LAYOUT_NHWC, "wide": B.LANCE_PLAN_WIDE_TILES, "packed": B.LANCE_CODES_PACKED4}[form]
+    X, Wt = Wk.make_inputs(L)
+    static = None
+    if option == "per_tensor":
+        flags |= B.LANCE_RANGE_PER_TENSOR
+    elif option == "static":
+        static = (O.ranges(O.input_transform_f32(X, pad, m)) * np.float32(0.5)).astype(np.float32)
+    elif option == "ties":
+        X = np.random.default_rng(661).integers(0, 2 ** bits, size=X.shape).astype(np.float32)
+        static = np.tile(np.array([0.0, 2.0 * (2 ** bits - 1)], np.float32), ((m + 2) ** 2, 1))
+    if static is not None:
+        flags |= B.LANCE_INPUT_RANGE_STATIC
+    conv, _ = _check_layer(L, X, Wt, flags=flags, static_v_range=static, staged=False)
+    assert _kernels(conv, _zeros(conv, form == "nhwc"))[3] == kernel
+
+
+@pytest.mark.parametrize("plan", [p for p in _PLANS if p[9] in ("", "nhwc")], ids=_plan_id)
+def test_twin_and_graph_of_every_plan(plan):
+    """The timing twin and graph replays (test_gpu_parity.py) on layers that are the plans' own."""
+    _, N, C, K, H, W, pad, m, bits, form = plan
+    L = Wk.Layer("plan_" + form, N, C, K, H, W, pad=pad, m=m, bits=bits, seed=670 + C)
+    parity.test_timing_twin_runs_the_same_kernels(L)
+    parity.test_fused_call_replays_from_a_hip_graph(L)
+
+
+@pytest.mark.parametrize("L", [
+    Wk.Layer("pos", 4, 64, 48, 16, 16, m=2, seed=680),
+    Wk.Layer("pos_nhwc", 4, 130, 48, 16, 16, m=4, seed=681),
+    Wk.Layer("split", 2, 600, 48, 12, 12, m=2, seed=682),
+    Wk.Layer("split_nhwc", 2, 330, 48, 12, 12, m=4, seed=683),
+    Wk.Layer("reduction_kernel", 40, 3, 70, 65, 63, m=4, seed=684),
+], ids=lambda l: l.name)
+def test_twin_and_graph_of_few_tile_plans(L):
+    parity.test_timing_twin_runs_the_same_kernels(L)
+    parity.test_fused_call_replays_from_a_hip_graph(L)
 
 
 # N, C, K, H, W, pad, m, bits_w: one and two tile groups, one, two and four filter groups, partial
@@ -318,7 +398,7 @@ def test_weight_only_infinities(N, K, C, m, nhwc):
     fin, big = np.isfinite(ref), np.abs(ref) > 1e30
     assert (fin & big).any()
     for part in (fin & big, fin & ~big & (np.arange(H - 2) >= m)[:, None]):  # (row 0's tiles hold the 1e37)
-        assert np.linalg.norm((got - ref)[part]) <= 4e-6 * np.linalg.norm(ref[part])
+        assert np.linalg.norm(got[part] - ref[part]) <= 4e-6 * np.linalg.norm(ref[part])
 
 
 # K, C, m, bits_w: one kernel / two kernels, 256- and 512-thread workgroups, workgroups with unequal
