@@ -35,18 +35,18 @@
 // offsets of the other.
 #include "lance_device.h"
 #include "lance_internal.h"
-#include "tile_loader.h"
+#include "pos_phases.h"
 
 namespace lance {
 namespace {
 
 constexpr int kThreads = 256;
 
-typedef short bf8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef unsigned v4u __attribute__((ext_vector_type(4)));
-typedef unsigned v2u __attribute__((ext_vector_type(2)));
+using pos::kOobY;
+using pos::v2u;
 using pos::v4f;
+using pos::v4u;
 
 struct WmArgs {
   const float* x;
@@ -57,24 +57,7 @@ struct WmArgs {
   unsigned x_bytes, y_bytes;
 };
 
-constexpr unsigned kOobY = 0xFFFFFFF0u;
 constexpr float kUp = 16777216.0f;  // 2^24
-
-__device__ __forceinline__ void store1(float* y, unsigned y_bytes, unsigned off, float v) {
-  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(y, 0, y_bytes, 0x00020000);
-  __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, off, 0, 0);
-}
-template <int M>
-__device__ __forceinline__ void store_row(float* y, unsigned y_bytes, unsigned off, const float (&v)[M]) {
-  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(y, 0, y_bytes, 0x00020000);
-  if constexpr (M == 2) {
-    const v2u u = {__float_as_uint(v[0]), __float_as_uint(v[1])};
-    __builtin_amdgcn_raw_buffer_store_b64(u, r, off, 0, 0);
-  } else {
-    const v4u u = {__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])};
-    __builtin_amdgcn_raw_buffer_store_b128(u, r, off, 0, 0);
-  }
-}
 
 // Eight stored codes (two dwords of a code row) as multiples of step counted from z, in bf16;
 // exact.  unit: 2^(8-b); zero: z + (128 - 2^(b-1)) * unit.
@@ -414,11 +397,11 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void weight_only_mfma_kernel(c
       const bool row = oy0 + r < a.Ho;
       if (whole) {
         const unsigned off = (unsigned)dev::act_index(false, on, k, oy0 + r, ox0, K, a.Ho, a.Wo) * 4u;
-        store_row<M>(a.y, a.y_bytes, row ? off : kOobY, o[t][r]);
+        pos::store_row<M>(a.y, a.y_bytes, row ? off : kOobY, o[t][r]);
       } else {
 #pragma unroll
         for (int s = 0; s < M; s++)
-          store1(a.y, a.y_bytes, row && ox0 + s < a.Wo
+          pos::store_b32(a.y, a.y_bytes, row && ox0 + s < a.Wo
                                      ? (unsigned)dev::act_index(kNhwc, on, k, oy0 + r, ox0 + s, K, a.Ho, a.Wo) * 4u
                                      : kOobY, o[t][r][s]);
       }
