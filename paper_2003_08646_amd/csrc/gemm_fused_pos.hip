@@ -15,36 +15,28 @@
 namespace lance {
 namespace pos {
 
-struct QpArgs {
-  CpArgs c;
-  int blocks, groups;  // channel blocks per workgroup (1), block groups
-};
-
 template <int M, int CPL, int LOAD, bool CLAMP>
-__global__ __launch_bounds__(256, M == 2 ? 4 : 3) void quant_pos_kernel(const QpArgs q) {
+__global__ __launch_bounds__(256, M == 2 ? 4 : 3) void quant_pos_kernel(const CpArgs a) {
   constexpr int E = (M + 2) * (M + 2), NW = 4, NT = 256;
-  const CpArgs& a = q.c;
   extern __shared__ char smem[];
   const Consts<M> cst(smem);
   char* ring = smem + kConstBytes;
   float* red = reinterpret_cast<float*>(ring);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int blk0 = (blockIdx.x % q.groups) * q.blocks, p0 = (blockIdx.x / q.groups) * 16;
-  const int nb = min(q.blocks, a.NB - blk0);
+  const int blk = blockIdx.x % a.NB, p0 = (blockIdx.x / a.NB) * 16;
   {
     const Quantizer<M, NW, CPL, LOAD, CLAMP> qz(a, p0, lane, wave);
-    qz.run(blk0, nb, cst.qp, ring, [&]() { cst.template form<NT>(a, a.is_static, red, tid); });
+    qz.run(blk, 1, cst.qp, ring, [&]() { cst.template form<NT>(a, a.is_static, red, tid); });
   }
   lds_barrier();
   const __amdgpu_buffer_rsrc_t res = __builtin_amdgcn_make_buffer_rsrc(a.vq, 0, a.vq_bytes, 0x00020000);
   const int row = lane >> 2, chunk = lane & 3;
   const unsigned src = (unsigned)row * 64u + (unsigned)((chunk ^ swz(row)) * 16);
   const unsigned dst = p0 + row < a.P ? (unsigned)(p0 + row) * 64u + 16u * chunk : kOobY;
-  for (int i = wave; i < E * nb; i += NW) {  // one KB of one position and block per wave and turn
-    const int e = i / nb, b = i % nb;
-    const v4u v = *reinterpret_cast<const v4u*>(ring + i * 1024 + src);
-    __builtin_amdgcn_raw_buffer_store_b128(v, res, dst, ((unsigned)e * (unsigned)a.NB + (unsigned)(blk0 + b)) * (unsigned)a.P * 64u, 0);
+  for (int e = wave; e < E; e += NW) {  // one KB of one position per wave and turn
+    const v4u v = *reinterpret_cast<const v4u*>(ring + e * 1024 + src);
+    __builtin_amdgcn_raw_buffer_store_b128(v, res, dst, ((unsigned)e * (unsigned)a.NB + (unsigned)blk) * (unsigned)a.P * 64u, 0);
   }
 }
 
@@ -129,14 +121,14 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void gemm_pos_kernel(const CpA
 }
 
 template <int M, bool CLAMP>
-static hipError_t launch_quant(const QpArgs& q, int load, hipStream_t s) {
-  const unsigned grid = (unsigned)((q.c.P + 15) / 16) * (unsigned)q.groups;
-  const size_t lds = kConstBytes + (size_t)q.blocks * (M + 2) * (M + 2) * 1024;
+static hipError_t launch_quant(const CpArgs& a, int load, hipStream_t s) {
+  const unsigned grid = (unsigned)((a.P + 15) / 16) * (unsigned)a.NB;
+  constexpr int lds = kConstBytes + (M + 2) * (M + 2) * 1024;
   auto go = [&](auto kern) -> hipError_t {
-    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), kConstBytes + (M + 2) * (M + 2) * 1024);
+    const hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds);
     if (e != hipSuccess) return e;
     note_kernel("quant_pos_kernel");
-    kern<<<grid, 256, lds, s>>>(q);
+    kern<<<grid, 256, lds, s>>>(a);
     return hipGetLastError();
   };
   switch (load) {
@@ -199,20 +191,19 @@ bool gemm_fused_pos_preferred(const Geo& g) {
 hipError_t launch_quant_pos(const Geo& g, const float* x, const float* u_range, const float* partial,
                             int count, float* v_range, int8_t* vq, hipStream_t s) {
   const bool is_static = (g.flags & LANCE_INPUT_RANGE_STATIC) != 0;
-  pos::QpArgs q{{x, nullptr, u_range, nullptr, partial, v_range, nullptr, vq, count,
-                 (g.flags & LANCE_RANGE_PER_TENSOR) ? 1 : 0, is_static ? 1 : 0,
-                 g.N, g.C, g.H, g.W, g.K, g.pad, g.P, g.th, g.tw, g.Ho, g.Wo, g.bits, g.bits_w,
-                 g.NB, g.Q, 0, 1, (unsigned)((size_t)g.N * g.C * g.H * g.W * 4), 0,
-                 (unsigned)((size_t)g.E * g.NB * g.P * 64)},
-                1, g.NB};
+  const pos::CpArgs a{x, nullptr, u_range, nullptr, partial, v_range, nullptr, vq, count,
+                      (g.flags & LANCE_RANGE_PER_TENSOR) ? 1 : 0, is_static ? 1 : 0,
+                      g.N, g.C, g.H, g.W, g.K, g.pad, g.P, g.th, g.tw, g.Ho, g.Wo, g.bits, g.bits_w,
+                      g.NB, g.Q, 0, 1, (unsigned)((size_t)g.N * g.C * g.H * g.W * 4), 0,
+                      (unsigned)((size_t)g.E * g.NB * g.P * 64)};
   int load;
   if (is_nhwc(g))
     load = g.m == 2 && g.C % 4 == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0 ? pos::kNhwc4 : pos::kNhwc1;
   else
     load = patch_edge_cols_only(g) ? pos::kRowsEdge : pos::kRowsAny;
   const bool clamp = g.bits < 8;  // as in conv_fused_pos.hip
-  if (g.m == 4) return clamp ? pos::launch_quant<4, true>(q, load, s) : pos::launch_quant<4, false>(q, load, s);
-  return clamp ? pos::launch_quant<2, true>(q, load, s) : pos::launch_quant<2, false>(q, load, s);
+  if (g.m == 4) return clamp ? pos::launch_quant<4, true>(a, load, s) : pos::launch_quant<4, false>(a, load, s);
+  return clamp ? pos::launch_quant<2, true>(a, load, s) : pos::launch_quant<2, false>(a, load, s);
 }
 
 hipError_t launch_gemm_pos(const Geo& g, const int8_t* uq, const int8_t* vq, const float* u_range,
