@@ -65,7 +65,7 @@ struct TileLoader {
     ix0 = tx * M - g.pad;
     dl = dl_; C = g.C; W = g.W;
     bool first = false, last = false;
-    const bool cols = LOAD == kRowsEdge || (ix0 > -A && ix0 < W);  // some column lies inside the image
+    const bool cols = LOAD != kRowsAny || (ix0 > -A && ix0 < W);  // a row load meets the image
 #pragma unroll
     for (int r = 0; r < A; r++) {
       const int iy = iy0 + r;
