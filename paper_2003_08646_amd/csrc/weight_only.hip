@@ -154,7 +154,7 @@ __device__ __forceinline__ void plain_results(const WmArgs& a, const float* sc_s
 #pragma unroll
       for (int e = 0; e < E; e++) vs[i * kRow + e] = d[e / A][e % A];
     }
-#pragma unroll 4
+#pragma unroll 2
     for (int i = tid; i < nc * kFilters * E; i += NT) {
       const int e = i % E, kc = i / E;
       const int c = c0 + kc / kFilters, k = min(k0 + kc % kFilters, a.K - 1);
@@ -360,28 +360,29 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void weight_only_mfma_kernel(c
   __syncthreads();
   using PairsT = Pairs<M, TG, KG, kNhwc>;
   float o[PairsT::kTurns][M][M];
-  bool bad[PairsT::kTurns];
   const bool check = __builtin_amdgcn_readfirstlane(*huge_s) != 0;
 #pragma unroll
   for (int t = 0; t < PairsT::kTurns; t++) {
     const PairsT pr(tid, t);
-    bad[t] = false;
     if (!pr.exists()) continue;
     float mm[A][A];
 #pragma unroll
     for (int e = 0; e < E; e++) mm[e / A][e % A] = ex[e * KG * TG * 256 + pr.i];
     out2d<M>(mm, o[t]);
-    float zero = 0.0f;
 #pragma unroll
-    for (int r = 0; r < M * M; r++) {
-      zero += 0.0f * o[t][r / M][r % M];
-      o[t][r / M][r % M] *= 1.0f / kUp;
-    }
-    bad[t] = zero != 0.0f;  // not finite
+    for (int r = 0; r < M * M; r++) o[t][r / M][r % M] *= 1.0f / kUp;
   }
   if (check) {
     int own = tid;
-    asm volatile("" : "+v"(own));  // (nothing of that is computed ahead of here)
+    asm volatile("" : "+v"(own));  // (nothing of the following is computed ahead of here)
+    bool bad[PairsT::kTurns];
+#pragma unroll
+    for (int t = 0; t < PairsT::kTurns; t++) {
+      float zero = 0.0f;
+#pragma unroll
+      for (int r = 0; r < M * M; r++) zero += 0.0f * o[t][r / M][r % M];
+      bad[t] = PairsT(own, t).exists() && zero != 0.0f;  // not finite
+    }
     plain_results<M, TG, KG, kNhwc>(a, sc_s, k0, p0, own, ex, bad, o);
   }
 #pragma unroll
