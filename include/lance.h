@@ -93,8 +93,9 @@ enum {
   LANCE_RANGE_PER_TENSOR = 1u,    /* one (min,max) for the whole transformed tensor        */
   LANCE_INPUT_RANGE_STATIC = 2u,  /* v_range is given by the caller (calibrated ranges);
                                      values outside it are clamped to the end codes        */
-  LANCE_PLAN_WIDE_TILES = 4u,     /* tuning: the fused convolution of F(2x2,3x3) layers with
-                                     C > 64 multiplies with 128 x 64 workgroup tiles whatever
+  LANCE_PLAN_WIDE_TILES = 4u,     /* tuning: the fused convolution takes none of the plans for
+                                     layers of few tiles (any m, any C), and F(2x2,3x3) layers
+                                     with C > 64 multiply with 128 x 64 workgroup tiles whatever
                                      the layer size (by default only large layers do); the
                                      codes are the same, Y may differ in fp32 rounding order */
   LANCE_LAYOUT_NHWC = 8u,         /* X is [N][H][W][C] and Y is [N][Ho][Wo][K] (the layout of

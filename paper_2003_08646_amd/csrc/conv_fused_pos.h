@@ -24,7 +24,7 @@
 // transform - uq fragments - exchange - stores of one workgroup; 6 us for the smallest layers with
 // caller-supplied ranges, launch included (N122 16->16 7x7; 19 us before on conv_fused_c16), 11 us
 // with the range pass (one 16->16 32x32 image: 24.8 us before).  One image of the 512-channel 14x14
-// layer: 21 -> 13.3 us, N13 100->72 37x29 F(4x4): 43 -> 18 us.
+// layer: 21 -> 13.3 us, N13 100->72 37x29 F(4x4): 43 -> 17 us.
 #pragma once
 #include "pos_phases.h"
 

@@ -240,6 +240,9 @@ static int conv_check_args(const lance_conv_desc* desc, const float* x_dev, cons
 // (kPlanThreeKernels: range pass, reduction kernel, one kernel for everything else)
 enum ConvPlan { kPlanGeneral = 0, kPlanTwoKernels = 1, kPlanThreeKernels = 2 };
 
+// Layers of few tiles come first (unless the descriptor asks for wide tiles): one kernel behind the range
+// pass, or with many channel blocks a quantize pass and a product kernel (conv_fused_pos.h,
+// gemm_fused_pos.hip).  The others:
 // Layers with one 64-channel block (m = 2) run as two kernels: the range pass, then one kernel
 // that reduces the ranges, quantizes, multiplies and transforms back (V's codes stay on chip).
 // Layers with two blocks (m = 2) take the same two-kernel form (128 KB of codes in LDS) unless

@@ -559,8 +559,8 @@ WmShape wm_shape(const Geo& g) {
 int plain_filters(const Geo& g) { return g.m == 2 ? 8 : 4; }
 
 // Whether the vector-ALU kernel takes less time: both times in us from fits to sweeps over 1 to 64
-// channels, 1 to 600 filters, 9 to 506250 tiles, both layouts (each kernel on each of 3500 layers: of the
-// 20 on which the choice costs more than 5 %, twelve take up to 1.4 times the vector form's time, eight up to
+// channels, 1 to 600 filters, 9 to 506250 tiles, both layouts (each kernel on each of 7000 layers: of the
+// 52 on which the choice costs more than 5 %, 35 take up to 1.4 times the vector form's time, 17 up to
 // 1.25 times the matrix form's).  100352 tiles of F(2x2), vector and matrix form: 1 -> 8 channels 9 and 58 us,
 // 16 -> 8 40 and 58, 3 -> 40 42 and 88, 16 -> 64 220 and 93; NHWC 3 -> 4 13 and 58, 3 -> 16 105 and 59.
 bool vector_form_faster(const Geo& g, const WmShape& sh) {
