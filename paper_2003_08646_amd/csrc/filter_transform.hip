@@ -119,7 +119,8 @@ __global__ __launch_bounds__(NT) void filter_range_kernel(const FtArgs a) {
   }
 }
 
-template <int M, int NT>
+// NARROW: codes of fewer than 8 bits.
+template <int M, int NT, bool NARROW>
 __global__ __launch_bounds__(NT) void filter_quant_kernel(const FtArgs a) {
   constexpr int A = M + 2, E = A * A, kThreads = NT, kParts = kThreads / E;
   constexpr int kMaxFilters = 64;  // per workgroup
@@ -203,10 +204,12 @@ __global__ __launch_bounds__(NT) void filter_quant_kernel(const FtArgs a) {
 #pragma unroll
       for (int e = 0; e < E; e++) {
         const float2 p = qp_s[e];
-        // clamp(rne((x - min) * inv), 0, L): the conversion rounds to nearest even.  The ranges are those
-        // of these filters, but where x - min overflows the product is infinite, and 0 * infinity is
-        // undefined: those are L and (the median with one undefined value is the least of the others) 0
-        const float t = __builtin_amdgcn_fmed3f((u[e / A][e % A] - p.x) * p.y, 0.0f, L);
+        // clamp(rne((x - min) * inv), 0, L): the conversion rounds to nearest even and saturates to
+        // [0, 255].  The ranges are those of these filters, but where x - min overflows the product is
+        // infinite, and 0 * infinity is undefined: those are L and (the median with one undefined value
+        // is the least of the others; the conversion's result, too) 0
+        float t = (u[e / A][e % A] - p.x) * p.y;
+        if constexpr (NARROW) t = __builtin_amdgcn_fmed3f(t, 0.0f, L);
         codes[e] = __builtin_amdgcn_cvt_pk_u8_f32(t, q, q == 0 ? 0u : codes[e]);
       }
       // (one channel after the other, and the parameters read again for each)
@@ -302,11 +305,15 @@ hipError_t launch_filter_transform(const Geo& g, const float* w, int8_t* uq, flo
     quant<<<a.gb, nt_quant, 0, s>>>(a);
     return hipGetLastError();
   };
-  if (g.m == 2)
-    return large ? run(filter_range_kernel<2, 1024>, filter_quant_kernel<2, 512>)
-                 : run(filter_range_kernel<2, 256>, filter_quant_kernel<2, 256>);
-  return large ? run(filter_range_kernel<4, 1024>, filter_quant_kernel<4, 512>)
-               : run(filter_range_kernel<4, 256>, filter_quant_kernel<4, 256>);
+  auto sized = [&](auto narrow) -> hipError_t {
+    constexpr bool kNarrow = decltype(narrow)::value;
+    if (g.m == 2)
+      return large ? run(filter_range_kernel<2, 1024>, filter_quant_kernel<2, 512, kNarrow>)
+                   : run(filter_range_kernel<2, 256>, filter_quant_kernel<2, 256, kNarrow>);
+    return large ? run(filter_range_kernel<4, 1024>, filter_quant_kernel<4, 512, kNarrow>)
+                 : run(filter_range_kernel<4, 256>, filter_quant_kernel<4, 256, kNarrow>);
+  };
+  return g.bits_w < 8 ? sized(std::true_type{}) : sized(std::false_type{});
 }
 
 }  // namespace lance
