@@ -14,6 +14,8 @@
 // (uq, cache resident) from memory one grid row ahead.  Epilogue algebra:
 // M[e,k,p] = s_e*ACC + f[e,k] + g[e,p]; the three terms go through the linear map S = A^T M A
 // separately; f arrives pre-transformed in rk[a*m+b][k], g is formed from the column sums.
+//
+// NCHW layers with pad 1 and a width that is a multiple of 4 take conv_fused_pairs.hip instead.
 #include "lance_device.h"
 #include "lance_internal.h"
 #include "patch_loader.h"

@@ -245,14 +245,15 @@ enum ConvPlan { kPlanGeneral = 0, kPlanTwoKernels = 1, kPlanThreeKernels = 2 };
 // gemm_fused_pos.hip).  The others:
 // Layers with one 64-channel block (m = 2) run as two kernels: the range pass, then one kernel
 // that reduces the ranges, quantizes, multiplies and transforms back (V's codes stay on chip).
+// Where the tiles pair up (pad 1, width a multiple of 4, NCHW) that kernel is conv_fused_pairs.hip's.
 // Layers with two blocks (m = 2) take the same two-kernel form (128 KB of codes in LDS) unless
 // the descriptor asks for the general plan's wide tiles.  Layers of at most 16 channels (m = 2)
 // and F(4x4,3x3) layers of at most 128 channels: range pass, reduction kernel, one kernel for the
 // rest (the reduction kernel drops out where the last kernel can reduce for itself).
 struct PlanChoice {
-  bool split_p, fuse_p, fuse_q1, fuse_q2, fuse_s, fuse_m4;
+  bool split_p, fuse_p, fuse_pair, fuse_q1, fuse_q2, fuse_s, fuse_m4;
   ConvPlan plan() const {
-    return (fuse_p || fuse_q1 || fuse_q2) ? kPlanTwoKernels
+    return (fuse_p || fuse_pair || fuse_q1 || fuse_q2) ? kPlanTwoKernels
                                 : ((fuse_s || fuse_m4) ? kPlanThreeKernels : kPlanGeneral);
   }
 };
@@ -264,6 +265,8 @@ static PlanChoice choose_plan(const Geo& g, const float* x_dev) {
   c.fuse_p = conv_fused_pos_preferred(g) && !(g.flags & LANCE_PLAN_WIDE_TILES);
   if (c.fuse_p) return c;
   if (is_packed(g)) return c;  // packed codes: the general plan (quantize pass, product kernel)
+  c.fuse_pair = conv_fused_pairs_applicable(g) && (g.NB == 1 || !(g.flags & LANCE_PLAN_WIDE_TILES));
+  if (c.fuse_pair) return c;
   const bool x_ok = !is_nhwc(g) || (reinterpret_cast<uintptr_t>(x_dev) & 15) == 0;
   c.fuse_q1 = conv_fused_c64_applicable(g) && x_ok;
   c.fuse_q2 = !c.fuse_q1 && conv_fused_c128_applicable(g) && !(g.flags & LANCE_PLAN_WIDE_TILES) && x_ok;
@@ -294,7 +297,7 @@ static int conv_launch(const Geo& g, const Workspace& wl, const float* x_dev, co
   const DqOut dqo{u_range_dev, u_rowsum_dev, dq, rk, dqd, g.K, g.C, gemm_fused_wants_rk(g) ? 1 : 0,
                   g.bits_w, code_bias(g)};
   const PlanChoice pc = choose_plan(g, x_dev);
-  const bool fuse_q1 = pc.fuse_q1, fuse_q = pc.fuse_q1 || pc.fuse_q2, fuse_s = pc.fuse_s;
+  const bool fuse_q1 = pc.fuse_q1, fuse_q = pc.fuse_pair || pc.fuse_q1 || pc.fuse_q2, fuse_s = pc.fuse_s;
   if (plan_out) *plan_out = pc.plan();
   if (pc.split_p) {
     const bool is_static = (g.flags & LANCE_INPUT_RANGE_STATIC) != 0;
@@ -344,7 +347,10 @@ static int conv_launch(const Geo& g, const Workspace& wl, const float* x_dev, co
     if (e == hipSuccess && ev) e = hipEventRecord(ev[1], s);
     note_slot(3);
     if (e == hipSuccess)
-      e = fuse_q1 ? launch_conv_fused_c64(g, x_dev, uq_dev, u_range_dev, u_rowsum_dev, partial,
+      e = pc.fuse_pair
+              ? launch_conv_fused_pairs(g, x_dev, uq_dev, u_range_dev, u_rowsum_dev, partial, groups,
+                                        v_range, y_dev, s)
+          : fuse_q1 ? launch_conv_fused_c64(g, x_dev, uq_dev, u_range_dev, u_rowsum_dev, partial,
                                           groups, v_range, y_dev, s)
                   : launch_conv_fused_c128(g, x_dev, uq_dev, u_range_dev, u_rowsum_dev, partial,
                                            groups, v_range, y_dev, s);

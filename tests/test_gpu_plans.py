@@ -459,3 +459,33 @@ def test_filter_codes_at_the_end_of_binary32(m, bits_w, packed, kind):
     np.testing.assert_array_equal(conv.u_range.cpu().numpy(), np.stack([lo, hi], 1))
     _assert_codes(conv.codes_to_logical(conv.uq, K), ref, "filter codes")
     np.testing.assert_array_equal(conv.u_rowsum.cpu().numpy(), ref.sum(2))
+
+
+# N, C, K, H, W, bits: layers whose tiles pair up (pad 1, width a multiple of 4)
+_PAIRS = [
+    (1200, 20, 30, 7, 4, 8),      # one pair per row; blocks of several images; odd height
+    (500, 64, 64, 9, 8, 8),       # two pairs per row, whole channel block
+    (150, 61, 70, 12, 20, 5),     # rows that end inside a group of lanes
+    (60, 64, 384, 16, 32, 8),     # the most filters of one channel block
+    (60, 64, 385, 16, 32, 8),     # one more: one tile per lane
+    (3, 48, 33, 111, 224, 8),     # rows of several groups of lanes
+    (90, 128, 130, 14, 28, 8),    # two channel blocks, whole; two blocks of filters
+    (1400, 65, 17, 6, 4, 6),
+    (100, 100, 72, 15, 36, 8),
+    (30, 127, 640, 20, 24, 8),    # the most filters of two channel blocks
+    (30, 127, 641, 20, 24, 8),
+    (33, 70, 20, 33, 64, 8),      # non-temporal stores
+]
+
+
+@pytest.mark.parametrize("shape", _PAIRS, ids=lambda s: "n%d_c%d_k%d_%dx%d_b%d" % s)
+@pytest.mark.parametrize("option", ["dynamic", "static", "per_tensor"])
+def test_layers_whose_tiles_pair_up(shape, option):
+    from paper_2003_08646_amd import binding as B
+    N, C, K, H, W, bits = shape
+    L = Wk.Layer("pairs", N, C, K, H, W, m=2, bits=bits, seed=700 + C)
+    flags = {"dynamic": 0, "static": B.LANCE_INPUT_RANGE_STATIC, "per_tensor": B.LANCE_RANGE_PER_TENSOR}[option]
+    static = _range_of_another_batch(L) if option == "static" else None
+    conv, _ = _check_layer(L, flags=flags, static_v_range=static, staged=False)
+    names = _kernels(conv, _zeros(conv, False))
+    assert names[3] == ("conv_fused_c64_kernel" if C <= 64 else "conv_fused_c128_kernel"), names
