@@ -244,6 +244,11 @@ __global__ __launch_bounds__(kThreads, 2) void input_quant_m4_kernel(const QArgs
     const char* plane = xb + (size_t)plane_lo(k) * plane_bytes;
     if constexpr (kRows) {
       pl.issue_rows_shifted(plane, g.reach, is_first(k), is_last(k), buf[k & 1], lane_off(k));
+    } else if constexpr (MODE == 1) {
+      // (the lane halves read planes plane_lo and, at most, plane_lo + 2)
+      pl.issue_any(plane, g.reach,
+                   (pl.first_image && plane_lo(k) == 0) || (pl.last_image && chan_lo(k) + 2 >= g.C - 1), buf[k & 1],
+                   lane_off(k));
     } else {
       // pixel by pixel: the element loader takes the plane of the lower half; shift the offsets
       dev::PatchLoader<M> pl2 = pl;
@@ -282,6 +287,8 @@ __global__ __launch_bounds__(kThreads, 2) void input_quant_m4_kernel(const QArgs
     if constexpr (kRows) {
       if (may_be_first(k) || may_be_last(k)) pl.unshift(is_first(k), is_last(k), d);
       pl.template fix<true>(d);
+    } else if constexpr (MODE == 1) {
+      pl.template fix<false>(d);
     }
     dev::input_tile_transform<M>(d);
 #pragma unroll

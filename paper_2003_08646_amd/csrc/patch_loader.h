@@ -114,6 +114,20 @@ struct PatchLoader {
     }
   }
 
+  // A patch for layers whose patches may have any column outside the image (patch_load_mode 1): by rows,
+  // except in the tensor's first and last plane (ends, wave-uniform), where some row load would leave
+  // the tensor: there pixel by pixel.  lane_off: as below.  (All patches pixel by pixel: N64 128 -> 128
+  // 57x55 149 -> 126 us by rows, N64 256 -> 256 29x29 108 -> 92, F(4x4) 57x57 160 -> 134.)
+  __device__ __forceinline__ void issue_any(const char* plane, unsigned extent, bool ends, float (&b)[A * A],
+                                            unsigned lane_off = 0) const {
+    PatchLoader<M> pl = *this;
+#pragma unroll
+    for (int r = 0; r < A; r++)
+      if ((rowmask >> r) & 1u) pl.rowoff[r] += lane_off;
+    if (ends) pl.template issue<false>(plane, extent, b);
+    else pl.template issue<true>(plane, extent, b);
+  }
+
   // Row loads that are safe in the first (first_plane) or the last (last_plane) plane of the
   // tensor, for layers whose patches stick out of the image by at most one column on either side
   // (patch_edge_cols_only) and whose rows hold at least A pixels (lane_off: a per-lane constant

@@ -34,7 +34,7 @@ __device__ __forceinline__ unsigned code_row_offset(int row, int chunk) {
 }
 
 // B8: 8-bit codes.  FULL: all 64 channels c_base .. c_base+63 exist.  MODE: load mode of the
-// patches (patch_load_mode): by rows when it is 2, pixel by pixel otherwise.
+// patches (patch_load_mode).
 // p0: first tile of the block.  ring: [16][64][64 B].  cs_s: [16][64] int, zeroed by the caller
 // before its last barrier ahead of this call's end... (the atomics below are the only writers).
 // mid(): run once after the first loads have been requested (all threads; may use barriers).
@@ -82,8 +82,11 @@ __device__ __forceinline__ void quantize_block_to_lds(const QuantBlockGeo& g, in
   float buf[kBuf][E];
   auto issue = [&](int k) {
     const char* plane = xb + (size_t)plane_of(k) * HW * 4;
-    if constexpr (!kRows)
+    if constexpr (MODE == 0)
       pl.template issue<false>(plane, g.reach, buf[k % kBuf]);
+    else if constexpr (MODE == 1)
+      pl.issue_any(plane, g.reach,
+                   (pl.first_image && plane_of(k) == 0) || (pl.last_image && plane_of(k) == g.C - 1), buf[k % kBuf]);
     else if (may_be_first(k) || may_be_last(k))
       pl.issue_rows_shifted(plane, g.reach, is_first(k), is_last(k), buf[k % kBuf]);
     else
@@ -119,6 +122,8 @@ __device__ __forceinline__ void quantize_block_to_lds(const QuantBlockGeo& g, in
     if constexpr (kRows) {
       if (may_be_first(k) || may_be_last(k)) pl.unshift(is_first(k), is_last(k), d);
       pl.template fix<true>(d);
+    } else if constexpr (MODE == 1) {
+      pl.template fix<false>(d);
     }
     input_tile_transform<M>(d);
 #pragma unroll

@@ -23,7 +23,7 @@ namespace lance {
 namespace dev {
 
 // B8: 8-bit codes.  FULL: all 64 channels c_base .. c_base+63 exist.  MODE: load mode of the
-// patches (patch_load_mode): by rows when it is 2, pixel by pixel otherwise.
+// patches (patch_load_mode).
 // p0: first tile of the block.  ring: [16][32][64 B].  cs_s: [16][32] int, zeroed by the caller
 // before a barrier that precedes the first atomic below (mid() contains one).
 // mid(): run once after the first loads have been requested (all threads; may use barriers).
@@ -75,6 +75,10 @@ __device__ __forceinline__ void quantize_half_block_to_lds(const QuantBlockGeo& 
     const char* plane = xb + (size_t)plane_lo(k) * plane_bytes;
     if constexpr (kRows) {
       pl.issue_rows_shifted(plane, g.reach, is_first(k), is_last(k), buf[k % kBuf], lane_off(k));
+    } else if constexpr (MODE == 1) {
+      // (the lane groups read planes plane_lo .. plane_lo + 2)
+      pl.issue_any(plane, g.reach,
+                   (pl.first_image && plane_lo(k) == 0) || (pl.last_image && chan_lo(k) + 2 >= g.C - 1), buf[k % kBuf], lane_off(k));
     } else {
       // pixel by pixel: the element loader takes the plane of the lower half; shift the offsets
       PatchLoader<M> pl2 = pl;
@@ -115,6 +119,8 @@ __device__ __forceinline__ void quantize_half_block_to_lds(const QuantBlockGeo& 
     if constexpr (kRows) {
       if (may_be_first(k) || may_be_last(k)) pl.unshift(is_first(k), is_last(k), d);
       pl.template fix<true>(d);
+    } else if constexpr (MODE == 1) {
+      pl.template fix<false>(d);
     }
     input_tile_transform<M>(d);
 #pragma unroll

@@ -489,3 +489,21 @@ def test_layers_whose_tiles_pair_up(shape, option):
     conv, _ = _check_layer(L, flags=flags, static_v_range=static, staged=False)
     names = _kernels(conv, _zeros(conv, False))
     assert names[3] == ("conv_fused_c64_kernel" if C <= 64 else "conv_fused_c128_kernel"), names
+
+
+# N, C, K, H, W, pad, m: patches by rows with any column outside the image, the smallest images that are
+# loaded so; first and last plane of the tensor pixel by pixel
+_ROWS_ANY = [
+    (3, 20, 12, 2, 5, 1, 2), (1, 64, 20, 5, 7, 1, 2), (2, 33, 9, 4, 4, 0, 2), (1, 17, 5, 3, 4, 0, 2),
+    (2, 130, 17, 3, 5, 1, 2), (1, 150, 8, 7, 9, 0, 2), (70, 192, 20, 7, 9, 1, 2),
+    (2, 20, 12, 3, 7, 1, 4), (1, 64, 9, 6, 9, 1, 4), (2, 70, 17, 5, 6, 0, 4), (1, 17, 5, 3, 6, 0, 4),
+    (2, 130, 8, 7, 11, 1, 4), (1, 150, 20, 9, 6, 0, 4), (40, 192, 20, 13, 10, 1, 4),
+]
+
+
+@pytest.mark.parametrize("shape", _ROWS_ANY, ids=lambda s: "n%d_c%d_k%d_%dx%d_p%d_m%d" % s)
+def test_rows_of_any_width(shape):
+    from paper_2003_08646_amd import binding as B
+    N, C, K, H, W, pad, m = shape
+    L = Wk.Layer("rows", N, C, K, H, W, pad=pad, m=m, seed=740 + C)
+    _check_layer(L, flags=B.LANCE_PLAN_WIDE_TILES)
