@@ -66,6 +66,10 @@ __device__ __forceinline__ void spread(unsigned own, unsigned* g0, unsigned* g1)
 // aa*row_bytes.  kleft: filters that exist from the lane's first one on.  even_w (kernel-uniform):
 // the output width is even, so a patch never loses its second column and the pair is stored as
 // one 8-byte store.  Masked stores get an offset the buffer's range check drops.
+// STREAM: non-temporal, for rows of whole 64-byte sectors (N16 3 -> 64 224x224 68.5 -> 64.7 us, N16 16 -> 64
+// 112x112 43.1 -> 38.5; with other widths the pieces of a sector are better merged by the caches: N16 3 ->
+// 64 220x220 89 us, non-temporal 120).
+template <bool STREAM>
 __device__ __forceinline__ void store_patches(float* y, unsigned y_bytes, const float (&o)[16][2][2],
                                               unsigned base, unsigned plane_bytes,
                                               unsigned row_bytes, int kleft, bool tile_ok,
@@ -81,7 +85,7 @@ __device__ __forceinline__ void store_patches(float* y, unsigned y_bytes, const 
       for (int aa = 0; aa < 2; aa++) {
         const unsigned off = (k_ok && (aa == 0 || row1)) ? base + (unsigned)aa * row_bytes : kOob;
         const v2u v = {__float_as_uint(o[r][aa][0]), __float_as_uint(o[r][aa][1])};
-        __builtin_amdgcn_raw_buffer_store_b64(v, res, off, (unsigned)kk * plane_bytes, 0);
+        __builtin_amdgcn_raw_buffer_store_b64(v, res, off, (unsigned)kk * plane_bytes, STREAM ? 2 : 0);
       }
     }
   } else {
@@ -93,9 +97,9 @@ __device__ __forceinline__ void store_patches(float* y, unsigned y_bytes, const 
       for (int aa = 0; aa < 2; aa++) {
         const unsigned off = (k_ok && (aa == 0 || row1)) ? base + (unsigned)aa * row_bytes : kOob;
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o[r][aa][0]), res, off,
-                                              (unsigned)kk * plane_bytes, 0);
+                                              (unsigned)kk * plane_bytes, STREAM ? 2 : 0);
         __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(o[r][aa][1]), res,
-                                              col1 ? off + 4u : kOob, (unsigned)kk * plane_bytes, 0);
+                                              col1 ? off + 4u : kOob, (unsigned)kk * plane_bytes, STREAM ? 2 : 0);
       }
     }
   }
@@ -408,9 +412,13 @@ __global__ __launch_bounds__(kThreads, 2) void conv_fused_c16_kernel(const CsArg
               for (int b = 0; b < M; b++)
                 o[r][aa][b] = (out[aa * M + b][r] + f4[aa * M + b]) + __uint_as_float(gp_g[g][aa * M + b]);
           }
-          store_patches(a.y, a.y_bytes, o, (off_g[g] + (unsigned)kfirst * plane) * 4u, plane * 4u,
-                        (unsigned)Wo * 4u, K - kfirst, flags_g[g] & 1u, flags_g[g] & 2u,
-                        flags_g[g] & 4u, even_w);
+          const unsigned base = (off_g[g] + (unsigned)kfirst * plane) * 4u;
+          if ((Wo & 15) == 0)  // rows of whole 64-byte sectors
+            store_patches<true>(a.y, a.y_bytes, o, base, plane * 4u, (unsigned)Wo * 4u, K - kfirst,
+                                flags_g[g] & 1u, flags_g[g] & 2u, flags_g[g] & 4u, true);
+          else
+            store_patches<false>(a.y, a.y_bytes, o, base, plane * 4u, (unsigned)Wo * 4u, K - kfirst,
+                                 flags_g[g] & 1u, flags_g[g] & 2u, flags_g[g] & 4u, even_w);
         }
       }
     }
