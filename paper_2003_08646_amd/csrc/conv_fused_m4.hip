@@ -12,7 +12,7 @@
 // Phase T: quant_phase_m4.h, channels 0..63 then channels 64..127, each into its own code planes;
 // the column sums of both add up in one table.  The Eq. 7 / Eq. 8 constants come either finished
 // from the reduction kernel (qparams, dq, dqd) or are formed here from the caller's ranges or from
-// a few range records (range_reduce.h), after the first patch loads have been requested.
+// the range records; what they are formed from is requested before the first pixels (EarlyLoads).
 //
 // Phase G: filters in blocks of 64; wave w takes filters 16w.. of the block and all 16 tiles
 // (one v_mfma_i32_16x16x64_i8 per position and channel block).  The B fragments come from LDS two
@@ -23,12 +23,14 @@
 // M[e,k,p] = s_e*ACC + f[e,k] + g[e,p]; the three terms go through the linear map S = A^T M A
 // separately; f is formed here from the filter row sums (binary64), g from the column sums.
 //
-// Measured on the 128-channel 56 x 56 layer at N = 64 by leaving phases out: 10 us of constants and
-// filter-side terms, 29 us of phase T, 43 us of phase G, and they add up (83 us): the two workgroups
-// of a compute unit start together and stay in step.  Phase G is bound by instruction issue: per
-// position and accumulator register one conversion and about five multiply-adds of the fold stand
-// against a quarter of a matrix instruction; neither a deeper fragment ring (11 positions) nor
-// the order of products and fold changed its time.  A variant with one workgroup of eight waves
+// What bounds it, N64 128 -> 128 56x56 (with caller's ranges 94 us, now 86; with dynamic ones 118, now
+// 109): the phases add up - vector ALUs of the transform and of the fold (per position and
+// accumulator register one conversion and about five multiply-adds against a quarter of a matrix
+// instruction), then memory.  Neither a deeper fragment ring (11 positions) nor the order of products
+// and fold changed phase G.  What did help: constants requested before the pixels, the filter-side
+// terms in separable form (170 binary64 instructions instead of 470), no reduction kernel, the second
+// channel block's pixels requested under the first one's arithmetic, whole rows of the filter-side
+// terms read at once and range-checked stores in the tail.  A variant with one workgroup of eight waves
 // per compute unit - four waves quantizing tile block i+1 into one half of LDS while four
 // multiply block i from the other half, one barrier per block - was built and passed parity, and
 // was slower (107 us): a lone product wave per SIMD issues one instruction per five to six cycles,
@@ -55,6 +57,7 @@ constexpr int kE = 36;
 constexpr int kPlane = kTiles * 64;        // code plane of one position: 1 KB
 constexpr int kBlockPlanes = kE * kPlane;  // code planes of one channel block: 36 KB
 constexpr int kFilters = 64;               // filters per pass of phase G
+constexpr unsigned kOob = 0xFFFFFFF0u;
 
 struct C4Args {
   const float* x;
@@ -66,11 +69,12 @@ struct C4Args {
   const double* dqd;    // [E][2]  (merge == 0)
   int N, C, H, W, K, pad, P, th, tw, Ho, Wo, bits;
   unsigned reach;  // bytes from the plane (first image of a block, channel) that tiles of the block may read
+  unsigned y_bytes;
 };
 
 // LDS carve-up behind the code planes
 struct Lds {
-  float* rk_s;       // [16 outputs][64 filters]
+  float* rk_s;       // [64 filters][16 outputs]
   int* cs_s;         // [E][16] column sums (unsigned codes)
   float* sc_s;       // [E] s_e = scale_u * scale_v
   float* gc_s;       // [E] scale_v * offset_u
@@ -95,10 +99,123 @@ __device__ __forceinline__ Lds carve(char* p) {
   return l;
 }
 
+// What the constants are formed from, requested before the first pixels: loads return in order, and
+// behind the pixels these few bytes from L2 would wait for memory.
+template <int NB>
+struct EarlyLoads {
+  static constexpr int kPieces = kE / 2, kGroups = kThreads / kPieces;  // 16-byte pieces of a record
+  static constexpr int kRecords = 19;  // records per thread: 266 in a workgroup
+  v4f rec[kRecords];
+  float ur[2], vr[2], dq[2];  // threads 0..35: position tid
+  double dqd[2];
+
+  __device__ __forceinline__ EarlyLoads(const C4Args& a, int tid) {
+    const int e = min(tid, kE - 1);
+    if (!a.rs.merge) {  // the reduction kernel left the constants in memory
+#pragma unroll
+      for (int i = 0; i < 2; i++) {
+        vr[i] = a.rs.qparams[2 * e + i];
+        dq[i] = a.dq[4 * e + i];
+        dqd[i] = a.dqd[2 * e + i];
+      }
+      return;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; i++) ur[i] = a.rs.u_range[2 * e + i];
+    if (a.rs.is_static) {
+#pragma unroll
+      for (int i = 0; i < 2; i++) vr[i] = a.rs.v_range[2 * e + i];
+    } else {
+#pragma unroll
+      for (int u = 0; u < kRecords; u++)  // (past the last record: the last one again)
+        rec[u] = *reinterpret_cast<const v4f*>(
+            a.rs.partial + (size_t)min(tid / kPieces + u * kGroups, a.rs.count - 1) * (2 * kE) + 4 * (tid % kPieces));
+    }
+  }
+  __device__ __forceinline__ static void merge(v4f& v, const v4f& x) {
+    v[0] = fminf(v[0], x[0]); v[1] = fmaxf(v[1], x[1]);
+    v[2] = fminf(v[2], x[2]); v[3] = fmaxf(v[3], x[3]);
+  }
+  // The records into rec[0].  With one channel block this is done before the pixels are requested (their
+  // registers would cost the compute unit its third workgroup), with two while they are in flight.
+  __device__ __forceinline__ void merge_records(const C4Args& a) {
+    if (!a.rs.merge || a.rs.is_static) return;
+#pragma unroll
+    for (int u = 1; u < kRecords; u++) merge(rec[0], rec[u]);
+    if constexpr (NB == 1) asm volatile("" : "+v"(rec[0]));
+  }
+
+  // Eq. 7 and Eq. 8 constants in LDS, by all threads; ends in a barrier.  red: scratch of 14 records.
+  __device__ __forceinline__ void form(const C4Args& a, const Lds& l, float* red, int tid) {
+    const dev::RangeSource& r = a.rs;
+    if (!r.merge) {
+      if (tid < kE) {
+        l.qp_s[2 * tid] = vr[0]; l.qp_s[2 * tid + 1] = vr[1];
+        l.sc_s[tid] = dq[0]; l.gc_s[tid] = dq[1];
+        l.rmul_s[tid] = dqd[0]; l.kconst_s[tid] = dqd[1];
+      }
+      __syncthreads();
+      return;
+    }
+    if (!r.is_static) {
+      if constexpr (NB == 2) merge_records(a);
+      v4f v = rec[0];
+      for (int row = tid / kPieces + kRecords * kGroups; row < r.count; row += kGroups)
+        merge(v, *reinterpret_cast<const v4f*>(r.partial + (size_t)row * (2 * kE) + 4 * (tid % kPieces)));
+      if (tid < kGroups * kPieces) *reinterpret_cast<v4f*>(red + tid / kPieces * (2 * kE) + 4 * (tid % kPieces)) = v;
+      __syncthreads();
+      if (tid < kE) {
+        vr[0] = red[2 * tid]; vr[1] = red[2 * tid + 1];
+#pragma unroll
+        for (int i = 1; i < kGroups; i++) {
+          vr[0] = fminf(vr[0], red[i * (2 * kE) + 2 * tid]);
+          vr[1] = fmaxf(vr[1], red[i * (2 * kE) + 2 * tid + 1]);
+        }
+      }
+      if (r.per_tensor) {
+        if (tid < kE) { l.res_s[2 * tid] = vr[0]; l.res_s[2 * tid + 1] = vr[1]; }
+        __syncthreads();
+        if (tid < kE)
+          for (int e = 0; e < kE; e++) { vr[0] = fminf(vr[0], l.res_s[2 * e]); vr[1] = fmaxf(vr[1], l.res_s[2 * e + 1]); }
+      }
+      if (blockIdx.x == 0 && tid < kE) { r.v_range[2 * tid] = vr[0]; r.v_range[2 * tid + 1] = vr[1]; }
+    }
+    if (tid < kE) {
+      float iu, su, inv, sv;
+      dev::quant_params(ur[0], ur[1], r.bits_w, &iu, &su);
+      dev::quant_params(vr[0], vr[1], r.bits, &inv, &sv);
+      const double ou = (double)ur[0] + (double)su * (double)(1 << (r.bits_w - 1));
+      const double ov = (double)vr[0] + (double)sv * (double)(1 << (r.bits - 1));
+      l.qp_s[2 * tid] = vr[0]; l.qp_s[2 * tid + 1] = inv;
+      l.sc_s[tid] = (float)((double)su * (double)sv);
+      l.gc_s[tid] = (float)((double)sv * ou);
+      l.rmul_s[tid] = (double)su * ov;
+      l.kconst_s[tid] = (double)r.C * ou * ov;
+    }
+    __syncthreads();
+  }
+};
+
+// The four pixels of an output row of a tile; stores that must not happen get an offset beyond the
+// buffer.  (The scalar offset stays 0: see conv_fused_pairs.hip.)  whole: the tile's columns all exist.
+// STREAM: non-temporal, for rows of whole 64-byte sectors.
+template <bool STREAM>
+__device__ __forceinline__ void store_row(float* y, unsigned bytes, unsigned off, bool whole, int cols, const float (&o)[4]) {
+  const __amdgpu_buffer_rsrc_t res = __builtin_amdgcn_make_buffer_rsrc(y, 0, bytes, 0x00020000);
+  typedef unsigned v4u __attribute__((ext_vector_type(4)));
+  const v4u v = {__float_as_uint(o[0]), __float_as_uint(o[1]), __float_as_uint(o[2]), __float_as_uint(o[3])};
+  __builtin_amdgcn_raw_buffer_store_b128(v, res, whole ? off : kOob, 0, STREAM ? 2 : 0);
+  if (!STREAM && !whole) {
+#pragma unroll
+    for (int b = 0; b < 3; b++)
+      __builtin_amdgcn_raw_buffer_store_b32(v[b], res, b < cols && off != kOob ? off + 4u * b : kOob, 0, 0);
+  }
+}
+
 // B8: 8-bit codes.  FULL: all 64 * NB channels exist.  MODE: patch load mode (patch_load_mode).
 // NB: channel blocks (1 or 2).
 template <bool B8, bool FULL, int MODE, int NB>
-__global__ __launch_bounds__(kThreads, 2) void conv_fused_m4_kernel(const C4Args a) {
+__global__ __launch_bounds__(kThreads, NB == 1 ? 3 : 2) void conv_fused_m4_kernel(const C4Args a) {
   constexpr int M = 4, A = 6, E = kE;
   constexpr int kAhead = 5;  // positions whose A fragments are in flight ahead of the products
   static_assert(E % (kAhead + 1) == 0, "the fragment ring keeps its phase across filter blocks");
@@ -111,62 +228,53 @@ __global__ __launch_bounds__(kThreads, 2) void conv_fused_m4_kernel(const C4Args
   const int p0 = dev::xcd_contiguous(blockIdx.x, gridDim.x) * kTiles;
   const int K = a.K, P = a.P;
 
-  // rk_s[(a*4 + b)*64 + filter] = sum_e A^T[a][i] A^T[b][j] (su*ov*rowsum[e][k] + C*ou*ov) for the
-  // 64 filters of block kb, in binary64: thread = (a = wave, filter = lane), all four b
-  auto rk_block = [&](int kb) {
+  // rk_s[filter*16 + a*4 + b] = sum_e A^T[a][i] A^T[b][j] (su*ov*rowsum[e][k] + C*ou*ov) for the 64
+  // filters of block kb, in binary64: thread = (a = wave, filter = lane), all four b
+  int32_t rs[E];
+  auto rk_load = [&](int kb) {
+    const int k = min(kb * kFilters + lane, K - 1);
+#pragma unroll
+    for (int e = 0; e < E; e++) rs[e] = a.u_rowsum[(size_t)e * K + k];
+  };
+  auto rk_block = [&]() {
     // a from a copy of the wave number the compiler cannot see through: the binary64
     // coefficients are then formed at each call instead of living in registers between calls
     int w = wave;
     asm volatile("" : "+s"(w));
-    const int k = min(kb * kFilters + lane, K - 1);
-    double ca[A], cb[M][A];
-#pragma unroll
-    for (int i = 0; i < A; i++) {
-      ca[i] = (double)dev::at_coef(M, w, i);
-#pragma unroll
-      for (int b = 0; b < M; b++) cb[b][i] = (double)dev::at_coef(M, b, i);
-    }
-    int32_t rs[E];
-#pragma unroll
-    for (int e = 0; e < E; e++) rs[e] = a.u_rowsum[(size_t)e * K + k];
     double acc[M] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int e = 0; e < E; e++) {
-      const double f = l.rmul_s[e] * (double)rs[e] + l.kconst_s[e];
-      const double ci = ca[e / A];
+    for (int i = 0; i < A; i++) {
+      const double ci = (double)dev::at_coef(M, w, i);
+      double row[M] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-      for (int b = 0; b < M; b++) acc[b] += ci * cb[b][e % A] * f;
+      for (int j = 0; j < A; j++) {
+        const int e = i * A + j;
+        const double f = __builtin_fma(l.rmul_s[e], (double)rs[e], l.kconst_s[e]);
+#pragma unroll
+        for (int b = 0; b < M; b++) {
+          const double cb = (double)dev::Wino<M>::at(b, j);
+          if (cb != 0.0) row[b] = __builtin_fma(cb, f, row[b]);
+        }
+      }
+#pragma unroll
+      for (int b = 0; b < M; b++) acc[b] = __builtin_fma(ci, row[b], acc[b]);
     }
-#pragma unroll
-    for (int b = 0; b < M; b++) l.rk_s[(w * M + b) * kFilters + lane] = (float)acc[b];
+    *reinterpret_cast<v4f*>(l.rk_s + lane * 16 + w * M) = v4f{(float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3]};
   };
 
   // ============================ phase T ============================
   {
     const dev::QuantBlockGeo qg{a.x, a.N, a.C, a.H, a.W, a.pad, a.th, a.tw, a.P, a.bits, a.reach};
+    EarlyLoads<NB> early(a, tid);
+    rk_load(0);
+    if constexpr (NB == 1) early.merge_records(a);
     auto phase_r = [&]() {
       for (int i = tid; i < E * kTiles; i += kThreads) l.cs_s[i] = 0;
-      const dev::Eq8Lds lds{l.sc_s, l.gc_s, l.rmul_s, l.kconst_s};
-      // the code planes are free until the first codes are written
-      dev::ranges_to_lds<E>(a.rs, reinterpret_cast<float*>(ring), l.res_s, l.qp_s, tid,
-                            blockIdx.x == 0, a.rs.merge ? &lds : nullptr);
-      if (!a.rs.merge) {  // the reduction kernel left the constants in memory
-        if (tid < E) {
-          l.sc_s[tid] = a.dq[4 * tid];
-          l.gc_s[tid] = a.dq[4 * tid + 1];
-          l.rmul_s[tid] = a.dqd[2 * tid];
-          l.kconst_s[tid] = a.dqd[2 * tid + 1];
-        }
-        __syncthreads();
-      }
-      rk_block(0);
+      // (the code planes are free until the first codes are written)
+      early.form(a, l, reinterpret_cast<float*>(ring), tid);
+      rk_block();
     };
-    auto nothing = []() {};
-    dev::quantize_m4_block16_to_lds<B8, FULL, MODE>(qg, p0, 0, ring, l.cs_s, l.qp_s, lane, wave,
-                                                    phase_r);
-    if constexpr (NB == 2)
-      dev::quantize_m4_block16_to_lds<B8, FULL, MODE>(qg, p0, 64, ring + kBlockPlanes, l.cs_s,
-                                                      l.qp_s, lane, wave, nothing);
+    dev::quantize_m4_tiles16_to_lds<B8, FULL, MODE, NB>(qg, p0, ring, l.cs_s, l.qp_s, lane, wave, phase_r);
   }
 
   // ============================ phase G ============================
@@ -230,12 +338,19 @@ __global__ __launch_bounds__(kThreads, 2) void conv_fused_m4_kernel(const C4Args
   const int tx = pc % a.tw, t2 = pc / a.tw;
   const int ty = t2 % a.th, n = t2 / a.th;
   const int Ho = a.Ho, Wo = a.Wo;
-  const bool vec_ok = (Wo % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.y) & 15) == 0);
+  const int cols = Wo - tx * M;  // output columns of the tile that exist, if below 4
+  unsigned y_off[M];             // byte offsets of the tile's rows in filter 0
+#pragma unroll
+  for (int aa = 0; aa < M; aa++)
+    y_off[aa] = p < P && ty * M + aa < Ho
+                    ? (((unsigned)n * (unsigned)K * (unsigned)Ho + (unsigned)(ty * M + aa)) * (unsigned)Wo + (unsigned)(tx * M)) * 4u
+                    : kOob;
 
   for (int kb = 0; kb < nkb; kb++) {
     if (kb > 0) {
+      rk_load(kb);
       __syncthreads();  // the previous block's tail has read rk_s
-      rk_block(kb);
+      rk_block();
     }
     v4f out[M][M];  // [a][b][accumulator register]
     v4f rowacc[M];  // [b][accumulator register]
@@ -288,36 +403,25 @@ __global__ __launch_bounds__(kThreads, 2) void conv_fused_m4_kernel(const C4Args
     // lane holds filters k0 + r (r = accumulator register) of tile p. ----
     const int kin = wave * 16 + 4 * kq;
     const int k0 = kb * kFilters + kin;
-    if (p < P && k0 < K) {
+    const unsigned plane = (unsigned)Ho * (unsigned)Wo * 4u;
+    auto tail = [&](auto stream) {
 #pragma unroll
       for (int r = 0; r < 4; r++) {
         const int k = k0 + r;
-        if (k < K) {
-          float* yk = a.y + ((size_t)n * K + k) * Ho * Wo;
 #pragma unroll
-          for (int aa = 0; aa < M; aa++) {
-            const int yy = ty * M + aa;
-            if (yy < Ho) {
-              float o[M];
+        for (int aa = 0; aa < M; aa++) {
+          const v4f f4 = *reinterpret_cast<const v4f*>(l.rk_s + (kin + r) * 16 + aa * M);
+          float o[M];
 #pragma unroll
-              for (int b = 0; b < M; b++)
-                o[b] = (out[aa][b][r] + l.rk_s[(aa * M + b) * kFilters + kin + r]) + gp[aa][b];
-              float* dst = yk + (size_t)yy * Wo + tx * M;
-              if (vec_ok) {  // the tile's four columns are inside and 16-byte aligned
-                *reinterpret_cast<v4f*>(dst) = v4f{o[0], o[1], o[2], o[3]};
-              } else if (tx * M + 3 < Wo) {  // inside, any 4-byte alignment: still one store
-                typedef float v4fu __attribute__((ext_vector_type(4), aligned(4)));
-                *reinterpret_cast<v4fu*>(dst) = v4fu{o[0], o[1], o[2], o[3]};
-              } else {
-#pragma unroll
-                for (int b = 0; b < M; b++)
-                  if (tx * M + b < Wo) dst[b] = o[b];
-              }
-            }
-          }
+          for (int b = 0; b < M; b++) o[b] = (out[aa][b][r] + f4[b]) + gp[aa][b];
+          const unsigned off = k < K && y_off[aa] != kOob ? y_off[aa] + (unsigned)k * plane : kOob;
+          store_row<decltype(stream)::value>(a.y, a.y_bytes, off, cols >= M, cols, o);
         }
       }
-    }
+    };
+    // non-temporal: N16 64 -> 64 224x224 175 -> 157 us, 128 -> 128 112x112 107 -> 100; N64 64 -> 64 56x56, whose
+    // rows end inside a sector, 61 us, non-temporal 67
+    if (Wo % 16 == 0) tail(std::true_type{}); else tail(std::false_type{});
   }
 }
 
@@ -366,11 +470,13 @@ bool conv_fused_m4_applicable(const Geo& g) {
   return block_reach_bytes(g) < (1LL << 31) && (long long)(g.P + kTiles - 1) / kTiles < (1LL << 31);
 }
 
-// Every workgroup reads all `count` records of the range pass: worth it while that stays a small
-// part of the pass (the bound of the quantize passes that reduce for themselves).
+// Every workgroup reads all `count` records of the range pass (EarlyLoads), about 0.7 us of a compute
+// unit's time for 256 of them, or a reduction kernel does it once, 8 us with its launch.  Measured with
+// and without that kernel: 56 MB of record reads (N64 128 -> 128 56x56) 113 / 109 us, 231 MB (N16 64 ->
+// 64 224x224) 155 / 155.
 bool conv_fused_m4_can_merge(const Geo& g, int count) {
   const long long grid = (g.P + kTiles - 1) / kTiles;
-  return grid * count * (8LL * g.E) <= (32LL << 20);
+  return grid * count * (8LL * g.E) <= (250LL << 20);
 }
 
 // merge != 0: the kernel forms the Eq. 7 / Eq. 8 constants itself, from v_range (static ranges)
@@ -391,6 +497,7 @@ hipError_t launch_conv_fused_m4(const Geo& g, const float* x, const int8_t* uq,
   a.N = g.N; a.C = g.C; a.H = g.H; a.W = g.W; a.K = g.K; a.pad = g.pad; a.P = g.P;
   a.th = g.th; a.tw = g.tw; a.Ho = g.Ho; a.Wo = g.Wo; a.bits = g.bits;
   a.reach = (unsigned)block_reach_bytes(g);
+  a.y_bytes = (unsigned)((size_t)g.N * g.K * g.Ho * g.Wo * 4);
   const unsigned grid = (unsigned)((g.P + kTiles - 1) / kTiles);
   return g.NB == 1 ? launch_blocks<1>(g, a, grid, s) : launch_blocks<2>(g, a, grid, s);
 }

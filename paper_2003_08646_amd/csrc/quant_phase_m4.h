@@ -1,13 +1,13 @@
-// Transform + quantize of one block of 16 tiles x 64 channels of F(4x4,3x3) into LDS, for kernels
+// Transform + quantize of 16 tiles x NB blocks of 64 channels of F(4x4,3x3) into LDS, for kernels
 // that keep the codes of V on chip: v^ = Q(B^T d B) (Algorithm 1; Eq. 7) formed in registers, the
-// signed 8-bit codes written as code rows [36][16 tiles][64 B], the column sums of the unsigned
+// signed 8-bit codes written as code rows [NB][36][16 tiles][64 B], the column sums of the unsigned
 // codes accumulated in LDS.
 //
 // Called by all 256 threads (4 waves) of a workgroup.  Wave w owns the 16-byte chunk w of every
 // code row and lane = (tile = lane % 16, dword hd = lane / 16 of that chunk): a lane quantizes
-// the four channels c_base + 4w + hd + 16q, q = 0..3 (byte q of its dword; the blocked channel
-// order of the code layout), one channel's 6x6 patch in registers while the next one's loads are
-// in flight.  The four lane groups read four different channel planes with one buffer
+// the four channels 4w + hd + 16q, q = 0..3 (byte q of its dword; the blocked channel order of the
+// code layout) of each block, one channel's 6x6 patch in registers while the next one's loads are
+// in flight, across the end of a block too.  The four lane groups read four different channel planes with one buffer
 // descriptor: a group carries its plane's distance from the first one in its offsets.  After its
 // four channels a lane owns one dword of all 36 positions: 36 ds_write_b32.  Column sums:
 // v_sad_u8, then LDS atomics.
@@ -22,19 +22,18 @@
 namespace lance {
 namespace dev {
 
-// B8: 8-bit codes.  FULL: all 64 channels c_base .. c_base+63 exist.  MODE: load mode of the
+// B8: 8-bit codes.  FULL: all 64 * NB channels exist.  MODE: load mode of the
 // patches (patch_load_mode).
-// p0: first tile of the block.  planes: [36][16][64 B].  cs_s: [36][16] int, zeroed by the caller
+// p0: first tile of the block.  planes: [NB][36][16][64 B].  cs_s: [36][16] int, zeroed by the caller
 // before a barrier that precedes the first atomic below (mid() contains one).
 // mid(): run once after the first loads have been requested (all threads; may use barriers);
 // after it qp_s[2e], qp_s[2e+1] = {min, inv} of Eq. 7 for position e.
 // g.reach must cover three channel planes beyond the block's images (the lane groups' planes).
-template <bool B8, bool FULL, int MODE, class Mid>
-__device__ __forceinline__ void quantize_m4_block16_to_lds(const QuantBlockGeo& g, int p0,
-                                                           int c_base, char* planes, int* cs_s,
-                                                           const float* qp_s, int lane, int wave,
-                                                           Mid&& mid) {
-  constexpr int M = 4, A = 6, E = 36, kTiles = 16, kSteps = 4, kPlane = kTiles * 64;
+template <bool B8, bool FULL, int MODE, int NB, class Mid>
+__device__ __forceinline__ void quantize_m4_tiles16_to_lds(const QuantBlockGeo& g, int p0, char* planes,
+                                                           int* cs_s, const float* qp_s, int lane,
+                                                           int wave, Mid&& mid) {
+  constexpr int M = 4, A = 6, E = 36, kTiles = 16, kSteps = 4 * NB, kPlane = kTiles * 64;
   constexpr bool kRows = MODE == 2;
   const int P = g.P;
   const unsigned HW = (unsigned)g.H * (unsigned)g.W;
@@ -49,9 +48,9 @@ __device__ __forceinline__ void quantize_m4_block16_to_lds(const QuantBlockGeo& 
   pl.setup((unsigned)(n - n0) * (unsigned)g.C * HW, n0, n, g.N, ty, tx, g.pad, g.H, g.W);
   const char* xb = reinterpret_cast<const char*>(g.x + (size_t)n0 * g.C * HW);
 
-  // step k = byte k of the lane's dword.  chan_lo: the channel of lane group 0 (the descriptor's
+  // step k = byte k % 4 of the lane's dword of block k / 4.  chan_lo: the channel of lane group 0 (the descriptor's
   // plane); group hd is hd channels above.
-  auto chan_lo = [&](int k) { return c_base + 4 * wave + 16 * k; };
+  auto chan_lo = [&](int k) { return 4 * wave + 16 * k; };
   auto chan_own = [&](int k) { return chan_lo(k) + hd; };
   // channels beyond C (FULL is false) read the last plane; their bytes are masked below
   const unsigned plane_bytes = HW * 4u;
@@ -122,31 +121,33 @@ __device__ __forceinline__ void quantize_m4_block16_to_lds(const QuantBlockGeo& 
     for (int e = 0; e < E; e++) {
       float tq = (d[e / A][e % A] - qmn[e]) * qinv[e];
       if constexpr (!B8) tq = fminf(tq, L);
-      codes[e] = __builtin_amdgcn_cvt_pk_u8_f32(tq, k, k == 0 ? 0u : codes[e]);
+      codes[e] = __builtin_amdgcn_cvt_pk_u8_f32(tq, k & 3, (k & 3) == 0 ? 0u : codes[e]);
     }
     // pin this channel's arithmetic to its step (see quant_phase.h)
 #pragma unroll
     for (int e = 0; e < E; e++) asm volatile("" : "+v"(codes[e]));
     __builtin_amdgcn_sched_barrier(0);
-  }
-  unsigned realmask = 0;
+    if ((k & 3) != 3) continue;
+    // the lane's dword of this block
+    unsigned realmask = 0;
 #pragma unroll
-  for (int i = 0; i < 4; i++)
-    if (c_base + 4 * wave + hd + 16 * i < g.C) realmask |= 0xFFu << (8 * i);
-  const unsigned l_off = code_row_offset(trow, wave) + 4u * (unsigned)hd;
+    for (int i = 0; i < 4; i++)
+      if (chan_own(k - 3 + i) < g.C) realmask |= 0xFFu << (8 * i);
+    char* dst = planes + (k >> 2) * (E * kPlane) + code_row_offset(trow, wave) + 4u * (unsigned)hd;
 #pragma unroll
-  for (int e = 0; e < E; e++) {
-    unsigned u = codes[e];
-    if constexpr (!FULL) u &= realmask;
-    const unsigned cs = __builtin_amdgcn_sad_u8(u, 0u, 0u);
-    unsigned v;
-    if constexpr (B8)
-      v = u ^ H8;
-    else
-      v = ((u | H8) - (hh & ~H8)) ^ ((u ^ ~hh) & H8);
-    if constexpr (!FULL) v &= realmask;
-    *reinterpret_cast<unsigned*>(planes + e * kPlane + l_off) = v;
-    atomicAdd(&cs_s[e * kTiles + trow], (int)cs);
+    for (int e = 0; e < E; e++) {
+      unsigned u = codes[e];
+      if constexpr (!FULL) u &= realmask;
+      const unsigned cs = __builtin_amdgcn_sad_u8(u, 0u, 0u);
+      unsigned v;
+      if constexpr (B8)
+        v = u ^ H8;
+      else
+        v = ((u | H8) - (hh & ~H8)) ^ ((u ^ ~hh) & H8);
+      if constexpr (!FULL) v &= realmask;
+      *reinterpret_cast<unsigned*>(dst + e * kPlane) = v;
+      atomicAdd(&cs_s[e * kTiles + trow], (int)cs);
+    }
   }
 }
 

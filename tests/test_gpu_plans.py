@@ -507,3 +507,10 @@ def test_rows_of_any_width(shape):
     N, C, K, H, W, pad, m = shape
     L = Wk.Layer("rows", N, C, K, H, W, pad=pad, m=m, seed=740 + C)
     _check_layer(L, flags=B.LANCE_PLAN_WIDE_TILES)
+
+
+def test_fused_m4_reduction_kernel_on_many_tiles():
+    """F(4x4): enough workgroups and range records that the reduction kernel runs between the passes."""
+    L = Wk.Layer("m4_many_tiles", 36, 20, 8, 224, 224, m=4, seed=760)
+    conv, _ = _check_layer(L, staged=False)
+    assert _kernels(conv, _zeros(conv, False))[1:] == ["range_finalize_kernel", "", "conv_fused_m4_kernel"]
