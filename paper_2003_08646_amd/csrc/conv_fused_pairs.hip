@@ -176,6 +176,10 @@ struct Constants {
   }
 };
 
+// Workgroup barrier that waits for this wave's LDS operations only: loads from memory stay in flight
+// across it, which __syncthreads() would wait for.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // NB: channel blocks.  B8: 8-bit codes.  FULL: all channels of the blocks exist.
 template <int NB, bool B8, bool FULL>
 __device__ __forceinline__ void conv_body(const CpArgs& a) {
@@ -187,7 +191,7 @@ __device__ __forceinline__ void conv_body(const CpArgs& a) {
   using Phase = dev::PairPhase<B8, FULL, kPairs>;
   extern __shared__ char smem[];
   char* ring = smem;                                            // [NB][E][kTiles rows][64 B]
-  int* cs_s = reinterpret_cast<int*>(smem + kCodeBytes);         // [E][kTiles] column sums (unsigned codes)
+  int* cs_s = reinterpret_cast<int*>(smem + kCodeBytes);         // [E][kTiles] column sums (signed codes)
   float* sc_s = reinterpret_cast<float*>(cs_s + E * kTiles);    // [E] s_e = scale_u * scale_v
   float* gc_s = sc_s + E;                                       // [E] scale_v * offset_u
   float* qp_s = gc_s + E;                                       // [E][2] = {min, inv} of Eq. 7
@@ -214,7 +218,6 @@ __device__ __forceinline__ void conv_body(const CpArgs& a) {
     ph.setup(a.g, blk, (NB == 2 ? 64 * upper : 2 * upper) + 4 * chunk, lane);
 #pragma unroll
     for (int k = 0; k < kStepsAhead; k++) ph.issue(a.g, k, px[k]);
-    for (int i = tid; i < E * kTiles; i += kThreads) cs_s[i] = 0;
     // (the code rows are free until the first codes are written)
     const Constants cst{sc_s, gc_s, qp_s, rmul_s, kconst_s, reinterpret_cast<float*>(ring)};
     cst.form(a, tid, early);
@@ -255,7 +258,7 @@ __device__ __forceinline__ void conv_body(const CpArgs& a) {
       ph.quantize(px[k % (kStepsAhead + 1)], qmn, qinv, L, k, codes);
     }
     ph.store(a.g, chunk, (NB == 2 ? 0 : 2 * upper) + lane / kPairs, lane,
-             ring + (NB == 2 ? upper * (E * kPlane) : 0), cs_s, codes);
+             ring + (NB == 2 ? upper * (E * kPlane) : 0), codes);
   }
 
   // ============================ phase G ============================
@@ -283,17 +286,36 @@ __device__ __forceinline__ void conv_body(const CpArgs& a) {
   v4i afrag[kFragsAhead + 1][NB];  // ring over positions (16 positions = four turns)
 #pragma unroll
   for (int e = 0; e < kFragsAhead; e++) load_afrags(0, e, afrag[e]);
-  __syncthreads();  // codes and column sums of all waves are in LDS
+  lds_barrier();  // the codes of all waves are in LDS
+  // Column sums: one more matrix instruction per fragment, with an operand of ones; wave w takes the
+  // positions 2w and 2w + 1 of all tiles.  (v_sad_u8 and LDS atomics, in phase T: 89.3 / 88.1 us on N64 128 ->
+  // 128 56x56 with the other barrier, 44.8 / 42.6 on N64 100 -> 100 36x36.)
+  {
+    const v4i ones = {0x01010101, 0x01010101, 0x01010101, 0x01010101};
+#pragma unroll
+    for (int e2 = 0; e2 < 2; e2++)
+#pragma unroll
+      for (int t = 0; t < kTiles / 16; t++) {
+        const int e = 2 * wave + e2, row = 16 * t + col;
+        const unsigned off = (unsigned)row * 64u + (unsigned)((kq ^ dev::row_swizzle_mfma32(row)) * 16);
+        v4i sum = {0, 0, 0, 0};
+#pragma unroll
+        for (int nb = 0; nb < NB; nb++)
+          sum = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+              ones, *reinterpret_cast<const v4i*>(ring + (nb * E + e) * kPlane + off), sum, 0, 0, 0);
+        if (kq == 0) cs_s[e * kTiles + row] = sum[0];  // every row of the product is the same
+      }
+  }
+  lds_barrier();
 
   float gp[2][M * M];  // input-side terms of the lane's tiles through A^T . A
-  const int ch_h = a.g.C * (int)(1u << (a.g.bits - 1));  // signed code = unsigned code - h
 #pragma unroll
   for (int s = 0; s < 2; s++) {
 #pragma unroll
     for (int ab = 0; ab < M * M; ab++) gp[s][ab] = 0.0f;
 #pragma unroll
     for (int e = 0; e < E; e++) {
-      const float ge = gc_s[e] * (float)(cs_s[e * kTiles + kPairs * s + pair] - ch_h);
+      const float ge = gc_s[e] * (float)cs_s[e * kTiles + kPairs * s + pair];
 #pragma unroll
       for (int ab = 0; ab < M * M; ab++) {
         const float coef = kAt2[ab >> 1][e / A] * kAt2[ab & 1][e % A];

@@ -1,7 +1,6 @@
 // Transform + quantize of F(2x2,3x3) tiles into LDS, two horizontally adjacent tiles per lane:
 // v^ = Q(B^T d B) (Algorithm 1; Eq. 7) formed in registers, the signed 8-bit codes written as code
-// rows [E][TILES][64 B], the column sums of the unsigned codes accumulated in LDS.  NCHW tensors,
-// pad 1, image widths that are multiples of 4: a lane's pair of tiles 2q, 2q+1 of a tile row then
+// rows [E][TILES][64 B].  NCHW tensors, pad 1, image widths that are multiples of 4: a lane's pair of tiles 2q, 2q+1 of a tile row then
 // owns the aligned 16-byte segment 4q .. 4q+3 of each of its four image rows.
 //
 // What it saves against one tile per lane (quant_phase.h): one 16-byte load per row for two tiles
@@ -157,9 +156,8 @@ struct PairPhase {
     __builtin_amdgcn_sched_barrier(0);
   }
 
-  // The lane's dwords into the code rows [E][kTiles][64 B] at ring, and the sums of the unsigned codes
-  // of the channels that exist added to cs[E][kTiles].  d: the lane's dword of chunk `chunk`.
-  __device__ __forceinline__ void store(const PairGeo& g, int chunk, int d, int lane, char* ring, int* cs,
+  // The lane's dwords into the code rows [E][kTiles][64 B] at ring.  d: the lane's dword of chunk `chunk`.
+  __device__ __forceinline__ void store(const PairGeo& g, int chunk, int d, int lane, char* ring,
                                         const unsigned (&codes)[2][E]) const {
     const unsigned h = 1u << (g.bits - 1);
     const unsigned H8 = 0x80808080u, hh = h * 0x01010101u;
@@ -167,17 +165,13 @@ struct PairPhase {
 #pragma unroll
     for (int b = 0; b < 4; b++)
       if (c_wave + 16 * b + group < g.C) mask |= 0xFFu << (8 * b);
-    const int pair = lane % PAIRS;
-    unsigned sums[2][E];
 #pragma unroll
     for (int s = 0; s < 2; s++) {
-      const int row = PAIRS * s + pair;
+      const int row = PAIRS * s + lane % PAIRS;
       char* dst = ring + (unsigned)row * 64u + (unsigned)((chunk ^ row_swizzle_mfma32(row)) * 16) + 4u * (unsigned)d;
 #pragma unroll
       for (int e = 0; e < E; e++) {
-        unsigned u = codes[s][e];
-        if constexpr (!FULL) u &= mask;
-        sums[s][e] = __builtin_amdgcn_sad_u8(u, 0u, 0u);
+        const unsigned u = codes[s][e];
         // per-byte (code - h) mod 256 without borrows between bytes (h = 128: flip the top bit)
         unsigned v;
         if constexpr (B8)
@@ -187,15 +181,6 @@ struct PairPhase {
         if constexpr (!FULL) v &= mask;
         *reinterpret_cast<unsigned*>(dst + e * (kTiles * 64)) = v;
       }
-    }
-    // both lane halves hold the same pairs (other dwords): the lower half takes the left tile's
-    // sums of both, the upper half the right tile's
-    int* sum = cs + (lane < 32 ? 0 : PAIRS) + pair;
-#pragma unroll
-    for (int e = 0; e < E; e++) {
-      typedef unsigned v2u __attribute__((ext_vector_type(2)));
-      const v2u x = __builtin_amdgcn_permlane32_swap(sums[0][e], sums[1][e], false, false);
-      atomicAdd(&sum[e * kTiles], (int)(x[0] + x[1]));
     }
   }
 };
