@@ -317,9 +317,15 @@ __global__ __launch_bounds__(kThreads, 2) void conv_fused_c128_kernel(const CgAr
                 const int oy = ty * M + aa, ox = tx * M + b;
                 const unsigned pix = (((unsigned)n * (unsigned)a.Ho + (unsigned)oy) * Wo_u +
                                       (unsigned)ox) * (unsigned)K * 4u;
-                dev::store_nhwc_k4(a.y, a.y_bytes, pix, (unsigned)kfirst * 4u,
-                                   p < P && oy < a.Ho && ox < a.Wo, K - kfirst, (K & 3) == 0,
-                                   o[0][aa][b], o[1][aa][b], o[2][aa][b], o[3][aa][b]);
+                const unsigned kb4 = (unsigned)kfirst * 4u;
+                const bool ok = p < P && oy < a.Ho && ox < a.Wo;
+                // (N64 128 -> 128 56x56: 121.6 -> 111.9 us with non-temporal stores)
+                if ((K & 15) == 0)
+                  dev::store_nhwc_k4<true>(a.y, a.y_bytes, pix, kb4, ok, K - kfirst, true, o[0][aa][b],
+                                           o[1][aa][b], o[2][aa][b], o[3][aa][b]);
+                else
+                  dev::store_nhwc_k4(a.y, a.y_bytes, pix, kb4, ok, K - kfirst, (K & 3) == 0, o[0][aa][b],
+                                     o[1][aa][b], o[2][aa][b], o[3][aa][b]);
               }
           } else {
             store_patches4(a.y, a.y_bytes, o, base, plane_px * 4u, Wo_u * 4u, K - kfirst, p < P,

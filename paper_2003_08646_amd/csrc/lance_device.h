@@ -207,7 +207,9 @@ __device__ __forceinline__ size_t act_index(bool nhwc, int n, int k, int yy, int
 // NHWC output: stores v = the values of filters k .. k+3 of one output pixel at byte offset
 // pix_bytes + 4*k of y (Y is [pixel][K]).  pix_ok: the pixel exists; kleft: filters that exist
 // from k on; k4 (kernel-uniform): K is a multiple of 4, so the four are stored at once.  Stores
-// that must not happen get an offset the buffer's range check drops.  y_bytes < 0xFFFFFFF0.
+// that must not happen get an offset the buffer's range check drops.  y_bytes < 0xFFFFFFF0.  STREAM:
+// non-temporal (where four lanes fill a 64-byte sector, i.e. K is a multiple of 16).
+template <bool STREAM = false>
 __device__ __forceinline__ void store_nhwc_k4(float* y, unsigned y_bytes, unsigned pix_bytes,
                                               unsigned k_bytes, bool pix_ok, int kleft, bool k4,
                                               float v0, float v1, float v2, float v3) {
@@ -217,7 +219,7 @@ __device__ __forceinline__ void store_nhwc_k4(float* y, unsigned y_bytes, unsign
   if (k4) {
     const v4u v = {__float_as_uint(v0), __float_as_uint(v1), __float_as_uint(v2), __float_as_uint(v3)};
     __builtin_amdgcn_raw_buffer_store_b128(v, res, (pix_ok && kleft >= 4) ? pix_bytes + k_bytes : kOob,
-                                           0, 0);
+                                           0, STREAM ? 2 : 0);
   } else {
     const float vv[4] = {v0, v1, v2, v3};
 #pragma unroll
