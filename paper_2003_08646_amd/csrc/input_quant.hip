@@ -7,6 +7,9 @@
 // position planes of 64 rows x 64 bytes to vq with fully coalesced 16-byte stores (the rows of
 // consecutive tiles are contiguous in vq).  Each XCD takes a contiguous range of tile blocks.
 //
+// Layers of 4 to 8 channel blocks and 1521 to 4096 tiles take a workgroup for all blocks of 16 tiles
+// (input_quant_m2_whole_kernel).
+//
 // F(4x4,3x3) layers (36 positions, 6x6 patches) use the same scheme with blocks of 32 tiles: lane
 // = (tile, half of the wave's 16-byte chunk), eight channels per lane, two channels' pixels in
 // registers at a time.
@@ -374,6 +377,158 @@ __global__ __launch_bounds__(kThreads, 2) void input_quant_m4_kernel(const QArgs
   }
 }
 
+// F(2x2,3x3), all channel blocks of 16 tiles in one workgroup (4 to 8 waves, a channel block each): the
+// column sums are complete when it ends, so nothing has to be cleared before the pass (a kernel of its own
+// with caller's ranges) and nothing is added with atomics.  Lane = (tile = lane % 16, 16-byte chunk = lane / 16
+// of its code rows): 16 channels 4*chunk + d + 16q, two requested ahead; the chunks go straight to vq, 64
+// bytes per tile and position.
+template <bool B8, bool FULL, int MODE, bool PACKED>
+__global__ __launch_bounds__(512, 2) void input_quant_m2_whole_kernel(const QArgs a) {
+  constexpr int M = 2, A = 4, E = 16, kTiles = 16, kSteps = 16, kAhead = 2, kBuf = kAhead + 1;
+  __shared__ __align__(16) float red[1024];
+  __shared__ float res_s[2 * E], qp_s[2 * E];
+  __shared__ int cs_s[E * kTiles];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int cb = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int item = dev::xcd_contiguous(blockIdx.x, gridDim.x);
+  const int p0 = item * kTiles;
+  const dev::QuantBlockGeo& g = a.g;
+  const int P = g.P;
+  const unsigned HW = (unsigned)g.H * (unsigned)g.W;
+  const int trow = lane & 15, grp = lane >> 4;
+  if (tid < E * kTiles) cs_s[tid] = 0;
+
+  const int pt = min(p0 + trow, P - 1);
+  const int tx = pt % g.tw, t2 = pt / g.tw;
+  const int ty = t2 % g.th, n = t2 / g.th;
+  const int n0 = p0 / (g.th * g.tw);  // image of the block's first tile (wave-uniform)
+  dev::PatchLoader<M> pl;
+  // the wave's last lane (tile 15) holds the largest image index, as setup() expects
+  pl.setup((unsigned)(n - n0) * (unsigned)g.C * HW, n0, n, g.N, ty, tx, g.pad, g.H, g.W);
+  const char* xb = reinterpret_cast<const char*>(g.x + (size_t)n0 * g.C * HW);
+
+  // step k: dword d = k / 4 of the chunk, byte q = k % 4.  chan_lo: the channel of lane group 0 (the
+  // descriptor's plane); group grp is 4 * grp channels above.  Channels beyond C (FULL is false) read
+  // the last plane; their bytes are masked below.
+  auto chan_lo = [&](int k) { return cb * 64 + (k >> 2) + 16 * (k & 3); };
+  auto chan_own = [&](int k) { return chan_lo(k) + 4 * grp; };
+  const unsigned plane_bytes = HW * 4u;
+  auto plane_lo = [&](int k) { return FULL ? chan_lo(k) : min(chan_lo(k), g.C - 1); };
+  auto plane_own = [&](int k) { return FULL ? chan_own(k) : min(chan_own(k), g.C - 1); };
+  auto lane_off = [&](int k) -> unsigned { return (unsigned)(plane_own(k) - plane_lo(k)) * plane_bytes; };
+  // first / last plane of the tensor (per lane: the groups differ), as in quant_phase32.h
+  auto may_be_first = [&](int k) { return !FULL || k == 0; };
+  auto may_be_last = [&](int k) { return !FULL || k == kSteps - 1; };
+  auto is_first = [&](int k) { return may_be_first(k) && pl.first_image && plane_own(k) == 0; };
+  auto is_last = [&](int k) { return may_be_last(k) && pl.last_image && plane_own(k) == g.C - 1; };
+  float buf[kBuf][E];
+  auto issue = [&](int k) {
+    const char* plane = xb + (size_t)plane_lo(k) * plane_bytes;
+    const unsigned lo = lane_off(k);
+    if constexpr (MODE == 2) {
+      pl.issue_rows_shifted(plane, g.reach, is_first(k), is_last(k), buf[k % kBuf], lo);
+    } else if constexpr (MODE == 1) {
+      // (the lane groups read planes plane_lo .. plane_lo + 12)
+      pl.issue_any(plane, g.reach,
+                   (pl.first_image && plane_lo(k) == 0) || (pl.last_image && chan_lo(k) + 12 >= g.C - 1), buf[k % kBuf], lo);
+    } else {
+      dev::PatchLoader<M> pl2 = pl;
+#pragma unroll
+      for (int r = 0; r < A; r++)
+        if ((pl2.rowmask >> r) & 1u) pl2.rowoff[r] += lo;
+      pl2.template issue<false>(plane, g.reach, buf[k % kBuf]);
+    }
+  };
+#pragma unroll
+  for (int k = 0; k < kAhead; k++) issue(k);
+  dev::ranges_to_lds<E>(a.rs, red, res_s, qp_s, tid, item == 0);
+
+  float qmn[E], qinv[E];
+#pragma unroll
+  for (int e = 0; e < E; e++) {
+    qmn[e] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(qp_s[2 * e])));
+    qinv[e] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(qp_s[2 * e + 1])));
+  }
+  const float L = (float)((1 << g.bits) - 1);
+  const unsigned h = 1u << (g.bits - 1);
+  const unsigned H8 = 0x80808080u, hh = h * 0x01010101u;
+  v4i codes[E];
+#pragma unroll
+  for (int k = 0; k < kSteps; k++) {
+    if (k + kAhead < kSteps) issue(k + kAhead);
+    const int q = k & 3, dd = k >> 2;
+    float d[A][A];
+#pragma unroll
+    for (int r = 0; r < A; r++)
+#pragma unroll
+      for (int c = 0; c < A; c++) d[r][c] = buf[k % kBuf][r * A + c];
+    if constexpr (MODE == 2) {
+      if (may_be_first(k) || may_be_last(k)) pl.unshift(is_first(k), is_last(k), d);
+      pl.template fix<true>(d);
+    } else if constexpr (MODE == 1) {
+      pl.template fix<false>(d);
+    }
+    dev::input_tile_transform<M>(d);
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+      float tq = (d[e / A][e % A] - qmn[e]) * qinv[e];
+      if constexpr (!B8) tq = fminf(tq, L);
+      codes[e][dd] = (int)__builtin_amdgcn_cvt_pk_u8_f32(tq, q, q == 0 ? 0u : (unsigned)codes[e][dd]);
+    }
+    // pin this channel's arithmetic to its step (see quant_phase.h)
+#pragma unroll
+    for (int e = 0; e < E; e++) asm volatile("" : "+v"(codes[e][dd]));
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  unsigned mask[4];  // bytes of channels that exist
+#pragma unroll
+  for (int dd = 0; dd < 4; dd++) {
+    mask[dd] = 0;
+#pragma unroll
+    for (int i = 0; i < 4; i++)
+      if (cb * 64 + 4 * grp + dd + 16 * i < g.C) mask[dd] |= 0xFFu << (8 * i);
+  }
+  constexpr int kRow = PACKED ? 32 : 64;
+  const bool ok = p0 + trow < P && (!PACKED || grp < 2);
+  int8_t* dst = a.vq + ((size_t)cb * P + p0 + trow) * kRow + 16 * grp;
+  const size_t estride = (size_t)a.NB * P * kRow;
+#pragma unroll
+  for (int e = 0; e < E; e++) {
+    unsigned cs = 0;
+    v4i sg;
+#pragma unroll
+    for (int dd = 0; dd < 4; dd++) {
+      unsigned u = (unsigned)codes[e][dd];
+      if constexpr (!FULL) u &= mask[dd];
+      cs = __builtin_amdgcn_sad_u8(u, 0u, cs);
+      // per-byte (code - h) mod 256 without borrows between bytes (h = 128: flip the top bit)
+      unsigned v;
+      if constexpr (B8)
+        v = u ^ H8;
+      else
+        v = ((u | H8) - (hh & ~H8)) ^ ((u ^ ~hh) & H8);
+      if constexpr (!FULL) v &= mask[dd];
+      sg[dd] = (int)v;
+    }
+    atomicAdd(&cs_s[e * kTiles + trow], (int)cs);
+    if constexpr (PACKED) {  // chunks 0 and 1 take chunks 2 and 3 (32 lanes above) into their high bits
+      v4i hi;
+#pragma unroll
+      for (int dd = 0; dd < 4; dd++) {
+        typedef unsigned v2u __attribute__((ext_vector_type(2)));
+        const v2u x = __builtin_amdgcn_permlane32_swap((unsigned)sg[dd], (unsigned)sg[dd], false, false);
+        hi[dd] = (int)x[1];
+      }
+      sg = pack_nibbles(sg, hi);
+    }
+    if (ok) *reinterpret_cast<v4i*>(dst + e * estride) = sg;
+  }
+  __syncthreads();
+  const int t = tid & 15;
+  if (tid < E * kTiles && p0 + t < P)  // signed codes: (sum of the unsigned bytes) - h * channels
+    a.colsum[(size_t)(tid >> 4) * P + p0 + t] = cs_s[tid] - g.C * (int)h;
+}
+
 constexpr size_t kLdsBytesM4 =
     36 * 32 * 64 + 36 * 32 * sizeof(int) + dev::range_reduce_lds_floats<36>() * sizeof(float);
 
@@ -382,6 +537,13 @@ constexpr size_t kLdsBytes =
 
 constexpr size_t kLdsBytesHalf =
     16 * 2048 + 16 * 32 * sizeof(int) + dev::range_reduce_lds_floats<16>() * sizeof(float);
+
+template <bool B8, bool FULL, int MODE, bool PACKED>
+hipError_t launch_whole(const QArgs& a, hipStream_t s) {
+  note_kernel("input_quant_m2_whole_kernel");
+  input_quant_m2_whole_kernel<B8, FULL, MODE, PACKED><<<a.TB, 64 * a.NB, 0, s>>>(a);
+  return hipGetLastError();
+}
 
 // m: 2, 4, or 1 for F(2x2,3x3) on blocks of 32 tiles
 template <bool B8, bool FULL, int MODE>
@@ -397,15 +559,40 @@ hipError_t launch_variant(const QArgs& a, unsigned grid, hipStream_t s, int m) {
   return hipGetLastError();
 }
 
-// Tiles per workgroup: 32 for F(4x4,3x3); for F(2x2,3x3) 64, or 32 when 64-tile blocks would
+// All channel blocks in one workgroup (input_quant_m2_whole_kernel): while the workgroups run in one round
+// and reach most compute units.  Us per call with caller's ranges / with dynamic ones, a workgroup per
+// channel block against this one: N64 512 -> 512 14x14 (196 workgroups) 56.5 / 64.6 -> 54.3 / 63.0, N64 384 ->
+// 128 14x14 35.0 / 42.1 -> 30.6 / 39.9, N32 512 -> 512 14x14 (98) 40.0 / 46.0 -> 39.5 / 45.9; but N16 512 -> 512
+// 14x14 (49) 28.1 / 31.8, here 29.0 / 34.6, N24 512 -> 256 28x28 (294) 61.3 / 68.4, here 63.5 / 69.2, N64 256 -> 64
+// 56x56 (3136) 163, here 175.
+bool whole_blocks(const Geo& g) {
+  return g.m == 2 && g.CB == 64 && g.NB >= 4 && g.NB <= 8 && g.P > 95 * 16 && g.P <= 256 * 16;
+}
+
+// Tiles per workgroup: 16 with all channel blocks (whole_blocks); 32 for F(4x4,3x3); for F(2x2,3x3) 64, or 32 when 64-tile blocks would
 // give fewer than 192 workgroups (most compute units idle).
 int tile_block(const Geo& g) {
   if (g.m == 4) return 32;
+  if (whole_blocks(g)) return 16;
   return (long long)g.NB * ((g.P + 63) / 64) < 192 ? 32 : 64;
 }
 
 template <bool B8, bool FULL>
 hipError_t launch_rows(const Geo& g, const QArgs& a, unsigned grid, hipStream_t s) {
+  if (whole_blocks(g)) {
+    auto go = [&](auto packed) -> hipError_t {
+      constexpr bool kPacked = decltype(packed)::value;
+      switch (patch_load_mode(g)) {
+        case 0: return launch_whole<B8, FULL, 0, kPacked>(a, s);
+        case 1: return launch_whole<B8, FULL, 1, kPacked>(a, s);
+        default: return launch_whole<B8, FULL, 2, kPacked>(a, s);
+      }
+    };
+    if constexpr (!B8) {
+      if (is_packed(g)) return go(std::true_type{});
+    }
+    return go(std::false_type{});
+  }
   const int m = (g.m == 2 && tile_block(g) == 32) ? 1 : g.m;
   switch (patch_load_mode(g)) {
     case 0: return launch_variant<B8, FULL, 0>(a, grid, s, m);
@@ -418,8 +605,8 @@ long long block_reach_bytes(const Geo& g) {
   const long long tiles = (long long)g.th * g.tw;
   const int block = tile_block(g);
   const long long images = (block - 1) / tiles + 2;  // images a block of consecutive tiles can touch
-  // + two channel planes: the upper lane half of the 32-tile kernels reads two channels above
-  return images * g.C * g.H * g.W * 4LL + (block == 32 ? 2LL * g.H * g.W * 4LL : 0LL);
+  // + two channel planes: the upper lane half of the 32-tile kernels reads two channels above (16-tile: 12)
+  return images * g.C * g.H * g.W * 4LL + (block == 32 ? 2LL : block == 16 ? 12LL : 0LL) * g.H * g.W * 4LL;
 }
 
 }  // namespace
@@ -433,11 +620,15 @@ bool input_quant_applicable(const Geo& g) {
          (long long)g.NB * ((g.P + block - 1) / block) < (1LL << 31);
 }
 
+bool input_quant_adds_colsum_atomically(const Geo& g) {
+  return g.NB > 1 && !(input_quant_applicable(g) && whole_blocks(g));
+}
+
 // Every workgroup reads all records: worth it while that stays a small part of the pass
 // (measured: a gain of 4-6 us per layer up to about 20 MB of record reads, a loss of 2-4 us at 78 MB).
 bool input_quant_can_merge(const Geo& g, int count) {
   const int block = tile_block(g);
-  const long long grid = (long long)g.NB * ((g.P + block - 1) / block);
+  const long long grid = (whole_blocks(g) ? 1LL : g.NB) * ((g.P + block - 1) / block);
   return grid * count * (8LL * g.E) <= (32LL << 20);
 }
 

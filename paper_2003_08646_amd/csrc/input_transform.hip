@@ -303,7 +303,7 @@ hipError_t launch_input_transform(const Geo& g, const float* x, int8_t* vq, floa
   hipError_t e;
   int range_groups = 0;
   // column sums that are added to with atomics start at zero
-  const bool need_zero = nhwc ? input_nhwc_adds_colsum_atomically(g) : g.NB > 1;
+  const bool need_zero = nhwc ? input_nhwc_adds_colsum_atomically(g) : input_quant_adds_colsum_atomically(g);
   if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return e;
   note_slot(0);
   if (!is_static) {

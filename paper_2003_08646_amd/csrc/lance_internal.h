@@ -158,6 +158,8 @@ struct QuantSource {
   float* v_range;
   const DqOut* dqo;
 };
+// True if the pass adds to the column sums with atomics (they must be zero before it).
+bool input_quant_adds_colsum_atomically(const Geo& g);
 bool input_quant_can_merge(const Geo& g, int count);
 hipError_t launch_input_quant(const Geo& g, const float* x, const QuantSource& src, int8_t* vq,
                               int32_t* colsum, hipStream_t s);

@@ -514,3 +514,26 @@ def test_fused_m4_reduction_kernel_on_many_tiles():
     L = Wk.Layer("m4_many_tiles", 36, 20, 8, 224, 224, m=4, seed=760)
     conv, _ = _check_layer(L, staged=False)
     assert _kernels(conv, _zeros(conv, False))[1:] == ["range_finalize_kernel", "", "conv_fused_m4_kernel"]
+
+
+# N, C, K, H, W, pad, bits: quantize pass with all channel blocks in one workgroup (four to eight blocks, 1521
+# to 4096 tiles); the last two: one tile less and one block of tiles more
+_WHOLE = [
+    (32, 256, 20, 14, 13, 1, 8), (20, 300, 17, 18, 18, 1, 8), (33, 512, 9, 14, 14, 1, 8), (30, 449, 8, 16, 17, 0, 6),
+    (2, 270, 5, 78, 80, 1, 8), (32, 260, 20, 14, 14, 1, 4), (33, 512, 9, 15, 15, 0, 3),
+    (1, 256, 5, 80, 76, 1, 8), (1, 256, 5, 128, 130, 1, 8),
+]
+
+
+@pytest.mark.parametrize("shape", _WHOLE, ids=lambda s: "n%d_c%d_k%d_%dx%d_p%d_b%d" % s)
+@pytest.mark.parametrize("static", [False, True], ids=["dynamic", "static"])
+def test_quantize_pass_with_all_channel_blocks(shape, static):
+    from paper_2003_08646_amd import binding as B
+    N, C, K, H, W, pad, bits = shape
+    L = Wk.Layer("whole", N, C, K, H, W, pad=pad, m=2, bits=bits, seed=800 + C)
+    flags = B.LANCE_PLAN_WIDE_TILES | (B.LANCE_INPUT_RANGE_STATIC if static else 0)
+    for packed in ([0, B.LANCE_CODES_PACKED4] if bits <= 4 else [0]):
+        conv, _ = _check_layer(L, flags=flags | packed,
+                               static_v_range=_range_of_another_batch(L) if static else None)
+        P = conv.sz.P
+        assert (_kernels(conv, _zeros(conv, False))[2] == "input_quant_m2_whole_kernel") == (1520 < P <= 4096)
