@@ -53,13 +53,17 @@ static bool conv_fused_pos_applicable(const Geo& g) {
 //    chip idle (N3 4->43 112x95 32 -> 16, N11 5->58 58^2 46 -> 24, N1 3->64 224^2 20.5 -> 19.3,
 //    N4 3->64 224^2 33 against 66).
 //  * F(2x2), 17 to 128 channels: up to two workgroups of eight waves per compute unit (N4 32->128 63^2
-//    31.5 -> 21, N1 64->128 112^2 18.9 -> 14.4, N1 64->64 224^2 15.6 against 27).
+//    31.5 -> 21, N1 64->128 112^2 18.9 -> 14.4); one per compute unit where conv_fused_pairs.hip takes the
+//    layer in one block of filters (caller's ranges, this plan / that one: N1 128->128 112^2 17.9 / 11.3, N16
+//    128->128 28^2 17.2 / 12.2, N10 64->64 56^2 14.9 / 10.8; at 256 workgroups they meet: N4 64->64 56^2 9.7 /
+//    9.9, N8 128->128 28^2 11.1 / 11.6; with two blocks of filters N20 48->96 28^2 13.4 / 14.1).
 //  * the rest: one workgroup per compute unit (N1 512->512 28^2 23 -> 16.7, N1 128->256 56^2 F(4x4)
 //    44 -> 15, N4 256->512 28^2 24 against 28, N23 38->52 108^2 F(4x4) 51 against 95).
 bool conv_fused_pos_preferred(const Geo& g) {
   if (!conv_fused_pos_applicable(g)) return false;
   if (g.C <= 16) return g.m == 4 || g.P <= 12800;
-  return pos::shape_of(g).groups <= (g.m == 2 && g.NB <= 2 ? 512 : 256);
+  const bool two = g.m == 2 && g.NB <= 2 && !(conv_fused_pairs_applicable(g) && g.K <= 64 * g.NB);
+  return pos::shape_of(g).groups <= (two ? 512 : 256);
 }
 
 // Whether every workgroup reduces the records of the range pass for itself, or a reduction kernel does
