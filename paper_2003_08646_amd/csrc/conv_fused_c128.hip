@@ -104,9 +104,9 @@ __device__ __forceinline__ void static_for(F&& f) {
 constexpr float kAt2[2][4] = {{1, 1, 1, 0}, {0, 1, -1, -1}};
 
 // B8: 8-bit codes.  FULL: all 128 channels exist.  MODE: patch load mode (patch_load_mode), or
-// kModeNhwc: X is [N][H][W][C] (C a multiple of 4, a.reach = its size in bytes) and Y is
+// kModeNhwc, kModeNhwcRoll: X is [N][H][W][C] (C a multiple of 4, a.reach = its size in bytes) and Y is
 // [N][Ho][Wo][K].
-constexpr int kModeNhwc = 3;
+constexpr int kModeNhwc = 3, kModeNhwcRoll = 4;
 
 template <bool B8, bool FULL, int MODE>
 __global__ __launch_bounds__(kThreads, 2) void conv_fused_c128_kernel(const CgArgs a) {
@@ -164,8 +164,8 @@ __global__ __launch_bounds__(kThreads, 2) void conv_fused_c128_kernel(const CgAr
     };
     auto nothing = []() {};
     auto qp = [&](int e, float* mn, float* inv) { *mn = qp_s[2 * e]; *inv = qp_s[2 * e + 1]; };
-    if constexpr (MODE == kModeNhwc) {
-      dev::quantize_block_nhwc_to_lds<B8, kTiles, NB>(qg, p0, ring, cs_s, tid, phase_r, qp);
+    if constexpr (MODE >= kModeNhwc) {
+      dev::quantize_block_nhwc_to_lds<B8, kTiles, NB, MODE == kModeNhwcRoll>(qg, p0, ring, cs_s, tid, phase_r, qp);
     } else {
       dev::quantize_half_block_to_lds<B8, FULL, MODE, 3>(qg, p0, 0, ring, cs_s, lane, wave, phase_r, qp);
       dev::quantize_half_block_to_lds<B8, FULL, MODE, 3>(qg, p0, 64, ring + kBlockPlanes, cs_s, lane,
@@ -308,7 +308,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_fused_c128_kernel(const CgAr
             for (int ab = 0; ab < M * M; ab++)
               o[r][ab >> 1][ab & 1] = (out[mt][t][ab][r] + f4[ab]) + gp[ab];
           }
-          if constexpr (MODE == kModeNhwc) {
+          if constexpr (MODE >= kModeNhwc) {
             // the lane's four filters are consecutive: one store per output pixel
 #pragma unroll
             for (int aa = 0; aa < M; aa++)
@@ -393,6 +393,9 @@ hipError_t launch_conv_fused_c128(const Geo& g, const float* x, const int8_t* uq
   const bool b8 = g.bits == 8, full = g.C == 128;
   if (is_nhwc(g)) {
     if ((reinterpret_cast<uintptr_t>(x) & 15) != 0) return hipErrorInvalidValue;
+    if (g.tw % 4 == 0)  // (quant_phase_nhwc.h; other widths would cross rows inside four tiles)
+      return b8 ? launch_variant<true, false, kModeNhwcRoll>(a, grid, s)
+                : launch_variant<false, false, kModeNhwcRoll>(a, grid, s);
     return b8 ? launch_variant<true, false, kModeNhwc>(a, grid, s)
               : launch_variant<false, false, kModeNhwc>(a, grid, s);
   }

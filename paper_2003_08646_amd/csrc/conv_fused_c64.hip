@@ -86,8 +86,8 @@ __device__ __forceinline__ void store_patches(float* y, unsigned y_bytes, const 
 }
 
 // B8: 8-bit codes.  FULL: all 64 channels of the block exist.  MODE: patch load mode
-// (patch_load_mode), or kModeNhwc: X is [N][H][W][C] and Y is [N][Ho][Wo][K] (C a multiple of 4).
-constexpr int kModeNhwc = 3;
+// (patch_load_mode), or kModeNhwc, kModeNhwcRoll: X is [N][H][W][C] and Y is [N][Ho][Wo][K] (C a multiple of 4).
+constexpr int kModeNhwc = 3, kModeNhwcRoll = 4;
 template <bool B8, bool FULL, int MODE>
 __global__ __launch_bounds__(kThreads, 2) void conv_fused_c64_kernel(const CfArgs a) {
   constexpr int M = 2, A = 4, E = 16;
@@ -226,8 +226,8 @@ __global__ __launch_bounds__(kThreads, 2) void conv_fused_c64_kernel(const CfArg
       rk_store([&](int e) { return rs_s[e * 64 + lane]; });
     };
     auto qp = [&](int e, float* mn, float* inv) { *mn = qp_s[2 * e]; *inv = qp_s[2 * e + 1]; };
-    if constexpr (MODE == kModeNhwc)
-      dev::quantize_block_nhwc_to_lds<B8, 64, 1>(qg, p0, ring, cs_s, tid, phase_r, qp);
+    if constexpr (MODE >= kModeNhwc)
+      dev::quantize_block_nhwc_to_lds<B8, 64, 1, MODE == kModeNhwcRoll>(qg, p0, ring, cs_s, tid, phase_r, qp);
     else
       dev::quantize_block_to_lds<B8, FULL, MODE>(qg, p0, 0, ring, cs_s, lane, wave, phase_r, qp);
   }
@@ -368,7 +368,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_fused_c64_kernel(const CfArg
 #pragma unroll
           for (int b = 0; b < M; b++) o[r][aa][b] = (out[aa][b][r] + f4[aa * M + b]) + gp[aa][b];
       }
-      if constexpr (MODE == kModeNhwc) {
+      if constexpr (MODE >= kModeNhwc) {
         // the lane's filters come in groups of four consecutive ones: one store per group and pixel
         const bool k4 = (K & 3) == 0;
 #pragma unroll
@@ -450,6 +450,9 @@ hipError_t launch_conv_fused_c64(const Geo& g, const float* x, const int8_t* uq,
   const bool b8 = g.bits == 8, full = g.C == 64;
   if (is_nhwc(g)) {
     if ((reinterpret_cast<uintptr_t>(x) & 15) != 0) return hipErrorInvalidValue;
+    if (g.tw % 4 == 0)  // (quant_phase_nhwc.h; other widths would cross rows inside four tiles)
+      return b8 ? launch_variant<true, false, kModeNhwcRoll>(a, grid, s)
+                : launch_variant<false, false, kModeNhwcRoll>(a, grid, s);
     return b8 ? launch_variant<true, false, kModeNhwc>(a, grid, s)
               : launch_variant<false, false, kModeNhwc>(a, grid, s);
   }

@@ -537,3 +537,25 @@ def test_quantize_pass_with_all_channel_blocks(shape, static):
                                static_v_range=_range_of_another_batch(L) if static else None)
         P = conv.sz.P
         assert (_kernels(conv, _zeros(conv, False))[2] == "input_quant_m2_whole_kernel") == (1520 < P <= 4096)
+
+
+# N, C, K, H, W, pad, bits: NHWC, tile rows of a multiple of four tiles (four tiles of a row per thread group): the
+# narrowest row, padding of 0 to 2, ragged heights, a last workgroup of four tiles, whole and partial blocks
+_ROLL = [
+    (330, 20, 17, 13, 8, 1, 8), (421, 64, 32, 9, 7, 1, 5), (141, 44, 20, 11, 26, 0, 8), (150, 64, 48, 13, 14, 2, 8),
+    (330, 68, 17, 13, 8, 1, 8), (421, 128, 32, 9, 7, 1, 5), (141, 100, 20, 11, 26, 0, 8), (150, 128, 48, 13, 14, 2, 8),
+    (91, 128, 130, 16, 24, 1, 8), (70, 64, 65, 16, 32, 1, 8),
+]
+
+
+@pytest.mark.parametrize("shape", _ROLL, ids=lambda s: "n%d_c%d_k%d_%dx%d_p%d_b%d" % s)
+@pytest.mark.parametrize("static", [False, True], ids=["dynamic", "static"])
+def test_nhwc_four_tiles_of_a_row(shape, static):
+    from paper_2003_08646_amd import binding as B
+    N, C, K, H, W, pad, bits = shape
+    L = Wk.Layer("roll", N, C, K, H, W, pad=pad, m=2, bits=bits, seed=860 + C)
+    conv, _ = _check_layer(L, flags=B.LANCE_LAYOUT_NHWC | (B.LANCE_INPUT_RANGE_STATIC if static else 0), staged=False,
+                           static_v_range=_range_of_another_batch(L) if static else None)
+    assert -(-(W + 2 * pad - 2) // 2) % 4 == 0
+    names = _kernels(conv, _zeros(conv, True))
+    assert names[3] == ("conv_fused_c64_kernel" if C <= 64 else "conv_fused_c128_kernel"), names
