@@ -249,75 +249,86 @@ __global__ __launch_bounds__(kThreads, 2) void input_nhwc_range_kernel(const NhA
   write_range_record<E>(mn, mx, red, a.partial, tid);
 }
 
-// Range pass of F(2x2,3x3) layers whose channels come four at a time (16-byte loads): the pass
-// above issues 16 loads per tile of which a quarter of the bytes are new, and measured it is
-// bound by the rate at which the vector memory unit takes load instructions, not by bytes or
-// arithmetic.  Here a lane group (16 lanes, four channels each) walks down a strip of R tile
-// rows of one tile column: the two pixel rows a tile shares with the one below stay in
-// registers, so a tile costs two new rows (8 loads), requested before the current tile is
-// transformed.  Work unit = (image, strip, tile column, channel block), tile columns and blocks
-// of a wave next to each other.
-template <int UNUSED = 0>
+// Range pass of F(2x2,3x3) layers whose channels come four at a time (16-byte loads) and whose tile rows
+// hold at least two tiles.  The pass above issues 16 loads per tile, of which a quarter of the bytes
+// are new.  Here a lane group (16 lanes, four channels each) walks down a strip of R tile rows of two
+// neighbouring tile columns: the two pixel rows a tile shares with the one below stay in registers,
+// and the two tiles share two of six pixel columns, so two tiles cost two new rows of six pixels (6 loads
+// per tile and two more rows per strip), requested before the current tiles are transformed; the column
+// pass is shared too.  With an odd number of tile columns the last pair starts one column earlier (minima
+// and maxima do not notice).  Work unit = (image, strip, pair of tile columns, channel block), pairs and
+// blocks of a wave next to each other, each die taking neighbouring units.   Against one
+// tile column and strips of four rows, X in the last-level cache / from memory: N64 C128 56x56 29.3 / 33.2 ->
+// 24.3 / 27.6 us, N16 C64 224x224 51.7 / 62.5 -> 42.2 / 59.4, N128 C64 32x32 12.4 / 17.1 -> 10.9 / 14.3.
 __global__ __launch_bounds__(kThreads, 2) void input_nhwc_range_roll_kernel(const NhArgs a) {
-  constexpr int M = 2, A = 4, E = 16;
+  constexpr int M = 2, A = 4, E = 16, kCols = A + M;
   __shared__ float red[kThreads / 64][E][2];
   const int tid = threadIdx.x, cl = tid & 15;
   float mn[E], mx[E];
 #pragma unroll
   for (int e = 0; e < E; e++) { mn[e] = INFINITY; mx[e] = -INFINITY; }
   const unsigned px = (unsigned)a.C * 4u;
-  for (int u = blockIdx.x * kGroupsPerWg + (tid >> 4); u < a.units; u += gridDim.x * kGroupsPerWg) {
+  const int npr = (a.tw + 1) / 2;
+  for (int u = dev::xcd_contiguous(blockIdx.x, gridDim.x) * kGroupsPerWg + (tid >> 4); u < a.units;
+       u += gridDim.x * kGroupsPerWg) {
     int t = u / a.NB;
     const int cb = u - t * a.NB;
-    const int tx = t % a.tw; t /= a.tw;
+    const int tx = min(2 * (t % npr), a.tw - 2); t /= npr;
     const int st = t % a.strips, n = t / a.strips;
     const int c0 = cb * a.CB + 4 * cl;
     const bool real = cl < a.Q && c0 < a.C;  // C is a multiple of 4: all four channels or none
     const int cc = min(c0, a.C - 4);
     const int ty0 = st * a.R, ty1 = min(ty0 + a.R, a.th);
-    unsigned coloff[A];
-    bool cok[A];
+    unsigned coloff[kCols];
+    bool cok[kCols];
 #pragma unroll
-    for (int s = 0; s < A; s++) {
+    for (int s = 0; s < kCols; s++) {
       const int gx = tx * M - a.pad + s;
       cok[s] = gx >= 0 && gx < a.W;
       coloff[s] = (unsigned)gx * px + (unsigned)cc * 4u;
     }
-    auto load_row = [&](int gy, f4 (&row)[A]) {
+    auto load_row = [&](int gy, f4 (&row)[kCols]) {
       const unsigned rowoff = ((unsigned)n * (unsigned)a.H + (unsigned)gy) * (unsigned)a.W * px;
-      dev::load_row_nhwc<A>(a.x, a.x_bytes, rowoff, gy >= 0 && gy < a.H, coloff, cok, row);
+      dev::load_row_nhwc<kCols>(a.x, a.x_bytes, rowoff, gy >= 0 && gy < a.H, coloff, cok, row);
     };
-    f4 w[A][A], nxt[2][A];
+    f4 w[A][kCols], nxt[2][kCols];
 #pragma unroll
-    for (int s = 0; s < A; s++) nxt[0][s] = nxt[1][s] = f4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int s = 0; s < kCols; s++) nxt[0][s] = nxt[1][s] = f4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int r = 0; r < A; r++) load_row(ty0 * M - a.pad + r, w[r]);
     for (int ty = ty0; ty < ty1; ty++) {
-      if (ty + 1 < ty1) {  // the next tile's two new rows
+      if (ty + 1 < ty1) {  // the next tiles' two new rows
         load_row((ty + 1) * M - a.pad + 2, nxt[0]);
         load_row((ty + 1) * M - a.pad + 3, nxt[1]);
       }
+      if (real) {
 #pragma unroll
-      for (int hf = 0; hf < 2; hf++) {  // two channels at a time: three-operand minima and maxima
-        float d[2][A][A];
+        for (int q = 0; q < 4; q++) {  // one channel of both tiles: three-operand minima and maxima
+          float t6[A][kCols];
 #pragma unroll
-        for (int i = 0; i < 2; i++) {
+          for (int s = 0; s < kCols; s++) {
+            const float d[A] = {w[0][s][q], w[1][s][q], w[2][s][q], w[3][s][q]};
+            float o[A];
+            dev::Wino<M>::in1d(d, o);
 #pragma unroll
-          for (int r = 0; r < A; r++)
+            for (int i = 0; i < A; i++) t6[i][s] = o[i];
+          }
 #pragma unroll
-            for (int s = 0; s < A; s++) d[i][r][s] = w[r][s][2 * hf + i];
-          dev::input_tile_transform<M>(d[i]);
-        }
-        if (real) {
+          for (int i = 0; i < A; i++) {
+            const float ra[A] = {t6[i][0], t6[i][1], t6[i][2], t6[i][3]}, rb[A] = {t6[i][2], t6[i][3], t6[i][4], t6[i][5]};
+            float va[A], vb[A];
+            dev::Wino<M>::in1d(ra, va);
+            dev::Wino<M>::in1d(rb, vb);
 #pragma unroll
-          for (int e = 0; e < E; e++) {
-            mn[e] = fminf(mn[e], fminf(d[0][e / A][e % A], d[1][e / A][e % A]));
-            mx[e] = fmaxf(mx[e], fmaxf(d[0][e / A][e % A], d[1][e / A][e % A]));
+            for (int j = 0; j < A; j++) {
+              mn[A * i + j] = fminf(mn[A * i + j], fminf(va[j], vb[j]));
+              mx[A * i + j] = fmaxf(mx[A * i + j], fmaxf(va[j], vb[j]));
+            }
           }
         }
       }
 #pragma unroll
-      for (int s = 0; s < A; s++) {
+      for (int s = 0; s < kCols; s++) {
         w[0][s] = w[2][s]; w[1][s] = w[3][s];
         w[2][s] = nxt[0][s]; w[3][s] = nxt[1][s];
       }
@@ -541,18 +552,21 @@ hipError_t launch_input_nhwc_range(const Geo& g, const float* x, float* partial,
     return hipGetLastError();
   }
   const bool vec = vec_loads(g, x);
-  // (small layers keep the tile-per-group pass: with fewer than 4096 strips the chip is not full)
-  const bool roll = g.m == 2 && vec &&
+  // (small layers keep the tile-per-group pass: with fewer than 4096 strips of four tiles the chip is not full)
+  const bool roll = g.m == 2 && vec && g.tw >= 2 &&
                     (long long)g.N * g.tw * g.NB * ((g.th + 3) / 4) >= 4096;
   if (roll) {
-    // Strips of four tile rows: 10 loads per tile instead of 16.  Longer strips save little more
-    // and were slower (measured: a lane has one tile's loads in flight, so a strip is a chain of
-    // memory latencies and there must be many strips to overlap them).
-    const long long cols = (long long)g.N * g.tw * g.NB;
-    int R = 4;
-    if (R > g.th) R = g.th;
-    a.R = R;
-    a.strips = (g.th + R - 1) / R;
+    // Tile rows per strip: the smallest (rounds of 512 resident workgroups) x (pixel rows of a strip, and
+    // about four more that its first loads take).
+    const long long cols = (long long)g.N * ((g.tw + 1) / 2) * g.NB;
+    long long best = 0;
+    for (int R = 2; R <= 32; R++) {
+      const int strips = (g.th + R - 1) / R;
+      const long long wgs = (cols * strips + kGroupsPerWg - 1) / kGroupsPerWg;
+      const long long cost = (wgs + 511) / 512 * (2 * (R < g.th ? R : g.th) + 6);
+      if (best == 0 || cost < best) { best = cost; a.R = R; a.strips = strips; }
+      if (R >= g.th) break;
+    }
     const long long units = cols * a.strips;
     if (units >= (1LL << 30)) return hipErrorInvalidValue;
     a.units = (int)units;
@@ -590,7 +604,7 @@ hipError_t launch_input_nhwc_range(const Geo& g, const float* x, float* partial,
     return hipGetLastError();
   };
   note_kernel(roll ? "input_nhwc_range_roll_kernel" : "input_nhwc_range_kernel");
-  if (roll) return run(input_nhwc_range_roll_kernel<0>);
+  if (roll) return run(input_nhwc_range_roll_kernel);
   if (g.m == 2) return vec ? run(input_nhwc_range_kernel<2, true>) : run(input_nhwc_range_kernel<2, false>);
   return vec ? run(input_nhwc_range_kernel<4, true>) : run(input_nhwc_range_kernel<4, false>);
 }

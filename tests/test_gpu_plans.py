@@ -603,3 +603,16 @@ def test_nhwc_four_tiles_of_a_row(shape, static):
     assert -(-(W + 2 * pad - 2) // 2) % 4 == 0
     names = _kernels(conv, _zeros(conv, True))
     assert names[3] == ("conv_fused_c64_kernel" if C <= 64 else "conv_fused_c128_kernel"), names
+
+
+# N, C, H, W, pad: NHWC range pass on pairs of tile columns (at least 4096 strips): two and three columns, an odd
+# number of them, strips of the whole height and of a part of it
+@pytest.mark.parametrize("shape", [(2100, 20, 3, 4, 1), (1400, 68, 9, 5, 1), (300, 64, 30, 9, 0), (16, 130, 70, 75, 2),
+                                   (400, 256, 7, 13, 1)], ids=lambda s: "n%d_c%d_%dx%d_p%d" % s)
+def test_nhwc_ranges_from_pairs_of_tile_columns(shape):
+    from paper_2003_08646_amd import binding as B
+    N, C, H, W, pad = shape
+    C = C - C % 4
+    conv, _ = _check_layer(Wk.Layer("nhwc_range", N, C, 24, H, W, pad=pad, m=2, seed=890 + C), flags=B.LANCE_LAYOUT_NHWC,
+                           staged=False)
+    assert _kernels(conv, _zeros(conv, True))[0] == "input_nhwc_range_roll_kernel"
