@@ -1,5 +1,5 @@
 // Stages 2 (second pass) + 3 + 4 in one kernel for F(2x2,3x3) layers with one or two 64-channel
-// blocks whose tiles pair up (NCHW, pad 1, width a multiple of 4): v^ = Q(B^T d B) (Algorithm 1;
+// blocks whose tiles pair up (NCHW, pad 1, width a multiple of 4; NHWC, any padding and width): v^ = Q(B^T d B) (Algorithm 1;
 // Eq. 7) is formed in registers and written to LDS only, the int8 products of Sec. 3.3 run on
 // the matrix cores from there, and the de-quantization (Eq. 8) and output transform (Eq. 9) are
 // applied to the register accumulators.  The codes of V never touch device memory.
@@ -28,6 +28,15 @@
 // Against one tile per lane (conv_fused_c64.hip, conv_fused_c128.hip), whole call, dynamic ranges: N64
 // 128 -> 128 56x56 103.9 -> 89.3 us, N128 64 -> 64 32x32 29.9 -> 27.5, N16 64 -> 64 224x224 (caller's
 // ranges) 137 -> 115, N16 128 -> 128 112x112 100 -> 81.
+//
+// NHWC.  A thread takes one pair and four channels; a pair's window is six columns of four 16-byte loads, four
+// columns in flight before the constants are formed.  That leaves no registers for the filter row sums there,
+// so the filter-side terms are formed behind phase T (before it, with two columns in flight: 64 bytes spilled, N64
+// 128 -> 128 56x56 with caller's ranges 81 us instead of 67).  A pixel's 16 filters of a wave are one 64-byte run of Y.
+// Against four tiles per thread in workgroups of four waves, two tile columns of the window kept from tile to
+// tile, whole call with the faster range pass, dynamic ranges: N64 128 -> 128 56x56 106 -> 93 us, N16 64 -> 64
+// 224x224 190 -> 160, N128 64 -> 64 32x32 36.9 -> 29.9, N30 128 -> 512 33x35 68.1 -> 58.2; the kernel alone 81.6 -> 72.9,
+// 144 -> 125, 29.5 -> 24.7.  Bound by the same things as above.
 #include "lance_device.h"
 #include "lance_internal.h"
 #include "quant_pairs.h"
@@ -180,15 +189,35 @@ struct Constants {
 // across it, which __syncthreads() would wait for.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-// NB: channel blocks.  B8: 8-bit codes.  FULL: all channels of the blocks exist.
-template <int NB, bool B8, bool FULL>
+// LDS of a workgroup but the filter-side terms; two workgroups share a compute unit's 160 KB.
+template <int NB>
+constexpr int fixed_lds() {
+  return kCodeBytes + 16 * (64 / NB) * (int)sizeof(int) + (16 + 16 + 32) * (int)sizeof(float) +
+         2 * 16 * (int)sizeof(double);
+}
+constexpr int kMaxLds = 80 * 1024;
+
+// Pixels in flight: of the next channels (NCHW), or the six columns of the lane's window (NHWC).
+template <class Phase, int AHEAD, bool NHWC>
+struct PixelsOf {
+  typename Phase::Pixels buf[AHEAD + 1];
+};
+template <class Phase, int AHEAD>
+struct PixelsOf<Phase, AHEAD, true> {
+  v4f buf[Phase::kColumns][4];
+};
+
+// NB: channel blocks.  B8: 8-bit codes.  FULL: all channels of the blocks exist (NCHW).  STREAM (NHWC): Y is stored
+// past the caches; NCHW asks a.stream.
+template <int NB, bool B8, bool FULL, bool NHWC, bool STREAM = false>
 __device__ __forceinline__ void conv_body(const CpArgs& a) {
   constexpr int M = 2, A = 4, E = 16;
   constexpr int kPairs = 32 / NB, kTiles = 2 * kPairs, kPlane = kTiles * 64;
   constexpr int kFilters = 64 * NB;  // filters of a block
+  constexpr int kMostBlocks = (kMaxLds - fixed_lds<NB>()) / (kFilters * 16);  // 704 and 768 filters
   constexpr int kFragsAhead = 3;     // positions whose A fragments are in flight ahead of the products
   constexpr int kStepsAhead = 1;     // channels whose pixels are in flight ahead of the transform
-  using Phase = dev::PairPhase<B8, FULL, kPairs>;
+  using Phase = std::conditional_t<NHWC, dev::PairPhaseNhwc<B8, kPairs>, dev::PairPhase<B8, FULL, kPairs>>;
   extern __shared__ char smem[];
   char* ring = smem;                                            // [NB][E][kTiles rows][64 B]
   int* cs_s = reinterpret_cast<int*>(smem + kCodeBytes);         // [E][kTiles] column sums (signed codes)
@@ -201,34 +230,28 @@ __device__ __forceinline__ void conv_body(const CpArgs& a) {
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int K = a.K, nkb = (K + kFilters - 1) / kFilters;
+  const int K = a.K;
+  // the workgroup's blocks of filters: all, or (NHWC, more of them than LDS has room for the terms of) its share
+  const int kb0 = NHWC ? (int)blockIdx.y * kMostBlocks : 0;
+  const int nkb = NHWC ? min((K + kFilters - 1) / kFilters, kb0 + kMostBlocks) : (K + kFilters - 1) / kFilters;
+  const int kbase = kb0 * kFilters;
   const int blk = dev::xcd_contiguous(blockIdx.x, gridDim.x);
 
   // ============================ phase T ============================
   // wave & 3: 16-byte chunk of the code rows; wave >> 2: channel block, or half of the chunk
   const int chunk = wave & 3, upper = wave >> 2;
   Phase ph;
-  typename Phase::Pixels px[kStepsAhead + 1];
-  {
-    EarlyLoads early;
-    Constants::request(a, tid, early);
-    int32_t rowsum[E];  // of the filters of the first turn below
+  PixelsOf<Phase, kStepsAhead, NHWC> px;
+  auto request_rowsums = [&](int k0, int32_t (&rowsum)[E]) {
 #pragma unroll
-    for (int e = 0; e < E; e++) rowsum[e] = a.u_rowsum[(size_t)e * K + min(64 * upper + lane, K - 1)];
-    ph.setup(a.g, blk, (NB == 2 ? 64 * upper : 2 * upper) + 4 * chunk, lane);
-#pragma unroll
-    for (int k = 0; k < kStepsAhead; k++) ph.issue(a.g, k, px[k]);
-    // (the code rows are free until the first codes are written)
-    const Constants cst{sc_s, gc_s, qp_s, rmul_s, kconst_s, reinterpret_cast<float*>(ring)};
-    cst.form(a, tid, early);
-    // filter-side terms rk_s[4*filter + ab] = sum_e A^T[a][i] A^T[b][j] (su*ov*rowsum[e][k] + C*ou*ov):
-    // wave & 3 = ab, lane = filter
+    for (int e = 0; e < E; e++) rowsum[e] = a.u_rowsum[(size_t)e * K + min(k0 + lane, K - 1)];
+  };
+  // filter-side terms rk_s[4*filter + ab] = sum_e A^T[a][i] A^T[b][j] (su*ov*rowsum[e][k] + C*ou*ov):
+  // wave & 3 = ab, lane = filter; rowsum: of the first turn's filters
+  auto filter_terms = [&](int32_t (&rowsum)[E]) {
     const int aa = (wave >> 1) & 1, b = wave & 1;
-    for (int k0 = 64 * upper; k0 < nkb * kFilters; k0 += 128) {
-      if (k0 >= 128) {
-#pragma unroll
-        for (int e = 0; e < E; e++) rowsum[e] = a.u_rowsum[(size_t)e * K + min(k0 + lane, K - 1)];
-      }
+    for (int k0 = kbase + 64 * upper; k0 < nkb * kFilters; k0 += 128) {
+      if (k0 >= kbase + 128) request_rowsums(k0, rowsum);
       double acc = 0.0;
 #pragma unroll
       for (int j = 0; j < A; j++) {
@@ -239,8 +262,28 @@ __device__ __forceinline__ void conv_body(const CpArgs& a) {
                             __builtin_fma(rmul_s[4 * i + j], (double)rowsum[4 * i + j], kconst_s[4 * i + j]), s);
         acc = __builtin_fma((double)dev::at_coef(M, b, j), s, acc);
       }
-      rk_s[4 * (k0 + lane) + (wave & 3)] = (float)acc;
+      rk_s[4 * (k0 - kbase + lane) + (wave & 3)] = (float)acc;
     }
+  };
+  {
+    EarlyLoads early;
+    Constants::request(a, tid, early);
+    [[maybe_unused]] int32_t rowsum[E];
+    if constexpr (NHWC) {  // four pairs per wave
+      ph.setup(a.g, blk, 4 * (NB == 2 ? chunk : wave) + (lane >> 4), NB == 2 ? upper : 0, lane,
+               ring + (NB == 2 ? upper * (E * kPlane) : 0));
+#pragma unroll
+      for (int s = 0; s < Phase::kEarly; s++) ph.issue(a.g, s, px.buf[s]);
+    } else {
+      request_rowsums(64 * upper, rowsum);
+      ph.setup(a.g, blk, (NB == 2 ? 64 * upper : 2 * upper) + 4 * chunk, lane);
+#pragma unroll
+      for (int k = 0; k < kStepsAhead; k++) ph.issue(a.g, k, px.buf[k]);
+    }
+    // (the code rows are free until the first codes are written)
+    const Constants cst{sc_s, gc_s, qp_s, rmul_s, kconst_s, reinterpret_cast<float*>(ring)};
+    cst.form(a, tid, early);
+    if constexpr (!NHWC) filter_terms(rowsum);
   }
   const unsigned plane_px = (unsigned)a.g.H * (unsigned)a.g.W;
   {
@@ -250,15 +293,22 @@ __device__ __forceinline__ void conv_body(const CpArgs& a) {
       qmn[e] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(qp_s[2 * e])));
       qinv[e] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(qp_s[2 * e + 1])));
     }
-    const float L = (float)((1 << a.g.bits) - 1);
-    unsigned codes[2][E];
+    if constexpr (NHWC) {
+      int32_t rowsum[E];
+      ph.run(a.g, px.buf, qmn, qinv, [&]() { request_rowsums(kbase + 64 * upper, rowsum); });
+      filter_terms(rowsum);
+    } else {
+      const float L = (float)((1 << a.g.bits) - 1);
+      unsigned codes[2][E];
 #pragma unroll
-    for (int k = 0; k < Phase::kSteps; k++) {
-      if (k + kStepsAhead < Phase::kSteps) ph.issue(a.g, k + kStepsAhead, px[(k + kStepsAhead) % (kStepsAhead + 1)]);
-      ph.quantize(px[k % (kStepsAhead + 1)], qmn, qinv, L, k, codes);
+      for (int k = 0; k < Phase::kSteps; k++) {
+        if (k + kStepsAhead < Phase::kSteps)
+          ph.issue(a.g, k + kStepsAhead, px.buf[(k + kStepsAhead) % (kStepsAhead + 1)]);
+        ph.quantize(px.buf[k % (kStepsAhead + 1)], qmn, qinv, L, k, codes);
+      }
+      ph.store(a.g, chunk, (NB == 2 ? 0 : 2 * upper) + lane / kPairs, lane,
+               ring + (NB == 2 ? upper * (E * kPlane) : 0), codes);
     }
-    ph.store(a.g, chunk, (NB == 2 ? 0 : 2 * upper) + lane / kPairs, lane,
-             ring + (NB == 2 ? upper * (E * kPlane) : 0), codes);
   }
 
   // ============================ phase G ============================
@@ -285,7 +335,7 @@ __device__ __forceinline__ void conv_body(const CpArgs& a) {
   };
   v4i afrag[kFragsAhead + 1][NB];  // ring over positions (16 positions = four turns)
 #pragma unroll
-  for (int e = 0; e < kFragsAhead; e++) load_afrags(0, e, afrag[e]);
+  for (int e = 0; e < kFragsAhead; e++) load_afrags(kb0, e, afrag[e]);
   lds_barrier();  // the codes of all waves are in LDS
   // Column sums: one more matrix instruction per fragment, with an operand of ones; wave w takes the
   // positions 2w and 2w + 1 of all tiles.  (v_sad_u8 and LDS atomics, in phase T: 89.3 / 88.1 us on N64 128 ->
@@ -323,18 +373,27 @@ __device__ __forceinline__ void conv_body(const CpArgs& a) {
       }
     }
   }
-  unsigned y_off[2];  // byte offsets of the pair's two output rows in filter 0
+  // byte offsets of the pair's two output rows: of filter 0 (NCHW), or of their first pixels (NHWC)
+  unsigned y_off[2];
+  int cols = 4;  // pixels of a row that exist
   {
-    const int p = blk * kPairs + pair, pc = min(p, a.g.pairs - 1);
-    const int t2 = dev::fast_div(pc, a.g.npr_magic), q = pc - t2 * a.g.npr;
-    const int n = dev::fast_div(t2, a.g.th_magic), ty = t2 - n * a.g.th;
-    const unsigned base = ((unsigned)n * (unsigned)K * plane_px + (unsigned)(2 * ty) * (unsigned)a.g.W +
-                           4u * (unsigned)q) * 4u;
+    const int p = blk * kPairs + pair;
+    int q, ty, n;
+    dev::locate_pair<NHWC>(a.g, min(p, a.g.pairs - 1), &q, &ty, &n);
+    unsigned base, row;
+    if constexpr (NHWC) {
+      cols = a.g.Wo - 4 * q;
+      row = (unsigned)a.g.Wo * (unsigned)K * 4u;
+      base = ((unsigned)n * (unsigned)a.g.Ho + (unsigned)(2 * ty)) * row + (unsigned)(4 * q) * (unsigned)K * 4u;
+    } else {
+      row = (unsigned)a.g.W * 4u;
+      base = ((unsigned)n * (unsigned)K * plane_px + (unsigned)(2 * ty) * (unsigned)a.g.W + 4u * (unsigned)q) * 4u;
+    }
     y_off[0] = p < a.g.pairs ? base : kOob;
-    y_off[1] = p < a.g.pairs && 2 * ty + 1 < a.g.H ? base + (unsigned)a.g.W * 4u : kOob;
+    y_off[1] = p < a.g.pairs && 2 * ty + 1 < (NHWC ? a.g.Ho : a.g.H) ? base + row : kOob;
   }
 
-  for (int kb = 0; kb < nkb; kb++) {
+  for (int kb = kb0; kb < nkb; kb++) {
     v4f out[2][M * M];  // [tile of the pair][ab][accumulator register]
 #pragma unroll
     for (int s = 0; s < 2; s++)
@@ -387,6 +446,24 @@ __device__ __forceinline__ void conv_body(const CpArgs& a) {
     // (pairs past the last, filters past K, the second row of an odd height) get an offset
     // beyond the buffer instead of a branch. ----
     const int kfirst = kb * kFilters + kwave + 4 * kq;  // first of the lane's four filters
+    if constexpr (NHWC) {  // four consecutive filters of a pixel: one store
+      v4f f4[4];
+#pragma unroll
+      for (int r = 0; r < 4; r++) f4[r] = *reinterpret_cast<const v4f*>(rk_s + 4 * (kfirst - kbase + r));
+#pragma unroll
+      for (int ab = 0; ab < M * M; ab++)
+#pragma unroll
+        for (int s = 0; s < 2; s++) {
+          const int aa = ab >> 1, x = 2 * s + (ab & 1);
+          float o[4];
+#pragma unroll
+          for (int r = 0; r < 4; r++) o[r] = (out[s][ab][r] + f4[r][ab]) + gp[s][ab];
+          dev::store_nhwc_k4<STREAM>(a.y, a.y_bytes, y_off[aa] + (unsigned)x * (unsigned)K * 4u, (unsigned)kfirst * 4u,
+                                     y_off[aa] != kOob && x < cols, K - kfirst, STREAM || (K & 3) == 0, o[0], o[1],
+                                     o[2], o[3]);
+        }
+      continue;
+    }
     auto tail = [&](auto stream) {
 #pragma unroll
       for (int r = 0; r < 4; r++) {
@@ -412,40 +489,57 @@ __device__ __forceinline__ void conv_body(const CpArgs& a) {
 
 template <bool B8, bool FULL>
 __global__ __launch_bounds__(kThreads, 4) void conv_fused_pairs_c64_kernel(const CpArgs a) {
-  conv_body<1, B8, FULL>(a);
+  conv_body<1, B8, FULL, false>(a);
 }
 template <bool B8, bool FULL>
 __global__ __launch_bounds__(kThreads, 4) void conv_fused_pairs_c128_kernel(const CpArgs a) {
-  conv_body<2, B8, FULL>(a);
+  conv_body<2, B8, FULL, false>(a);
 }
+// The NHWC kernels of the plans of one and of two channel blocks.  STREAM is a parameter of the kernel: with both
+// kinds of stores in one the cached ones took up to 2 % longer.
+namespace nhwc {
+template <bool B8, bool STREAM>
+__global__ __launch_bounds__(kThreads, 4) void conv_fused_c64_kernel(const CpArgs a) {
+  conv_body<1, B8, false, true, STREAM>(a);
+}
+template <bool B8, bool STREAM>
+__global__ __launch_bounds__(kThreads, 4) void conv_fused_c128_kernel(const CpArgs a) {
+  conv_body<2, B8, false, true, STREAM>(a);
+}
+}  // namespace nhwc
 
-// LDS of a workgroup but the filter-side terms, and with them.
-template <int NB>
-constexpr int fixed_lds() {
-  return kCodeBytes + 16 * (64 / NB) * (int)sizeof(int) + (16 + 16 + 32) * (int)sizeof(float) +
-         2 * 16 * (int)sizeof(double);
-}
+// LDS of a workgroup with the terms of K filters.
 template <int NB>
 int lds_bytes(int K) {
   return fixed_lds<NB>() + (K + 64 * NB - 1) / (64 * NB) * (64 * NB) * 16;
 }
-constexpr int kMaxLds = 80 * 1024;  // two workgroups share a compute unit's 160 KB
 
-// Bytes from the first image of a block to the end of the last one that its pairs can touch.
+// Pairs in a tile row.
+int pairs_per_row(const Geo& g) { return is_nhwc(g) ? (g.tw + 1) / 2 : g.W / 4; }
+
+// Bytes from the first image of a block to the end of the last one that its pairs can touch; NHWC: of X.
 long long reach_bytes(const Geo& g) {
+  if (is_nhwc(g)) return (long long)g.N * g.C * g.H * g.W * 4;
   const int pairs = 32 / g.NB;
-  const long long per_image = (long long)g.th * (g.W / 4);
+  const long long per_image = (long long)g.th * pairs_per_row(g);
   return ((pairs - 1) / per_image + 2) * g.C * g.H * g.W * 4LL;
+}
+
+template <int NB>
+hipError_t launch_kernel(void (*kern)(CpArgs), const CpArgs& a, const char* name, hipStream_t s) {
+  hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), kMaxLds);
+  if (e != hipSuccess) return e;
+  note_kernel(name);
+  constexpr int kMost = (kMaxLds - fixed_lds<NB>()) / (64 * NB * 16) * (64 * NB);  // filters of a workgroup
+  const dim3 grid((a.g.pairs + 32 / NB - 1) / (32 / NB), (a.K + kMost - 1) / kMost);
+  kern<<<grid, kThreads, lds_bytes<NB>(a.K < kMost ? a.K : kMost), s>>>(a);
+  return hipGetLastError();
 }
 
 template <int NB, bool B8, bool FULL>
 hipError_t launch_variant(const CpArgs& a, hipStream_t s) {
-  auto kern = NB == 1 ? conv_fused_pairs_c64_kernel<B8, FULL> : conv_fused_pairs_c128_kernel<B8, FULL>;
-  hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), kMaxLds);
-  if (e != hipSuccess) return e;
-  note_kernel(NB == 1 ? "conv_fused_pairs_c64_kernel" : "conv_fused_pairs_c128_kernel");
-  kern<<<(a.g.pairs + 32 / NB - 1) / (32 / NB), kThreads, lds_bytes<NB>(a.K), s>>>(a);
-  return hipGetLastError();
+  return NB == 1 ? launch_kernel<1>(conv_fused_pairs_c64_kernel<B8, FULL>, a, "conv_fused_pairs_c64_kernel", s)
+                 : launch_kernel<2>(conv_fused_pairs_c128_kernel<B8, FULL>, a, "conv_fused_pairs_c128_kernel", s);
 }
 
 template <int NB>
@@ -455,6 +549,27 @@ hipError_t launch_blocks(const Geo& g, const CpArgs& a, hipStream_t s) {
   return full ? launch_variant<NB, false, true>(a, s) : launch_variant<NB, false, false>(a, s);
 }
 
+template <bool B8, bool STREAM>
+hipError_t launch_nhwc(const Geo& g, const CpArgs& a, hipStream_t s) {
+  return g.NB == 1 ? launch_kernel<1>(nhwc::conv_fused_c64_kernel<B8, STREAM>, a, "conv_fused_c64_kernel", s)
+                   : launch_kernel<2>(nhwc::conv_fused_c128_kernel<B8, STREAM>, a, "conv_fused_c128_kernel", s);
+}
+
+bool divisions_exact(long long pairs, long long npr, long long th) {
+  return pairs * npr < 1LL << 32 && pairs * th < 1LL << 32;
+}
+
+CpArgs make_args(const Geo& g, const float* x, const int8_t* uq, const float* u_range, const int32_t* u_rowsum,
+                 const float* partial, int count, float* v_range, float* y, bool stream) {
+  const int npr = pairs_per_row(g), pairs = g.N * g.th * npr;
+  return CpArgs{{x, g.C, g.H, g.W, g.Ho, g.Wo, g.pad, g.th, npr, pairs, g.bits, div_magic(g.th), div_magic(npr),
+                 divisions_exact(pairs, npr, g.th) ? 1 : 0, (unsigned)reach_bytes(g)},
+                uq, u_range, u_rowsum, partial, v_range, y, count,
+                (g.flags & LANCE_RANGE_PER_TENSOR) ? 1 : 0, (g.flags & LANCE_INPUT_RANGE_STATIC) ? 1 : 0,
+                g.bits_w, g.K, (unsigned)((size_t)g.E * g.NB * g.K * 64),
+                (unsigned)((size_t)g.N * g.K * g.Ho * g.Wo * 4), stream ? 1 : 0};
+}
+
 }  // namespace
 
 bool conv_fused_pairs_applicable(const Geo& g) {
@@ -462,24 +577,31 @@ bool conv_fused_pairs_applicable(const Geo& g) {
   if (g.pad != 1 || g.W % 4 != 0) return false;
   if ((long long)g.N * g.K * g.Ho * g.Wo * 4 >= 0xFFFFFFF0LL) return false;  // 32-bit store offsets
   if ((g.NB == 1 ? lds_bytes<1>(g.K) : lds_bytes<2>(g.K)) > kMaxLds) return false;  // 704 and 768 filters
-  const long long pairs = (long long)g.N * g.th * (g.W / 4);
-  if (pairs * (g.W / 4) >= 1LL << 32 || pairs * g.th >= 1LL << 32) return false;  // fast_div
-  return reach_bytes(g) < (1LL << 31);
+  const long long npr = pairs_per_row(g);
+  return divisions_exact(g.N * g.th * npr, npr, g.th) && reach_bytes(g) < (1LL << 31);
 }
 
 hipError_t launch_conv_fused_pairs(const Geo& g, const float* x, const int8_t* uq, const float* u_range,
                                    const int32_t* u_rowsum, const float* partial, int count,
                                    float* v_range, float* y, hipStream_t s) {
   if (!conv_fused_pairs_applicable(g)) return hipErrorInvalidValue;
-  const int npr = g.W / 4, pairs = g.N * g.th * npr;
-  const long long y_bytes = (long long)g.N * g.K * g.Ho * g.Wo * 4;
-  const CpArgs a{{x, g.C, g.H, g.W, g.th, npr, pairs, g.bits, div_magic(g.th), div_magic(npr),
-                  (unsigned)reach_bytes(g)},
-                 uq, u_range, u_rowsum, partial, v_range, y, count,
-                 (g.flags & LANCE_RANGE_PER_TENSOR) ? 1 : 0, (g.flags & LANCE_INPUT_RANGE_STATIC) ? 1 : 0,
-                 g.bits_w, g.K,
-                 (unsigned)((size_t)g.E * g.NB * g.K * 64), (unsigned)y_bytes, stores_past_caches(g, true) ? 1 : 0};
+  const CpArgs a = make_args(g, x, uq, u_range, u_rowsum, partial, count, v_range, y, stores_past_caches(g, true));
   return g.NB == 1 ? launch_blocks<1>(g, a, s) : launch_blocks<2>(g, a, s);
+}
+
+// NHWC: 16-byte pixel loads of four channels at 32-bit offsets, 32-bit store offsets; X 16-byte aligned.
+bool conv_fused_pairs_nhwc_applicable(const Geo& g) {
+  return g.m == 2 && g.CB == 64 && g.NB <= 2 && is_nhwc(g) && !is_packed(g) && g.C % 4 == 0 &&
+         (long long)g.N * g.K * g.Ho * g.Wo * 4 < 0xFFFFFFF0LL && (long long)g.N * g.C * g.H * g.W * 4 < 0xFFFFFFF0LL;
+}
+
+hipError_t launch_conv_fused_pairs_nhwc(const Geo& g, const float* x, const int8_t* uq, const float* u_range,
+                                        const int32_t* u_rowsum, const float* partial, int count,
+                                        float* v_range, float* y, bool stream, hipStream_t s) {
+  if (!conv_fused_pairs_nhwc_applicable(g) || (reinterpret_cast<uintptr_t>(x) & 15) != 0) return hipErrorInvalidValue;
+  const CpArgs a = make_args(g, x, uq, u_range, u_rowsum, partial, count, v_range, y, stream);
+  if (g.bits == 8) return stream ? launch_nhwc<true, true>(g, a, s) : launch_nhwc<true, false>(g, a, s);
+  return stream ? launch_nhwc<false, true>(g, a, s) : launch_nhwc<false, false>(g, a, s);
 }
 
 }  // namespace lance

@@ -60,12 +60,17 @@ static bool conv_fused_pos_applicable(const Geo& g) {
 //    channel block and at most 16 filters, of which that kernel computes 64: N20 56->8 109x8 8.6 / 9.7, N12
 //    17->12 112x20 9.0 / 9.8, N15 64->5 169x8 8.6 / 9.4 (dynamic ranges 15.0 / 15.7 at most); 17 to 21 filters
 //    9.8 / 9.8, two channel blocks from 5 filters on 12.5 / 10.5.
+//    On NHWC tensors with any number of filters (N64 128->128 14^2 dynamic 22.1 / 17.7, N500 64->64 8^2 19.0 / 16.5,
+//    N3 108->68 58x78 15.3 / 11.7, N49 52->64 23^2 11.1 / 10.4), but with one channel block only where four filters
+//    are one store there (N3 44->62 73^2 16.0 / 20.8, N20 56->61 37x35 11.4 / 14.3).
 //  * the rest: one workgroup per compute unit (N1 512->512 28^2 23 -> 16.7, N1 128->256 56^2 F(4x4)
 //    44 -> 15, N4 256->512 28^2 24 against 28, N23 38->52 108^2 F(4x4) 51 against 95).
-bool conv_fused_pos_preferred(const Geo& g) {
+bool conv_fused_pos_preferred(const Geo& g, bool x_aligned) {
   if (!conv_fused_pos_applicable(g)) return false;
   if (g.C <= 16) return g.m == 4 || g.P <= 12800;
-  const bool pairs = conv_fused_pairs_applicable(g) && g.K <= 64 * g.NB && (g.NB == 2 || g.K > 16);
+  const bool pairs = is_nhwc(g) ? x_aligned && conv_fused_pairs_nhwc_applicable(g) &&
+                                      (g.NB == 2 || (g.K > 16 && g.K % 4 == 0))
+                                : conv_fused_pairs_applicable(g) && g.K <= 64 * g.NB && (g.NB == 2 || g.K > 16);
   const bool two = g.m == 2 && g.NB <= 2 && !pairs;
   return pos::shape_of(g).groups <= (two ? 512 : 256);
 }

@@ -245,7 +245,8 @@ enum ConvPlan { kPlanGeneral = 0, kPlanTwoKernels = 1, kPlanThreeKernels = 2 };
 // gemm_fused_pos.hip).  The others:
 // Layers with one 64-channel block (m = 2) run as two kernels: the range pass, then one kernel
 // that reduces the ranges, quantizes, multiplies and transforms back (V's codes stay on chip).
-// Where the tiles pair up (pad 1, width a multiple of 4, NCHW) that kernel is conv_fused_pairs.hip's.
+// Where the tiles pair up (pad 1, width a multiple of 4, NCHW; every NHWC layer) that kernel is
+// conv_fused_pairs.hip's.
 // Layers with two blocks (m = 2) take the same two-kernel form (128 KB of codes in LDS) unless
 // the descriptor asks for the general plan's wide tiles.  Layers of at most 16 channels (m = 2)
 // and F(4x4,3x3) layers of at most 128 channels: range pass, reduction kernel, one kernel for the
@@ -262,12 +263,13 @@ static PlanChoice choose_plan(const Geo& g, const float* x_dev) {
   PlanChoice c{};
   c.split_p = gemm_fused_pos_preferred(g) && !(g.flags & LANCE_PLAN_WIDE_TILES);
   if (c.split_p) return c;
-  c.fuse_p = conv_fused_pos_preferred(g) && !(g.flags & LANCE_PLAN_WIDE_TILES);
+  const bool x_aligned = (reinterpret_cast<uintptr_t>(x_dev) & 15) == 0;
+  c.fuse_p = conv_fused_pos_preferred(g, x_aligned) && !(g.flags & LANCE_PLAN_WIDE_TILES);
   if (c.fuse_p) return c;
   if (is_packed(g)) return c;  // packed codes: the general plan (quantize pass, product kernel)
   c.fuse_pair = conv_fused_pairs_applicable(g) && (g.NB == 1 || !(g.flags & LANCE_PLAN_WIDE_TILES));
   if (c.fuse_pair) return c;
-  const bool x_ok = !is_nhwc(g) || (reinterpret_cast<uintptr_t>(x_dev) & 15) == 0;
+  const bool x_ok = !is_nhwc(g) || x_aligned;
   c.fuse_q1 = conv_fused_c64_applicable(g) && x_ok;
   c.fuse_q2 = !c.fuse_q1 && conv_fused_c128_applicable(g) && !(g.flags & LANCE_PLAN_WIDE_TILES) && x_ok;
   c.fuse_s = !c.fuse_q1 && !c.fuse_q2 && conv_fused_c16_applicable(g);

@@ -204,6 +204,12 @@ hipError_t launch_conv_fused_pairs(const Geo& g, const float* x, const int8_t* u
                                    const float* u_range, const int32_t* u_rowsum,
                                    const float* partial, int count, float* v_range, float* y,
                                    hipStream_t s);
+// The form of the two plans above on NHWC tensors (their kernels' names are theirs); x 16-byte aligned.
+// stream: Y is stored past the caches (only where stores_past_caches).
+bool conv_fused_pairs_nhwc_applicable(const Geo& g);
+hipError_t launch_conv_fused_pairs_nhwc(const Geo& g, const float* x, const int8_t* uq, const float* u_range,
+                                        const int32_t* u_rowsum, const float* partial, int count,
+                                        float* v_range, float* y, bool stream, hipStream_t s);
 // Quantize pass, products and epilogue in one kernel for F(2x2,3x3) layers with at most 16
 // channels (see conv_fused_c16.hip); qparams, dq and dqd come from launch_range_finalize.
 bool conv_fused_c16_applicable(const Geo& g);
@@ -217,7 +223,8 @@ hipError_t launch_conv_fused_c16(const Geo& g, const float* x, const int8_t* uq,
 // (conv_fused_pos.h): both tile sizes and layouts, any number of channels, packed filter codes.
 // merge != 0: every workgroup reduces the `count` records in `partial` and the first writes v_range
 // (with static ranges: all read v_range); merge == 0: v_range is finished (launch_range_finalize).
-bool conv_fused_pos_preferred(const Geo& g);
+// x_aligned: X is 16-byte aligned.
+bool conv_fused_pos_preferred(const Geo& g, bool x_aligned);
 bool conv_fused_pos_can_merge(const Geo& g, int count);
 hipError_t launch_conv_fused_pos(const Geo& g, const float* x, const int8_t* uq,
                                  const float* u_range, const int32_t* u_rowsum,

@@ -26,10 +26,30 @@ namespace dev {
 // What the kernel knows about the tensor; divisors as in fast_div.
 struct PairGeo {
   const float* x;
-  int C, H, W, th, npr, pairs, bits;  // npr: pairs per tile row; pairs: of the whole batch
+  int C, H, W, Ho, Wo, pad, th, npr, pairs, bits;  // npr: pairs per tile row; pairs: of the whole batch
   unsigned th_magic, npr_magic;
+  int exact;       // fast_div is exact for every pair (false only for NHWC rows of very many pairs)
   unsigned reach;  // extent of the buffer descriptors: bytes from a plane of a block's first image
 };
+
+// Pair p of the batch: pair q of tile row ty of image n.
+template <bool NHWC>
+__device__ __forceinline__ void locate_pair(const PairGeo& g, int p, int* q, int* ty, int* n) {
+  const bool fast = !NHWC || g.exact;
+  const int t2 = fast ? fast_div(p, g.npr_magic) : p / g.npr;
+  *q = p - t2 * g.npr;
+  *n = fast ? fast_div(t2, g.th_magic) : t2 / g.th;
+  *ty = t2 - *n * g.th;
+}
+
+// Four stored codes from four unsigned ones: per byte (code - h) mod 256 without borrows between bytes
+// (h = 128: flip the top bit).
+template <bool B8>
+__device__ __forceinline__ unsigned stored_codes(unsigned u, unsigned h) {
+  const unsigned H8 = 0x80808080u, hh = h * 0x01010101u;
+  if constexpr (B8) return u ^ H8;
+  return ((u | H8) - (hh & ~H8)) ^ ((u ^ ~hh) & H8);
+}
 
 // B8: 8-bit codes.  FULL: all 64 channels of every block exist.
 template <bool B8, bool FULL, int PAIRS>
@@ -47,12 +67,6 @@ struct PairPhase {
   const char* base;    // first image of the block
   int c_wave, group;   // the wave's first channel (+ 16 for each step); lane / PAIRS
 
-  __device__ __forceinline__ static void locate(const PairGeo& g, int p, int* q, int* ty, int* n) {
-    const int t2 = fast_div(p, g.npr_magic);
-    *q = p - t2 * g.npr;
-    *n = fast_div(t2, g.th_magic);
-    *ty = t2 - *n * g.th;
-  }
   // block: PAIRS consecutive pairs of the batch
   __device__ __forceinline__ void setup(const PairGeo& g, int block, int c_first, int lane) {
     const int p0 = block * PAIRS;
@@ -62,7 +76,7 @@ struct PairPhase {
     const int n0 = fast_div(fast_div(p0, g.npr_magic), g.th_magic);
     base = reinterpret_cast<const char*>(g.x + (size_t)n0 * g.C * HW);
     int q, ty, n;
-    locate(g, min(p0 + lane % PAIRS, g.pairs - 1), &q, &ty, &n);
+    locate_pair<false>(g, min(p0 + lane % PAIRS, g.pairs - 1), &q, &ty, &n);
     left_edge = q == 0;
     right_edge = q == g.npr - 1;
     const unsigned plane0 = FULL ? (unsigned)group * HW : 0u;
@@ -73,7 +87,7 @@ struct PairPhase {
       own_off[r] = y >= 0 && y < g.H ? (img + (unsigned)y * (unsigned)g.W + 4u * (unsigned)q) * 4u : kOutside;
     }
     const int i = lane & 15, side = (i >> 2) & 1;
-    locate(g, min(p0 + (lane % PAIRS & ~15) + 15 * side, g.pairs - 1), &q, &ty, &n);
+    locate_pair<false>(g, min(p0 + (lane % PAIRS & ~15) + 15 * side, g.pairs - 1), &q, &ty, &n);
     img = (unsigned)(n - n0) * (unsigned)g.C * HW + plane0;
     const int y = 2 * ty - 1 + (i & 3), xx = side ? 4 * q + 4 : 4 * q - 1;
     edge_off = i < 8 && y >= 0 && y < g.H && xx >= 0 && xx < g.W
@@ -160,7 +174,6 @@ struct PairPhase {
   __device__ __forceinline__ void store(const PairGeo& g, int chunk, int d, int lane, char* ring,
                                         const unsigned (&codes)[2][E]) const {
     const unsigned h = 1u << (g.bits - 1);
-    const unsigned H8 = 0x80808080u, hh = h * 0x01010101u;
     unsigned mask = 0;  // bytes of channels that exist
 #pragma unroll
     for (int b = 0; b < 4; b++)
@@ -171,17 +184,122 @@ struct PairPhase {
       char* dst = ring + (unsigned)row * 64u + (unsigned)((chunk ^ row_swizzle_mfma32(row)) * 16) + 4u * (unsigned)d;
 #pragma unroll
       for (int e = 0; e < E; e++) {
-        const unsigned u = codes[s][e];
-        // per-byte (code - h) mod 256 without borrows between bytes (h = 128: flip the top bit)
-        unsigned v;
-        if constexpr (B8)
-          v = u ^ H8;
-        else
-          v = ((u | H8) - (hh & ~H8)) ^ ((u ^ ~hh) & H8);
+        unsigned v = stored_codes<B8>(codes[s][e], h);
         if constexpr (!FULL) v &= mask;
         *reinterpret_cast<unsigned*>(dst + e * (kTiles * 64)) = v;
       }
     }
+  }
+};
+
+// The same from NHWC pixels, any padding and width, C a multiple of 4 and X 16-byte aligned: 16 lanes per
+// pair and channel block, lane j holds the channels 4j .. 4j+3 (dword j of the code row, channels in
+// their natural order).  The pair's window is six pixel columns of four 16-byte loads, taken column by
+// column: a column goes through B^T d once for both tiles, and a position's four codes are a whole dword that
+// goes to LDS at once, so no codes wait in registers.  Pixels outside the image have an offset beyond
+// the buffer: one add per load and nothing after it.
+//
+// Called by all 512 threads.  LDS rows and chunks as above.
+template <bool B8, int PAIRS>
+struct PairPhaseNhwc {
+  typedef float f4 __attribute__((ext_vector_type(4)));
+  static constexpr int E = 16, kTiles = 2 * PAIRS, kColumns = 6, kEarly = 4;
+  static constexpr unsigned kOutside = 0xFFFFFFF0u;  // beyond any X (the whole of which is one buffer)
+
+  unsigned rowoff[4], coloff[kColumns];  // rows that do not exist have kOutside
+  bool cok[kColumns];
+  char* dst;         // the lane's dword of position 0 of the left tile
+  unsigned mask;     // all ones where the lane's channels exist
+
+  // block: PAIRS consecutive pairs of the batch; pair: the lane's among them; cblk: channel block;
+  // ring: its code planes [E][kTiles][64 B]
+  __device__ __forceinline__ void setup(const PairGeo& g, int block, int pair, int cblk, int lane, char* ring) {
+    const int p0 = block * PAIRS;
+    const unsigned px = (unsigned)g.C * 4u, row_bytes = (unsigned)g.W * px;
+    int q, ty, n;
+    locate_pair<true>(g, min(p0 + pair, g.pairs - 1), &q, &ty, &n);
+    const int j = lane & 15, c = 64 * cblk + 4 * j;
+    mask = c < g.C ? 0xFFFFFFFFu : 0u;
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const int y = 2 * ty - g.pad + r;
+      rowoff[r] = y >= 0 && y < g.H ? ((unsigned)n * (unsigned)g.H + (unsigned)y) * row_bytes : kOutside;
+    }
+#pragma unroll
+    for (int s = 0; s < kColumns; s++) {
+      const int x = 4 * q - g.pad + s;
+      cok[s] = x >= 0 && x < g.W;
+      coloff[s] = (unsigned)x * px + (unsigned)min(c, g.C - 4) * 4u;
+    }
+    dst = ring + (unsigned)pair * 64u + (unsigned)(((j >> 2) ^ row_swizzle_mfma32(pair)) * 16 + 4 * (j & 3));
+  }
+
+  __device__ __forceinline__ void issue(const PairGeo& g, int s, f4 (&w)[4]) const {
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(g.x), 0, g.reach, 0x00020000);
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const unsigned off = cok[s] && rowoff[r] != kOutside ? rowoff[r] + coloff[s] : kOutside;
+      w[r] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0));
+    }
+  }
+
+  // B^T d of one pixel column, in place
+  __device__ __forceinline__ static void column(f4 (&w)[4]) {
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      const float d[4] = {w[0][q], w[1][q], w[2][q], w[3][q]};
+      float t[4];
+      Wino<2>::in1d(d, t);
+#pragma unroll
+      for (int i = 0; i < 4; i++) w[i][q] = t[i];
+    }
+  }
+
+  // The codes of position column j of tile s (0 left, 1 right): a + b or a - b of two pixel columns.
+  template <bool SUM>
+  __device__ __forceinline__ void codes(const PairGeo& g, int s, int j, const f4 (&a)[4], const f4 (&b)[4],
+                                        const float (&qmn)[E], const float (&qinv)[E]) const {
+    static_assert(PAIRS % 16 == 0, "both tiles of a pair have the same swizzle");
+    const float L = (float)((1 << g.bits) - 1);
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      const int e = 4 * i + j;
+      unsigned u = 0;
+#pragma unroll
+      for (int q = 0; q < 4; q++) {
+        const float v = SUM ? a[i][q] + b[i][q] : a[i][q] - b[i][q];
+        float tq = (v - qmn[e]) * qinv[e];  // Eq. 7 as in PairPhase
+        if constexpr (!B8) tq = fminf(tq, L);
+        u = __builtin_amdgcn_cvt_pk_u8_f32(tq, q, u);
+      }
+      *reinterpret_cast<unsigned*>(dst + (unsigned)(PAIRS * s * 64 + e * kTiles * 64)) =
+          stored_codes<B8>(u, 1u << (g.bits - 1)) & mask;
+    }
+  }
+  // All codes of the pair.  w: the first kEarly pixel columns, requested.  late(): requests what the caller
+  // needs next, when half of the columns' registers are free.
+  template <class Late>
+  __device__ __forceinline__ void run(const PairGeo& g, f4 (&w)[kColumns][4], const float (&qmn)[E],
+                                      const float (&qinv)[E], Late&& late) const {
+    issue(g, 4, w[4]);
+#pragma unroll
+    for (int s = 0; s < 3; s++) column(w[s]);
+    codes<false>(g, 0, 0, w[0], w[2], qmn, qinv);
+    codes<true>(g, 0, 1, w[1], w[2], qmn, qinv);
+    codes<false>(g, 0, 2, w[2], w[1], qmn, qinv);
+    column(w[3]);
+    codes<false>(g, 0, 3, w[1], w[3], qmn, qinv);
+    __builtin_amdgcn_sched_barrier(0);
+    issue(g, 5, w[5]);
+    column(w[4]);
+    codes<false>(g, 1, 0, w[2], w[4], qmn, qinv);
+    __builtin_amdgcn_sched_barrier(0);
+    late();
+    codes<true>(g, 1, 1, w[3], w[4], qmn, qinv);
+    codes<false>(g, 1, 2, w[4], w[3], qmn, qinv);
+    column(w[5]);
+    codes<false>(g, 1, 3, w[3], w[5], qmn, qinv);
   }
 };
 

@@ -605,6 +605,30 @@ def test_nhwc_four_tiles_of_a_row(shape, static):
     assert names[3] == ("conv_fused_c64_kernel" if C <= 64 else "conv_fused_c128_kernel"), names
 
 
+# N, C, K, H, W, pad, bits: NHWC pairs of tiles: one, two and three tile columns, odd numbers of them, widths that
+# are no multiple of anything, filters that are no multiple of four and of sixteen (streamed stores), padding lanes,
+# one share of the filters, one more filter, three shares; rows of so many pairs that multiplying does not divide them
+_NHWC_PAIRS = [
+    (1200, 20, 18, 13, 2, 1, 8), (900, 64, 20, 9, 3, 1, 8), (700, 40, 32, 9, 5, 1, 5), (420, 60, 21, 10, 11, 0, 8),
+    (300, 64, 16, 8, 9, 2, 8), (300, 64, 704, 8, 9, 1, 8), (100, 44, 705, 9, 13, 1, 6), (40, 24, 1500, 9, 13, 1, 8),
+    (1200, 68, 18, 9, 2, 1, 8), (900, 128, 37, 9, 5, 0, 4), (260, 100, 130, 10, 11, 1, 8), (200, 128, 48, 8, 9, 2, 8),
+    (60, 124, 768, 9, 13, 1, 8), (50, 72, 769, 9, 13, 1, 8), (1, 20, 17, 2, 262147, 1, 8),
+]
+
+
+@pytest.mark.parametrize("shape", _NHWC_PAIRS, ids=lambda s: "n%d_c%d_k%d_%dx%d_p%d_b%d" % s)
+@pytest.mark.parametrize("option", ["dynamic", "static", "per_tensor"])
+def test_nhwc_pairs_of_tiles(shape, option):
+    from paper_2003_08646_amd import binding as B
+    N, C, K, H, W, pad, bits = shape
+    L = Wk.Layer("nhwc_pairs", N, C, K, H, W, pad=pad, m=2, bits=bits, seed=880 + C)
+    flags = {"dynamic": 0, "static": B.LANCE_INPUT_RANGE_STATIC, "per_tensor": B.LANCE_RANGE_PER_TENSOR}[option]
+    conv, _ = _check_layer(L, flags=B.LANCE_LAYOUT_NHWC | flags, staged=False,
+                           static_v_range=_range_of_another_batch(L) if option == "static" else None)
+    names = _kernels(conv, _zeros(conv, True))
+    assert names[3] == ("conv_fused_c64_kernel" if C <= 64 else "conv_fused_c128_kernel"), names
+
+
 # N, C, H, W, pad: NHWC range pass on pairs of tile columns (at least 4096 strips): two and three columns, an odd
 # number of them, strips of the whole height and of a part of it
 @pytest.mark.parametrize("shape", [(2100, 20, 3, 4, 1), (1400, 68, 9, 5, 1), (300, 64, 30, 9, 0), (16, 130, 70, 75, 2),
@@ -616,3 +640,19 @@ def test_nhwc_ranges_from_pairs_of_tile_columns(shape):
     conv, _ = _check_layer(Wk.Layer("nhwc_range", N, C, 24, H, W, pad=pad, m=2, seed=890 + C), flags=B.LANCE_LAYOUT_NHWC,
                            staged=False)
     assert _kernels(conv, _zeros(conv, True))[0] == "input_nhwc_range_roll_kernel"
+
+
+def test_nhwc_of_four_byte_alignment_keeps_the_few_tile_plan():
+    """Between one and two workgroups per compute unit the pair kernel takes NHWC layers whose X is 16-byte aligned."""
+    from paper_2003_08646_amd import binding as B
+    L = Wk.Layer("nhwc_align", 64, 128, 128, 14, 14, m=2, seed=895)
+    conv, _ = _check_layer(L, flags=B.LANCE_LAYOUT_NHWC, staged=False)
+    assert _kernels(conv, _zeros(conv, True))[3] == "conv_fused_c128_kernel"
+    buf = torch.zeros(64 * 14 * 14 * 128 + 1, device="cuda")
+    x = torch.from_numpy(np.ascontiguousarray(Wk.make_inputs(L)[0].transpose(0, 2, 3, 1))).cuda()
+    y = conv.forward(x).clone()
+    shifted = buf[1:].view(x.shape)
+    shifted.copy_(x)
+    y2 = conv.forward(shifted)
+    assert (y - y2).abs().max() <= 1e-5 * y.abs().max()
+    assert _kernels(conv, shifted)[3] == "conv_fused_pos_kernel"
