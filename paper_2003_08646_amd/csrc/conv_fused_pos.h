@@ -24,7 +24,12 @@
 // transform - uq fragments - exchange - stores of one workgroup; 6 us for the smallest layers with
 // caller-supplied ranges, launch included (N122 16->16 7x7; 19 us before on conv_fused_c16), 11 us
 // with the range pass (one 16->16 32x32 image: 24.8 us before).  One image of the 512-channel 14x14
-// layer: 21 -> 13.3 us, N13 100->72 37x29 F(4x4): 43 -> 17 us.
+// layer: 21 -> 11.6 us, N13 100->72 37x29 F(4x4): 43 -> 16 us.  By the workgroups' clocks (one image, caller's
+// ranges): 512->512 28x28, 208 workgroups, 9 of 14 us are phase T (each compute unit transforms all channels of its
+// tiles: vector ALUs and the path from L2, about equally), 0.6 until the pixels are requested, 1 until the
+// constants are formed, 1 products, 0.4 sums, 0.6 stores.  What the constants are formed from is requested before
+// the pixels, and the filter-side terms are formed once per filter (pos_phases.h): 3->64 224x224 18.8 -> 15.2 us, 64->128
+// 112x112 12.0 -> 10.1, 256->256 56x56 13.8 -> 12.2, 512->512 14x14 12.1 -> 11.6; 160 random layers 1.05 on average.
 #pragma once
 #include "pos_phases.h"
 
@@ -52,8 +57,9 @@ __global__ __launch_bounds__(NW * 64, (M == 2 ? 16 : 12) / 4) void conv_fused_po
   const int nb = a.NB;
   const unsigned plane = (unsigned)nb * 1024u;  // code rows of one position
   {
+    typename Consts<M>::template Early<NT> early(a, a.is_static, tid);
     const Quantizer<M, NW, CPL, LOAD, CLAMP> qz(a, p0, lane, wave);
-    qz.run(0, nb, cst.qp, ring, [&]() { cst.template form<NT>(a, a.is_static, red, tid); });
+    qz.run(0, nb, cst.qp, ring, [&]() { cst.template form<NT>(a, a.is_static, early, red, tid); });
   }
 
   // ---- products: positions wave*PW .., accumulators [position][group of 16 filters] ----
@@ -78,13 +84,9 @@ __global__ __launch_bounds__(NW * 64, (M == 2 ? 16 : 12) / 4) void conv_fused_po
         if (b0 + u < nb) af[u][kg] = uq.load(e, b0 + u, kg);
   };
   load_batch(wave * PW, 0);
-  constexpr bool kEarlyRs = PW * KG <= 4;  // row sums of the lane's filters requested with them
-  int rs[PW][KG][4];
-  auto load_rs = [&]() {
+  int rs[PW];  // row sums of filter k0 + lane
 #pragma unroll
-    for (int w = 0; w < PW; w++) load_rowsums<KG>(a, wave * PW + w, k0, kq, rs[w]);
-  };
-  if constexpr (kEarlyRs) load_rs();
+  for (int w = 0; w < PW; w++) rs[w] = load_rowsum<KG>(a, wave * PW + w, k0, lane);
   lds_barrier();  // the codes of all waves are in LDS
 #pragma unroll
   for (int w = 0; w < PW; w++) {
@@ -104,7 +106,6 @@ __global__ __launch_bounds__(NW * 64, (M == 2 ? 16 : 12) / 4) void conv_fused_po
     }
   }
   lds_barrier();  // the code rows are free again
-  if constexpr (!kEarlyRs) load_rs();
 #pragma unroll
   for (int w = 0; w < PW; w++) sums_to_lds<KG, 1, kNhwc>(a, cst, wave * PW + w, lane, rs[w], acc[w], csum[w], ex);
   lds_barrier();

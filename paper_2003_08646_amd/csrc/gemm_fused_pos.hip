@@ -26,8 +26,9 @@ __global__ __launch_bounds__(256, M == 2 ? 4 : 3) void quant_pos_kernel(const Cp
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int blk = blockIdx.x % a.NB, p0 = (blockIdx.x / a.NB) * 16;
   {
+    typename Consts<M>::template Early<NT> early(a, a.is_static, tid);
     const Quantizer<M, NW, CPL, LOAD, CLAMP> qz(a, p0, lane, wave);
-    qz.run(blk, 1, cst.qp, ring, [&]() { cst.template form<NT>(a, a.is_static, red, tid); });
+    qz.run(blk, 1, cst.qp, ring, [&]() { cst.template form<NT>(a, a.is_static, early, red, tid); });
   }
   lds_barrier();
   const __amdgpu_buffer_rsrc_t res = __builtin_amdgcn_make_buffer_rsrc(a.vq, 0, a.vq_bytes, 0x00020000);
@@ -53,6 +54,7 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void gemm_pos_kernel(const CpA
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int ky = blockIdx.x % a.nky, p0 = (blockIdx.x / a.nky) * 16 * TG, k0 = ky * 16 * KG;
   const int nb = a.NB, col = lane & 15, kq = lane >> 4;
+  typename Consts<M>::template Early<NT> early(a, 1, tid);
   const UqReader<M, KG> uq(a, k0, col, kq);
   unsigned v_off[TG];
 #pragma unroll
@@ -74,6 +76,9 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void gemm_pos_kernel(const CpA
       }
   };
   request(af, bf, wave * PW, 0);
+  int rs[PW];  // row sums of filter k0 + lane
+#pragma unroll
+  for (int w = 0; w < PW; w++) rs[w] = load_rowsum<KG>(a, wave * PW + w, k0, lane);
   v4i acc[PW][TG][KG], csum[PW][TG];
 #pragma unroll
   for (int w = 0; w < PW; w++)
@@ -83,7 +88,7 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void gemm_pos_kernel(const CpA
 #pragma unroll
       for (int kg = 0; kg < KG; kg++) acc[w][t][kg] = v4i{0, 0, 0, 0};
     }
-  cst.template form<NT>(a, 1, ex, tid);
+  cst.template form<NT>(a, 1, early, ex, tid);
 #pragma unroll
   for (int w = 0; w < PW; w++) {
     const int e = wave * PW + w;
@@ -114,11 +119,7 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void gemm_pos_kernel(const CpA
     }
   }
 #pragma unroll
-  for (int w = 0; w < PW; w++) {
-    int rs[KG][4];
-    load_rowsums<KG>(a, wave * PW + w, k0, kq, rs);
-    sums_to_lds<KG, TG, NHWC>(a, cst, wave * PW + w, lane, rs, acc[w], csum[w], ex);
-  }
+  for (int w = 0; w < PW; w++) sums_to_lds<KG, TG, NHWC>(a, cst, wave * PW + w, lane, rs[w], acc[w], csum[w], ex);
   lds_barrier();
   store_patches<M, KG, TG, NT, NHWC>(a, ex, k0, p0, tid);
 }

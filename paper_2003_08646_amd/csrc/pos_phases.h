@@ -71,83 +71,100 @@ template <int M>
 struct Consts {
   static constexpr int E = (M + 2) * (M + 2);
   float* qp;     // [E][2] = {min, inv} of Eq. 7
-  float* res;    // [E][2] reduced ranges
   float* sc;     // [E] su*sv
   float* gc;     // [E] sv*ou
   double* rmul;  // [E] su*ov
   double* kc;    // [E] C*ou*ov
-  static_assert(E * (6 * sizeof(float) + 2 * sizeof(double)) <= kConstBytes, "parameter tables");
+  static_assert(E * (4 * sizeof(float) + 2 * sizeof(double)) <= kConstBytes, "parameter tables");
 
   __device__ __forceinline__ explicit Consts(char* smem) {
     qp = reinterpret_cast<float*>(smem);
-    res = qp + 2 * E;
-    sc = res + 2 * E;
+    sc = qp + 2 * E;
     gc = sc + E;
     rmul = reinterpret_cast<double*>(gc + E);
     kc = rmul + E;
   }
 
+  // What the constants are formed from, requested before the first pixels: loads return in order, and
+  // behind the pixels these few bytes from L2 would wait for memory.
+  template <int NT>
+  struct Early {
+    static constexpr int kCols = 2 * E, kGroups = NT / kCols, kBatch = 8;
+    float umin, umax, vmin, vmax;  // threads below E: filter range, caller's input range of position tid
+    float rec[kBatch];   // column tid % kCols of the records tid / kCols, + kGroups, ...
+
+    __device__ __forceinline__ Early(const CpArgs& a, int is_static, int tid) {
+      const int e = min(tid, E - 1), col = tid % kCols;
+      umin = a.u_range[2 * e];
+      umax = a.u_range[2 * e + 1];
+      const float* given = is_static ? a.v_range : a.u_range;  // (dynamic ranges: overwritten in form())
+      vmin = given[2 * e];
+      vmax = given[2 * e + 1];
+      if (!is_static) {
+#pragma unroll
+        for (int u = 0; u < kBatch; u++)  // (past the last record: the last one again)
+          rec[u] = a.partial[(size_t)min(tid / kCols + u * kGroups, a.count - 1) * kCols + col];
+      }
+    }
+  };
+
   // From v_range (is_static) or the records of the range pass; then workgroup 0 writes v_range.
   // red: NT floats of LDS that nobody else touches until this returns.  All threads; ends in a barrier.
   template <int NT>
-  __device__ __forceinline__ void form(const CpArgs& a, int is_static, float* red, int tid) const {
-    float su = 0.0f;
-    double ou = 0.0;
-    float ur0 = 0.0f, ur1 = 0.0f;
-    if (tid < E) { ur0 = a.u_range[2 * tid]; ur1 = a.u_range[2 * tid + 1]; }
-    if (is_static) {
-      if (tid < 2 * E) res[tid] = a.v_range[tid];
-    } else {
-      constexpr int kCols = 2 * E, kGroups = NT / kCols, kBatch = 8;
+  __device__ __forceinline__ void form(const CpArgs& a, int is_static, Early<NT>& early, float* red, int tid) const {
+    if (!is_static) {
+      constexpr int kCols = Early<NT>::kCols, kGroups = Early<NT>::kGroups, kBatch = Early<NT>::kBatch;
       const int col = tid % kCols, grp = tid / kCols;
       const bool is_max = col & 1;
-      float v = is_max ? -INFINITY : INFINITY;
-      if (grp < kGroups) {
-        for (int row0 = grp; row0 < a.count; row0 += kBatch * kGroups) {
-          float xv[kBatch];
+      float v = early.rec[0];
 #pragma unroll
-          for (int u = 0; u < kBatch; u++) {
-            const int row = row0 + u * kGroups;
-            xv[u] = row < a.count ? a.partial[(size_t)row * kCols + col] : v;
-          }
+      for (int u = 1; u < kBatch; u++) v = is_max ? fmaxf(v, early.rec[u]) : fminf(v, early.rec[u]);
+      for (int row0 = grp + kBatch * kGroups; row0 < a.count; row0 += kBatch * kGroups) {
+        float xv[kBatch];
 #pragma unroll
-          for (int u = 0; u < kBatch; u++) v = is_max ? fmaxf(v, xv[u]) : fminf(v, xv[u]);
-        }
+        for (int u = 0; u < kBatch; u++) xv[u] = a.partial[(size_t)min(row0 + u * kGroups, a.count - 1) * kCols + col];
+#pragma unroll
+        for (int u = 0; u < kBatch; u++) v = is_max ? fmaxf(v, xv[u]) : fminf(v, xv[u]);
       }
       red[tid] = v;
       lds_barrier();
-      if (tid < kCols) {
+      if (tid < E) {
+        v2f r = *reinterpret_cast<const v2f*>(red + 2 * tid);
 #pragma unroll
         for (int g2 = 1; g2 < kGroups; g2++) {
-          const float y = red[g2 * kCols + tid];
-          v = is_max ? fmaxf(v, y) : fminf(v, y);
+          const v2f y = *reinterpret_cast<const v2f*>(red + g2 * kCols + 2 * tid);
+          r[0] = fminf(r[0], y[0]);
+          r[1] = fmaxf(r[1], y[1]);
         }
-        res[tid] = v;
+        early.vmin = r[0];
+        early.vmax = r[1];
       }
     }
     if (tid < E) {
-      float iu;
-      dev::quant_params(ur0, ur1, a.bits_w, &iu, &su);
-      ou = (double)ur0 + (double)su * (double)(1 << (a.bits_w - 1));
-    }
-    lds_barrier();
-    if (tid < E) {
-      float lo = res[2 * tid], hi = res[2 * tid + 1];
-      if (a.per_tensor && !is_static)
-        for (int e = 0; e < E; e++) { lo = fminf(lo, res[2 * e]); hi = fmaxf(hi, res[2 * e + 1]); }
-      float inv, sv;
+      float lo = early.vmin, hi = early.vmax;
+      if (!is_static) {
+        if (a.per_tensor) {  // (all E threads are in one wave)
+          for (int e = 0; e < E; e++) {
+            lo = fminf(lo, __shfl(early.vmin, e, 64));
+            hi = fmaxf(hi, __shfl(early.vmax, e, 64));
+          }
+        }
+        if (blockIdx.x == 0) {
+          a.v_range[2 * tid] = lo;
+          a.v_range[2 * tid + 1] = hi;
+        }
+      }
+      float iu, su, inv, sv;
+      dev::quant_params(early.umin, early.umax, a.bits_w, &iu, &su);
       dev::quant_params(lo, hi, a.bits, &inv, &sv);
+      const double ou = (double)early.umin + (double)su * (double)(1 << (a.bits_w - 1));
+      const double ov = (double)lo + (double)sv * (double)(1 << (a.bits - 1));
       qp[2 * tid] = lo;
       qp[2 * tid + 1] = inv;
-      const double ov = (double)lo + (double)sv * (double)(1 << (a.bits - 1));
       sc[tid] = (float)((double)su * (double)sv);
       gc[tid] = (float)((double)sv * ou);
       rmul[tid] = (double)su * ov;
       kc[tid] = (double)a.C * ou * ov;
-      if (!is_static && blockIdx.x == 0) {
-        a.v_range[2 * tid] = lo;
-        a.v_range[2 * tid + 1] = hi;
-      }
     }
     lds_barrier();
   }
@@ -325,27 +342,40 @@ struct UqReader {
   }
 };
 
-// Row sums of the lane's filters k0 + 16*kg + 4*kq + r at position e.
+// Row sum at position e of filter k0 + lane (of the 16*KG; the lanes beyond hold the same ones again).
 template <int KG>
-__device__ __forceinline__ void load_rowsums(const CpArgs& a, int e, int k0, int kq, int (&rs)[KG][4]) {
-#pragma unroll
-  for (int kg = 0; kg < KG; kg++)
-#pragma unroll
-    for (int r = 0; r < 4; r++) rs[kg][r] = a.u_rowsum[(size_t)e * a.K + min(k0 + kg * 16 + 4 * kq + r, a.K - 1)];
+__device__ __forceinline__ int load_rowsum(const CpArgs& a, int e, int k0, int lane) {
+  return a.u_rowsum[(size_t)e * a.K + min(k0 + lane % (16 * KG), a.K - 1)];
 }
 
 // ---- from integer sums to patches ----
 // Sums of positions e of a wave -> M[e,k,p] (Eq. 8, expanded) in LDS: ex[(e*KG + kg)*TG + t][256], NCHW
 // as [r][kq][col], NHWC as [col][4*kq + r] (filter 4*kq + r of group kg, tile col of group t).
 // acc/csum: accumulator registers of v_mfma_i32_16x16x64_i8 with uq and with ones as first operand.
+// rs: load_rowsum().  The filter-side term su*ov*rs + C*ou*ov is formed once per filter, by the lane that holds
+// the row sum, and handed to the 16 lanes that use it through the words of ex that the wave is about to
+// write (one image 3 -> 64 224x224, 8 waves, four groups of filters: this step took 2.4 us of each workgroup's 7.4 with
+// the binary64 term formed in every lane, and waited for 32 loads of row sums).
 template <int KG, int TG, bool NHWC, class C>
-__device__ __forceinline__ void sums_to_lds(const CpArgs& a, const C& cst, int e, int lane, const int (&rs)[KG][4],
+__device__ __forceinline__ void sums_to_lds(const CpArgs& a, const C& cst, int e, int lane, int rs,
                                             const v4i (&acc)[TG][KG], const v4i (&csum)[TG], float* ex) {
   const int col = lane & 15, kq = lane >> 4;
   const bool b8 = a.bits == 8;
   const int h = 1 << (a.bits - 1);
   const float sc = cst.sc[e], gc = cst.gc[e];
-  const double rmul = cst.rmul[e], kc = cst.kc[e];
+  float* own = ex + e * (KG * TG * 256);
+  own[lane] = (float)(cst.rmul[e] * (double)rs + cst.kc[e]);
+  if (!b8) reinterpret_cast<int*>(own)[64 + lane] = h * rs;
+  asm volatile("" ::: "memory");  // (a wave's LDS operations complete in order)
+  v4f f[KG];
+  v4i hr[KG];
+#pragma unroll
+  for (int kg = 0; kg < KG; kg++) {
+    f[kg] = *reinterpret_cast<const v4f*>(own + 16 * kg + 4 * kq);
+    hr[kg] = v4i{0, 0, 0, 0};
+    if (!b8) hr[kg] = *reinterpret_cast<const v4i*>(own + 64 + 16 * kg + 4 * kq);
+  }
+  asm volatile("" ::: "memory");
 #pragma unroll
   for (int t = 0; t < TG; t++) {
     const int cs = csum[t][0];  // every row of the ones operand gives the same sums
@@ -356,8 +386,8 @@ __device__ __forceinline__ void sums_to_lds(const CpArgs& a, const C& cst, int e
       float m[4];
 #pragma unroll
       for (int r = 0; r < 4; r++) {
-        const int v = acc[t][kg][r] - bias - (b8 ? 0 : h * rs[kg][r]);
-        m[r] = __builtin_fmaf(sc, (float)v, (float)(rmul * (double)rs[kg][r] + kc) + g);
+        const int v = acc[t][kg][r] - bias - hr[kg][r];
+        m[r] = __builtin_fmaf(sc, (float)v, f[kg][r] + g);
       }
       float* dst = ex + ((e * KG + kg) * TG + t) * 256;
       if constexpr (NHWC) {

@@ -656,3 +656,19 @@ def test_nhwc_of_four_byte_alignment_keeps_the_few_tile_plan():
     y2 = conv.forward(shifted)
     assert (y - y2).abs().max() <= 1e-5 * y.abs().max()
     assert _kernels(conv, shifted)[3] == "conv_fused_pos_kernel"
+
+
+# N, C, K, H, W, pad, m, bits, nhwc: few-tile plans with one range for the whole tensor, reduced by every workgroup: one,
+# two and four groups of filters on 16 and 8 waves, F(4x4), two kernels; more records than a thread requests at once
+@pytest.mark.parametrize("shape", [(2, 20, 10, 9, 8, 1, 2, 8, False), (20, 33, 60, 14, 14, 1, 2, 6, False),
+                                   (45, 40, 70, 14, 15, 1, 2, 8, False), (33, 18, 70, 15, 16, 1, 4, 5, False),
+                                   (40, 30, 40, 16, 13, 1, 4, 8, True), (2, 330, 20, 9, 10, 1, 4, 8, False),
+                                   (3, 16, 40, 120, 120, 1, 4, 8, False), (2, 48, 20, 62, 60, 1, 2, 8, False)],
+                         ids=lambda s: "n%d_c%d_k%d_%dx%d_p%d_m%d_b%d%s" % (s[:8] + ("_nhwc" if s[8] else "",)))
+def test_position_parallel_per_tensor(shape):
+    from paper_2003_08646_amd import binding as B
+    N, C, K, H, W, pad, m, bits, nhwc = shape
+    L = Wk.Layer("per_tensor", N, C, K, H, W, pad=pad, m=m, bits=bits, seed=940 + C)
+    conv, _ = _check_layer(L, flags=B.LANCE_RANGE_PER_TENSOR | (B.LANCE_LAYOUT_NHWC if nhwc else 0), staged=False)
+    names = _kernels(conv, _zeros(conv, nhwc))
+    assert names[1] == "" and names[3] in ("conv_fused_pos_kernel", "gemm_pos_kernel"), names
