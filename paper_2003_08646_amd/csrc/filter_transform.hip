@@ -14,22 +14,22 @@
 // records that another one has not read.)  Small sets of filters need no first kernel: every
 // workgroup finds the ranges by itself.
 //
-// A thread of the second kernel forms whole dwords of a code row (four channels), so that 16 lanes
-// store 64 contiguous bytes per position.
+// A wave of the second kernel takes the 64 codes of one channel block of a filter (or of four filters of at most 16
+// channels): lane = channel, so that a wave reads 2304 contiguous bytes of weights and a thread transforms one filter
+// channel.  The codes cross LDS, wave by wave and without a barrier, into 16-byte pieces of code rows: one store per
+// thread and one addition of row sums, where a thread of four channels made 16 and 16.
 //
-// What bounds it: launches and latencies.  Kernel times before, with a one-workgroup reduction kernel
-// between the two: 512 -> 512 channels (9.4 MB of weights) 9.1 + 4.7 + 9.2 us, 64 -> 64 6.6 + 4.6 + 6.6
-// us; now 9.3 + 8.6 us, and about 7 us in one kernel.
+// What bounds it: launches and latencies, and for the largest layers the copies of the records, which the start of the
+// second kernel waits for.  By the workgroups' clocks, 64 -> 128 channels: range kernel 2.4 us (1.2 weights, 0.6
+// reduction), 1.2 until the next kernel starts, its records 1.8, constants 0.5, codes 0.9, sums 0.5.  Whole call, four
+// channels per thread / now: 3 -> 64 6.6 / 4.3 us, 64 -> 64 7.8 / 6.5, 128 -> 128 9.4 / 8.4, 256 -> 256 11.5 / 10.9, 512 -> 512
+// 16.3 / 16.3, 1024 -> 1024 41 / 30, 64 -> 64 F(4x4) 15.7 / 12.7; 150 random sets of 1 to 600 channels and filters 1.28 on
+// average, none slower by more than 1 %.  (Weights through LDS in 16-byte loads were slower at every size.)
 #include "lance_device.h"
 #include "lance_internal.h"
 
 namespace lance {
 namespace {
-
-// Rows of uq that workgroup j of n of the second kernel owns: filters first_filter(j) .. (j+1).
-__device__ __host__ __forceinline__ int first_filter(int j, int n, int K) {
-  return (int)((long long)j * K / n);
-}
 
 struct FtArgs {
   const float* w;
@@ -39,11 +39,17 @@ struct FtArgs {
   int C, K, CB, NB, Q, row;  // row: bytes of a code row
   int bits, natural, packed, per_tensor;
   int ga, gb, cap;  // workgroups of the two kernels; records per code-row strip of a workgroup
+  int base, extra;           // filters of a workgroup of the second kernel; the first `extra` have one more
+  unsigned cap_magic, nb_magic;  // divisors for dev::fast_div (a division by a variable takes 0.1 us here)
 };
+
+// First filter of workgroup j of the second kernel: it owns these rows of uq.
+__device__ __forceinline__ int first_filter(const FtArgs& a, int j) { return j * a.base + min(j, a.extra); }
 
 // Address of position e of record r in the copy of the workgroup whose first filter is k0.
 __device__ __forceinline__ float2* record(const FtArgs& a, int k0, int e, int r) {
-  return reinterpret_cast<float2*>(a.uq + (((size_t)e * a.NB + r / a.cap) * a.K + k0) * a.row) + r % a.cap;
+  const int strip = dev::fast_div(r, a.cap_magic);
+  return reinterpret_cast<float2*>(a.uq + (((size_t)e * a.NB + strip) * a.K + k0) * a.row) + (r - strip * a.cap);
 }
 
 // Running (min,max) per position of filters i0, i0 + step, ... below n; four are requested together.
@@ -115,60 +121,60 @@ __global__ __launch_bounds__(NT) void filter_range_kernel(const FtArgs a) {
   // the same record into every workgroup's copy: threads walk (copy, position)
   for (int i = threadIdx.x; i < a.gb * E; i += NT) {
     const int j = i / E, e = i % E;
-    *record(a, first_filter(j, a.gb, a.K), e, blockIdx.x) = res_s[e];
+    *record(a, first_filter(a, j), e, blockIdx.x) = res_s[e];
   }
 }
 
 // NARROW: codes of fewer than 8 bits.
 template <int M, int NT, bool NARROW>
 __global__ __launch_bounds__(NT) void filter_quant_kernel(const FtArgs a) {
-  constexpr int A = M + 2, E = A * A, kThreads = NT, kParts = kThreads / E;
+  constexpr int A = M + 2, E = A * A, kThreads = NT, kParts = kThreads / E, kWaves = NT / 64;
   constexpr int kMaxFilters = 64;  // per workgroup
+  typedef unsigned v4u __attribute__((ext_vector_type(4)));
   __shared__ float2 red[kThreads], res_s[E], qp_s[E];
   __shared__ int sum_s[kMaxFilters * E];
-  const int tid = threadIdx.x;
-  const int k0 = first_filter(blockIdx.x, a.gb, a.K), k1 = first_filter(blockIdx.x + 1, a.gb, a.K);
-  for (int i = tid; i < (k1 - k0) * E; i += kThreads) sum_s[i] = 0;
-  // The weights of dword dw of block b of filter k: byte q of the dword is channel b*CB + dw + Q*q
-  // (natural order: 4*dw + q).  mask: the bytes whose channel exists.
-  auto fetch = [&](int k, int b, int dw, float (&gw)[4][9], unsigned& mask) {
-    mask = 0;
+  __shared__ __align__(16) uint8_t rows_s[kWaves][E * 64 + 64];  // a wave's 64 codes of every position; byte mask
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int k0 = first_filter(a, blockIdx.x), k1 = first_filter(a, blockIdx.x + 1);
+  // the records of the range kernel are requested before the weights: loads return in order
+  constexpr int kBatch = 8;
+  const int e_red = tid % E, part = min(tid / E, kParts - 1);  // (threads beyond kParts * E repeat others)
+  float2 rec[kBatch] = {};
+  if (a.ga > 0) {
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
-      const int c = b * a.CB + (a.natural ? 4 * dw + q : dw + a.Q * q);
-      const float* src = a.w + ((size_t)k * a.C + min(c, a.C - 1)) * 9;
+    for (int u = 0; u < kBatch; u++)  // (past the last record: the last one again)
+      rec[u] = *record(a, k0, e_red, min(part + u * kParts, a.ga - 1));
+  }
+  // Unit: the 64 codes of one channel block of a filter, or of four filters of at most 16 channels.  Lane = code:
+  // channel c of filter k.
+  const bool wide = a.CB == 64;
+  const int units = wide ? (k1 - k0) * a.NB : (k1 - k0 + 3) / 4;  // (narrow: one block)
+  const int in_block = wide ? lane : lane & 15, sub = wide ? 0 : lane >> 4;
+  auto filter_of = [&](int unit) { return wide ? dev::fast_div(unit, a.nb_magic) : 4 * unit; };  // from k0 on, the first
+  auto block_of = [&](int unit) { return wide ? unit - dev::fast_div(unit, a.nb_magic) * a.NB : 0; };
+  auto fetch = [&](int unit, float (&g)[9]) {
+    const int c = block_of(unit) * 64 + in_block, k = k0 + filter_of(unit) + sub;
+    const float* src = a.w + ((size_t)min(k, a.K - 1) * a.C + min(c, a.C - 1)) * 9;
 #pragma unroll
-      for (int i = 0; i < 9; i++) gw[q][i] = src[i];
-      if (c < a.C) mask |= 0xFFu << (8 * q);
-    }
+    for (int i = 0; i < 9; i++) g[i] = src[i];
   };
-  const int per_row = a.packed ? 8 : a.Q;  // dwords of a code row
-  const int items = (k1 - k0) * a.NB * per_row;
-  // the first item's weights arrive while the ranges are reduced
-  float gw[4][9];
-  unsigned mask = 0;
-  if (tid < items) fetch(k0 + tid / per_row / a.NB, tid / per_row % a.NB, tid % per_row, gw, mask);
+  // the first unit's weights arrive while the ranges are reduced
+  float g[9];
+  if (wave < units) fetch(wave, g);
+  for (int i = tid; i < (k1 - k0) * E; i += kThreads) sum_s[i] = 0;
   if (a.ga == 0) {
     float mn[E], mx[E];
     range_of<M>(a.w, tid, kThreads, a.K * a.C, mn, mx);
     reduce_range<M, kThreads>(mn, mx, red, res_s);
   } else {
-    const int e = tid % E, part = tid / E;
-    float2 v = {INFINITY, -INFINITY};
-    if (part < kParts) {
-      constexpr int kBatch = 8;
-      for (int r0 = part; r0 < a.ga; r0 += kBatch * kParts) {
-        float2 x[kBatch];
+    float2 v = rec[0];
 #pragma unroll
-        for (int u = 0; u < kBatch; u++) {
-          const int r = r0 + u * kParts;
-          x[u] = r < a.ga ? *record(a, k0, e, r) : v;
-        }
-#pragma unroll
-        for (int u = 0; u < kBatch; u++) { v.x = fminf(v.x, x[u].x); v.y = fmaxf(v.y, x[u].y); }
-      }
-      red[tid] = v;
+    for (int u = 1; u < kBatch; u++) { v.x = fminf(v.x, rec[u].x); v.y = fmaxf(v.y, rec[u].y); }
+    for (int r = part + kBatch * kParts; r < a.ga; r += kParts) {
+      const float2 x = *record(a, k0, e_red, r);
+      v.x = fminf(v.x, x.x); v.y = fmaxf(v.y, x.y);
     }
+    red[tid] = v;
     __syncthreads();  // also: the workgroup's copy of the records has been read
     if (tid < E) {
 #pragma unroll
@@ -178,7 +184,7 @@ __global__ __launch_bounds__(NT) void filter_quant_kernel(const FtArgs a) {
       }
       res_s[tid] = v;
     }
-    __syncthreads();
+    if (a.per_tensor) __syncthreads();
   }
   if (tid < E) {
     float2 v = res_s[tid];
@@ -193,78 +199,78 @@ __global__ __launch_bounds__(NT) void filter_quant_kernel(const FtArgs a) {
 
   const float L = (float)((1 << a.bits) - 1);
   const unsigned h = 1u << (a.bits - 1), hh = h * 0x01010101u, H8 = 0x80808080u;
-  // codes: Eq. 7's unsigned codes of the four channels, 0 where the channel does not exist
-  auto dword_of = [&](const float (&gw)[4][9], unsigned mask, unsigned (&codes)[E]) {
+  // bytes u - h (mod 256); u <= 127 for codes below 8 bits
+  auto to_signed = [&](unsigned u) -> unsigned { return h == 128u ? u ^ H8 : ((u | H8) - hh) ^ H8; };
+  float2 qp[E];  // (F(4x4): read again for every unit instead of living in 72 registers)
 #pragma unroll
-    for (int q = 0; q < 4; q++) {
-      float gq[3][3], u[A][A];
+  for (int e = 0; e < E; e++)
+    if constexpr (M == 2) qp[e] = qp_s[e];
+  // byte of the lane's code among the unit's 64: its code row's, NCHW channel c of a block at 4 * (c % Q) + c / Q
+  const int byte = sub * 16 + (a.natural ? in_block : wide ? 4 * (in_block & 15) + (in_block >> 4)
+                                                          : 4 * (in_block & 3) + (in_block >> 2));
+  uint8_t* mine = rows_s[wave];
+  for (int unit = wave; unit < units; unit += kWaves) {
+    const int b = block_of(unit), kl = filter_of(unit);
+    float gq[3][3], u[A][A];
 #pragma unroll
-      for (int i = 0; i < 9; i++) gq[i / 3][i % 3] = gw[q][i];
-      dev::filter_tile_transform<M>(gq, u);
+    for (int i = 0; i < 9; i++) gq[i / 3][i % 3] = g[i];
+    dev::filter_tile_transform<M>(gq, u);
+    if (unit + kWaves < units) fetch(unit + kWaves, g);  // (in flight under this unit's codes)
+    mine[E * 64 + byte] = b * 64 + in_block < a.C ? 0xFF : 0;  // bytes of channels that do not exist become 0
 #pragma unroll
-      for (int e = 0; e < E; e++) {
-        const float2 p = qp_s[e];
-        // clamp(rne((x - min) * inv), 0, L): the conversion rounds to nearest even and saturates to
-        // [0, 255].  The ranges are those of these filters, but where x - min overflows the product is
-        // infinite, and 0 * infinity is undefined: those are L and (the median with one undefined value
-        // is the least of the others; the conversion's result, too) 0
-        float t = (u[e / A][e % A] - p.x) * p.y;
-        if constexpr (NARROW) t = __builtin_amdgcn_fmed3f(t, 0.0f, L);
-        codes[e] = __builtin_amdgcn_cvt_pk_u8_f32(t, q, q == 0 ? 0u : codes[e]);
-      }
-      // (one channel after the other, and the parameters read again for each)
-#pragma unroll
-      for (int e = 0; e < E; e++) asm volatile("" : "+v"(codes[e]));
-      asm volatile("" ::: "memory");
+    for (int e = 0; e < E; e++) {
+      const float2 p = M == 2 ? qp[e] : qp_s[e];
+      // clamp(rne((x - min) * inv), 0, L): the conversion rounds to nearest even and saturates to
+      // [0, 255].  The ranges are those of these filters, but where x - min overflows the product is
+      // infinite, and 0 * infinity is undefined: those are L and (the median with one undefined value
+      // is the least of the others; the conversion's result, too) 0
+      float t = (u[e / A][e % A] - p.x) * p.y;
+      if constexpr (NARROW) t = __builtin_amdgcn_fmed3f(t, 0.0f, L);
+      mine[e * 64 + byte] = (uint8_t)__builtin_amdgcn_cvt_pk_u8_f32(t, 0, 0u);
     }
+    asm volatile("" ::: "memory");  // (a wave's LDS operations complete in order)
+    // Back as 16-byte pieces of the rows: position i / 4, piece i % 4.  Pieces of narrow rows belong to filters.
 #pragma unroll
-    for (int e = 0; e < E; e++) codes[e] &= mask;
-  };
-  // bytes u - h (mod 256) where the channel exists, else 0; u <= 127 for codes below 8 bits
-  auto to_signed = [&](unsigned u, unsigned mask) -> unsigned {
-    return (h == 128u ? u ^ H8 : ((u | H8) - hh) ^ H8) & mask;
-  };
-  for (int i = tid; i < items; i += kThreads) {
-    const int dw = i % per_row, t = i / per_row;
-    const int b = t % a.NB, kl = t / a.NB;
-    int8_t* dst = a.uq + ((size_t)b * a.K + k0 + kl) * a.row + 4 * dw;
-    const size_t estride = (size_t)a.NB * a.K * a.row;
-    unsigned codes[E];
-    if (i != tid) fetch(k0 + kl, b, dw, gw, mask);
-    dword_of(gw, mask, codes);
-    if (a.packed) {
-      // byte q: the codes at positions 4*dw + q (low nibble) and 32 + 4*dw + q, each as code + 8
-      unsigned hi[E], mask_hi;
-      fetch(k0 + kl, b, dw + 8, gw, mask_hi);
-      dword_of(gw, mask_hi, hi);
-      const int off = (int)(h * (unsigned)((__popc(mask) + __popc(mask_hi)) / 8));
+    for (int i = lane; i < E * 4; i += 64) {
+      const int e = i >> 2, piece = i & 3;
+      const int own = kl + (wide ? 0 : piece);
+      v4u v = *reinterpret_cast<const v4u*>(mine + i * 16);
+      const v4u mask = *reinterpret_cast<const v4u*>(mine + E * 64 + piece * 16);
+      int sum = 0;
 #pragma unroll
-      for (int e = 0; e < E; e++) {
-        const int sum = (int)__builtin_amdgcn_sad_u8(hi[e], 0u, __builtin_amdgcn_sad_u8(codes[e], 0u, 0u)) - off;
-        atomicAdd(&sum_s[kl * E + e], sum);
-        const unsigned lo4 = (to_signed(codes[e], mask) & 0x0F0F0F0Fu) ^ 0x08080808u;
-        const unsigned hi4 = (to_signed(hi[e], mask_hi) & 0x0F0F0F0Fu) ^ 0x08080808u;
-        *reinterpret_cast<unsigned*>(dst + e * estride) = lo4 | (hi4 << 4);
+      for (int d = 0; d < 4; d++) {
+        v[d] = to_signed(v[d]) & mask[d];
+        sum = __builtin_amdgcn_sdot4((int)v[d], 0x01010101, sum, false);
       }
-    } else {
-      const int off = (int)(h * (unsigned)(__popc(mask) / 8));
+      const bool ok = k0 + own < k1;
+      int8_t* row = a.uq + (((size_t)e * a.NB + b) * a.K + k0 + own) * a.row;
+      if (a.packed) {
+        // byte q: the codes of bytes q (low nibble) and 32 + q, each as code + 8
+        if (piece < 2) {
+          const v4u hi = *reinterpret_cast<const v4u*>(mine + i * 16 + 32);
+          const v4u hi_mask = *reinterpret_cast<const v4u*>(mine + E * 64 + piece * 16 + 32);
+          v4u w;
 #pragma unroll
-      for (int e = 0; e < E; e++) {
-        *reinterpret_cast<unsigned*>(dst + e * estride) = to_signed(codes[e], mask);
-        int sum = (int)__builtin_amdgcn_sad_u8(codes[e], 0u, 0u) - off;
-        if (per_row == 16) {  // the 16 lanes of a code row: one filter, all present
-          sum = dev::row16_sum(sum);
-          if (dw == 0) atomicAdd(&sum_s[kl * E + e], sum);
-        } else {
-          atomicAdd(&sum_s[kl * E + e], sum);
+          for (int d = 0; d < 4; d++)
+            w[d] = ((v[d] & 0x0F0F0F0Fu) ^ 0x08080808u) |
+                   ((((to_signed(hi[d]) & hi_mask[d]) & 0x0F0F0F0Fu) ^ 0x08080808u) << 4);
+          *reinterpret_cast<v4u*>(row + 16 * piece) = w;
         }
+      } else if (ok) {
+        *reinterpret_cast<v4u*>(row + (wide ? 16 * piece : 0)) = v;
       }
+      if (wide) {  // the four pieces of a row
+        sum += __builtin_amdgcn_update_dpp(0, sum, 0xB1, 0xF, 0xF, false);  // quad_perm [1,0,3,2]
+        sum += __builtin_amdgcn_update_dpp(0, sum, 0x4E, 0xF, 0xF, false);  // quad_perm [2,3,0,1]
+      }
+      if (ok && (!wide || piece == 0)) atomicAdd(&sum_s[own * E + e], sum);
     }
+    asm volatile("" ::: "memory");
   }
   __syncthreads();
-  for (int i = tid; i < (k1 - k0) * E; i += kThreads) {
-    const int e = i / (k1 - k0), kl = i % (k1 - k0);
-    a.u_rowsum[(size_t)e * a.K + k0 + kl] = sum_s[kl * E + e];
+  for (int i = tid; i < E * kMaxFilters; i += kThreads) {
+    const int e = i / kMaxFilters, kl = i % kMaxFilters;
+    if (kl < k1 - k0) a.u_rowsum[(size_t)e * a.K + k0 + kl] = sum_s[kl * E + e];
   }
 }
 
@@ -275,27 +281,32 @@ hipError_t launch_filter_transform(const Geo& g, const float* w, int8_t* uq, flo
   FtArgs a{w, uq, u_range, u_rowsum, g.C, g.K, g.CB, g.NB, g.Q, code_row_bytes(g), g.bits_w,
            is_nhwc(g) ? 1 : 0, is_packed(g) ? 1 : 0, (g.flags & LANCE_RANGE_PER_TENSOR) ? 1 : 0, 0, 0, 1};
   const long long filters = (long long)g.K * g.C;
-  // Small workgroups have the shorter chain of steps, large ones keep the number of records and
-  // copies down: 256 threads up to 80 K filters (32 -> 400 channels: 9.8 us against 11.9 with 1024 and
-  // 512 threads), then 1024 and 512 (443 -> 222: 15.5 us against 17.1).
-  const bool large = filters > 81920;
-  const int nt_range = large ? 1024 : 256, nt_quant = large ? 512 : 256;
-  // Workgroups of the second kernel: one item (four or eight channels) per thread, at most 64
-  // filters each.
-  const long long items = (long long)g.K * g.NB * (is_packed(g) ? 8 : g.Q);
-  long long gb = (items + nt_quant - 1) / nt_quant;
+  // Up to 4096 filters every workgroup of the second kernel finds the ranges itself.
+  const bool one_kernel = filters <= 4096, large = filters > 81920;
+  // Small workgroups have the shorter chain of steps, large ones keep the number of records and copies down.
+  const int nt_range = large ? 1024 : 256;
+  const int nt_quant = one_kernel ? (filters > 1024 ? 1024 : 256) : (filters > 24576 ? 512 : 256);
+  // Workgroups of the second kernel: a unit of 64 codes per wave, then several, so that there are at most 64, 128 or
+  // 256 copies of the records (512 -> 512 channels: the start of the second kernel waits 3.3 us behind the last
+  // workgroup of the first with 128 copies of 8 KB, 4.9 with 256, 1.2 where there are few), at most 64 filters each.
+  const long long units = g.CB == 64 ? (long long)g.K * g.NB : (g.K + 3) / 4;
+  const long long most = filters > 400000 ? 256 : large ? 128 : 64;
+  const long long waves = nt_quant / 64, per_wave = (units + waves * most - 1) / (waves * most);
+  long long gb = (units + waves * per_wave - 1) / (waves * per_wave);
   if (gb < (g.K + 63) / 64) gb = (g.K + 63) / 64;
   if (gb > g.K) gb = g.K;
   a.gb = (int)gb;
+  a.base = g.K / a.gb;
+  a.extra = g.K % a.gb;
   // Records that fit into the rows of the workgroup with the fewest filters.
-  a.cap = (int)(g.K / gb) * a.row / 8;
+  a.cap = a.base * a.row / 8;
   const long long room = (long long)a.cap * g.NB;
   long long ga = large ? (filters + 2047) / 2048 : (filters + 1023) / 1024;
   if (large && ga > 64) ga = 64;
   if (ga > room) ga = room;
-  // Up to 4096 filters every workgroup of the second kernel finds the ranges itself (16 -> 16
-  // channels: 7.5 us in two kernels, 5.2 in one; 80 -> 192: 13.9 us in two, 39 in one).
-  a.ga = filters <= 4096 ? 0 : (int)ga;
+  a.ga = one_kernel ? 0 : (int)ga;
+  a.cap_magic = div_magic(a.cap);
+  a.nb_magic = div_magic(a.NB);
   auto run = [&](auto range, auto quant) -> hipError_t {
     if (a.ga > 0) {
       range<<<a.ga, nt_range, 0, s>>>(a);
@@ -307,11 +318,14 @@ hipError_t launch_filter_transform(const Geo& g, const float* w, int8_t* uq, flo
   };
   auto sized = [&](auto narrow) -> hipError_t {
     constexpr bool kNarrow = decltype(narrow)::value;
-    if (g.m == 2)
-      return large ? run(filter_range_kernel<2, 1024>, filter_quant_kernel<2, 512, kNarrow>)
-                   : run(filter_range_kernel<2, 256>, filter_quant_kernel<2, 256, kNarrow>);
-    return large ? run(filter_range_kernel<4, 1024>, filter_quant_kernel<4, 512, kNarrow>)
-                 : run(filter_range_kernel<4, 256>, filter_quant_kernel<4, 256, kNarrow>);
+    auto tile = [&](auto m) -> hipError_t {
+      constexpr int kM = decltype(m)::value;
+      return large               ? run(filter_range_kernel<kM, 1024>, filter_quant_kernel<kM, 512, kNarrow>)
+             : nt_quant == 1024 ? run(filter_range_kernel<kM, 256>, filter_quant_kernel<kM, 1024, kNarrow>)
+             : nt_quant == 512  ? run(filter_range_kernel<kM, 256>, filter_quant_kernel<kM, 512, kNarrow>)
+                                : run(filter_range_kernel<kM, 256>, filter_quant_kernel<kM, 256, kNarrow>);
+    };
+    return g.m == 2 ? tile(std::integral_constant<int, 2>{}) : tile(std::integral_constant<int, 4>{});
   };
   return g.bits_w < 8 ? sized(std::true_type{}) : sized(std::false_type{});
 }

@@ -658,6 +658,16 @@ def test_nhwc_of_four_byte_alignment_keeps_the_few_tile_plan():
     assert _kernels(conv, shifted)[3] == "conv_fused_pos_kernel"
 
 
+# K, C, m, bits_w: filters of a last unit of four that is not whole, padding lanes, one, several and many units of 64 codes
+# per wave on workgroups of 256, 512 and 1024 threads, unequal shares, 64, 128 and 256 copies of the records
+@pytest.mark.parametrize("K,C,m,bits_w", [(6, 16, 2, 8), (3, 17, 4, 2), (63, 65, 2, 4), (64, 64, 2, 3), (17, 63, 4, 8),
+                                          (1, 512, 2, 8), (260, 100, 2, 6), (90, 513, 4, 8), (600, 129, 2, 8),
+                                          (1025, 420, 2, 8), (4097, 1, 4, 4)])
+@pytest.mark.parametrize("flags", ["nchw", "nhwc", "packed", "per_tensor"])
+def test_filter_transform_units(K, C, m, bits_w, flags):
+    test_filter_transform_shapes(K, C, m, bits_w, flags)
+
+
 # N, C, K, H, W, pad, m, bits, nhwc: few-tile plans with one range for the whole tensor, reduced by every workgroup: one,
 # two and four groups of filters on 16 and 8 waves, F(4x4), two kernels; more records than a thread requests at once
 @pytest.mark.parametrize("shape", [(2, 20, 10, 9, 8, 1, 2, 8, False), (20, 33, 60, 14, 14, 1, 2, 6, False),
