@@ -12,6 +12,7 @@
 //   X  v_mfma_i32_32x32x16_i8 wants the codes of 32 tiles, the lower lanes holding contraction
 //      bytes 0-7 and the upper lanes bytes 8-15.  Two v_permlane32_swap per position turn the
 //      lane-per-tile registers into exactly that, for both groups of 32 tiles at once.
+//      (Layers of few tiles: two or four waves share 64 tiles, each repeats T and X and takes a part of G.)
 //   G  per filter tile (32 filters) and tile group: 16 matrix instructions, one per position,
 //      each folded at once into the four outputs of the 2x2 patch with the (compile-time sparse)
 //      coefficients A^T[a][i] A^T[b][j] s_e; then the two separable terms of the expanded Eq. 8
@@ -51,7 +52,12 @@ struct CsArgs {
   const float* v_range;  // [E][2], or nullptr: dynamic ranges, tables from the reduction kernel
   const float* u_range;  // [E][2]
   int bits_w;
+  int split;  // waves that share 64 tiles: 1, 2 or 4
 };
+
+// Workgroup barrier that waits for this wave's LDS operations only: loads from memory stay in flight
+// across it, which __syncthreads() would wait for.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // lanes 0-31 keep `own`, lanes 32-63 receive the value of lane - 32 (*g0); lanes 0-31 receive
 // the value of lane + 32, lanes 32-63 keep `own` (*g1): what the two tile groups' columns need.
@@ -110,7 +116,8 @@ constexpr int kModeNhwc = 3;
 // STREAM (NCHW): Y is stored past the caches (store_rule.h).  A parameter of the kernel: with both kinds of
 // stores in one kernel the others took 0.5 to 1.5 % longer (N19 4 -> 6 58x160 13.45 / 13.60 us, N15 6 -> 11 205x205
 // 35.2 / 35.8).
-template <bool B8, int MODE, bool STREAM>
+// SPLIT: a.split waves share 64 tiles.
+template <bool B8, int MODE, bool SPLIT, bool STREAM>
 __global__ __launch_bounds__(kThreads, 2) void conv_fused_c16_kernel(const CsArgs a) {
   constexpr int M = 2, A = 4, E = 16;
   constexpr bool kNhwc = MODE == kModeNhwc;
@@ -121,74 +128,41 @@ __global__ __launch_bounds__(kThreads, 2) void conv_fused_c16_kernel(const CsArg
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int K = a.K, P = a.P, C = a.C;
 
-  // Eq. 7 parameters and Eq. 8 constants: from the reduction kernel's tables, or (calibrated
-  // ranges) formed here exactly as that kernel forms them
-  if (tid < E) {
+  // What the constants are formed from is requested before the first pixels (loads return in order): the
+  // caller's ranges or the reduction kernel's tables, and the row sums of filter tid.
+  float lo = 0.0f, qpv = 0.0f, u0 = 0.0f, u1 = 0.0f;
+  double d0 = 0.0, d1 = 0.0;
+  {
+    const int e = min(tid, E - 1);
+    const float* range = a.v_range ? a.v_range : a.qparams;
+    lo = range[2 * e];
+    qpv = range[2 * e + 1];
     if (a.v_range) {
-      float inv, sv, iu, su;
-      const float lo = a.v_range[2 * tid], hi = a.v_range[2 * tid + 1];
-      dev::quant_params(lo, hi, a.bits, &inv, &sv);
-      dev::quant_params(a.u_range[2 * tid], a.u_range[2 * tid + 1], a.bits_w, &iu, &su);
-      const double ou = (double)a.u_range[2 * tid] + (double)su * (double)(1 << (a.bits_w - 1));
-      const double ov = (double)lo + (double)sv * (double)(1 << (a.bits - 1));
-      qp_s[2 * tid] = lo;
-      qp_s[2 * tid + 1] = inv;
-      dq_s[2 * tid] = (float)((double)su * (double)sv);
-      dq_s[2 * tid + 1] = (float)((double)sv * ou);
-      dqd_s[2 * tid] = (double)su * ov;
-      dqd_s[2 * tid + 1] = (double)C * ou * ov;
+      u0 = a.u_range[2 * e];
+      u1 = a.u_range[2 * e + 1];
     } else {
-      qp_s[2 * tid] = a.qparams[2 * tid];
-      qp_s[2 * tid + 1] = a.qparams[2 * tid + 1];
-      dq_s[2 * tid] = a.dq[4 * tid];
-      dq_s[2 * tid + 1] = a.dq[4 * tid + 1];
-      dqd_s[2 * tid] = a.dqd[2 * tid];
-      dqd_s[2 * tid + 1] = a.dqd[2 * tid + 1];
+      u0 = a.dq[4 * e];
+      u1 = a.dq[4 * e + 1];
+      d0 = a.dqd[2 * e];
+      d1 = a.dqd[2 * e + 1];
     }
   }
-  __syncthreads();
+  int32_t rowsum[E];
+  auto request_rowsums = [&](int k) {
+#pragma unroll
+    for (int e = 0; e < E; e++) rowsum[e] = a.u_rowsum[(size_t)e * K + min(k, K - 1)];
+  };
+  request_rowsums(tid);
 
-  // filter-side terms f[e,k] = su*ov*rowsum[e][k] + C*ou*ov through A^T . A, in binary64
-  // (thread = filter)
-  for (int k = tid; k < K; k += kThreads) {
-    double f[E];
-#pragma unroll
-    for (int e = 0; e < E; e++)
-      f[e] = dqd_s[2 * e] * (double)a.u_rowsum[(size_t)e * K + k] + dqd_s[2 * e + 1];
-    v4f r4;
-#pragma unroll
-    for (int ab = 0; ab < M * M; ab++) {
-      double accd = 0.0;
-#pragma unroll
-      for (int e = 0; e < E; e++) {
-        const float coef = dev::Wino<M>::at(ab >> 1, e / A) * dev::Wino<M>::at(ab & 1, e % A);
-        if (coef != 0.0f) accd += (double)coef * f[e];
-      }
-      r4[ab] = (float)accd;
-    }
-    *reinterpret_cast<v4f*>(rk_s + 4 * k) = r4;
-  }
-  __syncthreads();
-  const int p0 = (dev::xcd_contiguous(blockIdx.x, gridDim.x) * 4 + wave) * 64;
-  if (p0 >= P) return;  // (no barrier below)
-
-  // Eq. 7 parameters and the scales of the expanded Eq. 8, wave-uniform
-  float qmn[E], qinv[E], sc[E], gc[E];
-#pragma unroll
-  for (int e = 0; e < E; e++) {
-    qmn[e] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(qp_s[2 * e])));
-    qinv[e] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(qp_s[2 * e + 1])));
-    sc[e] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(dq_s[2 * e])));
-    gc[e] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(dq_s[2 * e + 1])));
-  }
-
-  // ============================ T: transform + quantize ============================
+  // The wave's tiles.  a.split waves share 64 tiles, and divide the filter tiles and tile groups of phase G.
+  const int unit = dev::xcd_contiguous(blockIdx.x, gridDim.x) * 4 + wave;
+  const int p0 = (SPLIT ? unit / a.split : unit) * 64, share = SPLIT ? unit % a.split : 0;
   const bool valid = p0 + lane < P;
   const int pt = min(p0 + lane, P - 1);
   const int tx = pt % a.tw, t2 = pt / a.tw;
   const int ty = t2 % a.th, n = t2 / a.th;
   const unsigned HW = (unsigned)a.H * (unsigned)a.W;
-  const int n0 = p0 / (a.th * a.tw);  // image of the block's first tile (wave-uniform)
+  const int n0 = min(p0, P - 1) / (a.th * a.tw);  // image of the block's first tile (wave-uniform)
   dev::PatchLoader<M> pl;
   unsigned pixoff[A * A];  // NHWC: byte offsets of the window's pixels
   if constexpr (kNhwc)
@@ -220,6 +194,65 @@ __global__ __launch_bounds__(kThreads, 2) void conv_fused_c16_kernel(const CsArg
       if (c < C) issue(c);
   }
 
+
+  // Eq. 7 parameters and Eq. 8 constants: from the reduction kernel's tables, or (calibrated
+  // ranges) formed here exactly as that kernel forms them
+  if (tid < E) {
+    if (a.v_range) {
+      float inv, sv, iu, su;
+      dev::quant_params(lo, qpv, a.bits, &inv, &sv);
+      dev::quant_params(u0, u1, a.bits_w, &iu, &su);
+      const double ou = (double)u0 + (double)su * (double)(1 << (a.bits_w - 1));
+      const double ov = (double)lo + (double)sv * (double)(1 << (a.bits - 1));
+      qpv = inv;
+      u0 = (float)((double)su * (double)sv);
+      u1 = (float)((double)sv * ou);
+      d0 = (double)su * ov;
+      d1 = (double)C * ou * ov;
+    }
+    qp_s[2 * tid] = lo;
+    qp_s[2 * tid + 1] = qpv;
+    dq_s[2 * tid] = u0;
+    dq_s[2 * tid + 1] = u1;
+    dqd_s[2 * tid] = d0;
+    dqd_s[2 * tid + 1] = d1;
+  }
+  lds_barrier();
+
+  // filter-side terms f[e,k] = su*ov*rowsum[e][k] + C*ou*ov through A^T . A, in binary64
+  // (thread = filter)
+  for (int k = tid; k < K; k += kThreads) {
+    if (k != tid) request_rowsums(k);
+    double f[E];
+#pragma unroll
+    for (int e = 0; e < E; e++) f[e] = dqd_s[2 * e] * (double)rowsum[e] + dqd_s[2 * e + 1];
+    v4f r4;
+#pragma unroll
+    for (int ab = 0; ab < M * M; ab++) {
+      double accd = 0.0;
+#pragma unroll
+      for (int e = 0; e < E; e++) {
+        const float coef = dev::Wino<M>::at(ab >> 1, e / A) * dev::Wino<M>::at(ab & 1, e % A);
+        if (coef != 0.0f) accd += (double)coef * f[e];
+      }
+      r4[ab] = (float)accd;
+    }
+    *reinterpret_cast<v4f*>(rk_s + 4 * k) = r4;
+  }
+  lds_barrier();
+  if (p0 >= P) return;  // (no barrier below)
+
+  // Eq. 7 parameters and the scales of the expanded Eq. 8, wave-uniform
+  float qmn[E], qinv[E], sc[E], gc[E];
+#pragma unroll
+  for (int e = 0; e < E; e++) {
+    qmn[e] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(qp_s[2 * e])));
+    qinv[e] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(qp_s[2 * e + 1])));
+    sc[e] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(dq_s[2 * e])));
+    gc[e] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(dq_s[2 * e + 1])));
+  }
+
+  // ============================ T: transform + quantize ============================
   // codes[e][d]: channel c sits in dword c % 4, byte c / 4 (the blocked order of the code layout)
   unsigned codes[E][4];
 #pragma unroll
@@ -332,7 +365,8 @@ __global__ __launch_bounds__(kThreads, 2) void conv_fused_c16_kernel(const CsArg
   const int col = lane & 31, half = lane >> 5;
   const bool even_w = (Wo & 1) == 0;
   const int nkt = (K + 31) / 32;
-  for (int kt = 0; kt < nkt; kt++) {
+  // the wave's filter tiles and groups: with two shares one group each, with four also every other filter tile
+  for (int kt = SPLIT ? share >> 1 : 0; kt < nkt; kt += SPLIT ? a.split >> 1 : 1) {
     // filter operands of this tile: row = filter, bytes 8*half .. 8*half+7 of its 16
     long af[E];
     {
@@ -344,6 +378,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_fused_c16_kernel(const CsArg
     }
 #pragma unroll
     for (int g = 0; g < 2; g++) {
+      if (SPLIT && g != (share & 1)) continue;  // wave-uniform
       v16f out[M * M];
 #pragma unroll
       for (int ab = 0; ab < M * M; ab++)
@@ -440,6 +475,31 @@ bool conv_fused_c16_applicable(const Geo& g) {
   return reach < (1LL << 31) && y_elems * 4 < 0xFFFFFFF0LL;  // 32-bit store offsets
 }
 
+// Time of the kernel in us with `split` waves to 64 tiles: a fixed part, and for each workgroup of a compute unit (the
+// second one adds to the first one's time, the vector ALUs are shared) the constants, the channels' transforms and
+// the wave's products of 32 filters x 32 tiles.  Fitted on 110 layers of 5000 to 90000 tiles with caller's ranges, three
+// splits each: 10 % off on average (NHWC 25 %).
+static double c16_us(const Geo& g, int split) {
+  const long long wgs = ((g.P + 63LL) / 64 * split + 3) / 4, kt = (g.K + 31) / 32;
+  const double load = (double)((wgs + 255) / 256) * 0.8;
+  const double parts = (double)(split == 1 ? 2 * kt : split == 2 ? kt : (kt + 1) / 2);
+  return is_nhwc(g) ? -0.8 + (load > 1.0 ? load : 1.0) * (3.3 + 1.1 * g.C + 5.4 * parts)
+                    : 3.9 + (load > 1.0 ? load : 1.0) * (1.8 + 0.37 * g.C + 3.9 * parts);
+}
+
+// Waves that share 64 tiles: more than one where workgroups of 256 tiles leave compute units idle and the
+// transform, which every wave repeats, is the smaller part.  Us per call with 1 / 2 / 4 (caller's ranges): N8 1->272
+// 99^2 NHWC 74 / 45 / 41, N11 3->103 105^2 42 / 29 / 27, N128 16->16 32^2 18 / 15 / 17, N53 3->33 19x57 23 / 16 / 12, N16 3->64
+// 224^2 55 / 58 / 70.
+static int c16_split(const Geo& g) {
+  const double one = c16_us(g, 1), two = c16_us(g, 2), four = c16_us(g, 4);
+  // (of 200 other layers none lost more than 2 % with these margins)
+  if ((is_nhwc(g) ? 0.75 : 0.85) * one <= (two < four ? two : four)) return 1;
+  return two <= four ? 2 : 4;
+}
+
+double conv_fused_c16_us(const Geo& g) { return c16_us(g, c16_split(g)); }
+
 hipError_t launch_conv_fused_c16(const Geo& g, const float* x, const int8_t* uq,
                                  const float* qparams, const float* dq, const double* dqd,
                                  const int32_t* u_rowsum, float* y, const float* static_v_range,
@@ -450,12 +510,16 @@ hipError_t launch_conv_fused_c16(const Geo& g, const float* x, const int8_t* uq,
   CsArgs a{x, uq, qparams, dq, dqd, u_rowsum, y, g.N, g.C, g.H, g.W, g.K, g.pad, g.P, g.th, g.tw, g.Ho, g.Wo,
            g.bits,
            is_nhwc(g) ? (unsigned)((long long)g.N * g.C * g.H * g.W * 4) : (unsigned)(images * g.C * g.H * g.W * 4LL),
-           (unsigned)((size_t)g.N * g.K * g.Ho * g.Wo * 4), static_v_range, u_range, g.bits_w};
-  const unsigned grid = (unsigned)((g.P + 255) / 256);
+           (unsigned)((size_t)g.N * g.K * g.Ho * g.Wo * 4), static_v_range, u_range, g.bits_w, c16_split(g)};
+  const unsigned grid = (unsigned)(((g.P + 63) / 64 * a.split + 3) / 4);
   const size_t lds = (size_t)4 * g.K * sizeof(float);
   const bool rows = patch_load_mode(g) == 2, stream = stores_past_caches(g);
   note_kernel("conv_fused_c16_kernel");
-#define LANCE_C16(B8, MODE, STREAM) conv_fused_c16_kernel<B8, MODE, STREAM><<<grid, kThreads, lds, s>>>(a)
+#define LANCE_C16(B8, MODE, STREAM) \
+  do { \
+    if (a.split > 1) conv_fused_c16_kernel<B8, MODE, true, STREAM><<<grid, kThreads, lds, s>>>(a); \
+    else conv_fused_c16_kernel<B8, MODE, false, STREAM><<<grid, kThreads, lds, s>>>(a); \
+  } while (0)
 #define LANCE_C16_STORES(B8, MODE) \
   do { if (stream) LANCE_C16(B8, MODE, true); else LANCE_C16(B8, MODE, false); } while (0)
   if (is_nhwc(g)) {

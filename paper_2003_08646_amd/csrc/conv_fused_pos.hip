@@ -9,6 +9,7 @@ hipError_t launch_m4(const CpArgs& a, bool clamp, int cpl, int load, int kg, hip
 struct Shape {
   int kg, nw, nky;
   long long groups;
+  double cost;  // rounds x relative time of a workgroup
 };
 
 // The shape with the smallest (rounds of resident workgroups) x (relative time of a workgroup).  A
@@ -19,15 +20,11 @@ struct Shape {
 // waves, 27 us with eight; 61 filters, 135 blocks: 15.5 and 15.9 us); m = 4: 1.12x and 1.45x.
 static Shape shape_of(const Geo& g) {
   const long long tb = (g.P + 15) / 16;
-  Shape best{1, 16, 0, 0};
-  double best_cost = 0.0;
+  Shape best{1, 16, 0, 0, 0.0};
   auto consider = [&](int nw, int kg, int slots, double cost) {
     const int nky = (g.K + 16 * kg - 1) / (16 * kg);
     const double c = (double)((tb * nky + slots - 1) / slots) * cost;
-    if (best.nky == 0 || c < best_cost) {
-      best = Shape{kg, nw, nky, tb * nky};
-      best_cost = c;
-    }
+    if (best.nky == 0 || c < best.cost) best = Shape{kg, nw, nky, tb * nky, c};
   };
   constexpr double kCost16[3] = {1.0, 1.08, 1.25}, kCost8[3] = {1.3, 1.4, 1.6}, kCost12[3] = {1.0, 1.12, 1.45};
   for (int i = 0; i < 3; i++) {
@@ -49,9 +46,12 @@ static bool conv_fused_pos_applicable(const Geo& g) {
 // K, image):
 //  * F(4x4), at most 16 channels: always (the fallback plan: N14 16->32 116x130 124 -> 41,
 //    N9 16->128 97^2 NHWC 194 -> 111, N5 16->512 12^2 123 -> 16; N62 4->68 213x224 1474 -> 1082).
-//  * F(2x2), at most 16 channels: while conv_fused_c16's workgroups of 256 tiles leave most of the
-//    chip idle (N3 4->43 112x95 32 -> 16, N11 5->58 58^2 46 -> 24, N1 3->64 224^2 20.5 -> 19.3,
-//    N4 3->64 224^2 33 against 66).
+//  * F(2x2), at most 16 channels: up to 12800 tiles, and not where conv_fused_c16 with several waves to 64
+//    tiles is estimated to take less than 0.85 of this plan's time, 1.2 us + 3.9 us per round (17 % off on 75 layers of
+//    4000 to 12800 tiles), with dynamic ranges counting its reduction kernel.  This plan / that one, caller's ranges: N1
+//    3->64 224^2 15.7 / 10.6, 7->68 with 12540 tiles 25.8 / 16.8, 2->40 with 8658 12.9 / 9.9, 5->50 with 5780 9.0 / 12.1, 16->61
+//    with 11913 14.9 / 19.0; dynamic: N1 3->64 224^2 22.2 / 19.3, and little with more than 256 filters (2->371 with 7752 tiles
+//    51.2 / 48.2, 16->290 with 7605 44.5 / 44.7), which stay here.  NHWC layers too (9->430 with 7569 tiles 45.7 / 70.6).
 //  * F(2x2), 17 to 128 channels: up to two workgroups of eight waves per compute unit (N4 32->128 63^2
 //    31.5 -> 21, N1 64->128 112^2 18.9 -> 14.4); one per compute unit where conv_fused_pairs.hip takes the
 //    layer in one block of filters (caller's ranges, this plan / that one: N1 128->128 112^2 17.9 / 11.3, N16
@@ -67,7 +67,13 @@ static bool conv_fused_pos_applicable(const Geo& g) {
 //    44 -> 15, N4 256->512 28^2 24 against 28, N23 38->52 108^2 F(4x4) 51 against 95).
 bool conv_fused_pos_preferred(const Geo& g, bool x_aligned) {
   if (!conv_fused_pos_applicable(g)) return false;
-  if (g.C <= 16) return g.m == 4 || g.P <= 12800;
+  if (g.C <= 16) {
+    if (g.m == 4) return true;
+    if (g.P > 12800) return false;
+    const bool is_static = (g.flags & LANCE_INPUT_RANGE_STATIC) != 0;
+    if (is_nhwc(g) || !conv_fused_c16_applicable(g) || (!is_static && g.K > 256)) return true;
+    return conv_fused_c16_us(g) + (is_static ? 0.0 : 5.0) >= 0.85 * (1.2 + 3.9 * pos::shape_of(g).cost);
+  }
   const bool pairs = is_nhwc(g) ? x_aligned && conv_fused_pairs_nhwc_applicable(g) &&
                                       (g.NB == 2 || (g.K > 16 && g.K % 4 == 0))
                                 : conv_fused_pairs_applicable(g) && g.K <= 64 * g.NB && (g.NB == 2 || g.K > 16);

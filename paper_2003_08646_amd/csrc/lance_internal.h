@@ -213,6 +213,8 @@ hipError_t launch_conv_fused_pairs_nhwc(const Geo& g, const float* x, const int8
 // Quantize pass, products and epilogue in one kernel for F(2x2,3x3) layers with at most 16
 // channels (see conv_fused_c16.hip); qparams, dq and dqd come from launch_range_finalize.
 bool conv_fused_c16_applicable(const Geo& g);
+// Estimate of its time in us.
+double conv_fused_c16_us(const Geo& g);
 // static_v_range != nullptr (caller-supplied ranges): the kernel forms parameters and constants
 // itself from it and u_range, and qparams, dq, dqd are not read.
 hipError_t launch_conv_fused_c16(const Geo& g, const float* x, const int8_t* uq,

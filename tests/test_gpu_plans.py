@@ -682,3 +682,27 @@ def test_position_parallel_per_tensor(shape):
     conv, _ = _check_layer(L, flags=B.LANCE_RANGE_PER_TENSOR | (B.LANCE_LAYOUT_NHWC if nhwc else 0), staged=False)
     names = _kernels(conv, _zeros(conv, nhwc))
     assert names[1] == "" and names[3] in ("conv_fused_pos_kernel", "gemm_pos_kernel"), names
+
+
+# N, C, K, H, W, pad, bits, nhwc: the small-channel kernel with two and four waves to 64 tiles: one, two, three and many tiles
+# of 32 filters (waves without any), a last block of one tile, odd sizes; below 12800 tiles where it takes over from the
+# few-tile plan
+_C16_SHARED = [
+    (48, 5, 17, 10, 134, 1, 8, False), (53, 3, 33, 19, 57, 1, 8, False), (128, 16, 16, 32, 32, 1, 8, False),
+    (16, 4, 65, 57, 55, 1, 5, False), (11, 3, 103, 75, 75, 0, 8, False), (1, 16, 200, 225, 229, 1, 8, False),
+    (1, 3, 64, 224, 224, 1, 8, False), (9, 2, 100, 65, 65, 1, 4, False), (8, 1, 272, 83, 81, 1, 8, True),
+    (12, 2, 92, 79, 75, 1, 6, True), (3, 7, 66, 131, 133, 1, 8, True), (13, 1, 40, 63, 64, 1, 8, False),
+]
+
+
+@pytest.mark.parametrize("shape", _C16_SHARED, ids=lambda s: "n%d_c%d_k%d_%dx%d_p%d_b%d%s" % (s[:7] + ("_nhwc" if s[7] else "",)))
+@pytest.mark.parametrize("static", [False, True], ids=["dynamic", "static"])
+def test_small_channel_waves_that_share_tiles(shape, static):
+    from paper_2003_08646_amd import binding as B
+    N, C, K, H, W, pad, bits, nhwc = shape
+    L = Wk.Layer("c16_shared", N, C, K, H, W, pad=pad, m=2, bits=bits, seed=960 + C)
+    flags = (B.LANCE_LAYOUT_NHWC if nhwc else 0) | (B.LANCE_INPUT_RANGE_STATIC if static else 0)
+    conv, _ = _check_layer(L, flags=flags, static_v_range=_range_of_another_batch(L) if static else None, staged=False)
+    names = _kernels(conv, _zeros(conv, nhwc))
+    if static or conv.sz.P > 12800:  # (with dynamic ranges the few-tile plan keeps more of the others)
+        assert names[3] == "conv_fused_c16_kernel", names
