@@ -706,3 +706,13 @@ def test_small_channel_waves_that_share_tiles(shape, static):
     names = _kernels(conv, _zeros(conv, nhwc))
     if static or conv.sz.P > 12800:  # (with dynamic ranges the few-tile plan keeps more of the others)
         assert names[3] == "conv_fused_c16_kernel", names
+
+
+# N, C, H, W: F(4x4) range pass in strips of an even and of an odd number of tile rows, several strips to a plane, one
+# segment to a row and as many as a wave has lanes
+@pytest.mark.parametrize("shape", [(40, 20, 13, 20), (40, 20, 17, 20), (90, 33, 27, 4), (2, 24, 36, 256), (3, 20, 150, 12)],
+                         ids=lambda s: "n%d_c%d_%dx%d" % s)
+def test_m4_ranges_from_strips(shape):
+    N, C, H, W = shape
+    conv, _ = _check_layer(Wk.Layer("strip_m4", N, C, 24, H, W, pad=1, m=4, seed=900 + H), staged=False)
+    assert _kernels(conv, _zeros(conv, False))[0] == "input_range_strip_m4_kernel"
