@@ -23,11 +23,12 @@
 // M[e,k,p] = s_e*ACC + f[e,k] + g[e,p]; the three terms go through the linear map S = A^T M A
 // separately; f is formed here from the filter row sums (binary64), g from the column sums.
 //
-// What bounds it, N64 128 -> 128 56x56 (with caller's ranges 94 us, now 86; with dynamic ones 118, now
-// 109): the phases add up - vector ALUs of the transform and of the fold (per position and
+// What bounds it, N64 128 -> 128 56x56 (on one pair of buffers 71 us with caller's ranges and 93 with dynamic
+// ones): the phases add up - vector ALUs of the transform and of the fold (per position and
 // accumulator register one conversion and about five multiply-adds against a quarter of a matrix
 // instruction), then memory.  Neither a deeper fragment ring (11 positions) nor the order of products
-// and fold changed phase G.  What did help: constants requested before the pixels, the filter-side
+// and fold changed phase G, nor a fold by sums and differences of the point pairs (154 operations per register
+// instead of 216: 92.7 -> 92.6 us): behind it stand the 590 KB of uq that each workgroup reads.  What did help: constants requested before the pixels, the filter-side
 // terms in separable form (170 binary64 instructions instead of 470), no reduction kernel, the second
 // channel block's pixels requested under the first one's arithmetic, whole rows of the filter-side
 // terms read at once and range-checked stores in the tail.  A variant with one workgroup of eight waves
