@@ -497,16 +497,14 @@ __global__ __launch_bounds__(kThreads, 4) void conv_fused_pairs_c128_kernel(cons
 }
 // The NHWC kernels of the plans of one and of two channel blocks.  STREAM is a parameter of the kernel: with both
 // kinds of stores in one the cached ones took up to 2 % longer.
-namespace nhwc {
 template <bool B8, bool STREAM>
-__global__ __launch_bounds__(kThreads, 4) void conv_fused_c64_kernel(const CpArgs a) {
+__global__ __launch_bounds__(kThreads, 4) void conv_fused_pairs_nhwc_c64_kernel(const CpArgs a) {
   conv_body<1, B8, false, true, STREAM>(a);
 }
 template <bool B8, bool STREAM>
-__global__ __launch_bounds__(kThreads, 4) void conv_fused_c128_kernel(const CpArgs a) {
+__global__ __launch_bounds__(kThreads, 4) void conv_fused_pairs_nhwc_c128_kernel(const CpArgs a) {
   conv_body<2, B8, false, true, STREAM>(a);
 }
-}  // namespace nhwc
 
 // LDS of a workgroup with the terms of K filters.
 template <int NB>
@@ -551,8 +549,8 @@ hipError_t launch_blocks(const Geo& g, const CpArgs& a, hipStream_t s) {
 
 template <bool B8, bool STREAM>
 hipError_t launch_nhwc(const Geo& g, const CpArgs& a, hipStream_t s) {
-  return g.NB == 1 ? launch_kernel<1>(nhwc::conv_fused_c64_kernel<B8, STREAM>, a, "conv_fused_c64_kernel", s)
-                   : launch_kernel<2>(nhwc::conv_fused_c128_kernel<B8, STREAM>, a, "conv_fused_c128_kernel", s);
+  return g.NB == 1 ? launch_kernel<1>(conv_fused_pairs_nhwc_c64_kernel<B8, STREAM>, a, "conv_fused_pairs_nhwc_c64_kernel", s)
+                   : launch_kernel<2>(conv_fused_pairs_nhwc_c128_kernel<B8, STREAM>, a, "conv_fused_pairs_nhwc_c128_kernel", s);
 }
 
 bool divisions_exact(long long pairs, long long npr, long long th) {

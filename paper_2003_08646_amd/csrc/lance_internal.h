@@ -204,7 +204,7 @@ hipError_t launch_conv_fused_pairs(const Geo& g, const float* x, const int8_t* u
                                    const float* u_range, const int32_t* u_rowsum,
                                    const float* partial, int count, float* v_range, float* y,
                                    hipStream_t s);
-// The form of the two plans above on NHWC tensors (their kernels' names are theirs); x 16-byte aligned.
+// The form of the two plans above on NHWC tensors; x 16-byte aligned.
 // stream: Y is stored past the caches (only where stores_past_caches).
 bool conv_fused_pairs_nhwc_applicable(const Geo& g);
 hipError_t launch_conv_fused_pairs_nhwc(const Geo& g, const float* x, const int8_t* uq, const float* u_range,

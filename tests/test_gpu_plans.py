@@ -158,11 +158,11 @@ def test_packed_on_many_tiles(m):
 # does only with LANCE_PLAN_WIDE_TILES (last item), a layer large enough to be its own.
 _PLANS = [
     ("conv_fused_c64_kernel", 200, 50, 70, 13, 14, 1, 2, 5, ""),
-    ("conv_fused_c64_kernel", 330, 60, 40, 10, 9, 1, 2, 8, "nhwc"),
+    ("conv_fused_pairs_nhwc_c64_kernel", 330, 60, 40, 10, 9, 1, 2, 8, "nhwc"),
     ("conv_fused_c128_kernel", 100, 96, 70, 16, 18, 1, 2, 6, ""),
     ("conv_fused_pairs_c64_kernel", 200, 50, 70, 13, 16, 1, 2, 5, ""),
     ("conv_fused_pairs_c128_kernel", 100, 96, 70, 16, 16, 1, 2, 6, ""),
-    ("conv_fused_c128_kernel", 110, 72, 130, 14, 13, 0, 2, 8, "nhwc"),
+    ("conv_fused_pairs_nhwc_c128_kernel", 110, 72, 130, 14, 13, 0, 2, 8, "nhwc"),
     ("conv_fused_c16_kernel", 60, 12, 40, 33, 31, 1, 2, 8, ""),
     ("conv_fused_c16_kernel", 60, 3, 70, 32, 32, 1, 2, 4, "nhwc"),
     ("conv_fused_m4_kernel", 100, 40, 130, 20, 21, 1, 4, 8, ""),
@@ -583,26 +583,26 @@ def test_quantize_pass_with_all_channel_blocks(shape, static):
         assert (_kernels(conv, _zeros(conv, False))[2] == "input_quant_m2_whole_kernel") == whole
 
 
-# N, C, K, H, W, pad, bits: NHWC, tile rows of a multiple of four tiles (four tiles of a row per thread group): the
-# narrowest row, padding of 0 to 2, ragged heights, a last workgroup of four tiles, whole and partial blocks
-_ROLL = [
+# N, C, K, H, W, pad, bits: NHWC, tile rows of whole pairs (a multiple of four tiles): a row of two pairs, padding of 0
+# to 2, ragged heights, a last workgroup of two pairs, whole and partial blocks
+_WHOLE_PAIRS = [
     (330, 20, 17, 13, 8, 1, 8), (421, 64, 32, 9, 7, 1, 5), (141, 44, 20, 11, 26, 0, 8), (150, 64, 48, 13, 14, 2, 8),
     (330, 68, 17, 13, 8, 1, 8), (421, 128, 32, 9, 7, 1, 5), (141, 100, 20, 11, 26, 0, 8), (150, 128, 48, 13, 14, 2, 8),
     (91, 128, 130, 16, 24, 1, 8), (70, 64, 65, 16, 32, 1, 8),
 ]
 
 
-@pytest.mark.parametrize("shape", _ROLL, ids=lambda s: "n%d_c%d_k%d_%dx%d_p%d_b%d" % s)
+@pytest.mark.parametrize("shape", _WHOLE_PAIRS, ids=lambda s: "n%d_c%d_k%d_%dx%d_p%d_b%d" % s)
 @pytest.mark.parametrize("static", [False, True], ids=["dynamic", "static"])
-def test_nhwc_four_tiles_of_a_row(shape, static):
+def test_nhwc_rows_of_whole_pairs(shape, static):
     from paper_2003_08646_amd import binding as B
     N, C, K, H, W, pad, bits = shape
-    L = Wk.Layer("roll", N, C, K, H, W, pad=pad, m=2, bits=bits, seed=860 + C)
+    L = Wk.Layer("whole_pairs", N, C, K, H, W, pad=pad, m=2, bits=bits, seed=860 + C)
     conv, _ = _check_layer(L, flags=B.LANCE_LAYOUT_NHWC | (B.LANCE_INPUT_RANGE_STATIC if static else 0), staged=False,
                            static_v_range=_range_of_another_batch(L) if static else None)
     assert -(-(W + 2 * pad - 2) // 2) % 4 == 0
     names = _kernels(conv, _zeros(conv, True))
-    assert names[3] == ("conv_fused_c64_kernel" if C <= 64 else "conv_fused_c128_kernel"), names
+    assert names[3] == "conv_fused_pairs_nhwc_%s_kernel" % ("c64" if C <= 64 else "c128"), names
 
 
 # N, C, K, H, W, pad, bits: NHWC pairs of tiles: one, two and three tile columns, odd numbers of them, widths that
@@ -626,7 +626,7 @@ def test_nhwc_pairs_of_tiles(shape, option):
     conv, _ = _check_layer(L, flags=B.LANCE_LAYOUT_NHWC | flags, staged=False,
                            static_v_range=_range_of_another_batch(L) if option == "static" else None)
     names = _kernels(conv, _zeros(conv, True))
-    assert names[3] == ("conv_fused_c64_kernel" if C <= 64 else "conv_fused_c128_kernel"), names
+    assert names[3] == "conv_fused_pairs_nhwc_%s_kernel" % ("c64" if C <= 64 else "c128"), names
 
 
 # N, C, H, W, pad: NHWC range pass on pairs of tile columns (at least 4096 strips): two and three columns, an odd
@@ -647,7 +647,7 @@ def test_nhwc_of_four_byte_alignment_keeps_the_few_tile_plan():
     from paper_2003_08646_amd import binding as B
     L = Wk.Layer("nhwc_align", 64, 128, 128, 14, 14, m=2, seed=895)
     conv, _ = _check_layer(L, flags=B.LANCE_LAYOUT_NHWC, staged=False)
-    assert _kernels(conv, _zeros(conv, True))[3] == "conv_fused_c128_kernel"
+    assert _kernels(conv, _zeros(conv, True))[3] == "conv_fused_pairs_nhwc_c128_kernel"
     buf = torch.zeros(64 * 14 * 14 * 128 + 1, device="cuda")
     x = torch.from_numpy(np.ascontiguousarray(Wk.make_inputs(L)[0].transpose(0, 2, 3, 1))).cuda()
     y = conv.forward(x).clone()
