@@ -60,11 +60,22 @@ static bool conv_fused_pos_applicable(const Geo& g) {
 //    channel block and at most 16 filters, of which that kernel computes 64: N20 56->8 109x8 8.6 / 9.7, N12
 //    17->12 112x20 9.0 / 9.8, N15 64->5 169x8 8.6 / 9.4 (dynamic ranges 15.0 / 15.7 at most); 17 to 21 filters
 //    9.8 / 9.8, two channel blocks from 5 filters on 12.5 / 10.5.
-//    On NHWC tensors with any number of filters (N64 128->128 14^2 dynamic 22.1 / 17.7, N500 64->64 8^2 19.0 / 16.5,
-//    N3 108->68 58x78 15.3 / 11.7, N49 52->64 23^2 11.1 / 10.4), but with one channel block only where four filters
-//    are one store there (N3 44->62 73^2 16.0 / 20.8, N20 56->61 37x35 11.4 / 14.3).
+//    NHWC, 1258 layers between one and two workgroups per compute unit, the median of this plan's time over that one's for
+//    17..32 / 33..64 / 65..128 / 129..192 / 257..399 filters, with caller's ranges: one channel block 0.97 / 1.12 / 0.84 / 0.69 /
+//    0.49, two blocks 1.12 / 1.25 / 1.29 / 0.92 / 0.71 (dynamic ranges 0.05 to 0.1 more): in one block of filters
+//    there too, from 17 or 33 filters on.  Where four filters are not one store (one block 0.83 / 0.87 / 0.62 / ..., two
+//    1.03 / 1.10 / 1.08 / 0.73 / 0.49) two blocks only, with caller's ranges 33 to 96 filters (97..128: 0.86 to 1.17).
+//    Two blocks and dynamic ranges: from one filter on (1.07 and 1.10 up to 16).  With several blocks of filters
+//    few workgroups do all the work: N2 64->704 28^2 15.9 / 51.2 us, N1 100->3218 15x24 19.1 / 68.0.
 //  * the rest: one workgroup per compute unit (N1 512->512 28^2 23 -> 16.7, N1 128->256 56^2 F(4x4)
 //    44 -> 15, N4 256->512 28^2 24 against 28, N23 38->52 108^2 F(4x4) 51 against 95).
+static bool nhwc_pairs_preferred(const Geo& g) {
+  if (!conv_fused_pairs_nhwc_applicable(g) || g.K > 64 * g.NB) return false;
+  const bool is_static = (g.flags & LANCE_INPUT_RANGE_STATIC) != 0, whole = g.K % 4 == 0;
+  if (g.NB == 1) return whole && g.K > (is_static ? 32 : 16);
+  return !is_static || (whole ? g.K > 16 : g.K > 32 && g.K <= 96);
+}
+
 bool conv_fused_pos_preferred(const Geo& g, bool x_aligned) {
   if (!conv_fused_pos_applicable(g)) return false;
   if (g.C <= 16) {
@@ -74,8 +85,7 @@ bool conv_fused_pos_preferred(const Geo& g, bool x_aligned) {
     if (is_nhwc(g) || !conv_fused_c16_applicable(g) || (!is_static && g.K > 256)) return true;
     return conv_fused_c16_us(g) + (is_static ? 0.0 : 5.0) >= 0.85 * (1.2 + 3.9 * pos::shape_of(g).cost);
   }
-  const bool pairs = is_nhwc(g) ? x_aligned && conv_fused_pairs_nhwc_applicable(g) &&
-                                      (g.NB == 2 || (g.K > 16 && g.K % 4 == 0))
+  const bool pairs = is_nhwc(g) ? x_aligned && nhwc_pairs_preferred(g)
                                 : conv_fused_pairs_applicable(g) && g.K <= 64 * g.NB && (g.NB == 2 || g.K > 16);
   const bool two = g.m == 2 && g.NB <= 2 && !pairs;
   return pos::shape_of(g).groups <= (two ? 512 : 256);

@@ -611,7 +611,7 @@ def test_nhwc_rows_of_whole_pairs(shape, static):
 _NHWC_PAIRS = [
     (1200, 20, 18, 13, 2, 1, 8), (900, 64, 20, 9, 3, 1, 8), (700, 40, 32, 9, 5, 1, 5), (420, 60, 21, 10, 11, 0, 8),
     (300, 64, 16, 8, 9, 2, 8), (300, 64, 704, 8, 9, 1, 8), (100, 44, 705, 9, 13, 1, 6), (40, 24, 1500, 9, 13, 1, 8),
-    (1200, 68, 18, 9, 2, 1, 8), (900, 128, 37, 9, 5, 0, 4), (260, 100, 130, 10, 11, 1, 8), (200, 128, 48, 8, 9, 2, 8),
+    (1800, 68, 18, 9, 2, 1, 8), (900, 128, 37, 9, 5, 0, 4), (260, 100, 130, 10, 11, 1, 8), (200, 128, 48, 8, 9, 2, 8),
     (60, 124, 768, 9, 13, 1, 8), (50, 72, 769, 9, 13, 1, 8), (1, 20, 17, 2, 262147, 1, 8),
 ]
 
@@ -656,6 +656,30 @@ def test_nhwc_of_four_byte_alignment_keeps_the_few_tile_plan():
     y2 = conv.forward(shifted)
     assert (y - y2).abs().max() <= 1e-5 * y.abs().max()
     assert _kernels(conv, shifted)[3] == "conv_fused_pos_kernel"
+
+
+# Between one and two workgroups of the few-tile plan per compute unit: (N, C, K, H, W), caller's ranges, whether the pair
+# kernel takes the layer
+@pytest.mark.parametrize("shape,static,pairs", [
+    ((2, 64, 704, 28, 28), False, False), ((2, 64, 704, 28, 28), True, False),     # several blocks of filters
+    ((1, 100, 1025, 38, 38), False, False), ((4, 68, 174, 47, 55), True, False), ((12, 88, 130, 40, 20), False, False),
+    ((16, 64, 65, 30, 30), False, False),
+    ((20, 64, 64, 37, 35), True, True), ((20, 64, 61, 37, 35), True, False), ((20, 64, 61, 37, 35), False, False),
+    ((20, 64, 32, 37, 35), True, False), ((20, 64, 20, 37, 35), False, True), ((20, 64, 16, 37, 35), False, False),
+    ((64, 128, 128, 14, 14), True, True), ((64, 128, 125, 14, 14), True, False), ((64, 128, 94, 14, 14), True, True),
+    ((64, 128, 125, 14, 14), False, True), ((20, 128, 33, 37, 35), True, True), ((20, 128, 31, 37, 35), True, False),
+    ((20, 128, 20, 37, 35), True, True), ((20, 128, 16, 37, 35), True, False), ((20, 128, 5, 37, 35), False, True),
+], ids=lambda v: str(v) if isinstance(v, bool) else "n%d_c%d_k%d_%dx%d" % v)
+def test_where_the_nhwc_pair_kernel_takes_over(shape, static, pairs):
+    from paper_2003_08646_amd import binding as B
+    N, C, K, H, W = shape
+    groups = -(-N * -(-H // 2) * -(-W // 2) // 16) * -(-K // 64)
+    assert 256 < groups <= 512
+    L = Wk.Layer("meet_nhwc", N, C, K, H, W, m=2, seed=900 + C)
+    conv, _ = _check_layer(L, flags=B.LANCE_LAYOUT_NHWC | (B.LANCE_INPUT_RANGE_STATIC if static else 0), staged=False,
+                           static_v_range=_range_of_another_batch(L) if static else None)
+    names = _kernels(conv, _zeros(conv, True))
+    assert names[3] == ("conv_fused_pairs_nhwc_%s_kernel" % ("c64" if C <= 64 else "c128") if pairs else "conv_fused_pos_kernel"), names
 
 
 # K, C, m, bits_w: filters of a last unit of four that is not whole, padding lanes, one, several and many units of 64 codes
