@@ -197,19 +197,19 @@ constexpr int fixed_lds() {
 }
 constexpr int kMaxLds = 80 * 1024;
 
-// Pixels in flight: of the next channels (NCHW), or the six columns of the lane's window (NHWC).
+// Pixels in flight: of the next channels (NCHW), or columns of the lane's windows (NHWC).
 template <class Phase, int AHEAD, bool NHWC>
 struct PixelsOf {
   typename Phase::Pixels buf[AHEAD + 1];
 };
 template <class Phase, int AHEAD>
 struct PixelsOf<Phase, AHEAD, true> {
-  v4f buf[Phase::kColumns][4];
+  v4f buf[Phase::kBuffers][4];
 };
 
 // NB: channel blocks.  B8: 8-bit codes.  FULL: all channels of the blocks exist (NCHW).  STREAM (NHWC): Y is stored
-// past the caches; NCHW asks a.stream.
-template <int NB, bool B8, bool FULL, bool NHWC, bool STREAM = false>
+// past the caches; NCHW asks a.stream.  ANY (NHWC): pairs of any two consecutive tiles.
+template <int NB, bool B8, bool FULL, bool NHWC, bool STREAM = false, bool ANY = false>
 __device__ __forceinline__ void conv_body(const CpArgs& a) {
   constexpr int M = 2, A = 4, E = 16;
   constexpr int kPairs = 32 / NB, kTiles = 2 * kPairs, kPlane = kTiles * 64;
@@ -217,7 +217,7 @@ __device__ __forceinline__ void conv_body(const CpArgs& a) {
   constexpr int kMostBlocks = (kMaxLds - fixed_lds<NB>()) / (kFilters * 16);  // 704 and 768 filters
   constexpr int kFragsAhead = 3;     // positions whose A fragments are in flight ahead of the products
   constexpr int kStepsAhead = 1;     // channels whose pixels are in flight ahead of the transform
-  using Phase = std::conditional_t<NHWC, dev::PairPhaseNhwc<B8, kPairs>, dev::PairPhase<B8, FULL, kPairs>>;
+  using Phase = std::conditional_t<NHWC, dev::PairPhaseNhwc<B8, kPairs, ANY>, dev::PairPhase<B8, FULL, kPairs>>;
   extern __shared__ char smem[];
   char* ring = smem;                                            // [NB][E][kTiles rows][64 B]
   int* cs_s = reinterpret_cast<int*>(smem + kCodeBytes);         // [E][kTiles] column sums (signed codes)
@@ -373,24 +373,28 @@ __device__ __forceinline__ void conv_body(const CpArgs& a) {
       }
     }
   }
-  // byte offsets of the pair's two output rows: of filter 0 (NCHW), or of their first pixels (NHWC)
-  unsigned y_off[2];
-  int cols = 4;  // pixels of a row that exist
-  {
-    const int p = blk * kPairs + pair;
+  // byte offsets of the pair's two output rows: of filter 0 (NCHW), or of their first pixels (NHWC; ANY: of each tile's)
+  constexpr int kRuns = ANY ? 2 : 1, kRunPixels = 4 / kRuns;
+  unsigned y_off[kRuns][2];
+  int cols[kRuns];  // pixels of a row that exist
+#pragma unroll
+  for (int run = 0; run < kRuns; run++) {
+    const int p = ANY ? 2 * (blk * kPairs + pair) + run : blk * kPairs + pair, most = ANY ? a.g.tiles : a.g.pairs;
     int q, ty, n;
-    dev::locate_pair<NHWC>(a.g, min(p, a.g.pairs - 1), &q, &ty, &n);
+    dev::locate_pair<NHWC>(a.g, min(p, most - 1), &q, &ty, &n);
     unsigned base, row;
     if constexpr (NHWC) {
-      cols = a.g.Wo - 4 * q;
+      cols[run] = a.g.Wo - kRunPixels * q;
       row = (unsigned)a.g.Wo * (unsigned)K * 4u;
-      base = ((unsigned)n * (unsigned)a.g.Ho + (unsigned)(2 * ty)) * row + (unsigned)(4 * q) * (unsigned)K * 4u;
+      base = ((unsigned)n * (unsigned)a.g.Ho + (unsigned)(2 * ty)) * row +
+             (unsigned)(kRunPixels * q) * (unsigned)K * 4u;
     } else {
+      cols[run] = 4;
       row = (unsigned)a.g.W * 4u;
       base = ((unsigned)n * (unsigned)K * plane_px + (unsigned)(2 * ty) * (unsigned)a.g.W + 4u * (unsigned)q) * 4u;
     }
-    y_off[0] = p < a.g.pairs ? base : kOob;
-    y_off[1] = p < a.g.pairs && 2 * ty + 1 < (NHWC ? a.g.Ho : a.g.H) ? base + row : kOob;
+    y_off[run][0] = p < most ? base : kOob;
+    y_off[run][1] = p < most && 2 * ty + 1 < (NHWC ? a.g.Ho : a.g.H) ? base + row : kOob;
   }
 
   for (int kb = kb0; kb < nkb; kb++) {
@@ -454,13 +458,13 @@ __device__ __forceinline__ void conv_body(const CpArgs& a) {
       for (int ab = 0; ab < M * M; ab++)
 #pragma unroll
         for (int s = 0; s < 2; s++) {
-          const int aa = ab >> 1, x = 2 * s + (ab & 1);
+          const int aa = ab >> 1, run = ANY ? s : 0, x = (ANY ? 0 : 2 * s) + (ab & 1);
           float o[4];
 #pragma unroll
           for (int r = 0; r < 4; r++) o[r] = (out[s][ab][r] + f4[r][ab]) + gp[s][ab];
-          dev::store_nhwc_k4<STREAM>(a.y, a.y_bytes, y_off[aa] + (unsigned)x * (unsigned)K * 4u, (unsigned)kfirst * 4u,
-                                     y_off[aa] != kOob && x < cols, K - kfirst, STREAM || (K & 3) == 0, o[0], o[1],
-                                     o[2], o[3]);
+          dev::store_nhwc_k4<STREAM>(a.y, a.y_bytes, y_off[run][aa] + (unsigned)x * (unsigned)K * 4u,
+                                     (unsigned)kfirst * 4u, y_off[run][aa] != kOob && x < cols[run], K - kfirst,
+                                     STREAM || (K & 3) == 0, o[0], o[1], o[2], o[3]);
         }
       continue;
     }
@@ -478,7 +482,7 @@ __device__ __forceinline__ void conv_body(const CpArgs& a) {
 #pragma unroll
             for (int b = 0; b < M; b++)
               o[2 * s + b] = (out[s][2 * aa + b][r] + f4[2 * aa + b]) + gp[s][2 * aa + b];
-          const unsigned off = k_ok && y_off[aa] != kOob ? y_off[aa] + koff : kOob;
+          const unsigned off = k_ok && y_off[0][aa] != kOob ? y_off[0][aa] + koff : kOob;
           store_row<decltype(stream)::value>(a.y, a.y_bytes, off, o[0], o[1], o[2], o[3]);
         }
       }
@@ -495,8 +499,9 @@ template <bool B8, bool FULL>
 __global__ __launch_bounds__(kThreads, 4) void conv_fused_pairs_c128_kernel(const CpArgs a) {
   conv_body<2, B8, FULL, false>(a);
 }
-// The NHWC kernels of the plans of one and of two channel blocks.  STREAM is a parameter of the kernel: with both
-// kinds of stores in one the cached ones took up to 2 % longer.
+// The NHWC kernels of the plans of one and of two channel blocks, on pairs of a tile row and (conv_fused_any_pairs) of any
+// two tiles.  STREAM is a parameter of the kernel: with both kinds of stores in one the cached ones took up to 2 %
+// longer.
 template <bool B8, bool STREAM>
 __global__ __launch_bounds__(kThreads, 4) void conv_fused_pairs_nhwc_c64_kernel(const CpArgs a) {
   conv_body<1, B8, false, true, STREAM>(a);
@@ -504,6 +509,14 @@ __global__ __launch_bounds__(kThreads, 4) void conv_fused_pairs_nhwc_c64_kernel(
 template <bool B8, bool STREAM>
 __global__ __launch_bounds__(kThreads, 4) void conv_fused_pairs_nhwc_c128_kernel(const CpArgs a) {
   conv_body<2, B8, false, true, STREAM>(a);
+}
+template <bool B8, bool STREAM>
+__global__ __launch_bounds__(kThreads, 4) void conv_fused_any_pairs_nhwc_c64_kernel(const CpArgs a) {
+  conv_body<1, B8, false, true, STREAM, true>(a);
+}
+template <bool B8, bool STREAM>
+__global__ __launch_bounds__(kThreads, 4) void conv_fused_any_pairs_nhwc_c128_kernel(const CpArgs a) {
+  conv_body<2, B8, false, true, STREAM, true>(a);
 }
 
 // LDS of a workgroup with the terms of K filters.
@@ -514,6 +527,10 @@ int lds_bytes(int K) {
 
 // Pairs in a tile row.
 int pairs_per_row(const Geo& g) { return is_nhwc(g) ? (g.tw + 1) / 2 : g.W / 4; }
+
+// Filters of a workgroup: those LDS has room for the terms of.
+template <int NB>
+constexpr int most_filters() { return (kMaxLds - fixed_lds<NB>()) / (64 * NB * 16) * (64 * NB); }
 
 // Bytes from the first image of a block to the end of the last one that its pairs can touch; NHWC: of X.
 long long reach_bytes(const Geo& g) {
@@ -528,7 +545,7 @@ hipError_t launch_kernel(void (*kern)(CpArgs), const CpArgs& a, const char* name
   hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), kMaxLds);
   if (e != hipSuccess) return e;
   note_kernel(name);
-  constexpr int kMost = (kMaxLds - fixed_lds<NB>()) / (64 * NB * 16) * (64 * NB);  // filters of a workgroup
+  constexpr int kMost = most_filters<NB>();
   const dim3 grid((a.g.pairs + 32 / NB - 1) / (32 / NB), (a.K + kMost - 1) / kMost);
   kern<<<grid, kThreads, lds_bytes<NB>(a.K < kMost ? a.K : kMost), s>>>(a);
   return hipGetLastError();
@@ -549,6 +566,10 @@ hipError_t launch_blocks(const Geo& g, const CpArgs& a, hipStream_t s) {
 
 template <bool B8, bool STREAM>
 hipError_t launch_nhwc(const Geo& g, const CpArgs& a, hipStream_t s) {
+  if (conv_fused_any_pairs(g))
+    return g.NB == 1
+               ? launch_kernel<1>(conv_fused_any_pairs_nhwc_c64_kernel<B8, STREAM>, a, "conv_fused_any_pairs_nhwc_c64_kernel", s)
+               : launch_kernel<2>(conv_fused_any_pairs_nhwc_c128_kernel<B8, STREAM>, a, "conv_fused_any_pairs_nhwc_c128_kernel", s);
   return g.NB == 1 ? launch_kernel<1>(conv_fused_pairs_nhwc_c64_kernel<B8, STREAM>, a, "conv_fused_pairs_nhwc_c64_kernel", s)
                    : launch_kernel<2>(conv_fused_pairs_nhwc_c128_kernel<B8, STREAM>, a, "conv_fused_pairs_nhwc_c128_kernel", s);
 }
@@ -559,9 +580,10 @@ bool divisions_exact(long long pairs, long long npr, long long th) {
 
 CpArgs make_args(const Geo& g, const float* x, const int8_t* uq, const float* u_range, const int32_t* u_rowsum,
                  const float* partial, int count, float* v_range, float* y, bool stream) {
-  const int npr = pairs_per_row(g), pairs = g.N * g.th * npr;
-  return CpArgs{{x, g.C, g.H, g.W, g.Ho, g.Wo, g.pad, g.th, npr, pairs, g.bits, div_magic(g.th), div_magic(npr),
-                 divisions_exact(pairs, npr, g.th) ? 1 : 0, (unsigned)reach_bytes(g)},
+  const bool any = is_nhwc(g) && conv_fused_any_pairs(g);
+  const int npr = any ? g.tw : pairs_per_row(g), pairs = any ? (g.P + 1) / 2 : g.N * g.th * npr;
+  return CpArgs{{x, g.C, g.H, g.W, g.Ho, g.Wo, g.pad, g.th, npr, pairs, g.bits, g.P, div_magic(g.th), div_magic(npr),
+                 divisions_exact(any ? g.P : pairs, npr, g.th) ? 1 : 0, (unsigned)reach_bytes(g)},
                 uq, u_range, u_rowsum, partial, v_range, y, count,
                 (g.flags & LANCE_RANGE_PER_TENSOR) ? 1 : 0, (g.flags & LANCE_INPUT_RANGE_STATIC) ? 1 : 0,
                 g.bits_w, g.K, (unsigned)((size_t)g.E * g.NB * g.K * 64),
@@ -569,6 +591,22 @@ CpArgs make_args(const Geo& g, const float* x, const int8_t* uq, const float* u_
 }
 
 }  // namespace
+
+// NHWC: pairs of any two consecutive tiles, where that takes fewer rounds of one workgroup per compute unit.  With an
+// odd number of tile columns every row of pairs ends in half a pair, with one column all pairs are halves; a pair of any
+// two tiles costs 32 pixel loads and 8 column passes instead of 24 and 6.  Caller's ranges, pairs of a row / any pairs / four
+// tiles per thread: N3571 128 -> 128 14x1 53.6 / 35.5 / 41.8 us, N96 120 -> 374 18x18 (270 and 243 workgroups) 70.4 / 44.2 / 51.0,
+// N2940 128 -> 620 5x6 137.9 / 123.0 / 130.5.  Of 1500 random layers with more than two workgroups of the few-tile plan per
+// compute unit 301 take this form; 0.05 % over the better form's time on average.  With the same number of rounds it
+// is 2 % (300 filters and more) to 7 % (up to 16) slower.  Many filters that are no multiple of four are bound by 4-byte
+// stores, for which more workgroups are the better (N6382 44 -> 629 6x6 401 / 434, N232 128 -> 3943 6x5 106 / 120): not there, but with one tile column.
+bool conv_fused_any_pairs(const Geo& g) {
+  if (g.K > 512 && g.K % 4 != 0 && g.tw > 1) return false;
+  const long long per_wg = 32 / g.NB, most = g.NB == 1 ? most_filters<1>() : most_filters<2>();
+  const long long shares = (g.K + most - 1) / most;
+  auto rounds = [&](long long pairs) { return ((pairs + per_wg - 1) / per_wg * shares + 255) / 256; };
+  return rounds((g.P + 1LL) / 2) < rounds((long long)g.N * g.th * pairs_per_row(g));
+}
 
 bool conv_fused_pairs_applicable(const Geo& g) {
   if (g.m != 2 || g.CB != 64 || g.NB > 2 || is_nhwc(g) || is_packed(g)) return false;

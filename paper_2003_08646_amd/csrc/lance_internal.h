@@ -207,6 +207,7 @@ hipError_t launch_conv_fused_pairs(const Geo& g, const float* x, const int8_t* u
 // The form of the two plans above on NHWC tensors; x 16-byte aligned.
 // stream: Y is stored past the caches (only where stores_past_caches).
 bool conv_fused_pairs_nhwc_applicable(const Geo& g);
+bool conv_fused_any_pairs(const Geo& g);  // whether it pairs any two tiles instead of those of a row
 hipError_t launch_conv_fused_pairs_nhwc(const Geo& g, const float* x, const int8_t* uq, const float* u_range,
                                         const int32_t* u_rowsum, const float* partial, int count,
                                         float* v_range, float* y, bool stream, hipStream_t s);

@@ -27,12 +27,13 @@ namespace dev {
 struct PairGeo {
   const float* x;
   int C, H, W, Ho, Wo, pad, th, npr, pairs, bits;  // npr: pairs per tile row; pairs: of the whole batch
+  int tiles;       // of the whole batch (pairs of any two tiles, where npr is the tiles per row)
   unsigned th_magic, npr_magic;
   int exact;       // fast_div is exact for every pair (false only for NHWC rows of very many pairs)
   unsigned reach;  // extent of the buffer descriptors: bytes from a plane of a block's first image
 };
 
-// Pair p of the batch: pair q of tile row ty of image n.
+// Pair (or tile) p of the batch: pair q of tile row ty of image n.
 template <bool NHWC>
 __device__ __forceinline__ void locate_pair(const PairGeo& g, int p, int* q, int* ty, int* n) {
   const bool fast = !NHWC || g.exact;
@@ -198,16 +199,20 @@ struct PairPhase {
 // column: a column goes through B^T d once for both tiles, and a position's four codes are a whole dword that
 // goes to LDS at once, so no codes wait in registers.  Pixels outside the image have an offset beyond
 // the buffer: one add per load and nothing after it.
+// ANY: the pair is any two consecutive tiles of the batch, each with its own window of four columns (32 loads, eight
+// column passes), so that no tile row ends in half a pair.
 //
 // Called by all 512 threads.  LDS rows and chunks as above.
-template <bool B8, int PAIRS>
+template <bool B8, int PAIRS, bool ANY>
 struct PairPhaseNhwc {
   typedef float f4 __attribute__((ext_vector_type(4)));
-  static constexpr int E = 16, kTiles = 2 * PAIRS, kColumns = 6, kEarly = 4;
+  static constexpr int E = 16, kTiles = 2 * PAIRS, kEarly = 4;
+  static constexpr int kBuffers = 6;                          // pixel columns in flight or in use
+  static constexpr int kWindows = ANY ? 2 : 1, kColumns = ANY ? 4 : 6;  // columns of a window
   static constexpr unsigned kOutside = 0xFFFFFFF0u;  // beyond any X (the whole of which is one buffer)
 
-  unsigned rowoff[4], coloff[kColumns];  // rows that do not exist have kOutside
-  bool cok[kColumns];
+  unsigned rowoff[kWindows][4], coloff[kWindows][kColumns];  // rows that do not exist have kOutside
+  bool cok[kWindows][kColumns];
   char* dst;         // the lane's dword of position 0 of the left tile
   unsigned mask;     // all ones where the lane's channels exist
 
@@ -216,30 +221,35 @@ struct PairPhaseNhwc {
   __device__ __forceinline__ void setup(const PairGeo& g, int block, int pair, int cblk, int lane, char* ring) {
     const int p0 = block * PAIRS;
     const unsigned px = (unsigned)g.C * 4u, row_bytes = (unsigned)g.W * px;
-    int q, ty, n;
-    locate_pair<true>(g, min(p0 + pair, g.pairs - 1), &q, &ty, &n);
     const int j = lane & 15, c = 64 * cblk + 4 * j;
     mask = c < g.C ? 0xFFFFFFFFu : 0u;
 #pragma unroll
-    for (int r = 0; r < 4; r++) {
-      const int y = 2 * ty - g.pad + r;
-      rowoff[r] = y >= 0 && y < g.H ? ((unsigned)n * (unsigned)g.H + (unsigned)y) * row_bytes : kOutside;
-    }
+    for (int w = 0; w < kWindows; w++) {
+      int q, ty, n;
+      locate_pair<true>(g, ANY ? min(2 * (p0 + pair) + w, g.tiles - 1) : min(p0 + pair, g.pairs - 1), &q, &ty, &n);
 #pragma unroll
-    for (int s = 0; s < kColumns; s++) {
-      const int x = 4 * q - g.pad + s;
-      cok[s] = x >= 0 && x < g.W;
-      coloff[s] = (unsigned)x * px + (unsigned)min(c, g.C - 4) * 4u;
+      for (int r = 0; r < 4; r++) {
+        const int y = 2 * ty - g.pad + r;
+        rowoff[w][r] = y >= 0 && y < g.H ? ((unsigned)n * (unsigned)g.H + (unsigned)y) * row_bytes : kOutside;
+      }
+#pragma unroll
+      for (int s = 0; s < kColumns; s++) {
+        const int x = (ANY ? 2 : 4) * q - g.pad + s;
+        cok[w][s] = x >= 0 && x < g.W;
+        coloff[w][s] = (unsigned)x * px + (unsigned)min(c, g.C - 4) * 4u;
+      }
     }
     dst = ring + (unsigned)pair * 64u + (unsigned)(((j >> 2) ^ row_swizzle_mfma32(pair)) * 16 + 4 * (j & 3));
   }
 
+  // pixel column s of the pair (ANY: 0 .. 3 of the first tile, 4 .. 7 of the second)
   __device__ __forceinline__ void issue(const PairGeo& g, int s, f4 (&w)[4]) const {
+    const int win = s / kColumns, i = s % kColumns;
     const __amdgpu_buffer_rsrc_t rsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(g.x), 0, g.reach, 0x00020000);
 #pragma unroll
     for (int r = 0; r < 4; r++) {
-      const unsigned off = cok[s] && rowoff[r] != kOutside ? rowoff[r] + coloff[s] : kOutside;
+      const unsigned off = cok[win][i] && rowoff[win][r] != kOutside ? rowoff[win][r] + coloff[win][i] : kOutside;
       w[r] = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0));
     }
   }
@@ -280,8 +290,34 @@ struct PairPhaseNhwc {
   // All codes of the pair.  w: the first kEarly pixel columns, requested.  late(): requests what the caller
   // needs next, when half of the columns' registers are free.
   template <class Late>
-  __device__ __forceinline__ void run(const PairGeo& g, f4 (&w)[kColumns][4], const float (&qmn)[E],
+  __device__ __forceinline__ void run(const PairGeo& g, f4 (&w)[kBuffers][4], const float (&qmn)[E],
                                       const float (&qinv)[E], Late&& late) const {
+    if constexpr (ANY) {
+      issue(g, 4, w[4]);
+#pragma unroll
+      for (int s = 0; s < 3; s++) column(w[s]);
+      codes<false>(g, 0, 0, w[0], w[2], qmn, qinv);
+      codes<true>(g, 0, 1, w[1], w[2], qmn, qinv);
+      codes<false>(g, 0, 2, w[2], w[1], qmn, qinv);
+      __builtin_amdgcn_sched_barrier(0);
+      issue(g, 5, w[5]);
+      issue(g, 6, w[0]);
+      column(w[3]);
+      codes<false>(g, 0, 3, w[1], w[3], qmn, qinv);
+      __builtin_amdgcn_sched_barrier(0);
+      issue(g, 7, w[2]);
+      column(w[4]);
+      column(w[5]);
+      column(w[0]);
+      codes<false>(g, 1, 0, w[4], w[0], qmn, qinv);
+      __builtin_amdgcn_sched_barrier(0);
+      late();
+      codes<true>(g, 1, 1, w[5], w[0], qmn, qinv);
+      codes<false>(g, 1, 2, w[0], w[5], qmn, qinv);
+      column(w[2]);
+      codes<false>(g, 1, 3, w[5], w[2], qmn, qinv);
+      return;
+    }
     issue(g, 4, w[4]);
 #pragma unroll
     for (int s = 0; s < 3; s++) column(w[s]);

@@ -609,14 +609,24 @@ def test_nhwc_rows_of_whole_pairs(shape, static):
 # are no multiple of anything, filters that are no multiple of four and of sixteen (streamed stores), padding lanes,
 # one share of the filters, one more filter, three shares; rows of so many pairs that multiplying does not divide them
 _NHWC_PAIRS = [
-    (1200, 20, 18, 13, 2, 1, 8), (900, 64, 20, 9, 3, 1, 8), (700, 40, 32, 9, 5, 1, 5), (420, 60, 21, 10, 11, 0, 8),
+    (500, 20, 130, 13, 2, 1, 8), (900, 64, 20, 9, 3, 1, 8), (700, 40, 32, 9, 5, 1, 5), (420, 60, 21, 10, 11, 0, 8),
     (300, 64, 16, 8, 9, 2, 8), (300, 64, 704, 8, 9, 1, 8), (100, 44, 705, 9, 13, 1, 6), (40, 24, 1500, 9, 13, 1, 8),
-    (1800, 68, 18, 9, 2, 1, 8), (900, 128, 37, 9, 5, 0, 4), (260, 100, 130, 10, 11, 1, 8), (200, 128, 48, 8, 9, 2, 8),
+    (500, 68, 260, 9, 2, 1, 8), (900, 128, 37, 9, 5, 0, 4), (260, 100, 130, 10, 11, 1, 8), (200, 128, 48, 8, 9, 2, 8),
     (60, 124, 768, 9, 13, 1, 8), (50, 72, 769, 9, 13, 1, 8), (1, 20, 17, 2, 262147, 1, 8),
 ]
 
 
-@pytest.mark.parametrize("shape", _NHWC_PAIRS, ids=lambda s: "n%d_c%d_k%d_%dx%d_p%d_b%d" % s)
+# The same with pairs of any two tiles, where that takes fewer rounds of workgroups (one per compute unit): one tile column,
+# three, five and nine (pairs across tile rows and images), half a pair at the end, no and wide padding, two shares of the
+# filters, a row of so many tiles that multiplying does not divide them
+_NHWC_ANY_PAIRS = [
+    (1801, 20, 18, 13, 1, 1, 8), (1801, 64, 17, 13, 2, 1, 5), (1801, 68, 18, 9, 2, 1, 8), (985, 40, 32, 9, 5, 1, 8),
+    (683, 60, 21, 10, 11, 0, 8), (277, 128, 130, 18, 18, 1, 8), (1601, 100, 64, 5, 6, 1, 6), (274, 44, 720, 9, 9, 1, 8),
+    (2801, 128, 36, 5, 3, 0, 8), (650, 68, 130, 5, 3, 2, 4), (1, 20, 17, 10, 58981, 1, 8),
+]
+
+
+@pytest.mark.parametrize("shape", _NHWC_PAIRS + _NHWC_ANY_PAIRS, ids=lambda s: "n%d_c%d_k%d_%dx%d_p%d_b%d" % s)
 @pytest.mark.parametrize("option", ["dynamic", "static", "per_tensor"])
 def test_nhwc_pairs_of_tiles(shape, option):
     from paper_2003_08646_amd import binding as B
@@ -626,7 +636,8 @@ def test_nhwc_pairs_of_tiles(shape, option):
     conv, _ = _check_layer(L, flags=B.LANCE_LAYOUT_NHWC | flags, staged=False,
                            static_v_range=_range_of_another_batch(L) if option == "static" else None)
     names = _kernels(conv, _zeros(conv, True))
-    assert names[3] == "conv_fused_pairs_nhwc_%s_kernel" % ("c64" if C <= 64 else "c128"), names
+    kernel = "conv_fused_any_pairs_nhwc_%s_kernel" if shape in _NHWC_ANY_PAIRS else "conv_fused_pairs_nhwc_%s_kernel"
+    assert names[3] == kernel % ("c64" if C <= 64 else "c128"), names
 
 
 # N, C, H, W, pad: NHWC range pass on pairs of tile columns (at least 4096 strips): two and three columns, an odd
@@ -666,8 +677,9 @@ def test_nhwc_of_four_byte_alignment_keeps_the_few_tile_plan():
     ((16, 64, 65, 30, 30), False, False),
     ((20, 64, 64, 37, 35), True, True), ((20, 64, 61, 37, 35), True, False), ((20, 64, 61, 37, 35), False, False),
     ((20, 64, 32, 37, 35), True, False), ((20, 64, 20, 37, 35), False, True), ((20, 64, 16, 37, 35), False, False),
-    ((64, 128, 128, 14, 14), True, True), ((64, 128, 125, 14, 14), True, False), ((64, 128, 94, 14, 14), True, True),
-    ((64, 128, 125, 14, 14), False, True), ((20, 128, 33, 37, 35), True, True), ((20, 128, 31, 37, 35), True, False),
+    ((64, 128, 128, 14, 14), True, True), ((64, 128, 125, 14, 14), True, False), ((64, 128, 65, 14, 14), True, False),
+    ((64, 128, 125, 14, 14), False, True), ((20, 128, 33, 37, 35), True, True), ((20, 128, 62, 37, 35), True, True), ((20, 128, 31, 37, 35), True, False),
+    ((896, 84, 53, 6, 6), True, False), ((896, 84, 12, 6, 6), False, False),      # pairs of any two tiles
     ((20, 128, 20, 37, 35), True, True), ((20, 128, 16, 37, 35), True, False), ((20, 128, 5, 37, 35), False, True),
 ], ids=lambda v: str(v) if isinstance(v, bool) else "n%d_c%d_k%d_%dx%d" % v)
 def test_where_the_nhwc_pair_kernel_takes_over(shape, static, pairs):
