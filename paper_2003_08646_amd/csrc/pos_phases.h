@@ -102,8 +102,11 @@ struct Consts {
       vmax = given[2 * e + 1];
       if (!is_static) {
 #pragma unroll
-        for (int u = 0; u < kBatch; u++)  // (past the last record: the last one again)
-          rec[u] = a.partial[(size_t)min(tid / kCols + u * kGroups, a.count - 1) * kCols + col];
+        for (int u = 0; u < kBatch; u++) {  // (past the last record: the last one again, or none of the batch)
+          rec[u] = col & 1 ? -INFINITY : INFINITY;
+          if (u * kGroups < a.count)
+            rec[u] = a.partial[(size_t)min(tid / kCols + u * kGroups, a.count - 1) * kCols + col];
+        }
       }
     }
   };

@@ -705,7 +705,7 @@ def test_filter_transform_units(K, C, m, bits_w, flags):
 
 
 # N, C, K, H, W, pad, m, bits, nhwc: few-tile plans with one range for the whole tensor, reduced by every workgroup: one,
-# two and four groups of filters on 16 and 8 waves, F(4x4), two kernels; more records than a thread requests at once
+# two and four groups of filters on 16 and 8 waves, F(4x4), two kernels
 @pytest.mark.parametrize("shape", [(2, 20, 10, 9, 8, 1, 2, 8, False), (20, 33, 60, 14, 14, 1, 2, 6, False),
                                    (45, 40, 70, 14, 15, 1, 2, 8, False), (33, 18, 70, 15, 16, 1, 4, 5, False),
                                    (40, 30, 40, 16, 13, 1, 4, 8, True), (2, 330, 20, 9, 10, 1, 4, 8, False),
@@ -718,6 +718,27 @@ def test_position_parallel_per_tensor(shape):
     conv, _ = _check_layer(L, flags=B.LANCE_RANGE_PER_TENSOR | (B.LANCE_LAYOUT_NHWC if nhwc else 0), staged=False)
     names = _kernels(conv, _zeros(conv, nhwc))
     assert names[1] == "" and names[3] in ("conv_fused_pos_kernel", "gemm_pos_kernel"), names
+
+
+# N, C, K, H, W, m, batch: the same plans with more records of the range pass than the threads of a workgroup request at
+# once (batch): 8 waves, F(4x4), the quantize pass of the plans in two kernels; whole turns and a part of one
+_MANY_RECORDS = [(10, 128, 200, 27, 27, 2, 128), (9, 128, 200, 27, 29, 2, 128), (80, 128, 40, 15, 15, 4, 80),
+                 (60, 120, 40, 15, 13, 4, 80), (9, 600, 20, 9, 7, 2, 64), (10, 330, 20, 9, 10, 4, 24)]
+
+
+@pytest.mark.parametrize("shape", _MANY_RECORDS, ids=lambda s: "n%d_c%d_k%d_%dx%d_m%d_%d" % s)
+@pytest.mark.parametrize("per_tensor", [False, True], ids=["per_position", "per_tensor"])
+def test_position_parallel_with_many_records(shape, per_tensor):
+    from paper_2003_08646_amd import binding as B
+    N, C, K, H, W, m, batch = shape
+    blocks = -(-N * -(-H // m) * -(-W // m) // 64)                     # of the lane-per-tile range pass:
+    chunk = -(-C // min(512 // blocks, -(-C // 8)))                    # channels of a work unit,
+    records = -(-blocks * -(-C // (-(-chunk // 4) * 4)) // 2)          # two units to a workgroup and record
+    assert records > batch
+    L = Wk.Layer("records", N, C, K, H, W, m=m, seed=950 + C)
+    conv, _ = _check_layer(L, flags=B.LANCE_RANGE_PER_TENSOR if per_tensor else 0, staged=False)
+    names = _kernels(conv, _zeros(conv, False))
+    assert names[:2] == ["input_range_kernel", ""] and names[3] in ("conv_fused_pos_kernel", "gemm_pos_kernel"), names
 
 
 # N, C, K, H, W, pad, bits, nhwc: the small-channel kernel with two and four waves to 64 tiles: one, two, three and many tiles
