@@ -25,6 +25,7 @@
 #include "lance_device.h"
 #include "lance_internal.h"
 #include "nhwc_window.h"
+#include "xcd_range.h"
 
 namespace lance {
 namespace {
@@ -39,7 +40,9 @@ struct NhArgs {
   const float* qparams;  // quantize pass: [E][2] = {min, inv}
   float* partial;        // range pass: records [grid][E][2]
   int C, H, W, pad, th, tw, P, CB, NB, Q, bits;
-  int R, strips, units;  // rolling range pass: tile rows per strip, strips per image column, work units
+  int R, strips, units;  // rolling range pass: tile rows per strip, strips per image column, work units,
+  int each, rest;        // sixteens of them for each workgroup and left over, divisor of the grid (xcd_range.h)
+  unsigned grid_magic;
   int groups;        // P * NB
   unsigned x_bytes;  // size of X (used by the 16-byte loads: below 0xFFFFFFF0 then)
   int packed;        // quantize pass: vq is [E][NB][P][32], two 4-bit codes per byte
@@ -269,8 +272,10 @@ __global__ __launch_bounds__(kThreads, 2) void input_nhwc_range_roll_kernel(cons
   for (int e = 0; e < E; e++) { mn[e] = INFINITY; mx[e] = -INFINITY; }
   const unsigned px = (unsigned)a.C * 4u;
   const int npr = (a.tw + 1) / 2;
-  for (int u = dev::xcd_contiguous(blockIdx.x, gridDim.x) * kGroupsPerWg + (tid >> 4); u < a.units;
-       u += gridDim.x * kGroupsPerWg) {
+  const dev::XcdRange range(a.each, a.rest, a.grid_magic, blockIdx.x, gridDim.x);
+  for (int i = range.first; i < range.end; i += range.step) {
+    const int u = i * kGroupsPerWg + (tid >> 4);
+    if (u >= a.units) break;
     int t = u / a.NB;
     const int cb = u - t * a.NB;
     const int tx = min(2 * (t % npr), a.tw - 2); t /= npr;
@@ -600,6 +605,9 @@ hipError_t launch_input_nhwc_range(const Geo& g, const float* x, float* partial,
     if (grid > kMaxRangeGroups) grid = kMaxRangeGroups;
     if (grid > wgs) grid = wgs;
     *groups_out = grid;
+    a.each = wgs / grid;
+    a.rest = wgs % grid;
+    a.grid_magic = div_magic(grid);
     kern<<<grid, kThreads, 0, s>>>(a);
     return hipGetLastError();
   };
