@@ -252,33 +252,34 @@ __global__ __launch_bounds__(kThreads, 2) void input_nhwc_range_kernel(const NhA
   write_range_record<E>(mn, mx, red, a.partial, tid);
 }
 
-// Range pass of F(2x2,3x3) layers whose channels come four at a time (16-byte loads) and whose tile rows
-// hold at least two tiles.  The pass above issues 16 loads per tile, of which a quarter of the bytes
-// are new.  Here a lane group (16 lanes, four channels each) walks down a strip of R tile rows of two
-// neighbouring tile columns: the two pixel rows a tile shares with the one below stay in registers,
-// and the two tiles share two of six pixel columns, so two tiles cost two new rows of six pixels (6 loads
-// per tile and two more rows per strip), requested before the current tiles are transformed; the column
-// pass is shared too.  With an odd number of tile columns the last pair starts one column earlier (minima
-// and maxima do not notice).  Work unit = (image, strip, pair of tile columns, channel block), pairs and
-// blocks of a wave next to each other, each die taking neighbouring units.   Against one
-// tile column and strips of four rows, X in the last-level cache / from memory: N64 C128 56x56 29.3 / 33.2 ->
-// 24.3 / 27.6 us, N16 C64 224x224 51.7 / 62.5 -> 42.2 / 59.4, N128 C64 32x32 12.4 / 17.1 -> 10.9 / 14.3.
+// Range pass of F(2x2,3x3) layers whose channels come four at a time (16-byte loads).  The pass above issues 16
+// loads per tile, of which a quarter of the bytes are new.  Here a lane group (16 lanes, four channels each) walks down a
+// strip of R tile rows of one or two neighbouring tile columns (TILES): the two pixel rows a tile shares with
+// the one below stay in registers, and two tiles share two of six pixel columns, so two tiles cost two new rows of six
+// pixels (6 loads per tile instead of 8, and two more rows per strip), requested before the current tiles are transformed;
+// the column pass is shared too.  With an odd number of tile columns the last pair starts one column earlier (minima
+// and maxima do not notice).  Work unit = (image, strip, tile columns, channel block), columns and blocks of a wave next
+// to each other, each die taking neighbouring units.   Pairs against one tile column and strips of four rows, X in
+// the last-level cache / from memory: N64 C128 56x56 29.3 / 33.2 -> 24.3 / 27.6 us, N16 C64 224x224 51.7 / 62.5 -> 42.2 / 59.4,
+// N128 C64 32x32 12.4 / 17.1 -> 10.9 / 14.3.  One column instead of pairs on narrow rows (X in the last-level cache): N1297
+// C128 6x6 11.9 -> 9.1, N331 C512 6x6 12.7 -> 10.2; instead of the pass above: N3571 C64 14x2 12.3 -> 10.0.
+template <int TILES>
 __global__ __launch_bounds__(kThreads, 2) void input_nhwc_range_roll_kernel(const NhArgs a) {
-  constexpr int M = 2, A = 4, E = 16, kCols = A + M;
+  constexpr int M = 2, A = 4, E = 16, kCols = A + (TILES - 1) * M;
   __shared__ float red[kThreads / 64][E][2];
   const int tid = threadIdx.x, cl = tid & 15;
   float mn[E], mx[E];
 #pragma unroll
   for (int e = 0; e < E; e++) { mn[e] = INFINITY; mx[e] = -INFINITY; }
   const unsigned px = (unsigned)a.C * 4u;
-  const int npr = (a.tw + 1) / 2;
+  const int npr = (a.tw + TILES - 1) / TILES;
   const dev::XcdRange range(a.each, a.rest, a.grid_magic, blockIdx.x, gridDim.x);
   for (int i = range.first; i < range.end; i += range.step) {
     const int u = i * kGroupsPerWg + (tid >> 4);
     if (u >= a.units) break;
     int t = u / a.NB;
     const int cb = u - t * a.NB;
-    const int tx = min(2 * (t % npr), a.tw - 2); t /= npr;
+    const int tx = min(TILES * (t % npr), a.tw - TILES); t /= npr;
     const int st = t % a.strips, n = t / a.strips;
     const int c0 = cb * a.CB + 4 * cl;
     const bool real = cl < a.Q && c0 < a.C;  // C is a multiple of 4: all four channels or none
@@ -306,7 +307,27 @@ __global__ __launch_bounds__(kThreads, 2) void input_nhwc_range_roll_kernel(cons
         load_row((ty + 1) * M - a.pad + 2, nxt[0]);
         load_row((ty + 1) * M - a.pad + 3, nxt[1]);
       }
-      if (real) {
+      if constexpr (TILES == 1) {
+#pragma unroll
+        for (int hf = 0; hf < 2; hf++) {  // two channels at a time: three-operand minima and maxima
+          float d[2][A][A];
+#pragma unroll
+          for (int i = 0; i < 2; i++) {
+#pragma unroll
+            for (int r = 0; r < A; r++)
+#pragma unroll
+              for (int s = 0; s < A; s++) d[i][r][s] = w[r][s][2 * hf + i];
+            dev::input_tile_transform<M>(d[i]);
+          }
+          if (real) {
+#pragma unroll
+            for (int e = 0; e < E; e++) {
+              mn[e] = fminf(mn[e], fminf(d[0][e / A][e % A], d[1][e / A][e % A]));
+              mx[e] = fmaxf(mx[e], fmaxf(d[0][e / A][e % A], d[1][e / A][e % A]));
+            }
+          }
+        }
+      } else if (real) {
 #pragma unroll
         for (int q = 0; q < 4; q++) {  // one channel of both tiles: three-operand minima and maxima
           float t6[A][kCols];
@@ -557,21 +578,29 @@ hipError_t launch_input_nhwc_range(const Geo& g, const float* x, float* partial,
     return hipGetLastError();
   }
   const bool vec = vec_loads(g, x);
-  // (small layers keep the tile-per-group pass: with fewer than 4096 strips of four tiles the chip is not full)
-  const bool roll = g.m == 2 && vec && g.tw >= 2 &&
+  // (small layers keep the tile-per-group pass: with fewer than 4096 strips of four tiles the chip is not full; so do
+  // images of one tile, which have nothing to share: N47694 C24 1x2 12.8 / 14.4 us)
+  const bool roll = g.m == 2 && vec && g.th * g.tw > 1 &&
                     (long long)g.N * g.tw * g.NB * ((g.th + 3) / 4) >= 4096;
+  bool pairs = false;  // two tile columns per lane group
   if (roll) {
-    // Tile rows per strip: the smallest (rounds of 512 resident workgroups) x (pixel rows of a strip, and
-    // about four more that its first loads take).
-    const long long cols = (long long)g.N * ((g.tw + 1) / 2) * g.NB;
+    // Tile columns and rows of a strip: the smallest (rounds of 512 resident workgroups) x (pixel rows of a strip, and
+    // about four more that its first loads take); a row of one column counts 0.85 of a row of two, and its first loads two
+    // rows less, or three where pairs overlap (fitted).  On 700 random layers this takes 1.04 of the best choice's time
+    // on average; pairs alone took up to 1.5 times that with three tile columns.
+    const int odd = g.tw % 2 && g.th > 1;
     long long best = 0;
-    for (int R = 2; R <= 32; R++) {
-      const int strips = (g.th + R - 1) / R;
-      const long long wgs = (cols * strips + kGroupsPerWg - 1) / kGroupsPerWg;
-      const long long cost = (wgs + 511) / 512 * (2 * (R < g.th ? R : g.th) + 6);
-      if (best == 0 || cost < best) { best = cost; a.R = R; a.strips = strips; }
-      if (R >= g.th) break;
+    for (int tiles = g.tw >= 2 ? 2 : 1; tiles >= 1; tiles--) {
+      const long long cols = (long long)g.N * ((g.tw + tiles - 1) / tiles) * g.NB;
+      for (int R = 2; R <= 32; R++) {
+        const int strips = (g.th + R - 1) / R, rows = 2 * (R < g.th ? R : g.th);
+        const long long wgs = (cols * strips + kGroupsPerWg - 1) / kGroupsPerWg;
+        const long long cost = (wgs + 511) / 512 * (tiles == 2 ? 20 * (rows + 6) : 17 * (rows + 4 - odd));
+        if (best == 0 || cost < best) { best = cost; a.R = R; a.strips = strips; pairs = tiles == 2; }
+        if (R >= g.th) break;
+      }
     }
+    const long long cols = (long long)g.N * (pairs ? (g.tw + 1) / 2 : g.tw) * g.NB;
     const long long units = cols * a.strips;
     if (units >= (1LL << 30)) return hipErrorInvalidValue;
     a.units = (int)units;
@@ -582,10 +611,10 @@ hipError_t launch_input_nhwc_range(const Geo& g, const float* x, float* partial,
   // round, no tail), at most one record each of kMaxRangeGroups.
   // Resident workgroups of each kernel variant on each device: a property of the kernel and the
   // chip, asked for once per device and kept (a cache of a constant: concurrent callers may both
-  // ask and store the same value).  [device][m == 4, or 2 for the rolling kernel][vec]
+  // ask and store the same value).  [device][m == 4, or 2 and 3 for the rolling kernels][vec]
   constexpr int kMaxDevices = 64;
-  static std::atomic<int> resident[kMaxDevices][3][2];
-  const int which = roll ? 2 : (g.m == 4 ? 1 : 0);
+  static std::atomic<int> resident[kMaxDevices][4][2];
+  const int which = roll ? (pairs ? 2 : 3) : (g.m == 4 ? 1 : 0);
   auto run = [&](auto kern) {
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
@@ -612,7 +641,7 @@ hipError_t launch_input_nhwc_range(const Geo& g, const float* x, float* partial,
     return hipGetLastError();
   };
   note_kernel(roll ? "input_nhwc_range_roll_kernel" : "input_nhwc_range_kernel");
-  if (roll) return run(input_nhwc_range_roll_kernel);
+  if (roll) return pairs ? run(input_nhwc_range_roll_kernel<2>) : run(input_nhwc_range_roll_kernel<1>);
   if (g.m == 2) return vec ? run(input_nhwc_range_kernel<2, true>) : run(input_nhwc_range_kernel<2, false>);
   return vec ? run(input_nhwc_range_kernel<4, true>) : run(input_nhwc_range_kernel<4, false>);
 }

@@ -640,11 +640,13 @@ def test_nhwc_pairs_of_tiles(shape, option):
     assert names[3] == kernel % ("c64" if C <= 64 else "c128"), names
 
 
-# N, C, H, W, pad: NHWC range pass on pairs of tile columns (at least 4096 strips): two and three columns, an odd
-# number of them, strips of the whole height and of a part of it
+# N, C, H, W, pad: NHWC range pass in strips of one and of two tile columns (at least 4096 strips): one, two and three
+# columns, an odd number of them, strips of the whole height and of a part of it
 @pytest.mark.parametrize("shape", [(2100, 20, 3, 4, 1), (1400, 68, 9, 5, 1), (300, 64, 30, 9, 0), (16, 130, 70, 75, 2),
-                                   (400, 256, 7, 13, 1)], ids=lambda s: "n%d_c%d_%dx%d_p%d" % s)
-def test_nhwc_ranges_from_pairs_of_tile_columns(shape):
+                                   (400, 256, 7, 13, 1), (1301, 20, 31, 2, 1), (2100, 64, 14, 1, 1), (2200, 36, 9, 1, 1),
+                                   (1801, 128, 5, 6, 1), (900, 40, 13, 11, 0)],
+                         ids=lambda s: "n%d_c%d_%dx%d_p%d" % s)
+def test_nhwc_ranges_from_strips(shape):
     from paper_2003_08646_amd import binding as B
     N, C, H, W, pad = shape
     C = C - C % 4
