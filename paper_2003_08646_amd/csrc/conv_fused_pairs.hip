@@ -597,14 +597,16 @@ CpArgs make_args(const Geo& g, const float* x, const int8_t* uq, const float* u_
 // two tiles costs 32 pixel loads and 8 column passes instead of 24 and 6.  Caller's ranges, pairs of a row / any pairs / four
 // tiles per thread: N3571 128 -> 128 14x1 53.6 / 35.5 / 41.8 us, N96 120 -> 374 18x18 (270 and 243 workgroups) 70.4 / 44.2 / 51.0,
 // N2940 128 -> 620 5x6 137.9 / 123.0 / 130.5.  Of 1500 random layers with more than two workgroups of the few-tile plan per
-// compute unit 301 take this form; 0.05 % over the better form's time on average.  With the same number of rounds it
+// compute unit 292 take this form; 0.14 % over the better form's time on average.  With the same number of rounds it
 // is 2 % (300 filters and more) to 7 % (up to 16) slower.  Many filters that are no multiple of four are bound by 4-byte
-// stores, for which more workgroups are the better (N6382 44 -> 629 6x6 401 / 434, N232 128 -> 3943 6x5 106 / 120): not there, but with one tile column.
+// stores, for which more workgroups are the better (N6382 44 -> 629 6x6 401 / 434, N232 128 -> 3943 6x5 106 / 120): not
+// there, but with one tile column.
 bool conv_fused_any_pairs(const Geo& g) {
   if (g.K > 512 && g.K % 4 != 0 && g.tw > 1) return false;
-  const long long per_wg = 32 / g.NB, most = g.NB == 1 ? most_filters<1>() : most_filters<2>();
-  const long long shares = (g.K + most - 1) / most;
-  auto rounds = [&](long long pairs) { return ((pairs + per_wg - 1) / per_wg * shares + 255) / 256; };
+  // blocks of filters, and of a workgroup; the last share of the filters may be small
+  const long long per_wg = 32 / g.NB, most = (g.NB == 1 ? most_filters<1>() : most_filters<2>()) / (64 * g.NB);
+  const long long blocks = (g.K + 64 * g.NB - 1) / (64 * g.NB), work = blocks > most ? blocks : most;
+  auto rounds = [&](long long pairs) { return ((pairs + per_wg - 1) / per_wg * work + 256 * most - 1) / (256 * most); };
   return rounds((g.P + 1LL) / 2) < rounds((long long)g.N * g.th * pairs_per_row(g));
 }
 

@@ -621,7 +621,7 @@ _NHWC_PAIRS = [
 # filters, a row of so many tiles that multiplying does not divide them
 _NHWC_ANY_PAIRS = [
     (1801, 20, 18, 13, 1, 1, 8), (1801, 64, 17, 13, 2, 1, 5), (1801, 68, 18, 9, 2, 1, 8), (985, 40, 32, 9, 5, 1, 8),
-    (683, 60, 21, 10, 11, 0, 8), (277, 128, 130, 18, 18, 1, 8), (1601, 100, 64, 5, 6, 1, 6), (274, 44, 720, 9, 9, 1, 8),
+    (683, 60, 21, 10, 11, 0, 8), (277, 128, 130, 18, 18, 1, 8), (1601, 100, 64, 5, 6, 1, 6), (501, 44, 720, 9, 9, 1, 8),
     (2801, 128, 36, 5, 3, 0, 8), (650, 68, 130, 5, 3, 2, 4), (1, 20, 17, 10, 58981, 1, 8),
 ]
 
