@@ -183,17 +183,15 @@ __global__ __launch_bounds__(kThreads, 2) void conv_fused_c16_kernel(const CsArg
     else
       pl.template issue<false>(plane, a.reach, buf[c % kBuf]);
   };
-  // NHWC layers with at most four channels (an RGB image): a pixel is one load
+  // NHWC layers with at most four channels (an RGB image): a pixel is one load, requested behind the constants (before
+  // them: N16 3 -> 64 224x224 65.4 -> 70.3 us, N64 1 -> 4 56x56 11.6 -> 12.6)
   const bool pix = kNhwc && C <= 4;  // kernel-uniform
   float px[A * A][4];
-  if (pix) {
-    dev::load_pixels_nhwc<M>(a.x, a.reach, pixoff, C, px);
-  } else {
+  if (!pix) {
 #pragma unroll
     for (int c = 0; c < kAhead; c++)
       if (c < C) issue(c);
   }
-
 
   // Eq. 7 parameters and Eq. 8 constants: from the reduction kernel's tables, or (calibrated
   // ranges) formed here exactly as that kernel forms them
@@ -241,6 +239,7 @@ __global__ __launch_bounds__(kThreads, 2) void conv_fused_c16_kernel(const CsArg
   }
   lds_barrier();
   if (p0 >= P) return;  // (no barrier below)
+  if (pix) dev::load_pixels_nhwc<M>(a.x, a.reach, pixoff, C, px);
 
   // Eq. 7 parameters and the scales of the expanded Eq. 8, wave-uniform
   float qmn[E], qinv[E], sc[E], gc[E];
