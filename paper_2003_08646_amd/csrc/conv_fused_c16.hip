@@ -25,6 +25,7 @@
 #include "lance_internal.h"
 #include "nhwc_window.h"
 #include "patch_loader.h"
+#include "share_rule.h"
 
 namespace lance {
 namespace {
@@ -118,7 +119,7 @@ constexpr int kModeNhwc = 3;
 // 35.2 / 35.8).
 // SPLIT: a.split waves share 64 tiles.
 template <bool B8, int MODE, bool SPLIT, bool STREAM>
-__global__ __launch_bounds__(kThreads, 2) void conv_fused_c16_kernel(const CsArgs a) {
+__device__ __forceinline__ void conv_body(const CsArgs& a) {
   constexpr int M = 2, A = 4, E = 16;
   constexpr bool kNhwc = MODE == kModeNhwc;
   extern __shared__ float rk_s[];  // [K][M*M]
@@ -458,6 +459,15 @@ __global__ __launch_bounds__(kThreads, 2) void conv_fused_c16_kernel(const CsArg
   }
 }
 
+template <bool B8, int MODE, bool STREAM>
+__global__ __launch_bounds__(kThreads, 2) void conv_fused_c16_kernel(const CsArgs a) {
+  conv_body<B8, MODE, false, STREAM>(a);
+}
+template <bool B8, int MODE, bool STREAM>
+__global__ __launch_bounds__(kThreads, 2) void conv_fused_c16_shared_kernel(const CsArgs a) {
+  conv_body<B8, MODE, true, STREAM>(a);
+}
+
 }  // namespace
 
 // F(2x2,3x3), one 16-channel block, byte offsets below 2^31 from the first image of a wave's 64
@@ -474,30 +484,11 @@ bool conv_fused_c16_applicable(const Geo& g) {
   return reach < (1LL << 31) && y_elems * 4 < 0xFFFFFFF0LL;  // 32-bit store offsets
 }
 
-// Time of the kernel in us with `split` waves to 64 tiles: a fixed part, and for each workgroup of a compute unit (the
-// second one adds to the first one's time, the vector ALUs are shared) the constants, the channels' transforms and
-// the wave's products of 32 filters x 32 tiles.  Fitted on 110 layers of 5000 to 90000 tiles with caller's ranges, three
-// splits each: 10 % off on average (NHWC 25 %).
-static double c16_us(const Geo& g, int split) {
-  const long long wgs = ((g.P + 63LL) / 64 * split + 3) / 4, kt = (g.K + 31) / 32;
-  const double load = (double)((wgs + 255) / 256) * 0.8;
-  const double parts = (double)(split == 1 ? 2 * kt : split == 2 ? kt : (kt + 1) / 2);
-  return is_nhwc(g) ? -0.8 + (load > 1.0 ? load : 1.0) * (3.3 + 1.1 * g.C + 5.4 * parts)
-                    : 3.9 + (load > 1.0 ? load : 1.0) * (1.8 + 0.37 * g.C + 3.9 * parts);
+static int split_of(const Geo& g) {
+  return c16_split(g.P, g.C, g.K, is_nhwc(g), (long long)g.N * g.K * g.Ho * g.Wo * 4);
 }
 
-// Waves that share 64 tiles: more than one where workgroups of 256 tiles leave compute units idle and the
-// transform, which every wave repeats, is the smaller part.  Us per call with 1 / 2 / 4 (caller's ranges): N8 1->272
-// 99^2 NHWC 74 / 45 / 41, N11 3->103 105^2 42 / 29 / 27, N128 16->16 32^2 18 / 15 / 17, N53 3->33 19x57 23 / 16 / 12, N16 3->64
-// 224^2 55 / 58 / 70.
-static int c16_split(const Geo& g) {
-  const double one = c16_us(g, 1), two = c16_us(g, 2), four = c16_us(g, 4);
-  // (of 200 other layers none lost more than 2 % with these margins)
-  if ((is_nhwc(g) ? 0.75 : 0.85) * one <= (two < four ? two : four)) return 1;
-  return two <= four ? 2 : 4;
-}
-
-double conv_fused_c16_us(const Geo& g) { return c16_us(g, c16_split(g)); }
+double conv_fused_c16_us(const Geo& g) { return c16_us(g.P, g.C, g.K, is_nhwc(g), split_of(g)); }
 
 hipError_t launch_conv_fused_c16(const Geo& g, const float* x, const int8_t* uq,
                                  const float* qparams, const float* dq, const double* dqd,
@@ -509,15 +500,15 @@ hipError_t launch_conv_fused_c16(const Geo& g, const float* x, const int8_t* uq,
   CsArgs a{x, uq, qparams, dq, dqd, u_rowsum, y, g.N, g.C, g.H, g.W, g.K, g.pad, g.P, g.th, g.tw, g.Ho, g.Wo,
            g.bits,
            is_nhwc(g) ? (unsigned)((long long)g.N * g.C * g.H * g.W * 4) : (unsigned)(images * g.C * g.H * g.W * 4LL),
-           (unsigned)((size_t)g.N * g.K * g.Ho * g.Wo * 4), static_v_range, u_range, g.bits_w, c16_split(g)};
+           (unsigned)((size_t)g.N * g.K * g.Ho * g.Wo * 4), static_v_range, u_range, g.bits_w, split_of(g)};
   const unsigned grid = (unsigned)(((g.P + 63) / 64 * a.split + 3) / 4);
   const size_t lds = (size_t)4 * g.K * sizeof(float);
   const bool rows = patch_load_mode(g) == 2, stream = stores_past_caches(g);
-  note_kernel("conv_fused_c16_kernel");
+  note_kernel(a.split > 1 ? "conv_fused_c16_shared_kernel" : "conv_fused_c16_kernel");
 #define LANCE_C16(B8, MODE, STREAM) \
   do { \
-    if (a.split > 1) conv_fused_c16_kernel<B8, MODE, true, STREAM><<<grid, kThreads, lds, s>>>(a); \
-    else conv_fused_c16_kernel<B8, MODE, false, STREAM><<<grid, kThreads, lds, s>>>(a); \
+    if (a.split > 1) conv_fused_c16_shared_kernel<B8, MODE, STREAM><<<grid, kThreads, lds, s>>>(a); \
+    else conv_fused_c16_kernel<B8, MODE, STREAM><<<grid, kThreads, lds, s>>>(a); \
   } while (0)
 #define LANCE_C16_STORES(B8, MODE) \
   do { if (stream) LANCE_C16(B8, MODE, true); else LANCE_C16(B8, MODE, false); } while (0)

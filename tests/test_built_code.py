@@ -44,8 +44,9 @@ def test_wide_buffer_stores_have_no_register_as_scalar_offset(buffer_stores):
     assert not [w for w in wide if re.match(r"s\d|m0|ttmp|vcc", w[1])]
 
 
-@pytest.mark.parametrize("name", ["conv_fused_c16_kernel", "conv_fused_pairs_nhwc_c64_kernel",
-                                  "conv_fused_pairs_nhwc_c128_kernel"])
+@pytest.mark.parametrize("name", ["conv_fused_c16_kernel", "conv_fused_c16_shared_kernel", "conv_fused_pairs_nhwc_c64_kernel",
+                                  "conv_fused_pairs_nhwc_c128_kernel", "conv_fused_any_pairs_nhwc_c64_kernel",
+                                  "conv_fused_any_pairs_nhwc_c128_kernel"])
 def test_kernels_of_cached_stores(buffer_stores, name):
     """Cached and non-temporal stores in one kernel cost the layers whose stores are cached: each of these kernels
     has a form without non-temporal stores (last template argument)."""

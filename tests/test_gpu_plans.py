@@ -163,8 +163,11 @@ _PLANS = [
     ("conv_fused_pairs_c64_kernel", 200, 50, 70, 13, 16, 1, 2, 5, ""),
     ("conv_fused_pairs_c128_kernel", 100, 96, 70, 16, 16, 1, 2, 6, ""),
     ("conv_fused_pairs_nhwc_c128_kernel", 110, 72, 130, 14, 13, 0, 2, 8, "nhwc"),
-    ("conv_fused_c16_kernel", 60, 12, 40, 33, 31, 1, 2, 8, ""),
-    ("conv_fused_c16_kernel", 60, 3, 70, 32, 32, 1, 2, 4, "nhwc"),
+    ("conv_fused_c16_shared_kernel", 60, 12, 40, 33, 31, 1, 2, 8, ""),
+    ("conv_fused_c16_shared_kernel", 60, 3, 70, 32, 32, 1, 2, 4, "nhwc"),
+    ("conv_fused_c16_kernel", 250, 12, 40, 33, 31, 1, 2, 8, ""),
+    ("conv_fused_c16_kernel", 250, 3, 20, 32, 32, 1, 2, 4, "nhwc"),
+    ("conv_fused_c16_kernel", 200, 7, 20, 33, 31, 1, 2, 6, "nhwc"),
     ("conv_fused_m4_kernel", 100, 40, 130, 20, 21, 1, 4, 8, ""),
     ("gemm_fused_rows_kernel", 90, 150, 40, 14, 14, 1, 2, 8, ""),
     ("gemm_fused_rows_kernel", 70, 140, 130, 14, 15, 0, 2, 7, "nhwc"),
@@ -743,14 +746,15 @@ def test_position_parallel_with_many_records(shape, per_tensor):
     assert names[:2] == ["input_range_kernel", ""] and names[3] in ("conv_fused_pos_kernel", "gemm_pos_kernel"), names
 
 
-# N, C, K, H, W, pad, bits, nhwc: the small-channel kernel with two and four waves to 64 tiles: one, two, three and many tiles
-# of 32 filters (waves without any), a last block of one tile, odd sizes; below 12800 tiles where it takes over from the
-# few-tile plan
+# N, C, K, H, W, pad, bits, nhwc, waves: the small-channel kernel with two and four waves to 64 tiles (test_share_rule.py checks
+# that each shape is divided so): one, two, three and many tiles of 32 filters, odd numbers of them, a last block of one
+# tile and of whole ones, odd sizes; below 12800 tiles where it takes over from the few-tile plan
 _C16_SHARED = [
-    (48, 5, 17, 10, 134, 1, 8, False), (53, 3, 33, 19, 57, 1, 8, False), (128, 16, 16, 32, 32, 1, 8, False),
-    (16, 4, 65, 57, 55, 1, 5, False), (11, 3, 103, 75, 75, 0, 8, False), (1, 16, 200, 225, 229, 1, 8, False),
-    (1, 3, 64, 224, 224, 1, 8, False), (9, 2, 100, 65, 65, 1, 4, False), (8, 1, 272, 83, 81, 1, 8, True),
-    (12, 2, 92, 79, 75, 1, 6, True), (3, 7, 66, 131, 133, 1, 8, True), (13, 1, 40, 63, 64, 1, 8, False),
+    (48, 5, 17, 10, 134, 1, 8, False, 2), (53, 3, 33, 19, 57, 1, 8, False, 4), (128, 16, 16, 32, 32, 1, 8, False, 2),
+    (16, 4, 65, 57, 55, 1, 5, False, 4), (11, 3, 103, 75, 75, 0, 8, False, 4), (1, 16, 200, 225, 229, 1, 8, False, 4),
+    (1, 3, 64, 224, 224, 1, 8, False, 4), (9, 2, 100, 65, 65, 1, 4, False, 4), (8, 1, 272, 83, 81, 1, 8, True, 4),
+    (12, 2, 92, 79, 75, 1, 6, True, 2), (3, 7, 66, 131, 133, 1, 8, True, 4), (13, 1, 40, 63, 64, 1, 8, False, 4),
+    (43, 16, 16, 37, 33, 1, 8, False, 2), (89, 4, 65, 25, 25, 1, 8, False, 4), (43, 2, 40, 37, 33, 1, 8, True, 4),
 ]
 
 
@@ -758,13 +762,13 @@ _C16_SHARED = [
 @pytest.mark.parametrize("static", [False, True], ids=["dynamic", "static"])
 def test_small_channel_waves_that_share_tiles(shape, static):
     from paper_2003_08646_amd import binding as B
-    N, C, K, H, W, pad, bits, nhwc = shape
+    N, C, K, H, W, pad, bits, nhwc, _ = shape
     L = Wk.Layer("c16_shared", N, C, K, H, W, pad=pad, m=2, bits=bits, seed=960 + C)
     flags = (B.LANCE_LAYOUT_NHWC if nhwc else 0) | (B.LANCE_INPUT_RANGE_STATIC if static else 0)
     conv, _ = _check_layer(L, flags=flags, static_v_range=_range_of_another_batch(L) if static else None, staged=False)
     names = _kernels(conv, _zeros(conv, nhwc))
     if static or conv.sz.P > 12800:  # (with dynamic ranges the few-tile plan keeps more of the others)
-        assert names[3] == "conv_fused_c16_kernel", names
+        assert names[3] == "conv_fused_c16_shared_kernel", names
 
 
 # N, C, H, W: F(4x4) range pass in strips of an even and of an odd number of tile rows, several strips to a plane, one
