@@ -22,9 +22,11 @@
 // What bounds it: launches and latencies, and for the largest layers the copies of the records, which the start of the
 // second kernel waits for.  By the workgroups' clocks, 64 -> 128 channels: range kernel 2.4 us (1.2 weights, 0.6
 // reduction), 1.2 until the next kernel starts, its records 1.8, constants 0.5, codes 0.9, sums 0.5.  Whole call, four
-// channels per thread / now: 3 -> 64 6.6 / 4.3 us, 64 -> 64 7.8 / 6.5, 128 -> 128 9.4 / 8.4, 256 -> 256 11.5 / 10.9, 512 -> 512
-// 16.3 / 16.3, 1024 -> 1024 41 / 30, 64 -> 64 F(4x4) 15.7 / 12.7; 150 random sets of 1 to 600 channels and filters 1.28 on
-// average, none slower by more than 1 %.  (Weights through LDS in 16-byte loads were slower at every size.)
+// channels per thread / now, on weights in the last-level cache and (cold) on sets that rotate past it: 3 -> 64 6.7 / 4.4
+// (cold 6.6 / 5.1) us, 64 -> 64 7.8 / 6.6 (8.4 / 6.6), 128 -> 128 9.5 / 8.5 (9.8 / 8.7), 256 -> 256 11.4 / 10.8 (12.2 / 11.4), 512 -> 512
+// 15.7 / 15.8 (17.5 / 17.5), 1024 -> 1024 41 / 30 (46 / 35), 64 -> 64 F(4x4) 15.9 / 12.8 (16.9 / 13.4); the thirteen 3x3
+// layers of VGG-16 162 / 153 (186 / 176).  1500 random sets of 1 to 8192 channels and up to 65535 filters 1.26 at the median,
+// five slower by more than 4 %.  (Weights through LDS in 16-byte loads were slower at every size.)
 #include "lance_device.h"
 #include "lance_internal.h"
 
@@ -36,7 +38,7 @@ struct FtArgs {
   int8_t* uq;
   float* u_range;
   int32_t* u_rowsum;
-  int C, K, CB, NB, Q, row;  // row: bytes of a code row
+  int C, K, CB, NB, row;  // row: bytes of a code row
   int bits, natural, packed, per_tensor;
   int ga, gb, cap;  // workgroups of the two kernels; records per code-row strip of a workgroup
   int base, extra;           // filters of a workgroup of the second kernel; the first `extra` have one more
@@ -278,23 +280,37 @@ __global__ __launch_bounds__(NT) void filter_quant_kernel(const FtArgs a) {
 
 hipError_t launch_filter_transform(const Geo& g, const float* w, int8_t* uq, float* u_range,
                                    int32_t* u_rowsum, hipStream_t s) {
-  FtArgs a{w, uq, u_range, u_rowsum, g.C, g.K, g.CB, g.NB, g.Q, code_row_bytes(g), g.bits_w,
+  FtArgs a{w, uq, u_range, u_rowsum, g.C, g.K, g.CB, g.NB, code_row_bytes(g), g.bits_w,
            is_nhwc(g) ? 1 : 0, is_packed(g) ? 1 : 0, (g.flags & LANCE_RANGE_PER_TENSOR) ? 1 : 0, 0, 0, 1};
   const long long filters = (long long)g.K * g.C;
   // Up to 4096 filters every workgroup of the second kernel finds the ranges itself.
-  const bool one_kernel = filters <= 4096, large = filters > 81920;
-  // Small workgroups have the shorter chain of steps, large ones keep the number of records and copies down.
+  const bool one_kernel = filters <= 4096, large = filters > 81920, wide = g.CB == 64;
+  const long long units = wide ? (long long)g.K * g.NB : (g.K + 3) / 4;
+  // Copies of the records that the first kernel writes: at most 64, 128 or 256 (512 -> 512 channels: the start of the second
+  // kernel waits 3.3 us behind the last workgroup of the first with 128 copies of 8 KB, 4.9 with 256, 1.2 where there
+  // are few), the more the longer the second kernel takes.
+  long long most = filters > 400000 ? 256 : large ? 128 : 64;
+  if (wide && units > 1024 && most < 128) most = 128;
+  if (wide && units > 6000) most = 256;
+  // Small workgroups have the shorter chain of steps, large ones keep the number of records and copies down, and where
+  // few filters of many channels allow few workgroups they have the waves for their units (us with 256 / 512 / 1024
+  // threads: 6066 -> 2 F(2x2) 25.4 / 18.6 / 16.7, 4066 -> 4 F(4x4) 35.7 / 25.5 / 22.6).  512 or 1024 from the number of units to
+  // a workgroup on; 1200 random sets of filters: 1.02 over the best of twelve choices on average.
   const int nt_range = large ? 1024 : 256;
-  const int nt_quant = one_kernel ? (filters > 1024 ? 1024 : 256) : (filters > 24576 ? 512 : 256);
-  // Workgroups of the second kernel: a unit of 64 codes per wave, then several, so that there are at most 64, 128 or
-  // 256 copies of the records (512 -> 512 channels: the start of the second kernel waits 3.3 us behind the last
-  // workgroup of the first with 128 copies of 8 KB, 4.9 with 256, 1.2 where there are few), at most 64 filters each.
-  const long long units = g.CB == 64 ? (long long)g.K * g.NB : (g.K + 3) / 4;
-  const long long most = filters > 400000 ? 256 : large ? 128 : 64;
+  int nt_quant = one_kernel ? (filters > 1024 ? 1024 : 256) : (filters > 24576 ? 512 : 256);
+  if (wide && !one_kernel) {
+    const long long each = (units + (most < g.K ? most : g.K) - 1) / (most < g.K ? most : g.K);
+    if (each > (g.m == 2 ? 12 : 8) && nt_quant < 512) nt_quant = 512;
+    if (g.m == 4 && each > 32) nt_quant = 1024;
+  }
+  // Workgroups of the second kernel: a unit of 64 codes per wave, then several, at most 64 filters each, and all the same
+  // number of filters where that takes no longer (7975 -> 248 F(4x4) on 243 workgroups, five of them with two filters: 99 us).
   const long long waves = nt_quant / 64, per_wave = (units + waves * most - 1) / (waves * most);
   long long gb = (units + waves * per_wave - 1) / (waves * per_wave);
   if (gb < (g.K + 63) / 64) gb = (g.K + 63) / 64;
   if (gb > g.K) gb = g.K;
+  const long long own = (g.K + gb - 1) / gb;
+  gb = own == 2 && g.K <= most ? g.K : (g.K + own - 1) / own;
   a.gb = (int)gb;
   a.base = g.K / a.gb;
   a.extra = g.K % a.gb;
@@ -320,7 +336,8 @@ hipError_t launch_filter_transform(const Geo& g, const float* w, int8_t* uq, flo
     constexpr bool kNarrow = decltype(narrow)::value;
     auto tile = [&](auto m) -> hipError_t {
       constexpr int kM = decltype(m)::value;
-      return large               ? run(filter_range_kernel<kM, 1024>, filter_quant_kernel<kM, 512, kNarrow>)
+      return large && nt_quant == 1024 ? run(filter_range_kernel<kM, 1024>, filter_quant_kernel<kM, 1024, kNarrow>)
+             : large             ? run(filter_range_kernel<kM, 1024>, filter_quant_kernel<kM, 512, kNarrow>)
              : nt_quant == 1024 ? run(filter_range_kernel<kM, 256>, filter_quant_kernel<kM, 1024, kNarrow>)
              : nt_quant == 512  ? run(filter_range_kernel<kM, 256>, filter_quant_kernel<kM, 512, kNarrow>)
                                 : run(filter_range_kernel<kM, 256>, filter_quant_kernel<kM, 256, kNarrow>);

@@ -700,10 +700,12 @@ def test_where_the_nhwc_pair_kernel_takes_over(shape, static, pairs):
 
 
 # K, C, m, bits_w: filters of a last unit of four that is not whole, padding lanes, one, several and many units of 64 codes
-# per wave on workgroups of 256, 512 and 1024 threads, unequal shares, 64, 128 and 256 copies of the records
+# per wave on workgroups of 256, 512 and 1024 threads, equal and unequal shares, one filter to a workgroup, few filters of
+# many channels, 64, 128 and 256 copies of the records
 @pytest.mark.parametrize("K,C,m,bits_w", [(6, 16, 2, 8), (3, 17, 4, 2), (63, 65, 2, 4), (64, 64, 2, 3), (17, 63, 4, 8),
                                           (1, 512, 2, 8), (260, 100, 2, 6), (90, 513, 4, 8), (600, 129, 2, 8),
-                                          (1025, 420, 2, 8), (4097, 1, 4, 4)])
+                                          (1025, 420, 2, 8), (4097, 1, 4, 4), (2, 2100, 2, 8), (3, 2113, 4, 4),
+                                          (60, 80, 2, 8), (100, 100, 4, 3), (3100, 70, 2, 8)])
 @pytest.mark.parametrize("flags", ["nchw", "nhwc", "packed", "per_tensor"])
 def test_filter_transform_units(K, C, m, bits_w, flags):
     test_filter_transform_shapes(K, C, m, bits_w, flags)
