@@ -374,27 +374,37 @@ __device__ __forceinline__ void conv_body(const CpArgs& a) {
     }
   }
   // byte offsets of the pair's two output rows: of filter 0 (NCHW), or of their first pixels (NHWC; ANY: of each tile's)
-  constexpr int kRuns = ANY ? 2 : 1, kRunPixels = 4 / kRuns;
+  constexpr int kRuns = ANY ? 2 : 1;
   unsigned y_off[kRuns][2];
   int cols[kRuns];  // pixels of a row that exist
+  cols[0] = 4;
+  if constexpr (ANY) {
 #pragma unroll
-  for (int run = 0; run < kRuns; run++) {
-    const int p = ANY ? 2 * (blk * kPairs + pair) + run : blk * kPairs + pair, most = ANY ? a.g.tiles : a.g.pairs;
+    for (int run = 0; run < 2; run++) {
+      const int t = 2 * (blk * kPairs + pair) + run;
+      int tx, ty, n;
+      dev::locate_pair<true>(a.g, min(t, a.g.tiles - 1), &tx, &ty, &n);
+      cols[run] = a.g.Wo - 2 * tx;
+      const unsigned row = (unsigned)a.g.Wo * (unsigned)K * 4u;
+      const unsigned base = ((unsigned)n * (unsigned)a.g.Ho + (unsigned)(2 * ty)) * row + (unsigned)(2 * tx) * (unsigned)K * 4u;
+      y_off[run][0] = t < a.g.tiles ? base : kOob;
+      y_off[run][1] = t < a.g.tiles && 2 * ty + 1 < a.g.Ho ? base + row : kOob;
+    }
+  } else {
+    const int p = blk * kPairs + pair;
     int q, ty, n;
-    dev::locate_pair<NHWC>(a.g, min(p, most - 1), &q, &ty, &n);
+    dev::locate_pair<NHWC>(a.g, min(p, a.g.pairs - 1), &q, &ty, &n);
     unsigned base, row;
     if constexpr (NHWC) {
-      cols[run] = a.g.Wo - kRunPixels * q;
+      cols[0] = a.g.Wo - 4 * q;
       row = (unsigned)a.g.Wo * (unsigned)K * 4u;
-      base = ((unsigned)n * (unsigned)a.g.Ho + (unsigned)(2 * ty)) * row +
-             (unsigned)(kRunPixels * q) * (unsigned)K * 4u;
+      base = ((unsigned)n * (unsigned)a.g.Ho + (unsigned)(2 * ty)) * row + (unsigned)(4 * q) * (unsigned)K * 4u;
     } else {
-      cols[run] = 4;
       row = (unsigned)a.g.W * 4u;
       base = ((unsigned)n * (unsigned)K * plane_px + (unsigned)(2 * ty) * (unsigned)a.g.W + 4u * (unsigned)q) * 4u;
     }
-    y_off[run][0] = p < most ? base : kOob;
-    y_off[run][1] = p < most && 2 * ty + 1 < (NHWC ? a.g.Ho : a.g.H) ? base + row : kOob;
+    y_off[0][0] = p < a.g.pairs ? base : kOob;
+    y_off[0][1] = p < a.g.pairs && 2 * ty + 1 < (NHWC ? a.g.Ho : a.g.H) ? base + row : kOob;
   }
 
   for (int kb = kb0; kb < nkb; kb++) {

@@ -294,7 +294,7 @@ hipError_t launch_filter_transform(const Geo& g, const float* w, int8_t* uq, flo
   if (wide && units > 6000) most = 256;
   // Small workgroups have the shorter chain of steps, large ones keep the number of records and copies down, and where
   // few filters of many channels allow few workgroups they have the waves for their units (us with 256 / 512 / 1024
-  // threads: 6066 -> 2 F(2x2) 25.4 / 18.6 / 16.7, 4066 -> 4 F(4x4) 35.7 / 25.5 / 22.6).  512 or 1024 from the number of units to
+  // threads: 6066 -> 2 F(2x2) 25.4 / 17.4 / 16.7, 4066 -> 4 F(4x4) 35.7 / 25.1 / 22.7).  512 or 1024 from the number of units to
   // a workgroup on; 1200 random sets of filters: 1.02 over the best of twelve choices on average.
   const int nt_range = large ? 1024 : 256;
   int nt_quant = one_kernel ? (filters > 1024 ? 1024 : 256) : (filters > 24576 ? 512 : 256);
@@ -304,7 +304,8 @@ hipError_t launch_filter_transform(const Geo& g, const float* w, int8_t* uq, flo
     if (g.m == 4 && each > 32) nt_quant = 1024;
   }
   // Workgroups of the second kernel: a unit of 64 codes per wave, then several, at most 64 filters each, and all the same
-  // number of filters where that takes no longer (7975 -> 248 F(4x4) on 243 workgroups, five of them with two filters: 99 us).
+  // number of filters where that takes no longer (7975 -> 248 F(4x4) on 243 workgroups, five of them with two filters, 99.6 us,
+  // on 248 69.7).
   const long long waves = nt_quant / 64, per_wave = (units + waves * most - 1) / (waves * most);
   long long gb = (units + waves * per_wave - 1) / (waves * per_wave);
   if (gb < (g.K + 63) / 64) gb = (g.K + 63) / 64;
