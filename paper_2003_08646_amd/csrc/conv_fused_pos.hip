@@ -64,7 +64,7 @@ static bool conv_fused_pos_applicable(const Geo& g) {
 //    17..32 / 33..64 / 65..128 / 129..192 / 257..399 filters, with caller's ranges: one channel block 0.97 / 1.12 / 0.84 / 0.69 /
 //    0.49, two blocks 1.12 / 1.25 / 1.29 / 0.92 / 0.71 (dynamic ranges 0.05 to 0.1 more): in one block of filters
 //    there too, from 17 or 33 filters on.  Where four filters are not one store (one block 0.83 / 0.87 / 0.62 / ..., two
-//    1.03 / 1.10 / 1.08 / 0.73 / 0.49) two blocks only, with caller's ranges 33 to 64 filters (65..128: 0.83 to 1.24).
+//    1.03 / 1.10 / 1.08 / 0.73 / 0.49) two blocks only, with caller's ranges 33 to 72 filters (73..128: 0.83 to 1.24).
 //    Two blocks and dynamic ranges: from one filter on (1.07 and 1.10 up to 16), where that kernel takes pairs of a
 //    tile row (of any two tiles: 0.89 to 0.96).  With several blocks of filters
 //    few workgroups do all the work: N2 64->704 28^2 15.9 / 51.2 us, N1 100->3218 15x24 19.1 / 68.0.
@@ -75,7 +75,7 @@ static bool nhwc_pairs_preferred(const Geo& g) {
   const bool is_static = (g.flags & LANCE_INPUT_RANGE_STATIC) != 0, whole = g.K % 4 == 0;
   if (g.NB == 1) return whole && g.K > (is_static ? 32 : 16);
   if (conv_fused_any_pairs(g)) return whole && g.K > 16;
-  return !is_static || (whole ? g.K > 16 : g.K > 32 && g.K <= 64);
+  return !is_static || (whole ? g.K > 16 : g.K > 32 && g.K <= 72);
 }
 
 bool conv_fused_pos_preferred(const Geo& g, bool x_aligned) {

@@ -682,7 +682,7 @@ def test_nhwc_of_four_byte_alignment_keeps_the_few_tile_plan():
     ((16, 64, 65, 30, 30), False, False),
     ((20, 64, 64, 37, 35), True, True), ((20, 64, 61, 37, 35), True, False), ((20, 64, 61, 37, 35), False, False),
     ((20, 64, 32, 37, 35), True, False), ((20, 64, 20, 37, 35), False, True), ((20, 64, 16, 37, 35), False, False),
-    ((64, 128, 128, 14, 14), True, True), ((64, 128, 125, 14, 14), True, False), ((64, 128, 65, 14, 14), True, False),
+    ((64, 128, 128, 14, 14), True, True), ((64, 128, 125, 14, 14), True, False), ((64, 128, 70, 14, 14), True, True), ((64, 128, 74, 14, 14), True, False),
     ((64, 128, 125, 14, 14), False, True), ((20, 128, 33, 37, 35), True, True), ((20, 128, 62, 37, 35), True, True), ((20, 128, 31, 37, 35), True, False),
     ((896, 84, 53, 6, 6), True, False), ((896, 84, 12, 6, 6), False, False),      # pairs of any two tiles
     ((20, 128, 20, 37, 35), True, True), ((20, 128, 16, 37, 35), True, False), ((20, 128, 5, 37, 35), False, True),
