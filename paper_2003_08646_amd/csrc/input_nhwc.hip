@@ -587,17 +587,22 @@ hipError_t launch_input_nhwc_range(const Geo& g, const float* x, float* partial,
     // Tile columns and rows of a strip: the smallest (rounds of 512 resident workgroups) x (pixel rows of a strip, and
     // about four more that its first loads take); a row of one column counts 0.85 of a row of two, and its first loads two
     // rows less, or three where pairs overlap (fitted).  On 700 random layers this takes 1.04 of the best choice's time
-    // on average; pairs alone took up to 1.5 times that with three tile columns.
+    // on average; pairs alone took up to 1.5 times that with three tile columns.  Pairs whose shortest strips take at most
+    // one workgroup per compute unit: no shorter in one column (8.2 us both), and one column's twice the records cost the
+    // reader about 1 us (whole calls N221 C100 K1 11x11 17.3 / 18.3, N1020 C56 K7 2x15 13.8 / 14.8, N32 C128 K61 32x32
+    // 21.9 / 23.0).
     const int odd = g.tw % 2 && g.th > 1;
     long long best = 0;
-    for (int tiles = g.tw >= 2 ? 2 : 1; tiles >= 1; tiles--) {
+    bool few = false;
+    for (int tiles = g.tw >= 2 ? 2 : 1; tiles >= 1 && !few; tiles--) {
       const long long cols = (long long)g.N * ((g.tw + tiles - 1) / tiles) * g.NB;
       for (int R = 2; R <= 32; R++) {
         const int strips = (g.th + R - 1) / R, rows = 2 * (R < g.th ? R : g.th);
         const long long wgs = (cols * strips + kGroupsPerWg - 1) / kGroupsPerWg;
         const long long cost = (wgs + 511) / 512 * (tiles == 2 ? 20 * (rows + 6) : 17 * (rows + 4 - odd));
         if (best == 0 || cost < best) { best = cost; a.R = R; a.strips = strips; pairs = tiles == 2; }
-        if (R >= g.th) break;
+        few |= tiles == 2 && R == 2 && wgs <= 256;
+        if (R >= g.th || few) break;
       }
     }
     const long long cols = (long long)g.N * (pairs ? (g.tw + 1) / 2 : g.tw) * g.NB;

@@ -647,7 +647,7 @@ def test_nhwc_pairs_of_tiles(shape, option):
 # columns, an odd number of them, strips of the whole height and of a part of it
 @pytest.mark.parametrize("shape", [(2100, 20, 3, 4, 1), (1400, 68, 9, 5, 1), (300, 64, 30, 9, 0), (16, 130, 70, 75, 2),
                                    (400, 256, 7, 13, 1), (1301, 20, 31, 2, 1), (2100, 64, 14, 1, 1), (2200, 36, 9, 1, 1),
-                                   (1801, 128, 5, 6, 1), (900, 40, 13, 11, 0)],
+                                   (1801, 128, 5, 6, 1), (900, 40, 13, 11, 0), (221, 100, 11, 11, 1)],
                          ids=lambda s: "n%d_c%d_%dx%d_p%d" % s)
 def test_nhwc_ranges_from_strips(shape):
     from paper_2003_08646_amd import binding as B
