@@ -103,9 +103,8 @@ __device__ __forceinline__ void static_for(F&& f) {
 // A^T of F(2x2,3x3) (points 0, 1, -1, inf), for compile-time indices.
 constexpr float kAt2[2][4] = {{1, 1, 1, 0}, {0, 1, -1, -1}};
 
-// B8: 8-bit codes.  FULL: all 128 channels exist.  MODE: patch load mode (patch_load_mode).  STREAM is the NHWC
-// form's (conv_fused_pairs.hip): here Y is stored through the caches.
-template <bool B8, bool FULL, int MODE, bool STREAM>
+// B8: 8-bit codes.  FULL: all 128 channels exist.  MODE: patch load mode (patch_load_mode).
+template <bool B8, bool FULL, int MODE>
 __global__ __launch_bounds__(kThreads, 2) void conv_fused_c128_kernel(const CgArgs a) {
   constexpr int M = 2, A = 4, E = 16, NB = 2;
   constexpr int kAhead = 3;  // positions whose A fragments are in flight ahead of the products
@@ -331,9 +330,9 @@ bool conv_fused_c128_applicable(const Geo& g) {
   return block_reach_bytes(g) < (1LL << 31);
 }
 
-template <bool B8, bool FULL, int MODE, bool STREAM = false>
+template <bool B8, bool FULL, int MODE>
 static hipError_t launch_variant(const CgArgs& a, unsigned grid, hipStream_t s) {
-  auto kern = conv_fused_c128_kernel<B8, FULL, MODE, STREAM>;
+  auto kern = conv_fused_c128_kernel<B8, FULL, MODE>;
   hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kern), (int)kLdsBytes);
   if (e != hipSuccess) return e;
   note_kernel("conv_fused_c128_kernel");
