@@ -56,10 +56,6 @@ struct CsArgs {
   int split;  // waves that share 64 tiles: 1, 2 or 4
 };
 
-// Workgroup barrier that waits for this wave's LDS operations only: loads from memory stay in flight
-// across it, which __syncthreads() would wait for.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // lanes 0-31 keep `own`, lanes 32-63 receive the value of lane - 32 (*g0); lanes 0-31 receive
 // the value of lane + 32, lanes 32-63 keep `own` (*g1): what the two tile groups' columns need.
 __device__ __forceinline__ void spread(unsigned own, unsigned* g0, unsigned* g1) {
@@ -216,7 +212,7 @@ __device__ __forceinline__ void conv_body(const CsArgs& a) {
     dqd_s[2 * tid] = d0;
     dqd_s[2 * tid + 1] = d1;
   }
-  lds_barrier();
+  dev::lds_barrier();
 
   // filter-side terms f[e,k] = su*ov*rowsum[e][k] + C*ou*ov through A^T . A, in binary64
   // (thread = filter)
@@ -238,7 +234,7 @@ __device__ __forceinline__ void conv_body(const CsArgs& a) {
     }
     *reinterpret_cast<v4f*>(rk_s + 4 * k) = r4;
   }
-  lds_barrier();
+  dev::lds_barrier();
   if (p0 >= P) return;  // (no barrier below)
   if (pix) dev::load_pixels_nhwc<M>(a.x, a.reach, pixoff, C, px);
 

@@ -185,10 +185,6 @@ struct Constants {
   }
 };
 
-// Workgroup barrier that waits for this wave's LDS operations only: loads from memory stay in flight
-// across it, which __syncthreads() would wait for.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // LDS of a workgroup but the filter-side terms; two workgroups share a compute unit's 160 KB.
 template <int NB>
 constexpr int fixed_lds() {
@@ -336,7 +332,7 @@ __device__ __forceinline__ void conv_body(const CpArgs& a) {
   v4i afrag[kFragsAhead + 1][NB];  // ring over positions (16 positions = four turns)
 #pragma unroll
   for (int e = 0; e < kFragsAhead; e++) load_afrags(kb0, e, afrag[e]);
-  lds_barrier();  // the codes of all waves are in LDS
+  dev::lds_barrier();  // the codes of all waves are in LDS
   // Column sums: one more matrix instruction per fragment, with an operand of ones; wave w takes the
   // positions 2w and 2w + 1 of all tiles.  (v_sad_u8 and LDS atomics, in phase T: 89.3 / 88.1 us on N64 128 ->
   // 128 56x56 with the other barrier, 44.8 / 42.6 on N64 100 -> 100 36x36.)
@@ -356,7 +352,7 @@ __device__ __forceinline__ void conv_body(const CpArgs& a) {
         if (kq == 0) cs_s[e * kTiles + row] = sum[0];  // every row of the product is the same
       }
   }
-  lds_barrier();
+  dev::lds_barrier();
 
   float gp[2][M * M];  // input-side terms of the lane's tiles through A^T . A
 #pragma unroll

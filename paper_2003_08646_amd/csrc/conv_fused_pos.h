@@ -87,7 +87,7 @@ __global__ __launch_bounds__(NW * 64, (M == 2 ? 16 : 12) / 4) void conv_fused_po
   int rs[PW];  // row sums of filter k0 + lane
 #pragma unroll
   for (int w = 0; w < PW; w++) rs[w] = load_rowsum<KG>(a, wave * PW + w, k0, lane);
-  lds_barrier();  // the codes of all waves are in LDS
+  dev::lds_barrier();  // the codes of all waves are in LDS
 #pragma unroll
   for (int w = 0; w < PW; w++) {
     const int e = wave * PW + w;
@@ -105,10 +105,10 @@ __global__ __launch_bounds__(NW * 64, (M == 2 ? 16 : 12) / 4) void conv_fused_po
       }
     }
   }
-  lds_barrier();  // the code rows are free again
+  dev::lds_barrier();  // the code rows are free again
 #pragma unroll
   for (int w = 0; w < PW; w++) sums_to_lds<KG, 1, kNhwc>(a, cst, wave * PW + w, lane, rs[w], acc[w], csum[w], ex);
-  lds_barrier();
+  dev::lds_barrier();
   store_patches<M, KG, 1, NT, kNhwc>(a, ex, k0, p0, tid);
 }
 

@@ -30,7 +30,7 @@ __global__ __launch_bounds__(256, M == 2 ? 4 : 3) void quant_pos_kernel(const Cp
     const Quantizer<M, NW, CPL, LOAD, CLAMP> qz(a, p0, lane, wave);
     qz.run(blk, 1, cst.qp, ring, [&]() { cst.template form<NT>(a, a.is_static, early, red, tid); });
   }
-  lds_barrier();
+  dev::lds_barrier();
   const __amdgpu_buffer_rsrc_t res = __builtin_amdgcn_make_buffer_rsrc(a.vq, 0, a.vq_bytes, 0x00020000);
   const int row = lane >> 2, chunk = lane & 3;
   const unsigned src = (unsigned)row * 64u + (unsigned)((chunk ^ swz(row)) * 16);
@@ -120,7 +120,7 @@ __global__ __launch_bounds__(M == 2 ? 1024 : 768) void gemm_pos_kernel(const CpA
   }
 #pragma unroll
   for (int w = 0; w < PW; w++) sums_to_lds<KG, TG, NHWC>(a, cst, wave * PW + w, lane, rs[w], acc[w], csum[w], ex);
-  lds_barrier();
+  dev::lds_barrier();
   store_patches<M, KG, TG, NT, NHWC>(a, ex, k0, p0, tid);
 }
 

@@ -190,6 +190,10 @@ __device__ __forceinline__ int fast_div(int x, unsigned magic) {
   return magic == 0 ? x : (int)__umulhi((unsigned)x, magic);
 }
 
+// Workgroup barrier that waits for this wave's LDS operations only: loads from memory (pixels, filter
+// codes) stay in flight across it, which __syncthreads() would wait for.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // Workgroups are dealt to the 8 accelerator dies (XCDs, each with its own L2) round robin by
 // their index.  This maps workgroup b of n to a work item such that every die gets one contiguous
 // range of items: neighbouring items (tile blocks that share halo rows) then share an L2.

@@ -39,10 +39,6 @@ constexpr unsigned kOobY = 0xFFFFFFF0u;
 
 __device__ __forceinline__ int swz(int row) { return (row >> 2) & 3; }
 
-// Workgroup barrier that waits for this wave's LDS operations only: loads from memory (pixels, filter
-// codes) stay in flight across it, which __syncthreads() would wait for.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 __device__ __forceinline__ v4i load_code(const int8_t* uq, unsigned bytes, unsigned off, unsigned soff) {
   const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(uq), 0, bytes, 0x00020000);
   return __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(r, off, soff, 0));
@@ -130,7 +126,7 @@ struct Consts {
         for (int u = 0; u < kBatch; u++) v = is_max ? fmaxf(v, xv[u]) : fminf(v, xv[u]);
       }
       red[tid] = v;
-      lds_barrier();
+      dev::lds_barrier();
       if (tid < E) {
         v2f r = *reinterpret_cast<const v2f*>(red + 2 * tid);
 #pragma unroll
@@ -169,7 +165,7 @@ struct Consts {
       rmul[tid] = (double)su * ov;
       kc[tid] = (double)a.C * ou * ov;
     }
-    lds_barrier();
+    dev::lds_barrier();
   }
 };
 
