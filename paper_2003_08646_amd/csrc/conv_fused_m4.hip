@@ -28,7 +28,9 @@
 // accumulator register one conversion and about five multiply-adds against a quarter of a matrix
 // instruction), then memory.  Neither a deeper fragment ring (11 positions) nor the order of products
 // and fold changed phase G, nor a fold by sums and differences of the point pairs (154 operations per register
-// instead of 216: 92.7 -> 92.6 us): behind it stand the 590 KB of uq that each workgroup reads.  What did help: constants requested before the pixels, the filter-side
+// instead of 216: 92.7 -> 92.6 us): behind it stand the 590 KB of uq that each workgroup reads.  About 12 of
+// the 71 us are the last, partial round: 784 workgroups are 3.06 times 256 (56 images, 2.68 times, 57.0 us; 64
+// images 71.0).  What did help: constants requested before the pixels, the filter-side
 // terms in separable form (170 binary64 instructions instead of 470), no reduction kernel, the second
 // channel block's pixels requested under the first one's arithmetic, whole rows of the filter-side
 // terms read at once and range-checked stores in the tail.  A variant with one workgroup of eight waves

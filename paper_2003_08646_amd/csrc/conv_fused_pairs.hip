@@ -1,6 +1,6 @@
 // Stages 2 (second pass) + 3 + 4 in one kernel for F(2x2,3x3) layers with one or two 64-channel
-// blocks whose tiles pair up (NCHW, pad 1, width a multiple of 4; NHWC, any padding and width): v^ = Q(B^T d B) (Algorithm 1;
-// Eq. 7) is formed in registers and written to LDS only, the int8 products of Sec. 3.3 run on
+// blocks whose tiles pair up (NCHW, pad 1, width a multiple of 4; NHWC, C a multiple of 4, X 16-byte aligned, any
+// padding and width): v^ = Q(B^T d B) (Algorithm 1; Eq. 7) is formed in registers and written to LDS only, the int8 products of Sec. 3.3 run on
 // the matrix cores from there, and the de-quantization (Eq. 8) and output transform (Eq. 9) are
 // applied to the register accumulators.  The codes of V never touch device memory.
 //
@@ -35,8 +35,15 @@
 // 128 -> 128 56x56 with caller's ranges 81 us instead of 67).  A pixel's 16 filters of a wave are one 64-byte run of Y.
 // Against four tiles per thread in workgroups of four waves, two tile columns of the window kept from tile to
 // tile, whole call with the faster range pass, dynamic ranges: N64 128 -> 128 56x56 106 -> 93 us, N16 64 -> 64
-// 224x224 190 -> 160, N128 64 -> 64 32x32 36.9 -> 29.9, N30 128 -> 512 33x35 68.1 -> 58.2; the kernel alone 81.6 -> 72.9,
-// 144 -> 125, 29.5 -> 24.7.  Bound by the same things as above.
+// 224x224 190 -> 162, N128 64 -> 64 32x32 36.7 -> 30.5, N30 128 -> 512 33x35 68.2 -> 57.4.  This kernel between two
+// events, same buffers (X in the last-level cache): 82.0 -> 73.2, 144 -> 124, 29.6 -> 24.6, 62.5 -> 52.9, and the range pass
+// 24.7, 43.0, 10.9, 9.6: about 5 us more than the call, for the events and a launch behind an idle chip each.  With inputs and
+// outputs that rotate past the cache the calls take 111 -> 97, 201 -> 179, 40.9 -> 34.8, 71.6 -> 61.5.  Bound by the same
+// things as above.
+//
+// The last, partial round: a workgroup beyond a multiple of 256 takes its whole time on an almost idle chip.  128 -> 128
+// 56x56 with caller's ranges, 62 / 63 / 64 images (5.93, 6.03 and 6.13 times 256 workgroups): NCHW 53.9 / 58.4 / 58.7 us,
+// NHWC 61.7 / 68.3 / 68.7.
 #include "lance_device.h"
 #include "lance_internal.h"
 #include "quant_pairs.h"

@@ -28,8 +28,8 @@
 // ranges): 512->512 28x28, 208 workgroups, 9 of 14 us are phase T (each compute unit transforms all channels of its
 // tiles: vector ALUs and the path from L2, about equally), 0.6 until the pixels are requested, 1 until the
 // constants are formed, 1 products, 0.4 sums, 0.6 stores.  What the constants are formed from is requested before
-// the pixels, and the filter-side terms are formed once per filter (pos_phases.h): 3->64 224x224 18.8 -> 15.2 us, 64->128
-// 112x112 12.0 -> 10.1, 256->256 56x56 13.8 -> 12.2, 512->512 14x14 12.1 -> 11.6; 160 random layers 1.05 on average.
+// the pixels, and the filter-side terms are formed once per filter (pos_phases.h): 64->128
+// 112x112 12.0 -> 10.1 us, 256->256 56x56 13.8 -> 12.2, 512->512 14x14 12.1 -> 11.6; 160 random layers 1.05 on average.
 #pragma once
 #include "pos_phases.h"
 

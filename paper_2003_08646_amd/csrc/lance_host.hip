@@ -245,8 +245,8 @@ enum ConvPlan { kPlanGeneral = 0, kPlanTwoKernels = 1, kPlanThreeKernels = 2 };
 // gemm_fused_pos.hip).  The others:
 // Layers with one 64-channel block (m = 2) run as two kernels: the range pass, then one kernel
 // that reduces the ranges, quantizes, multiplies and transforms back (V's codes stay on chip).
-// Where the tiles pair up (pad 1, width a multiple of 4, NCHW; every NHWC layer) that kernel is
-// conv_fused_pairs.hip's.
+// Where the tiles pair up (NCHW: pad 1, width a multiple of 4; NHWC: C a multiple of 4 and X 16-byte aligned) that
+// kernel is conv_fused_pairs.hip's.
 // Layers with two blocks (m = 2) take the same two-kernel form (128 KB of codes in LDS) unless
 // the descriptor asks for the general plan's wide tiles.  Layers of at most 16 channels (m = 2)
 // and F(4x4,3x3) layers of at most 128 channels: range pass, reduction kernel, one kernel for the
