@@ -611,14 +611,19 @@ CpArgs make_args(const Geo& g, const float* x, const int8_t* uq, const float* u_
 // tiles per thread: N3571 128 -> 128 14x1 53.6 / 35.5 / 41.8 us, N96 120 -> 374 18x18 (270 and 243 workgroups) 70.4 / 44.2 / 51.0,
 // N2940 128 -> 620 5x6 137.9 / 123.0 / 130.5.  Of 1500 random layers with more than two workgroups of the few-tile plan per
 // compute unit 292 take this form; 0.14 % over the better form's time on average.  With the same number of rounds it
-// is 2 % (300 filters and more) to 7 % (up to 16) slower.  Many filters that are no multiple of four are bound by 4-byte
-// stores, for which more workgroups are the better (N6382 44 -> 629 6x6 401 / 434, N232 128 -> 3943 6x5 106 / 120): not
-// there, but with one tile column.
+// is 2 % (300 filters and more) to 7 % (up to 16) slower.
+// Filters that are no multiple of four take 4-byte stores, for which more workgroups are the better.  One channel block, one
+// column of whole tiles, more than 128 filters: bound by them, pairs of a row (N17038 32 -> 1687 2x2 364 / 433 us, N20000 64 ->
+// 301 2x2 87 / 101).  A last share of the filters, however small, counts as a whole one there (N1091 128 -> 798 3x5 91 / 58, N166 128 ->
+// 1222 13x13 138 / 106): 0.6 % over the better form on 900 random layers with odd numbers of tile columns, 1.3 % with shares by
+// their work and no such layer of more than 512 filters and three columns; none 5 % slower than four tiles per thread, before ten.
 bool conv_fused_any_pairs(const Geo& g) {
-  if (g.K > 512 && g.K % 4 != 0 && g.tw > 1) return false;
+  const bool whole_stores = g.K % 4 == 0;
+  if (!whole_stores && g.NB == 1 && g.tw == 1 && g.Wo == 2 && g.K > 128) return false;
   // blocks of filters, and of a workgroup; the last share of the filters may be small
   const long long per_wg = 32 / g.NB, most = (g.NB == 1 ? most_filters<1>() : most_filters<2>()) / (64 * g.NB);
-  const long long blocks = (g.K + 64 * g.NB - 1) / (64 * g.NB), work = blocks > most ? blocks : most;
+  const long long blocks = (g.K + 64 * g.NB - 1) / (64 * g.NB), shares = (blocks + most - 1) / most;
+  const long long work = whole_stores && blocks > most ? blocks : shares * most;
   auto rounds = [&](long long pairs) { return ((pairs + per_wg - 1) / per_wg * work + 256 * most - 1) / (256 * most); };
   return rounds((g.P + 1LL) / 2) < rounds((long long)g.N * g.th * pairs_per_row(g));
 }

@@ -609,13 +609,13 @@ def test_nhwc_rows_of_whole_pairs(shape, static):
 
 
 # N, C, K, H, W, pad, bits: NHWC pairs of tiles: one, two and three tile columns, odd numbers of them, widths that
-# are no multiple of anything, filters that are no multiple of four and of sixteen (streamed stores), padding lanes,
+# are no multiple of anything, filters that are no multiple of four and of sixteen (streamed stores; bound by them), padding lanes,
 # one share of the filters, one more filter, three shares; rows of so many pairs that multiplying does not divide them
 _NHWC_PAIRS = [
     (500, 20, 130, 13, 2, 1, 8), (900, 64, 20, 9, 3, 1, 8), (700, 40, 32, 9, 5, 1, 5), (420, 60, 21, 10, 11, 0, 8),
     (300, 64, 16, 8, 9, 2, 8), (300, 64, 704, 8, 9, 1, 8), (100, 44, 705, 9, 13, 1, 6), (40, 24, 1500, 9, 13, 1, 8),
     (500, 68, 260, 9, 2, 1, 8), (900, 128, 37, 9, 5, 0, 4), (260, 100, 130, 10, 11, 1, 8), (200, 128, 48, 8, 9, 2, 8),
-    (60, 124, 768, 9, 13, 1, 8), (50, 72, 769, 9, 13, 1, 8), (1, 20, 17, 2, 262147, 1, 8),
+    (60, 124, 768, 9, 13, 1, 8), (50, 72, 769, 9, 13, 1, 8), (1, 20, 17, 2, 262147, 1, 8), (8200, 20, 130, 2, 2, 1, 8),
 ]
 
 
@@ -625,7 +625,8 @@ _NHWC_PAIRS = [
 _NHWC_ANY_PAIRS = [
     (1801, 20, 18, 13, 1, 1, 8), (1801, 64, 17, 13, 2, 1, 5), (1801, 68, 18, 9, 2, 1, 8), (985, 40, 32, 9, 5, 1, 8),
     (683, 60, 21, 10, 11, 0, 8), (277, 128, 130, 18, 18, 1, 8), (1601, 100, 64, 5, 6, 1, 6), (501, 44, 720, 9, 9, 1, 8),
-    (2801, 128, 36, 5, 3, 0, 8), (650, 68, 130, 5, 3, 2, 4), (1, 20, 17, 10, 58981, 1, 8),
+    (2801, 128, 36, 5, 3, 0, 8), (650, 68, 130, 5, 3, 2, 4), (1, 20, 17, 10, 58981, 1, 8), (700, 68, 518, 5, 6, 1, 8),
+    (401, 68, 830, 5, 6, 1, 8), (8200, 20, 127, 2, 2, 1, 8),
 ]
 
 
